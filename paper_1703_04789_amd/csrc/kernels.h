@@ -34,18 +34,42 @@ struct BufSet {
     double* p[kMaxBufs];
 };
 
-// diagonal of H_eff / N_eff for one packed block
-struct DiagBlk {
-    long long x_off;
-    long long l_off0;  // offset of (row ro) diagonal start inside a left env block, per term
-    int rows, cols, sigma, t0, t1;
-    int pad;
+// Diagonal of H_eff / N_eff, in three launches (the spin-diagonal part of
+// the rotated MPO acts on the diagonals of the environments alone):
+//   gather  Ld(g, z, p), Rd(g, z, p): the diagonals of the environment
+//           blocks of the particle-conserving channels z, state p of the bond
+//   mix     M(g, row, p) = sum over terms of coef * Ld(g, z, p)
+//   blocks  out(r, c) = sum over g and the block's units of
+//           M(g, row, r) Rd(g, z, c): one work-group per tile of at most
+//           kDiagTile x kDiagTile elements of an (N, M) block
+struct DiagSrc {
+    long long off;  // environment block (within one g); ld < 0: no block, zeros
+    int ld, pad;
 };
-struct DiagTerm {
-    long long l_off;  // env block offset (per g) in the left env + ro*(ld+1)
-    long long r_off;  // env block offset (per g) in the right env + co*(ld+1)
-    int l_ld, r_ld;   // row length of the env blocks (diagonal stride ld+1)
-    int cidx, pad;
+// one side of the gather: element (z, p) is env[src[z * nnb + nb[p]].off +
+// ro[p] * (ld + 1)], nb/ro the particle-number block of state p and its place
+struct DiagSide {
+    const DiagSrc* src;
+    const int* nb;
+    const int* ro;
+    const double* env;
+    long long esize;  // environment values per g
+    double* out;      // nz * D values per g
+    int nz, D, nnb, pad;
+};
+struct DiagMix {
+    int t0, t1;  // terms of one row of M
+};
+struct DiagMixTerm {
+    int z, cidx;
+};
+struct DiagBlk {
+    int x_off, ldc;        // element (r, c) of the tile at x_off + r * ldc + c
+    int rows, cols;
+    int row0, nrow;        // units: M rows row0 .. row0 + nrow
+    int p0, q0;            // first state of the tile on the left, right bond
+    int zl0;               // Rd channel of unit u: zlist[zl0 + u]
+    int is_n, pad0, pad1;  // 1: N_eff
 };
 
 // QR of one gathered sector matrix: pieces are row-major blocks of a packed
@@ -183,14 +207,18 @@ void bgemm(hipStream_t s, const BTask* tasks, int ntasks, const BTerm* terms, Bu
            const double* coef);
 void combine(hipStream_t s, const CTask* tasks, int ntasks, const CTerm* terms, BufSet bufs,
              const double* coef);
-// nsplit > 1: the (g, term) range of every block is cut into nsplit parts
-// summed in a fixed order through part (nsplit x ntot doubles, ntot = the
-// site size); nsplit = 1 sums straight into out
+// the three launches of the diagonals.  mix row r reads terms mix[r]; M is
+// mstride values per g.  nsplit > 1: the units of every H_eff tile are cut
+// into nsplit parts summed in a fixed order through part (nsplit x ntot
+// doubles, ntot = the site size); nsplit = 1 sums straight into dh
+constexpr int kDiagTile = 32;
 constexpr int kDiagSplitMax = 8;
-void heff_diag(hipStream_t s, const DiagBlk* blks, int nblk, const DiagTerm* terms,
-               const double* lenv, long long lsize, const double* renv, long long rsize,
-               const double* coef, int ncoef, int G, double* out, int nsplit = 1, double* part = nullptr,
-               long long ntot = 0);
+void diag_gather(hipStream_t s, const DiagSide& left, const DiagSide& right, int G);
+void diag_mix(hipStream_t s, const DiagMix* mix, int nmix, const DiagMixTerm* terms, const double* Ld, int nzl, int Dl,
+              const double* coef, int ncoef, int G, double* M);
+void diag_blocks(hipStream_t s, const DiagBlk* blks, int nblk, const int* zlist, const double* M, int nmix, int Dl,
+                 const double* Rd, int nzr, int Dr, int G, double* dh, double* dn, int nsplit, double* part,
+                 long long ntot);
 // Per-sector positive-diagonal QR.  Tasks whose two rows x cols matrices
 // fit kQrLdsMax doubles run in LDS (lds_doubles = the largest 2 rows cols
 // of the list); otherwise they use the scratch buffer in global memory.

@@ -133,43 +133,116 @@ __global__ __launch_bounds__(kThreads) void k_combine(const CTask* __restrict__ 
     }
 }
 
-// Diagonal of H_eff (or N_eff) for one packed (N, M) block: for element
-// (r, c), sum over g and the block's terms t of coef * L_g,t(r, r) * R_g,t(c, c).
-// The (g, t) range, g outer, is cut into gridDim.y equal parts: part j sums
-// its range in order and writes part[j * ntot + index] (one part: straight
-// to out), and k_diag_sum adds the parts in ascending j.  Wide MPOs have
-// thousands of terms per block, so one work-group per block would run them
-// all in sequence.
-__global__ __launch_bounds__(kThreads) void k_diag(const DiagBlk* __restrict__ blks,
-                                                     const DiagTerm* __restrict__ terms,
-                                                     const double* __restrict__ lenv, long long lsize,
-                                                     const double* __restrict__ renv, long long rsize,
-                                                     const double* __restrict__ coef, int ncoef, int G,
-                                                     double* __restrict__ out, double* __restrict__ part,
-                                                     long long ntot) {
-    const DiagBlk b = blks[blockIdx.x];
-    const int n = b.rows * b.cols;
-    const int T = b.t1 - b.t0, nsplit = gridDim.y, j = blockIdx.y;
-    const long long U = (long long)G * T;
-    const long long u0 = U * j / nsplit, u1 = U * (j + 1) / nsplit;
-    for (int e = threadIdx.x; e < n; e += kThreads) {
-        const int r = e / b.cols, c = e - r * b.cols;
+// Diagonals of the environment blocks, compact: Ld/Rd(g, z, p).  blockIdx.y
+// is g, blockIdx.z the side.  One strided 8-byte read per value; everything
+// after it reads contiguous rows.
+__global__ __launch_bounds__(kThreads) void k_diag_gather(DiagSide left, DiagSide right) {
+    const DiagSide& S = blockIdx.z ? right : left;
+    const int e = blockIdx.x * kThreads + threadIdx.x;
+    if (e >= S.nz * S.D) return;
+    const int z = e / S.D, p = e - z * S.D, g = blockIdx.y;
+    const DiagSrc src = S.src[z * S.nnb + S.nb[p]];
+    double v = 0.0;
+    if (src.ld >= 0) v = S.env[g * S.esize + src.off + (long long)S.ro[p] * (src.ld + 1)];
+    S.out[(long long)g * S.nz * S.D + e] = v;
+}
+
+// M(g, row, p) = sum over the row's terms of coef * Ld(g, z, p): one
+// work-group per (row, g), the terms staged in LDS 64 at a time so that the
+// loads of the sum are independent of each other.
+__global__ __launch_bounds__(kThreads) void k_diag_mix(const DiagMix* __restrict__ mix,
+                                                         const DiagMixTerm* __restrict__ terms,
+                                                         const double* __restrict__ Ld, int nzl, int Dl,
+                                                         const double* __restrict__ coef, int ncoef, int nmix,
+                                                         double* __restrict__ M) {
+    constexpr int kAtOnce = 64;
+    __shared__ int sz[kAtOnce];
+    __shared__ double sc[kAtOnce];
+    const DiagMix m = mix[blockIdx.x];
+    const int g = blockIdx.y;
+    const double* __restrict__ src = Ld + (long long)g * nzl * Dl;
+    double* __restrict__ out = M + ((long long)g * nmix + blockIdx.x) * Dl;
+    for (int p0 = 0; p0 < Dl; p0 += blockDim.x) {
+        const int p = p0 + threadIdx.x;
         double acc = 0.0;
-        if (T > 0) {
-            int g = int(u0 / T), t = b.t0 + int(u0 % T);
-            for (long long u = u0; u < u1; ++u) {
-                const DiagTerm tm = terms[t];
-                const double lv = lenv[g * lsize + tm.l_off + (long long)r * (tm.l_ld + 1)];
-                const double rv = renv[g * rsize + tm.r_off + (long long)c * (tm.r_ld + 1)];
-                acc = fma(coef[g * ncoef + tm.cidx], lv * rv, acc);
-                if (++t == b.t1) {
-                    t = b.t0;
-                    ++g;
-                }
+        for (int tb = m.t0; tb < m.t1; tb += kAtOnce) {
+            const int nt = min(kAtOnce, m.t1 - tb);
+            __syncthreads();
+            if ((int)threadIdx.x < nt) {
+                const DiagMixTerm tm = terms[tb + threadIdx.x];
+                sz[threadIdx.x] = tm.z * Dl;
+                sc[threadIdx.x] = coef[(long long)g * ncoef + tm.cidx];
+            }
+            __syncthreads();
+            if (p < Dl) {
+#pragma unroll 8
+                for (int t = 0; t < nt; ++t) acc = fma(sc[t], src[sz[t] + p], acc);
             }
         }
-        if (nsplit == 1) out[b.x_off + e] = acc;
-        else part[(long long)j * ntot + b.x_off + e] = acc;
+        if (p < Dl) out[p] = acc;
+    }
+}
+
+// One tile of the diagonal of H_eff or N_eff.  Its units u = (g, row) are an
+// outer-product sum out(r, c) += M(u, r) Rd(u, c), staged through LDS 32
+// units at a time with the next chunk's loads issued before the products of
+// the current one; a thread owns column tid % 32 and rows tid / 32 + 8 i.
+// Every environment value is read once per tile instead of once per element,
+// and a right channel's terms are mixed once per bond state: the centre of
+// the K = 12, D = 128, G = 11 ab-initio state has 8600 terms per sigma but 250
+// rows, and its three launches take the diagonal from 3.8 ms (one work-group
+// summing every term of every element of a block) to under 0.1 ms.  A part of
+// 256 units is 8 staged chunks; the Hubbard MPO (2 rows) has one part.
+__global__ __launch_bounds__(kThreads) void k_diag(const DiagBlk* __restrict__ blks, const int* __restrict__ zlist,
+                                                     const double* __restrict__ M, int nmix, int Dl,
+                                                     const double* __restrict__ Rd, int nzr, int Dr, int G,
+                                                     double* __restrict__ dh, double* __restrict__ dn,
+                                                     double* __restrict__ part, long long ntot) {
+    constexpr int T = kDiagTile, U = 32, PER = U * T / kThreads;
+    static_assert(PER == 4 && T == 32, "four staged values of either operand per thread");
+    __shared__ double Ls[U][T], Rs[U][T];
+    const DiagBlk b = blks[blockIdx.x];
+    const int nsplit = b.is_n ? 1 : gridDim.y, j = blockIdx.y;
+    if (j >= nsplit) return;
+    const int UT = G * b.nrow;
+    const int u0 = int((long long)UT * j / nsplit), u1 = int((long long)UT * (j + 1) / nsplit);
+    const int x = threadIdx.x % T, y = threadIdx.x / T;
+    double lv[PER], rv[PER], acc[PER] = {0.0, 0.0, 0.0, 0.0};
+    auto fetch = [&](int ub) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int u = ub + y + 8 * i;
+            lv[i] = rv[i] = 0.0;
+            if (u < u1) {
+                const int g = u / b.nrow, q = u - g * b.nrow;
+                if (x < b.rows) lv[i] = M[((long long)g * nmix + b.row0 + q) * Dl + b.p0 + x];
+                if (x < b.cols) rv[i] = Rd[((long long)g * nzr + zlist[b.zl0 + q]) * Dr + b.q0 + x];
+            }
+        }
+    };
+    if (u0 < u1) fetch(u0);
+    for (int ub = u0; ub < u1; ub += U) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            Ls[y + 8 * i][x] = lv[i];
+            Rs[y + 8 * i][x] = rv[i];
+        }
+        __syncthreads();
+        if (ub + U < u1) fetch(ub + U);
+        const int nu = min(U, u1 - ub);
+        for (int u = 0; u < nu; ++u) {
+            const double r = Rs[u][x];
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (8 * i < b.rows) acc[i] = fma(Ls[u][y + 8 * i], r, acc[i]);
+        }
+        __syncthreads();
+    }
+    double* __restrict__ out = b.is_n ? dn : (nsplit == 1 ? dh : part + (long long)j * ntot);
+    if (x < b.cols) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (y + 8 * i < b.rows) out[b.x_off + (y + 8 * i) * b.ldc + x] = acc[i];
     }
 }
 
@@ -1285,16 +1358,26 @@ void combine(hipStream_t s, const CTask* tasks, int ntasks, const CTerm* terms, 
              const double* coef) {
     if (ntasks > 0) hipLaunchKernelGGL(k_combine, dim3(ntasks), dim3(kThreads), 0, s, tasks, terms, bufs, coef);
 }
-void heff_diag(hipStream_t s, const DiagBlk* blks, int nb, const DiagTerm* terms, const double* lenv,
-               long long lsize, const double* renv, long long rsize, const double* coef, int ncoef,
-               int G, double* out, int nsplit, double* part, long long ntot) {
+void diag_gather(hipStream_t s, const DiagSide& left, const DiagSide& right, int G) {
+    const int n = std::max(left.nz * left.D, right.nz * right.D);
+    if (n > 0) hipLaunchKernelGGL(k_diag_gather, dim3(nblk(n), G, 2), dim3(kThreads), 0, s, left, right);
+}
+void diag_mix(hipStream_t s, const DiagMix* mix, int nmix, const DiagMixTerm* terms, const double* Ld, int nzl, int Dl,
+              const double* coef, int ncoef, int G, double* M) {
+    if (nmix > 0)
+        hipLaunchKernelGGL(k_diag_mix, dim3(nmix, G), dim3(std::min(kThreads, (Dl + 63) / 64 * 64)), 0, s, mix, terms, Ld,
+                           nzl, Dl, coef, ncoef, nmix, M);
+}
+void diag_blocks(hipStream_t s, const DiagBlk* blks, int nb, const int* zlist, const double* M, int nmix, int Dl,
+                 const double* Rd, int nzr, int Dr, int G, double* dh, double* dn, int nsplit, double* part,
+                 long long ntot) {
     if (nb <= 0) return;
     if (nsplit < 1 || (nsplit > 1 && !part)) nsplit = 1;
-    hipLaunchKernelGGL(k_diag, dim3(nb, nsplit), dim3(kThreads), 0, s, blks, terms, lenv, lsize, renv, rsize,
-                       coef, ncoef, G, out, part, ntot);
+    hipLaunchKernelGGL(k_diag, dim3(nb, nsplit), dim3(kThreads), 0, s, blks, zlist, M, nmix, Dl, Rd, nzr, Dr, G, dh, dn,
+                       part, ntot);
     if (nsplit > 1)
-        hipLaunchKernelGGL(k_diag_sum, dim3((unsigned)((ntot + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                           part, nsplit, ntot, out);
+        hipLaunchKernelGGL(k_diag_sum, dim3((unsigned)((ntot + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, part,
+                           nsplit, ntot, dh);
 }
 void qr_sectors(hipStream_t s, const QrTask* tasks, int ntasks, const QrPiece* pieces, double* site,
                 double* scratch, double* rout, int lds_doubles) {

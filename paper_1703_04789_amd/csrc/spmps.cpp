@@ -319,10 +319,17 @@ struct SitePlan {
     CList mixl, mixr;
     double heff_flops = 0.0;
     // diagonal
-    std::vector<spk::DiagBlk> dblk_h, dblk_n;
-    std::vector<spk::DiagTerm> dterm_h, dterm_n;
-    DArr<spk::DiagBlk> ddblk_h, ddblk_n;
-    DArr<spk::DiagTerm> ddterm_h, ddterm_n;
+    int dg_nzl = 0, dg_nzr = 0, dg_split = 1;  // particle-conserving channels of both bonds, parts of a tile
+    std::vector<spk::DiagSrc> dg_src;           // left, then right (nz * nnb each)
+    std::vector<int> dg_idx;                    // left nb, ro, right nb, ro, then the channel lists of the tiles
+    std::vector<spk::DiagMix> dg_mix;
+    std::vector<spk::DiagMixTerm> dg_term;
+    std::vector<spk::DiagBlk> dg_blk;
+    DArr<spk::DiagSrc> ddg_src;
+    DArr<int> ddg_idx;
+    DArr<spk::DiagMix> ddg_mix;
+    DArr<spk::DiagMixTerm> ddg_term;
+    DArr<spk::DiagBlk> ddg_blk;
     // gauge moves
     std::vector<spk::QrTask> qr_tasks, lq_tasks;
     std::vector<spk::QrPiece> qr_pieces, lq_pieces;
@@ -994,48 +1001,80 @@ void build_plan(sp_handle* h, int k) {
                 }
             }
         }
-    // ---- diagonal of H_eff and N_eff
-    for (const XBlk& X : si.blk) {
-        const Sector& SA = bl.sec[X.sa];
-        const Sector& SB = br.sec[X.sb];
-        spk::DiagBlk db{};
-        db.x_off = X.off;
-        db.rows = X.rows;
-        db.cols = X.cols;
-        db.sigma = X.s;
-        db.t0 = int(P.dterm_h.size());
-        for (const auto& ent : byD[X.s]) {
-            const int c = ent[0], cp = ent[1];
-            const int e = el.find(c, SA.nb);
-            if (e < 0 || el.blk[e].j != SA.nb) continue;
-            {
-                const int re = er.find(cp, SB.nb);
-                if (re < 0 || er.blk[re].j != SB.nb) continue;
-                spk::DiagTerm dt{};
-                dt.l_off = el.blk[e].off + (long long)SA.ro * (el.blk[e].cols + 1);
-                dt.r_off = er.blk[re].off + (long long)SB.ro * (er.blk[re].cols + 1);
-                dt.l_ld = el.blk[e].cols;
-                dt.r_ld = er.blk[re].cols;
-                dt.cidx = P.c_cwt(ent[2]);
-                P.dterm_h.push_back(dt);
+    // ---- diagonal of H_eff and N_eff: the particle-conserving channels z of
+    // both bonds, per sigma one mixed row per right channel with terms, and
+    // tiles of the site's blocks
+    {
+        std::vector<int> zl(wl, -1), zr(wr, -1);
+        auto side = [&](const Bond& bd, const EnvLayout& e, std::vector<int>& z, int& nz) {
+            for (int c = 0; c < e.nc; ++c) {
+                bool any = false;
+                for (int i = 0; i < e.nnb && !any; ++i) any = e.find(c, i) >= 0 && e.blk[e.find(c, i)].j == i;
+                if (!any) continue;
+                z[c] = nz++;
+                for (int i = 0; i < e.nnb; ++i) {
+                    const int q = e.find(c, i);
+                    P.dg_src.push_back(q >= 0 && e.blk[q].j == i ? spk::DiagSrc{e.blk[q].off, e.blk[q].cols, 0}
+                                                                 : spk::DiagSrc{0, -1, 0});
+                }
             }
+            for (int i = 0; i < int(bd.nb.size()); ++i)
+                P.dg_idx.insert(P.dg_idx.end(), bd.nb[i].dim, i);
+            for (const NBlock& nb : bd.nb)
+                for (int p = 0; p < nb.dim; ++p) P.dg_idx.push_back(p);
+        };
+        side(bl, el, zl, P.dg_nzl);
+        side(br, er, zr, P.dg_nzr);
+        SP_REQUIRE(zl[0] >= 0 && zr[lastR] >= 0, "internal: identity channels must conserve N");
+        std::array<int, 4> row0{}, nrow{}, zl0{}, row_n{};
+        int most = 1;
+        for (int sig = 0; sig < 4; ++sig) {
+            std::vector<std::vector<spk::DiagMixTerm>> of(wr);
+            for (const auto& ent : byD[sig])
+                if (zl[ent[0]] >= 0 && zr[ent[1]] >= 0) of[ent[1]].push_back({zl[ent[0]], P.c_cwt(ent[2])});
+            row0[sig] = int(P.dg_mix.size());
+            zl0[sig] = int(P.dg_idx.size());
+            for (int cp = 0; cp < wr; ++cp) {
+                if (of[cp].empty()) continue;
+                const int t0 = int(P.dg_term.size());
+                P.dg_term.insert(P.dg_term.end(), of[cp].begin(), of[cp].end());
+                P.dg_mix.push_back(spk::DiagMix{t0, int(P.dg_term.size())});
+                P.dg_idx.push_back(zr[cp]);
+            }
+            nrow[sig] = int(P.dg_mix.size()) - row0[sig];
+            most = std::max(most, G * nrow[sig]);
         }
-        db.t1 = int(P.dterm_h.size());
-        P.dblk_h.push_back(db);
-        db.t0 = int(P.dterm_n.size());
-        const int e0 = el.find(0, SA.nb);
-        const int re = er.find(lastR, SB.nb);
-        if (e0 >= 0 && re >= 0) {
-            spk::DiagTerm dt{};
-            dt.l_off = el.blk[e0].off + (long long)SA.ro * (el.blk[e0].cols + 1);
-            dt.r_off = er.blk[re].off + (long long)SB.ro * (er.blk[re].cols + 1);
-            dt.l_ld = el.blk[e0].cols;
-            dt.r_ld = er.blk[re].cols;
-            dt.cidx = P.c_gr(X.s, X.s);
-            P.dterm_n.push_back(dt);
+        const int zn = int(P.dg_idx.size());  // N_eff: the two identity strings
+        P.dg_idx.push_back(zr[lastR]);
+        for (int sig = 0; sig < 4; ++sig) {
+            row_n[sig] = int(P.dg_mix.size());
+            P.dg_term.push_back({zl[0], P.c_gr(sig, sig)});
+            P.dg_mix.push_back(spk::DiagMix{int(P.dg_term.size()) - 1, int(P.dg_term.size())});
         }
-        db.t1 = int(P.dterm_n.size());
-        P.dblk_n.push_back(db);
+        for (const XBlk& X : si.blk) {
+            const Sector& SA = bl.sec[X.sa];
+            const Sector& SB = br.sec[X.sb];
+            SP_REQUIRE(X.off + (long long)X.rows * X.cols < INT32_MAX, "site too large for 32-bit offsets");
+            for (int r = 0; r < X.rows; r += spk::kDiagTile)
+                for (int c = 0; c < X.cols; c += spk::kDiagTile)
+                    for (int n = 0; n < 2; ++n) {
+                        spk::DiagBlk d{};
+                        d.x_off = int(X.off) + r * X.cols + c;
+                        d.ldc = X.cols;
+                        d.rows = std::min(spk::kDiagTile, X.rows - r);
+                        d.cols = std::min(spk::kDiagTile, X.cols - c);
+                        d.row0 = n ? row_n[X.s] : row0[X.s];
+                        d.nrow = n ? 1 : nrow[X.s];
+                        d.p0 = SA.off + r;
+                        d.q0 = SB.off + c;
+                        d.zl0 = n ? zn : zl0[X.s];
+                        d.is_n = n;
+                        P.dg_blk.push_back(d);
+                    }
+        }
+        // parts of a tile: about 256 units (8 staged chunks) each, so that
+        // the hundreds of rows of a wide MPO run as parallel work-groups
+        P.dg_split = std::min(std::max(most / 256, 1), spk::kDiagSplitMax);
     }
     // ---- QR per right sector (left-orthonormalise) and LQ per left sector
     P.qr_roff.assign(br.sec.size(), -1);
@@ -1747,10 +1786,11 @@ void upload_plan(sp_handle* h, int k) {
     P.p1r.upload(s);
     P.mixr.upload(s);
     P.envr_out.upload(s);
-    P.ddblk_h.upload(P.dblk_h, s);
-    P.ddblk_n.upload(P.dblk_n, s);
-    P.ddterm_h.upload(P.dterm_h, s);
-    P.ddterm_n.upload(P.dterm_n, s);
+    P.ddg_src.upload(P.dg_src, s);
+    P.ddg_idx.upload(P.dg_idx, s);
+    P.ddg_mix.upload(P.dg_mix, s);
+    P.ddg_term.upload(P.dg_term, s);
+    P.ddg_blk.upload(P.dg_blk, s);
     P.dqr_tasks.upload(P.qr_tasks, s);
     P.dlq_tasks.upload(P.lq_tasks, s);
     P.dqr_pieces.upload(P.qr_pieces, s);
@@ -1903,6 +1943,42 @@ void validate_fused(sp_handle* h, int k) {
         if (seen[o] != 1) throw SpError(SP_EINVAL, "internal: fused outputs do not cover the site");
 }
 
+// bounds of the lists of the diagonals of site k
+void validate_diag(const sp_handle* h, int k) {
+    const SitePlan& P = h->plan[k - 1];
+    const Bond& bl = h->bonds[k - 1];
+    const Bond& br = h->bonds[k];
+    const int nidx = int(P.dg_idx.size()), nmix = int(P.dg_mix.size());
+    const size_t nl = size_t(P.dg_nzl) * bl.nb.size(), nr = size_t(P.dg_nzr) * br.nb.size();
+    if (P.dg_src.size() != nl + nr || nidx < 2 * (bl.D + br.D)) throw SpError(SP_EINVAL, "internal: diagonal sources");
+    for (size_t q = 0; q < nl + nr; ++q) {
+        const spk::DiagSrc& d = P.dg_src[q];
+        if (d.ld < 0) continue;
+        const NBlock& nb = q < nl ? bl.nb[q % bl.nb.size()] : br.nb[(q - nl) % br.nb.size()];
+        check_span(d.off, d.off + (long long)(nb.dim - 1) * (d.ld + 1), h->env[q < nl ? k - 1 : k].size, "diagonal source");
+    }
+    for (const spk::DiagMix& m : P.dg_mix)
+        if (m.t0 < 0 || m.t1 <= m.t0 || m.t1 > int(P.dg_term.size())) throw SpError(SP_EINVAL, "internal: diagonal row");
+    for (const spk::DiagMixTerm& t : P.dg_term) {
+        check_span(t.z, t.z, P.dg_nzl, "diagonal term");
+        check_span(t.cidx, t.cidx, P.nc, "diagonal coefficient");
+    }
+    for (const spk::DiagBlk& d : P.dg_blk) {
+        if (d.rows < 1 || d.cols < 1 || d.rows > spk::kDiagTile || d.cols > spk::kDiagTile || d.nrow < 0)
+            throw SpError(SP_EINVAL, "internal: diagonal tile");
+        check_span(d.x_off, d.x_off + (long long)(d.rows - 1) * d.ldc + d.cols - 1, h->sites[k - 1].size, "diagonal block");
+        check_span(d.p0, d.p0 + d.rows - 1, bl.D, "diagonal rows");
+        check_span(d.q0, d.q0 + d.cols - 1, br.D, "diagonal columns");
+        if (d.nrow == 0) continue;
+        check_span(d.row0, d.row0 + d.nrow - 1, nmix, "diagonal units");
+        check_span(d.zl0, d.zl0 + d.nrow - 1, nidx, "diagonal channels");
+        for (int u = 0; u < d.nrow; ++u) check_span(P.dg_idx[d.zl0 + u], P.dg_idx[d.zl0 + u], P.dg_nzr, "diagonal channel");
+    }
+    const long long G = h->G;
+    if (G * ((long long)P.dg_nzl * bl.D + (long long)P.dg_nzr * br.D) > h->T_cap || G * nmix * bl.D > h->V_cap)
+        throw SpError(SP_EINVAL, "internal: diagonal scratch too small");
+}
+
 void validate_plans(sp_handle* h) {
     const long long G = h->G;
     for (int k = 1; k <= h->L; ++k) {
@@ -1994,19 +2070,7 @@ void validate_plans(sp_handle* h) {
                 if (rows != t.rows) throw SpError(SP_EINVAL, "internal: QR rows");
             }
         }
-        for (int pass = 0; pass < 2; ++pass) {
-            const auto& blks = pass ? P.dblk_n : P.dblk_h;
-            const auto& terms = pass ? P.dterm_n : P.dterm_h;
-            for (const spk::DiagBlk& d : blks) {
-                check_span(d.x_off, d.x_off + (long long)d.rows * d.cols - 1, xs, "diagonal block");
-                for (int i = d.t0; i < d.t1; ++i) {
-                    const spk::DiagTerm& t = terms[i];
-                    check_span(t.l_off, t.l_off + (long long)(d.rows - 1) * (t.l_ld + 1), h->env[k - 1].size, "diag L");
-                    check_span(t.r_off, t.r_off + (long long)(d.cols - 1) * (t.r_ld + 1), h->env[k].size, "diag R");
-                    check_span(t.cidx, t.cidx, P.nc, "diag coefficient");
-                }
-            }
-        }
+        validate_diag(h, k);
     }
 }
 
@@ -2221,21 +2285,19 @@ void env_right(sp_handle* h, int k) {
 void diag(sp_handle* h, int k, double* dh, double* dn) {
     if (!h->Lvalid[k - 1] || !h->Rvalid[k]) throw SpError(SP_ESTATE, "environments for the diagonal are not built");
     SitePlan& P = h->plan[k - 1];
-    const EnvLayout& el = h->env[k - 1];
-    const EnvLayout& er = h->env[k];
-    // wide MPOs: cut each block's (g, term) range into parts summed in a
-    // fixed order, so that a block's thousands of terms run in parallel
-    auto split = [&](const std::vector<spk::DiagBlk>& bl) {
-        int tmax = 0;
-        for (const spk::DiagBlk& d : bl) tmax = std::max(tmax, d.t1 - d.t0);
-        const long long u = (long long)h->G * tmax / 1024;
-        return int(std::min<long long>(std::max<long long>(u, 1), spk::kDiagSplitMax));
-    };
-    const long long ntot = h->sites[k - 1].size;
-    spk::heff_diag(h->stream, P.ddblk_h.p, int(P.dblk_h.size()), P.ddterm_h.p, h->envL[k - 1].p, el.size,
-                   h->envR[k].p, er.size, P.coef.p, P.nc, h->G, dh, split(P.dblk_h), h->diag_part.p, ntot);
-    spk::heff_diag(h->stream, P.ddblk_n.p, int(P.dblk_n.size()), P.ddterm_n.p, h->envL[k - 1].p, el.size,
-                   h->envR[k].p, er.size, P.coef.p, P.nc, h->G, dn, split(P.dblk_n), h->diag_part.p, ntot);
+    const Bond& bl = h->bonds[k - 1];
+    const Bond& br = h->bonds[k];
+    const int* idx = P.ddg_idx.p;
+    const int nnbl = int(bl.nb.size()), nnbr = int(br.nb.size()), nmix = int(P.dg_mix.size());
+    double* Ld = h->T.p;  // scratch of the block products, idle here
+    double* Rd = h->T.p + (long long)h->G * P.dg_nzl * bl.D;
+    const spk::DiagSide left{P.ddg_src.p, idx, idx + bl.D, h->envL[k - 1].p, h->env[k - 1].size, Ld, P.dg_nzl, bl.D, nnbl, 0};
+    const spk::DiagSide right{P.ddg_src.p + (size_t)P.dg_nzl * nnbl, idx + 2 * bl.D, idx + 2 * bl.D + br.D, h->envR[k].p,
+                              h->env[k].size, Rd, P.dg_nzr, br.D, nnbr, 0};
+    spk::diag_gather(h->stream, left, right, h->G);
+    spk::diag_mix(h->stream, P.ddg_mix.p, nmix, P.ddg_term.p, Ld, P.dg_nzl, bl.D, P.coef.p, P.nc, h->G, h->V.p);
+    spk::diag_blocks(h->stream, P.ddg_blk.p, int(P.dg_blk.size()), idx, h->V.p, nmix, bl.D, Rd, P.dg_nzr, br.D, h->G, dh,
+                     dn, P.dg_split, h->diag_part.p, h->sites[k - 1].size);
 }
 
 // positive-diagonal QR per right sector of site k, R pushed into site k+1
@@ -3615,8 +3677,10 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
                 P1.h_tasks.clear();
             }
             const SitePlan& P = h->plan[k - 1];
-            Tmax = std::max({Tmax, P.Tsize, P.Zsize});
-            Vmax = std::max({Vmax, P.Vsize, P.Ztsize});
+            // the diagonals use the same scratch
+            const long long dgT = (long long)P.dg_nzl * h->bonds[k - 1].D + (long long)P.dg_nzr * h->bonds[k].D;
+            Tmax = std::max({Tmax, P.Tsize, P.Zsize, dgT});
+            Vmax = std::max({Vmax, P.Vsize, P.Ztsize, (long long)P.dg_mix.size() * h->bonds[k - 1].D});
             LTmax = std::max(LTmax, P.LTsize);
             qrs = std::max({qrs, P.qr_scratch, P.lq_scratch});
             qrr = std::max({qrr, P.qr_rsize, P.lq_rsize});

@@ -1,0 +1,502 @@
+// Chained block products for gfx950: every contraction of the tiled path --
+// H_eff x and N_eff x (Eq. [geproblem]) and the environment updates (Fig.
+// [spmpsOpt]) -- is a sum of outputs
+//     O(m x n) += P(m x kc) [ sum over segments coef A(kc x kj) B(kj x n) ]
+// over steps (P, a range of kc, its segments).  The inner product I stays in
+// registers: a matrix-core result holds, in lane l, rows that depend on l / 16
+// and the column l % 16, which is exactly what the second operand of the next
+// product takes, so I is never written to memory.
+//   H_eff x (transposed): m = columns of the output block, n = its rows,
+//     P = R(c') rows, A = the rotated site vector, B = L(c) or the left
+//     environment with the MPO mixed in
+//   left environment:  P = the bra tensor, A = L(c), B = the rotated ket tensor
+//   right environment: P = the bra tensor, A = R(c'), B = the rotated ket tensor
+// One work-group of four wavefronts per output tile; the steps of a tile are
+// dealt to the wavefronts, whose sums are added through LDS in a fixed order.
+#include "kernels.h"
+
+#include <type_traits>
+
+namespace spk {
+
+namespace {
+
+typedef double d4_t __attribute__((ext_vector_type(4)));
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef short s4_t __attribute__((ext_vector_type(4)));
+typedef double d2u_t __attribute__((ext_vector_type(2), aligned(8)));
+typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ inline unsigned short bf16_rne(float f) {
+    unsigned int u = __float_as_uint(f);
+    u += 0x7FFFu + ((u >> 16) & 1u);
+    return (unsigned short)(u >> 16);
+}
+// v ~ hi + lo, both bf16 rounded to nearest even (about 16 significant bits)
+template <class V>
+__device__ inline void split_bf16(V v, short& hi, short& lo) {
+    const unsigned short h = bf16_rne(float(v));
+    const V hv = V(__uint_as_float((unsigned int)h << 16));
+    hi = short(h);
+    lo = short(bf16_rne(float(v - hv)));
+}
+
+// the value at element i of a block: a uniform base and a 32-bit byte offset
+// per lane (a block holds fewer than 2^28 values)
+template <class E>
+__device__ inline E at(const E* __restrict__ p, unsigned i) {
+    return *reinterpret_cast<const E*>(reinterpret_cast<const char*>(p) + unsigned(sizeof(E)) * i);
+}
+template <int N>
+__device__ inline void read_run(const double* __restrict__ p, unsigned i, double (&v)[N]) {
+#pragma unroll
+    for (int t = 0; t < N; t += 2) {
+        const d2u_t w = *reinterpret_cast<const d2u_t*>(reinterpret_cast<const char*>(p + t) + 8u * i);
+        v[t] = w.x;
+        v[t + 1] = w.y;
+    }
+}
+template <int N>
+__device__ inline void read_run(const float* __restrict__ p, unsigned i, float (&v)[N]) {
+    static_assert(N == 4, "a run of four FP32 values");
+    const f4u_t w = *reinterpret_cast<const f4u_t*>(reinterpret_cast<const char*>(p) + 4u * i);
+    v[0] = w.x;
+    v[1] = w.y;
+    v[2] = w.z;
+    v[3] = w.w;
+}
+
+// one chunk of an inner product in a lane: KL consecutive kj values of row
+// (column) l % 16 of every block of A (B); the segment's coefficient, the kj
+// values left in the segment, whether the chunk ends the step
+template <class E, int NI, int NN, int KL>
+struct Frag {
+    E a[NI][KL], b[NN][KL];
+    E cf;
+    int nk;
+    bool last;
+};
+
+// MODE kChainF64: FP64 on v_mfma_f64_16x16x4; kChainF32: FP32 operands on
+// v_mfma_f32_16x16x4; kChainBF3: FP64 operands split into bf16 hi + lo, three
+// v_mfma_f32_16x16x16_bf16 per step (lo lo dropped), FP32 accumulation.
+// NM, NN: blocks of 16 of the output tile in m and n; NI: blocks of 16 kc
+// values formed at once.
+// Lane l holds kj = KL (l / 16) + t of a chunk in either operand (any
+// assignment of k values to lanes and steps gives the same products as long as
+// both operands share it).  Rows past an extent re-read its last one, kj and
+// kc values past a range are read from what follows (the buffers end in
+// read_pad values) and set to zero in both operands.
+template <int MODE, int LAY, int NM, int NI, int NN, bool BATCH>
+__global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const KInst* __restrict__ insts, KInst one) {
+    typedef typename std::conditional<MODE == kChainF32, float, double>::type E;         // operands
+    typedef typename std::conditional<MODE == kChainF64, d4_t, f4_t>::type A4;           // accumulators
+    typedef typename std::conditional<MODE == kChainF64, double, float>::type AE;
+    constexpr int KL = MODE == kChainF64 ? 2 : 4, KC = 4 * KL, W = kChainThreads / 64;
+    typedef Frag<E, NI, NN, KL> F;
+    __shared__ AE red[W][NM * NN * 4][64];
+    const KInst& I = BATCH ? insts[blockIdx.y] : one;
+    if (I.gate && *I.gate == 0) return;
+    // work-group w runs on XCD w mod 8: contiguous runs of the g-major list of
+    // tiles per XCD, so that its L2 holds the environments of a few g
+    const int T = I.ntile * I.G, per = (T + 7) / 8, pos = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (int(blockIdx.x >> 3) >= per || pos >= T) return;
+    const int g = pos / I.ntile;
+    const KTile tk = I.tiles[pos - g * I.ntile];
+    const double* __restrict__ coef = I.coef + (long long)g * I.nc;
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int li = lane % 16, lk = lane / 16;
+    // row of A that lane li supplies: FP64 results hold row 4 v + l / 16 in
+    // element v, so block row p carries kc = 4 (p mod 4) + p / 4 and a lane's
+    // four values of I are consecutive kc, as P is read
+    const int ai = MODE == kChainF64 ? 4 * (li % 4) + li / 4 : li;
+    int pm[NM], bn[NN];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) pm[i] = min(tk.m0 + 16 * i + li, tk.m1 - 1);
+#pragma unroll
+    for (int i = 0; i < NN; ++i) bn[i] = min(tk.n0 + 16 * i + li, tk.n1 - 1);
+    const int nm = (tk.m1 - tk.m0 + 15) / 16;
+    A4 acc[NM][NN], in[NI][NN];
+#pragma unroll
+    for (int i = 0; i < NM; ++i)
+#pragma unroll
+        for (int j = 0; j < NN; ++j) acc[i][j] = A4{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NN; ++j) in[i][j] = A4{0, 0, 0, 0};
+
+    // the chunks of this wavefront's steps as one sequence: every step holds
+    // a segment and every segment a kj value (checked with the lists)
+    int st = tk.s0 + wave;
+    KStep fs{};
+    KSeg sg{};
+    int s = 0, kb = 0;
+    if (st < tk.s1) {
+        fs = I.steps[st];
+        s = fs.g0;
+        sg = I.segs[s];
+        kb = sg.k0;
+    }
+    auto fetch = [&](F& f) {
+        f.cf = E(coef[sg.cidx]);
+        f.nk = sg.k1 - kb;
+        const E* __restrict__ A = static_cast<const E*>(I.in[sg.a_buf].p) + g * I.in[sg.a_buf].gs + sg.a_off;
+        const E* __restrict__ B = static_cast<const E*>(I.in[sg.b_buf].p) + g * I.in[sg.b_buf].gs + sg.b_off;
+        if constexpr (LAY == kChainHeff) {  // A(kc, kj) at kj * lda + kc
+            A += (long long)kb * sg.lda;
+#pragma unroll
+            for (int t = 0; t < KL; ++t) {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) {
+                    const int r = min(fs.kc0 + 16 * i + ai, fs.kc1 - 1);
+                    f.a[i][t] = at(A, unsigned(KL * lk * sg.lda + r));
+                }
+                A += sg.lda;
+            }
+        } else {  // A(kc, kj) at kc * lda + kj
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int r = min(fs.kc0 + 16 * i + ai, fs.kc1 - 1);
+                read_run(A + kb, unsigned(r * sg.lda + KL * lk), f.a[i]);
+            }
+        }
+        if constexpr (LAY == kChainEnvL) {  // B(kj, n) at kj * ldb + n
+            B += (long long)kb * sg.ldb;
+#pragma unroll
+            for (int t = 0; t < KL; ++t) {
+#pragma unroll
+                for (int j = 0; j < NN; ++j) f.b[j][t] = at(B, unsigned(KL * lk * sg.ldb + bn[j]));
+                B += sg.ldb;
+            }
+        } else {  // B(kj, n) at n * ldb + kj
+#pragma unroll
+            for (int j = 0; j < NN; ++j) read_run(B + kb, unsigned(bn[j] * sg.ldb + KL * lk), f.b[j]);
+        }
+        kb += KC;
+        f.last = false;
+        if (kb >= sg.k1) {
+            ++s;
+            if (s >= fs.g1) {
+                f.last = true;
+                st += W;
+                if (st < tk.s1) {
+                    fs = I.steps[st];
+                    s = fs.g0;
+                }
+            }
+            if (st < tk.s1) {
+                sg = I.segs[s];
+                kb = sg.k0;
+            }
+        }
+    };
+    KStep cs{};  // the step whose inner product is being formed
+    int cst = st;
+    if (cst < tk.s1) cs = fs;
+    auto products = [&](F& f) {
+        if (f.nk < KC) {
+#pragma unroll
+            for (int t = 0; t < KL; ++t) {
+                const bool on = KL * lk + t < f.nk;
+#pragma unroll
+                for (int i = 0; i < NI; ++i) f.a[i][t] = on ? f.a[i][t] : E(0);
+#pragma unroll
+                for (int j = 0; j < NN; ++j) f.b[j][t] = on ? f.b[j][t] : E(0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NN; ++j)
+#pragma unroll
+            for (int t = 0; t < KL; ++t) f.b[j][t] *= f.cf;
+        const int ni = (cs.kc1 - cs.kc0 + 15) / 16;
+        if constexpr (MODE == kChainBF3) {
+            s4_t bh[NN], bl[NN];
+#pragma unroll
+            for (int j = 0; j < NN; ++j)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    short h, l;
+                    split_bf16(f.b[j][t], h, l);
+                    bh[j][t] = h;
+                    bl[j][t] = l;
+                }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                if (i >= ni) break;
+                s4_t ah, al;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    short h, l;
+                    split_bf16(f.a[i][t], h, l);
+                    ah[t] = h;
+                    al[t] = l;
+                }
+#pragma unroll
+                for (int j = 0; j < NN; ++j) {
+                    in[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh[j], in[i][j], 0, 0, 0);
+                    in[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl[j], in[i][j], 0, 0, 0);
+                    in[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh[j], in[i][j], 0, 0, 0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                if (i >= ni) break;
+#pragma unroll
+                for (int j = 0; j < NN; ++j)
+#pragma unroll
+                    for (int t = 0; t < KL; ++t) {
+                        if constexpr (MODE == kChainF64)
+                            in[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[i][t], f.b[j][t], in[i][j], 0, 0, 0);
+                        else
+                            in[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[i][t], f.b[j][t], in[i][j], 0, 0, 0);
+                    }
+            }
+        }
+        if (!f.last) return;
+        // O += P I, 16 kc values at a time
+        const E* __restrict__ P = static_cast<const E*>(I.in[cs.p_buf].p) + g * I.in[cs.p_buf].gs + cs.p_off;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            if (i >= ni) break;
+            const int k0 = cs.kc0 + 16 * i;
+            E p[NM][4];
+            if constexpr (LAY == kChainEnvL) {  // P(m, kc) at kc * ldp + m
+                const E* __restrict__ q = P + (long long)k0 * cs.ldp;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                    for (int a = 0; a < NM; ++a) p[a][v] = at(q, unsigned(4 * lk * cs.ldp + pm[a]));
+                    q += cs.ldp;
+                }
+            } else {  // P(m, kc) at m * ldp + kc
+#pragma unroll
+                for (int a = 0; a < NM; ++a) read_run(P + k0, unsigned(pm[a] * cs.ldp + 4 * lk), p[a]);
+            }
+            if (k0 + 16 > cs.kc1) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const bool on = k0 + 4 * lk + v < cs.kc1;
+#pragma unroll
+                    for (int a = 0; a < NM; ++a) p[a][v] = on ? p[a][v] : E(0);
+#pragma unroll
+                    for (int j = 0; j < NN; ++j) in[i][j][v] = on ? in[i][j][v] : AE(0);
+                }
+            }
+            if constexpr (MODE == kChainBF3) {
+                s4_t ih[NN], il[NN];
+#pragma unroll
+                for (int j = 0; j < NN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        short h, l;
+                        split_bf16(in[i][j][v], h, l);
+                        ih[j][v] = h;
+                        il[j][v] = l;
+                    }
+#pragma unroll
+                for (int a = 0; a < NM; ++a) {
+                    if (a >= nm) break;
+                    s4_t ph, pl;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        short h, l;
+                        split_bf16(p[a][v], h, l);
+                        ph[v] = h;
+                        pl[v] = l;
+                    }
+#pragma unroll
+                    for (int j = 0; j < NN; ++j) {
+                        acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pl, ih[j], acc[a][j], 0, 0, 0);
+                        acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ph, il[j], acc[a][j], 0, 0, 0);
+                        acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ph, ih[j], acc[a][j], 0, 0, 0);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int a = 0; a < NM; ++a) {
+                    if (a >= nm) break;
+#pragma unroll
+                    for (int j = 0; j < NN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            if constexpr (MODE == kChainF64)
+                                acc[a][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[a][v], in[i][j][v], acc[a][j], 0, 0, 0);
+                            else
+                                acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[a][v], in[i][j][v], acc[a][j], 0, 0, 0);
+                        }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NN; ++j) in[i][j] = A4{0, 0, 0, 0};
+        }
+        cst += W;
+        if (cst < tk.s1) cs = I.steps[cst];
+    };
+    if (st < tk.s1) {
+        F f0, f1;
+        fetch(f0);
+        for (;;) {
+            const bool m1 = st < tk.s1;
+            if (m1) fetch(f1);
+            products(f0);
+            if (!m1) break;
+            const bool m0 = st < tk.s1;
+            if (m0) fetch(f0);
+            products(f1);
+            if (!m0) break;
+        }
+    }
+    // the wavefronts' sums in wavefront order
+    const int nw = min(W, tk.s1 - tk.s0);
+    if (wave < nw || wave == 0) {
+#pragma unroll
+        for (int a = 0; a < NM; ++a)
+#pragma unroll
+            for (int j = 0; j < NN; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[wave][(a * NN + j) * 4 + v][lane] = acc[a][j][v];
+    }
+    __syncthreads();
+    const double cs_out = tk.cidx < 0 ? 1.0 : coef[tk.cidx];
+    double* __restrict__ out = I.out[tk.out] + g * I.ogs + tk.o_off;
+    const int nelem = nm * NN * 4;
+    for (int e = wave; e < nelem; e += W) {
+        const int v = e % 4, j = (e / 4) % NN, a = e / (4 * NN);
+        const int m = tk.m0 + 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = tk.n0 + 16 * j + li;
+        if (m >= tk.m1 || n >= tk.n1) continue;
+        AE sum = red[0][e][lane];
+        for (int w = 1; w < nw; ++w) sum += red[w][e][lane];
+        const double val = cs_out * double(sum);
+        if constexpr (LAY == kChainHeff) {
+            const int q = I.map[tk.map_off + n * tk.o_ns + m];
+            if (q >= 0) out[q] = val;
+        } else {
+            out[(long long)m * tk.o_ms + n] = val;
+        }
+    }
+}
+
+// dense particle-number blocks of the site vector (blockIdx.y = 0) and, for
+// g = blockIdx.y - 1, the blocks of the two singly occupied states rotated by
+// r(beta_g) (Eq. [expSy]; it leaves the other two states alone)
+template <class E, bool BATCH>
+__global__ __launch_bounds__(256) void k_xprep(const KPrep* __restrict__ insts, KPrep one) {
+    const KPrep& I = BATCH ? insts[blockIdx.z] : one;
+    if (I.gate && *I.gate == 0) return;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.y == 0) {
+        if (e >= I.nd) return;
+        const int q = I.map[e];
+        static_cast<E*>(I.xd)[e] = q >= 0 ? E(I.x[q]) : E(0);
+        return;
+    }
+    const int g = int(blockIdx.y) - 1;
+    if (g >= I.G || e >= I.nr) return;
+    const int qa = I.rmap[2 * e], qb = I.rmap[2 * e + 1];
+    const double a = qa >= 0 ? I.x[qa] : 0.0, b = qb >= 0 ? I.x[qb] : 0.0;
+    const double* __restrict__ r = I.coef + (long long)g * I.nc + I.crot;  // r(s, u) at 4 s + u
+    E* __restrict__ out = static_cast<E*>(I.xr) + (long long)g * 2 * I.nr;
+    out[e] = E(r[4 * 1 + 1] * a + r[4 * 1 + 2] * b);
+    out[I.nr + e] = E(r[4 * 2 + 1] * a + r[4 * 2 + 2] * b);
+}
+
+template <int MODE, int LAY>
+void launch_shape(hipStream_t s, int shape, dim3 grid, const KInst* insts, const KInst& one) {
+#define SPK_CHAIN(NM, NI, NN)                                                                                      \
+    if (LAY == kChainHeff && insts)                                                                                \
+        hipLaunchKernelGGL((k_chain<MODE, LAY, NM, NI, NN, LAY == kChainHeff>), grid, dim3(kChainThreads), 0, s, insts, one); \
+    else                                                                                                           \
+        hipLaunchKernelGGL((k_chain<MODE, LAY, NM, NI, NN, false>), grid, dim3(kChainThreads), 0, s, insts, one)
+    switch (shape) {
+        case 0: SPK_CHAIN(2, 2, 1); break;
+        case 1: SPK_CHAIN(4, 4, 1); break;
+        default: SPK_CHAIN(8, 4, 1); break;
+    }
+#undef SPK_CHAIN
+}
+
+// out(g, e) = sum over the task's terms of coef[cidx] * in(g, a_off + e): the
+// environment of one side with the unrotated MPO mixed in, for every g.  The
+// terms are staged in LDS 64 at a time, so that the loads of the sum are
+// independent of each other; every element adds its terms in list order.
+template <class E>
+__global__ __launch_bounds__(256) void k_premix(const MTask* __restrict__ tasks, const MTerm* __restrict__ terms,
+                                                const E* __restrict__ in, long long igs, E* __restrict__ out,
+                                                long long ogs, const double* __restrict__ coef) {
+    constexpr int kAtOnce = 64, kPer = 4;
+    __shared__ const E* sp[kAtOnce];
+    __shared__ double sc[kAtOnce];
+    const MTask tk = tasks[blockIdx.x];
+    in += blockIdx.y * igs;
+    out += blockIdx.y * ogs + tk.o_off;
+    for (int eb = 0; eb < tk.n; eb += kPer * 256) {
+        double acc[kPer] = {0.0, 0.0, 0.0, 0.0};
+        for (int tb = tk.t0; tb < tk.t1; tb += kAtOnce) {
+            const int nt = min(kAtOnce, tk.t1 - tb);
+            __syncthreads();
+            if ((int)threadIdx.x < nt) {
+                const MTerm tm = terms[tb + threadIdx.x];
+                sp[threadIdx.x] = in + tm.a_off;
+                sc[threadIdx.x] = coef[tm.cidx];
+            }
+            __syncthreads();
+            for (int t = 0; t < nt; ++t) {
+                const E* __restrict__ a = sp[t];
+                const double c = sc[t];
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    const int e = eb + threadIdx.x + u * 256;
+                    if (e < tk.n) acc[u] = fma(c, double(a[e]), acc[u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int e = eb + threadIdx.x + u * 256;
+            if (e < tk.n) out[e] = E(acc[u]);
+        }
+    }
+}
+
+}  // namespace
+
+const KShape kChainShapes[kNumChainShapes] = {{2, 2, 1}, {4, 4, 1}, {8, 4, 1}};
+
+void chain(hipStream_t s, int mode, int lay, int shape, int max_tiles, int ninst, const KInst* insts, const KInst& one) {
+    if (max_tiles <= 0 || ninst <= 0) return;
+    const dim3 grid((max_tiles + 7) / 8 * 8, ninst);
+    if (lay == kChainHeff) {
+        if (mode == kChainF64) launch_shape<kChainF64, kChainHeff>(s, shape, grid, insts, one);
+        else if (mode == kChainF32) launch_shape<kChainF32, kChainHeff>(s, shape, grid, insts, one);
+        else launch_shape<kChainBF3, kChainHeff>(s, shape, grid, insts, one);
+    } else if (lay == kChainEnvL) {
+        launch_shape<kChainF64, kChainEnvL>(s, shape, grid, insts, one);
+    } else {
+        launch_shape<kChainF64, kChainEnvR>(s, shape, grid, insts, one);
+    }
+}
+
+void xprep(hipStream_t s, bool f32, int max_n, int max_G, int ninst, const KPrep* insts, const KPrep& one) {
+    if (max_n <= 0 || ninst <= 0) return;
+    const dim3 grid((max_n + 255) / 256, max_G + 1, ninst);
+    if (f32 && insts) hipLaunchKernelGGL((k_xprep<float, true>), grid, dim3(256), 0, s, insts, one);
+    else if (f32) hipLaunchKernelGGL((k_xprep<float, false>), grid, dim3(256), 0, s, insts, one);
+    else if (insts) hipLaunchKernelGGL((k_xprep<double, true>), grid, dim3(256), 0, s, insts, one);
+    else hipLaunchKernelGGL((k_xprep<double, false>), grid, dim3(256), 0, s, insts, one);
+}
+
+void premix(hipStream_t s, bool f32, const MTask* tasks, int ntask, const MTerm* terms, const void* in, long long igs,
+            void* out, long long ogs, const double* coef, int G) {
+    if (ntask <= 0) return;
+    if (f32)
+        hipLaunchKernelGGL(k_premix<float>, dim3(ntask, G), dim3(256), 0, s, tasks, terms, static_cast<const float*>(in), igs,
+                           static_cast<float*>(out), ogs, coef);
+    else
+        hipLaunchKernelGGL(k_premix<double>, dim3(ntask, G), dim3(256), 0, s, tasks, terms, static_cast<const double*>(in),
+                           igs, static_cast<double*>(out), ogs, coef);
+}
+
+}  // namespace spk
+

@@ -114,6 +114,84 @@ void gather(hipStream_t s, const int* map, const double* src, double* dst, long 
 void gsum2(hipStream_t s, const double* pa, const double* pb, long long stride, int G, int n, double* outa,
            double* outb);
 
+// Chained block products (chain.hip): the lists of one launch, the same for
+// every quadrature point; a buffer's values of point g start at g * gs.
+constexpr int kChainF64 = 0, kChainF32 = 1, kChainBF3 = 2;     // arithmetic
+constexpr int kChainHeff = 0, kChainEnvL = 1, kChainEnvR = 2;  // operand layouts
+constexpr int kChainThreads = 256;
+// operand buffers: the environments left and right of the site, the dense
+// site tensor, its rotated singly occupied blocks, the pre-mixed environment
+enum KBufId { K_L = 0, K_R = 1, K_X = 2, K_XR = 3, K_LT = 4, K_NBUF = 5 };
+struct KBuf {
+    const void* p;
+    long long gs;
+};
+// one product of the inner sum: A(kc, kj) B(kj, n) over kj in [k0, k1)
+struct KSeg {
+    long long a_off, b_off;
+    int a_buf, b_buf, lda, ldb, k0, k1, cidx, pad;
+};
+// kc values [kc0, kc1) of P and the segments [g0, g1) of the inner sum
+struct KStep {
+    long long p_off;
+    int p_buf, ldp, kc0, kc1, g0, g1;
+};
+// output tile [m0, m1) x [n0, n1) of a block, steps [s0, s1), the sum times
+// coef[cidx] (cidx < 0: 1).  Environments: element (m, n) at o_off + m * o_ms
+// + n; H_eff x: at o_off + map[map_off + n * o_ns + m] where that is >= 0
+struct KTile {
+    long long o_off, map_off;
+    int out, m0, m1, n0, n1, o_ms, o_ns, s0, s1, cidx;
+};
+struct KInst {
+    const KTile* tiles;
+    const KStep* steps;
+    const KSeg* segs;
+    const int* map;
+    const double* coef;
+    KBuf in[K_NBUF];  // FP64, or FP32 in the FP32 mode
+    double* out[2];
+    long long ogs;    // output values per g
+    const int* gate;  // when set, the instance's work-groups return at once while *gate == 0
+    int ntile, nc, G, pad;
+};
+// dense and rotated site vectors of one instance: xd (nd values, x[map] or 0)
+// and per g xr (2 nr values: states 1, then 2, from x[rmap[2 e]], x[rmap[2 e + 1]])
+struct KPrep {
+    const double* x;
+    const int* map;
+    const int* rmap;
+    const double* coef;
+    void* xd;
+    void* xr;
+    const int* gate;
+    int nd, nr, nc, crot, G, pad;
+};
+// blocks of 16 of a tile in m, of kc values formed at once, in n
+struct KShape {
+    int nm, ni, nn;
+};
+constexpr int kNumChainShapes = 3;
+extern const KShape kChainShapes[kNumChainShapes];
+// values that may be read past the end of an operand buffer of blocks at most
+// ld wide
+inline long long read_pad(int ld) { return 16LL * ld + 64; }
+// one block of a pre-mixed environment and its terms
+struct MTask {
+    long long o_off;
+    int n, t0, t1, pad;
+};
+struct MTerm {
+    long long a_off;
+    int cidx, pad;
+};
+void premix(hipStream_t s, bool f32, const MTask* tasks, int ntask, const MTerm* terms, const void* in, long long igs,
+            void* out, long long ogs, const double* coef, int G);
+// max_tiles: the largest tile count times G of the instances; insts = null:
+// the one instance `one`
+void chain(hipStream_t s, int mode, int lay, int shape, int max_tiles, int ninst, const KInst* insts, const KInst& one);
+void xprep(hipStream_t s, bool f32, int max_n, int max_G, int ninst, const KPrep* insts, const KPrep& one);
+
 // Fused H_eff x / N_eff x (all quadrature points in one launch).  One
 // work-group per (g, bra particle-number block i of the left bond, rows
 // [r0, r0 + rows)), rows <= RC (a compile-time row count, 1..8).

@@ -292,6 +292,64 @@ struct TList {
     }
 };
 
+// lists of a chained product (the same for every quadrature point)
+struct ChainList {
+    int lay = spk::kChainHeff, shape = 0;
+    std::vector<spk::KTile> tiles;
+    std::vector<spk::KStep> steps;
+    std::vector<spk::KSeg> segs;
+    DArr<spk::KTile> dtiles;
+    DArr<spk::KStep> dsteps;
+    DArr<spk::KSeg> dsegs;
+    void begin_tile(spk::KTile t) {
+        t.s0 = t.s1 = int(steps.size());
+        tiles.push_back(t);
+    }
+    // opens a step of the last tile; a step left without segments is dropped
+    void begin_step(int p_buf, long long p_off, int ldp, int kc0, int kc1) {
+        drop_empty();
+        steps.push_back(spk::KStep{p_off, p_buf, ldp, kc0, kc1, int(segs.size()), int(segs.size())});
+        tiles.back().s1 = int(steps.size());
+    }
+    void add_seg(int a_buf, long long a_off, int lda, int b_buf, long long b_off, int ldb, int k0, int k1, int cidx) {
+        segs.push_back(spk::KSeg{a_off, b_off, a_buf, b_buf, lda, ldb, k0, k1, cidx, 0});
+        steps.back().g1 = int(segs.size());
+    }
+    void drop_empty() {
+        if (!steps.empty() && tiles.back().s1 > tiles.back().s0 && steps.back().g0 == steps.back().g1) {
+            steps.pop_back();
+            --tiles.back().s1;
+        }
+    }
+    void upload(hipStream_t s) {
+        dtiles.upload(tiles, s);
+        dsteps.upload(steps, s);
+        dsegs.upload(segs, s);
+    }
+};
+// one side's environment with the unrotated MPO mixed in
+struct MixList {
+    std::vector<spk::MTask> tasks;
+    std::vector<spk::MTerm> terms;
+    DArr<spk::MTask> dtasks;
+    DArr<spk::MTerm> dterms;
+    long long size = 0;   // values per quadrature point
+    double flops = 0.0;   // per quadrature point
+    void add_task(int n) {
+        tasks.push_back(spk::MTask{size, n, int(terms.size()), int(terms.size()), 0});
+        size += n;
+    }
+    void add_term(long long a_off, int cidx) {
+        terms.push_back(spk::MTerm{a_off, cidx, 0});
+        tasks.back().t1 = int(terms.size());
+        flops += 2.0 * tasks.back().n;
+    }
+    void upload(hipStream_t s) {
+        dtasks.upload(tasks, s);
+        dterms.upload(terms, s);
+    }
+};
+
 // buffer slots of a launch; B_BRA is the site tensor on the bra side of the
 // plain-path environment updates (the same as B_X except for the mixed
 // environments of an orthogonality constraint)
@@ -313,6 +371,7 @@ struct SitePlan {
     int nWr = 0;
     int c_wr(int e) const { return 2 * nW + 18 + e; }
     int c_r(int s, int u) const { return 2 * nW + 18 + nWr + 4 * s + u; }
+    int c_minus() const { return 2 * nW + 18 + nWr + 16; }
     // scratch sizes per quadrature point
     long long Tsize = 0, Vsize = 0, Zsize = 0, Ztsize = 0;
     BList p1, yout, envl_out, p1r, envr_out;
@@ -350,6 +409,14 @@ struct SitePlan {
     // environment Lt(sigma, c', sigma', i) = sum_c W~_g[c, c', sigma, sigma'] L_g(c, i)
     // (premix, once per local problem), V = sum_sigma' Lt Xd(sigma') (t_leftv)
     // and the identity-channel products T(0, i, sigma') for N_eff (t_left0)
+    // chained products: the environment updates, the pre-mixed environments
+    // they (and H_eff x at wide MPOs) use, the packed indices of the rotated
+    // site vector's two states
+    std::vector<std::array<int, 4>> wr_ent;  // unrotated MPO entries (a, b, s, s')
+    ChainList c_envl, c_envr;
+    MixList mix_l, mix_r;                    // empty: the products read the environment itself
+    std::vector<int> rmap_h;
+    DArr<int> rmap;
     CList premix, xrmix;
     TList t_leftv, t_left0;
     long long LTsize = 0;
@@ -402,15 +469,16 @@ struct sp_handle {
     long long mps_size = 0, max_site = 0;
     std::vector<SitePlan> plan;            // index k-1
     int path = SP_PATH_TILED;
-    DArr<double> T, V, qr_scratch, qr_r, tmp_site, Xd, ypart, nypart;
+    DArr<double> T, V, qr_scratch, qr_r, tmp_site, Xd, Xr, ypart, nypart;
     // pre-mixed left environment of one site (tiled block products); valid
     // for site lt_site while the generation of L[lt_site - 1] is lt_gen
     DArr<double> LT;
     long long LT_cap = 0;
     DArr<double> diag_part;  // partial sums of the split diagonal (kDiagSplitMax x max_site)
     std::vector<long long> Lgen;
-    int lt_site = -1;
+    int lt_site = -1;   // -1: none (the scratch holds a right environment, or nothing)
     long long lt_gen = -1;
+    long long Xr_cap = 0;
     long long Xd_cap = 0;
     int tr_split_max = 1;  // partial slots per quadrature point (tiled lists)
     long long T_cap = 0, V_cap = 0, qr_scratch_cap = 0, qr_r_cap = 0;
@@ -640,6 +708,14 @@ void build_env_layouts(sp_handle* h) {
     h->Lgen.assign(L + 1, 0);
 }
 
+// values the block products may read past the end of an operand buffer
+long long read_pad(const sp_handle* h) {
+    int ld = 1;
+    for (const Bond& b : h->bonds)
+        for (const NBlock& nb : b.nb) ld = std::max(ld, nb.dim);
+    return spk::read_pad(ld);
+}
+
 // Interior bonds 1..L-1 hold one buffer shared by L[k] and R[k]; bonds 0
 // and L hold two (the boundary ones and the full contractions).
 template <class T>
@@ -651,11 +727,11 @@ void alloc_env_set(const sp_handle* h, std::vector<DArr<T>>& mem, std::vector<DR
     l.assign(L + 1, {});
     r.assign(L + 1, {});
     for (int k = 0; k <= L; ++k) {
-        mem[k].alloc(size_t(h->G) * h->env[k].size);
+        mem[k].alloc(size_t(h->G) * h->env[k].size + read_pad(h));
         l[k].p = r[k].p = mem[k].p;
     }
-    mem[L + 1].alloc(size_t(h->G) * h->env[0].size);
-    mem[L + 2].alloc(size_t(h->G) * h->env[L].size);
+    mem[L + 1].alloc(size_t(h->G) * h->env[0].size + read_pad(h));
+    mem[L + 2].alloc(size_t(h->G) * h->env[L].size + read_pad(h));
     r[0].p = mem[L + 1].p;
     r[L].p = mem[L + 2].p;
 }
@@ -744,11 +820,12 @@ void build_plan(sp_handle* h, int k) {
                     if (op[s2 * 4 + v] != 0.0) {
                         byWr[size_t(s2) * wr + ab.second].push_back({ab.first, v, int(wr_val.size())});
                         wr_val.push_back(op[s2 * 4 + v]);
+                        P.wr_ent.push_back({ab.first, ab.second, s2, v});
                     }
         }
     }
     P.nWr = int(wr_val.size());
-    P.nc = 2 * P.nW + 18 + P.nWr + 16;
+    P.nc = 2 * P.nW + 18 + P.nWr + 17;
     P.coef_h.assign(size_t(G) * P.nc, 0.0);
     for (int g = 0; g < G; ++g) {
         double* cf = &P.coef_h[size_t(g) * P.nc];
@@ -764,6 +841,7 @@ void build_plan(sp_handle* h, int k) {
         for (int s = 0; s < 4; ++s)
             for (int u = 0; u < 4; ++u) cf[P.c_gr(s, u)] = h->qcoef[g] * rot_value(s, u, h->qc[g], h->qs[g]);
         cf[P.c_one()] = 1.0;
+        cf[P.c_minus()] = -1.0;
         for (int e = 0; e < P.nWr; ++e) cf[P.c_wr(e)] = wr_val[e];
         for (int s = 0; s < 4; ++s)
             for (int u = 0; u < 4; ++u) cf[P.c_r(s, u)] = rot_value(s, u, h->qc[g], h->qs[g]);
@@ -1501,6 +1579,199 @@ void build_plan(sp_handle* h, int k) {
                 }
 }
 
+// chained-product lists of site k (tiled path)
+void build_chain(sp_handle* h, int k) {
+    SitePlan& P = h->plan[k - 1];
+    const Bond& bl = h->bonds[k - 1];
+    const Bond& br = h->bonds[k];
+    const SiteInfo& si = h->sites[k - 1];
+    const EnvLayout& el = h->env[k - 1];
+    const EnvLayout& er = h->env[k];
+    const int wl = h->w[k - 1], wr = h->w[k], nl = int(bl.nb.size());
+    // dense particle-number blocks X(j, sigma) (the layout of xmap) and, for
+    // the singly occupied states, the rotated ones
+    std::vector<long long> xd(size_t(nl) * 4, -1), xr(size_t(nl) * 4, -1);
+    long long nd = 0, nr = 0;
+    auto right_nb = [&](int j, int q) { return br.nblock(bl.nb[j].n + kSigmaN[q]); };
+    for (int j = 0; j < nl; ++j)
+        for (int q = 0; q < 4; ++q)
+            if (right_nb(j, q) >= 0) {
+                xd[size_t(j) * 4 + q] = nd;
+                nd += (long long)bl.nb[j].dim * br.nb[right_nb(j, q)].dim;
+            }
+    SP_REQUIRE(nd == P.Xd_size, "internal: dense site layout");
+    for (int j = 0; j < nl; ++j)
+        if (right_nb(j, 1) >= 0) {
+            const long long n = (long long)bl.nb[j].dim * br.nb[right_nb(j, 1)].dim;
+            for (long long e = 0; e < n; ++e) {
+                P.rmap_h.push_back(P.xmap_h[xd[size_t(j) * 4 + 1] + e]);
+                P.rmap_h.push_back(P.xmap_h[xd[size_t(j) * 4 + 2] + e]);
+            }
+            xr[size_t(j) * 4 + 1] = nr;
+            nr += n;
+        }
+    for (int j = 0; j < nl; ++j)
+        if (xr[size_t(j) * 4 + 1] >= 0) xr[size_t(j) * 4 + 2] = nr + xr[size_t(j) * 4 + 1];
+    auto xbuf = [&](int q) { return q == 1 || q == 2 ? spk::K_XR : spk::K_X; };
+    auto xoff = [&](int j, int q) { return (q == 1 || q == 2 ? xr : xd)[size_t(j) * 4 + q]; };
+    // the rows of N-block j that columns [c0, c1) of N-block jb reach through
+    // the rotated state q (every state the rotation mixes into q), and the
+    // columns that rows reach, as one range
+    auto rows_of = [&](int jb, int q, int c0, int c1, bool rotated, int& k0, int& k1) {
+        k0 = INT32_MAX;
+        k1 = -1;
+        const NBlock& NB = br.nb[jb];
+        for (int sb = NB.s0; sb < NB.s1; ++sb) {
+            const Sector& SB = br.sec[sb];
+            if (SB.ro + SB.dim <= c0 || SB.ro >= c1) continue;
+            for (int u = 0; u < 4; ++u) {
+                if (rotated ? !rot_nonzero(q, u) : u != q) continue;
+                const int sa = bl.sector(SB.n - kSigmaN[u], SB.m2 - kSigma2M[u]);
+                if (sa < 0) continue;
+                k0 = std::min(k0, bl.sec[sa].ro);
+                k1 = std::max(k1, bl.sec[sa].ro + bl.sec[sa].dim);
+            }
+        }
+        return k1 > k0;
+    };
+    auto cols_of = [&](int j, int q, int r0, int r1, bool rotated, int& k0, int& k1) {
+        k0 = INT32_MAX;
+        k1 = -1;
+        const NBlock& NA = bl.nb[j];
+        for (int sa = NA.s0; sa < NA.s1; ++sa) {
+            const Sector& SA = bl.sec[sa];
+            if (SA.ro + SA.dim <= r0 || SA.ro >= r1) continue;
+            for (int u = 0; u < 4; ++u) {
+                if (rotated ? !rot_nonzero(q, u) : u != q) continue;
+                const int sb = br.sector(SA.n + kSigmaN[u], SA.m2 + kSigma2M[u]);
+                if (sb < 0) continue;
+                k0 = std::min(k0, br.sec[sb].ro);
+                k1 = std::max(k1, br.sec[sb].ro + br.sec[sb].dim);
+            }
+        }
+        return k1 > k0;
+    };
+    // entries by (sigma, right channel) as (left channel, sigma', entry) and
+    // by (sigma, left channel) as (right channel, sigma', entry); where many
+    // channels meet in one (wide MPOs) the environment is mixed first: once
+    // for all the groups (sigma, channel, sigma') that sum the same blocks with
+    // the same coefficients up to a common sign (an operator that acts as the
+    // identity or the parity gives one group per local state), and groups of
+    // one term read the environment block itself (K = 12 centre: 231 mixed
+    // blocks instead of 1414)
+    std::vector<std::vector<std::array<int, 3>>> byR(size_t(4) * wr), byL(size_t(4) * wl);
+    std::set<std::array<int, 3>> gl, gr;
+    for (int e = 0; e < int(P.wr_ent.size()); ++e) {
+        const auto& q = P.wr_ent[e];
+        byR[size_t(q[2]) * wr + q[1]].push_back({q[0], q[3], e});
+        byL[size_t(q[2]) * wl + q[0]].push_back({q[1], q[3], e});
+        gl.insert({q[2], q[1], q[3]});
+        gr.insert({q[2], q[0], q[3]});
+    }
+    const bool mixed_l = 2 * P.wr_ent.size() > 3 * gl.size(), mixed_r = 2 * P.wr_ent.size() > 3 * gr.size();
+    // V(sigma, c', i) = sum of (block, coefficient, ket block j, sigma') terms
+    // of the left environment, Zt(sigma, c, b) likewise of the right one
+    struct Src {
+        int buf, cols, j, q, cidx;
+        long long off;
+    };
+    std::map<std::array<int, 3>, std::vector<Src>> vsrc, zsrc;
+    const double* wval = P.coef_h.data() + P.c_wr(0);
+    for (int side = 0; side < 2; ++side) {
+        const auto& by = side ? byL : byR;
+        const EnvLayout& e = side ? er : el;
+        MixList& mix = side ? P.mix_r : P.mix_l;
+        auto& src = side ? zsrc : vsrc;
+        const int nch = side ? wl : wr, nb = int((side ? br : bl).nb.size());
+        std::map<std::vector<std::pair<int, double>>, std::pair<long long, double>> same;  // terms -> mixed block, its sign
+        for (int sig = 0; sig < 4; ++sig)
+            for (int c = 0; c < nch; ++c)
+                for (int i = 0; i < nb; ++i) {
+                    std::map<std::pair<int, int>, std::vector<std::pair<int, int>>> groups;  // (j, q) -> (block, entry)
+                    for (const auto& ent : by[size_t(sig) * nch + c]) {
+                        const int b = e.find(ent[0], i), q = ent[1];
+                        if (b < 0) continue;
+                        const int j = e.blk[b].j;
+                        if (side == 0 ? right_nb(j, q) < 0 : bl.nblock(br.nb[j].n - kSigmaN[q]) < 0) continue;
+                        groups[{j, q}].push_back({b, ent[2]});
+                    }
+                    for (const auto& g : groups) {
+                        const EnvBlk& b0 = e.blk[g.second[0].first];
+                        if (!(side ? mixed_r : mixed_l) || g.second.size() == 1) {
+                            for (const auto& t : g.second)
+                                src[{sig, c, i}].push_back(Src{side ? spk::K_R : spk::K_L, b0.cols, g.first.first, g.first.second,
+                                                               P.c_wr(t.second), e.blk[t.first].off});
+                            continue;
+                        }
+                        const double sgn = wval[g.second[0].second] < 0.0 ? -1.0 : 1.0;
+                        std::vector<std::pair<int, double>> key;
+                        for (const auto& t : g.second) key.push_back({t.first, sgn * wval[t.second]});
+                        auto it = same.find(key);
+                        if (it == same.end()) {
+                            it = same.emplace(key, std::make_pair(mix.size, sgn)).first;
+                            mix.add_task(b0.rows * b0.cols);
+                            for (const auto& t : g.second) mix.add_term(e.blk[t.first].off, P.c_wr(t.second));
+                        }
+                        src[{sig, c, i}].push_back(Src{spk::K_LT, b0.cols, g.first.first, g.first.second,
+                                                       it->second.second == sgn ? P.c_one() : P.c_minus(), it->second.first});
+                    }
+                }
+    }
+    auto shape_for = [](int m) { return m <= 32 ? 0 : (m <= 64 ? 1 : 2); };
+    int dl = 1, dr = 1;
+    for (const NBlock& nb : bl.nb) dl = std::max(dl, nb.dim);
+    for (const NBlock& nb : br.nb) dr = std::max(dr, nb.dim);
+    // left environment L[k](c', b, b') = sum_sigma X(a, sigma, b)^T V(sigma, c', a)(a, b')
+    P.c_envl.lay = spk::kChainEnvL;
+    P.c_envl.shape = shape_for(dr);
+    P.c_envr.lay = spk::kChainEnvR;
+    P.c_envr.shape = shape_for(dl);
+    for (int side = 0; side < 2; ++side) {
+        ChainList& C = side ? P.c_envr : P.c_envl;
+        const spk::KShape sh = spk::kChainShapes[C.shape];
+        const int TM = 16 * sh.nm, TI = 16 * sh.ni, TN = 16 * sh.nn;
+        for (const EnvBlk& OB : (side ? el : er).blk)
+            for (int m0 = 0; m0 < OB.rows; m0 += TM)
+                for (int n0 = 0; n0 < OB.cols; n0 += TN) {
+                    const int m1 = std::min(OB.rows, m0 + TM), n1 = std::min(OB.cols, n0 + TN);
+                    C.begin_tile(spk::KTile{OB.off, 0, 0, m0, m1, n0, n1, OB.cols, 0, 0, 0, -1});
+                    for (int q = 0; q < 4; ++q) {
+                        int b0, b1;
+                        if (side == 0) {  // X(a, q)^T: b = OB.i, a on the left bond
+                            const int a = bl.nblock(br.nb[OB.i].n - kSigmaN[q]);
+                            if (a < 0) continue;
+                            auto it = vsrc.find({q, OB.c, a});
+                            if (it == vsrc.end() || !rows_of(OB.i, q, m0, m1, false, b0, b1)) continue;
+                            for (int c0 = b0; c0 < b1; c0 += TI) {
+                                C.begin_step(spk::K_X, xd[size_t(a) * 4 + q], OB.rows, c0, std::min(b1, c0 + TI));
+                                for (const Src& v : it->second) {
+                                    int k0, k1;
+                                    SP_REQUIRE(right_nb(v.j, v.q) == OB.j, "internal: left environment particle numbers");
+                                    if (rows_of(OB.j, v.q, n0, n1, true, k0, k1))
+                                        C.add_seg(v.buf, v.off, v.cols, xbuf(v.q), xoff(v.j, v.q), OB.cols, k0, k1, v.cidx);
+                                }
+                            }
+                        } else {  // X(a, q): a = OB.i, b on the right bond
+                            const int b = right_nb(OB.i, q);
+                            if (b < 0) continue;
+                            auto it = zsrc.find({q, OB.c, b});
+                            if (it == zsrc.end() || !cols_of(OB.i, q, m0, m1, false, b0, b1)) continue;
+                            for (int c0 = b0; c0 < b1; c0 += TI) {
+                                C.begin_step(spk::K_X, xd[size_t(OB.i) * 4 + q], br.nb[b].dim, c0, std::min(b1, c0 + TI));
+                                for (const Src& v : it->second) {
+                                    int k0, k1;
+                                    SP_REQUIRE(right_nb(OB.j, v.q) == v.j, "internal: right environment particle numbers");
+                                    if (cols_of(OB.j, v.q, n0, n1, true, k0, k1))
+                                        C.add_seg(v.buf, v.off, v.cols, xbuf(v.q), xoff(OB.j, v.q), br.nb[v.j].dim, k0, k1, v.cidx);
+                                }
+                            }
+                        }
+                    }
+                    C.drop_empty();
+                }
+    }
+}
+
 // fused H_eff x plan: column descriptors, products per bra block, channels
 // per output sigma, output lists and row-chunk tasks
 // LDS budget of the fused H_eff kernel per work-group (doubles): the default,
@@ -1807,6 +2078,11 @@ void upload_plan(sp_handle* h, int k) {
     P.t_envl.upload(s);
     P.t_zr.upload(s);
     P.t_envr.upload(s);
+    P.c_envl.upload(s);
+    P.c_envr.upload(s);
+    P.mix_l.upload(s);
+    P.mix_r.upload(s);
+    P.rmap.upload(P.rmap_h, s);
     upload_fused(h, k);
 }
 
@@ -1870,6 +2146,57 @@ void validate(const TList& b, const Sizes& sz, long long ncoef, long long map_si
             check_span(a_first, a_last, sz[g.a_buf], what);
             check_span(b_first, b_last, sz[g.b_buf], what);
             check_span(g.cidx, g.cidx, ncoef, what);
+        }
+    }
+}
+
+// bounds of a chained product: in[] the values per quadrature point of every
+// operand buffer, nout of the output, npart the outputs a tile may scatter to
+void validate(const ChainList& C, const std::array<long long, spk::K_NBUF>& in, long long nout, long long map_size,
+              long long npart, long long ncoef, const char* what) {
+    if (C.shape < 0 || C.shape >= spk::kNumChainShapes) throw SpError(SP_EINVAL, std::string("internal shape: ") + what);
+    const spk::KShape sh = spk::kChainShapes[C.shape];
+    for (const spk::KTile& t : C.tiles) {
+        if (t.m0 < 0 || t.n0 < 0 || t.m1 <= t.m0 || t.n1 <= t.n0 || t.m1 - t.m0 > 16 * sh.nm || t.n1 - t.n0 > 16 * sh.nn ||
+            t.s0 < 0 || t.s1 < t.s0 || t.s1 > int(C.steps.size()) || t.out < 0 || t.out > 1)
+            throw SpError(SP_EINVAL, std::string("internal tile: ") + what);
+        if (t.cidx >= 0) check_span(t.cidx, t.cidx, ncoef, what);
+        if (C.lay == spk::kChainHeff) {
+            check_span(t.map_off + (long long)t.n0 * t.o_ns + t.m0, t.map_off + (long long)(t.n1 - 1) * t.o_ns + t.m1 - 1, map_size, what);
+            check_span(t.o_off, t.o_off + npart - 1, nout, what);
+        } else {
+            check_span(t.o_off + (long long)t.m0 * t.o_ms + t.n0, t.o_off + (long long)(t.m1 - 1) * t.o_ms + t.n1 - 1, nout, what);
+        }
+        for (int q = t.s0; q < t.s1; ++q) {
+            const spk::KStep& p = C.steps[q];
+            if (p.kc0 < 0 || p.kc1 <= p.kc0 || p.kc1 - p.kc0 > 16 * sh.ni || p.g0 < 0 || p.g1 <= p.g0 || p.g1 > int(C.segs.size()))
+                throw SpError(SP_EINVAL, std::string("internal step: ") + what);
+            const bool pt = C.lay == spk::kChainEnvL;
+            check_span(p.p_off + (pt ? (long long)p.kc0 * p.ldp + t.m0 : (long long)t.m0 * p.ldp + p.kc0),
+                       p.p_off + (pt ? (long long)(p.kc1 - 1) * p.ldp + t.m1 - 1 : (long long)(t.m1 - 1) * p.ldp + p.kc1 - 1),
+                       in[p.p_buf], what);
+            for (int i = p.g0; i < p.g1; ++i) {
+                const spk::KSeg& g = C.segs[i];
+                if (g.k0 < 0 || g.k1 <= g.k0) throw SpError(SP_EINVAL, std::string("internal segment: ") + what);
+                const bool at = C.lay == spk::kChainHeff, bt = C.lay == spk::kChainEnvL;
+                check_span(g.a_off + (at ? (long long)g.k0 * g.lda + p.kc0 : (long long)p.kc0 * g.lda + g.k0),
+                           g.a_off + (at ? (long long)(g.k1 - 1) * g.lda + p.kc1 - 1 : (long long)(p.kc1 - 1) * g.lda + g.k1 - 1),
+                           in[g.a_buf], what);
+                check_span(g.b_off + (bt ? (long long)g.k0 * g.ldb + t.n0 : (long long)t.n0 * g.ldb + g.k0),
+                           g.b_off + (bt ? (long long)(g.k1 - 1) * g.ldb + t.n1 - 1 : (long long)(t.n1 - 1) * g.ldb + g.k1 - 1),
+                           in[g.b_buf], what);
+                check_span(g.cidx, g.cidx, ncoef, what);
+            }
+        }
+    }
+}
+
+void validate(const MixList& m, long long nin, long long nout, long long ncoef, const char* what) {
+    for (const spk::MTask& t : m.tasks) {
+        check_span(t.o_off, t.o_off + t.n - 1, nout, what);
+        for (int i = t.t0; i < t.t1; ++i) {
+            check_span(m.terms[i].a_off, m.terms[i].a_off + t.n - 1, nin, what);
+            check_span(m.terms[i].cidx, m.terms[i].cidx, ncoef, what);
         }
     }
 }
@@ -2033,6 +2360,18 @@ void validate_plans(sp_handle* h) {
             validate(P.t_envl, t, nco, ms, xs, "tiled left environment");
             t[B_OUT] = Lb;
             validate(P.t_envr, t, nco, ms, xs, "tiled right environment");
+            if (h->path == SP_PATH_TILED) {
+                const long long Lg = h->env[k - 1].size, Rg = h->env[k].size;
+                if (G * std::max(P.mix_l.size, P.mix_r.size) > h->LT_cap || G * (long long)P.rmap_h.size() > h->Xr_cap)
+                    throw SpError(SP_EINVAL, "internal: scratch of the chained products too small");
+                for (int e : P.rmap_h)
+                    if (e >= xs) throw SpError(SP_EINVAL, "internal: packed map out of range");
+                validate(P.mix_l, Lg, P.mix_l.size, P.nc, "pre-mixed left environment");
+                validate(P.mix_r, Rg, P.mix_r.size, P.nc, "pre-mixed right environment");
+                const long long nxr = (long long)P.rmap_h.size();
+                validate(P.c_envl, {Lg, 0, P.Xd_size, nxr, P.mix_l.size}, Rg, 0, 0, P.nc, "left environment update");
+                validate(P.c_envr, {0, Rg, P.Xd_size, nxr, P.mix_r.size}, Lg, 0, 0, P.nc, "right environment update");
+            }
             if (P.Xd_size > h->Xd_cap) throw SpError(SP_EINVAL, "internal: dense site scratch too small");
         }
         validate_fused(h, k);
@@ -2235,6 +2574,63 @@ bool heff_apply(sp_handle* h, int k, const double* x, double* y, double* ny, boo
     return false;
 }
 
+// operands of a chained product at site k (x prepared by site_vectors)
+spk::KInst chain_inst(sp_handle* h, int k, const ChainList& C, const MixList& mix) {
+    const SitePlan& P = h->plan[k - 1];
+    spk::KInst I{};
+    I.tiles = C.dtiles.p;
+    I.steps = C.dsteps.p;
+    I.segs = C.dsegs.p;
+    I.map = P.xmap.p;
+    I.coef = P.coef.p;
+    I.in[spk::K_L] = {h->envL[k - 1].p, h->env[k - 1].size};
+    I.in[spk::K_R] = {h->envR[k].p, h->env[k].size};
+    I.in[spk::K_X] = {h->Xd.p, 0};
+    I.in[spk::K_XR] = {h->Xr.p, (long long)P.rmap_h.size()};
+    I.in[spk::K_LT] = {h->LT.p, mix.size};
+    I.ntile = int(C.tiles.size());
+    I.nc = P.nc;
+    I.G = h->G;
+    return I;
+}
+
+// dense and rotated copies of the packed site vector x
+spk::KPrep prep_inst(sp_handle* h, int k, const double* x) {
+    const SitePlan& P = h->plan[k - 1];
+    spk::KPrep I{};
+    I.x = x;
+    I.map = P.xmap.p;
+    I.rmap = P.rmap.p;
+    I.coef = P.coef.p;
+    I.xd = h->Xd.p;
+    I.xr = h->Xr.p;
+    I.nd = int(P.Xd_size);
+    I.nr = int(P.rmap_h.size() / 2);
+    I.nc = P.nc;
+    I.crot = P.c_r(0, 0);
+    I.G = h->G;
+    return I;
+}
+void site_vectors(sp_handle* h, int k, const double* x) {
+    const spk::KPrep I = prep_inst(h, k, x);
+    spk::xprep(h->stream, false, std::max(I.nd, I.nr), h->G, 1, nullptr, I);
+}
+
+// one environment update as a chained product: out, of the given values per g
+void env_chain(sp_handle* h, int k, const ChainList& C, const MixList& mix, const double* env, long long esize, double* out,
+               long long osize) {
+    const SitePlan& P = h->plan[k - 1];
+    site_vectors(h, k, site_ptr(h, k));
+    if (!mix.tasks.empty()) {
+        spk::premix(h->stream, false, mix.dtasks.p, int(mix.tasks.size()), mix.dterms.p, env, esize, h->LT.p, mix.size, P.coef.p, h->G);
+        h->lt_site = -1;
+    }
+    spk::KInst I = chain_inst(h, k, C, mix);
+    I.out[0] = out;
+    I.ogs = osize;
+    spk::chain(h->stream, spk::kChainF64, C.lay, C.shape, I.ntile * I.G, 1, nullptr, I);
+}
+
 void env_left(sp_handle* h, int k) {
     if (!h->Lvalid[k - 1]) throw SpError(SP_ESTATE, "left environment of the previous bond is not built");
     SitePlan& P = h->plan[k - 1];
@@ -2245,11 +2641,7 @@ void env_left(sp_handle* h, int k) {
         P.mixl.launch(s, b, P.coef.p);
         P.envl_out.launch(s, b, P.coef.p);
     } else {
-        const spk::BufSet b = bufset(h, k, h->Xd.p, nullptr, nullptr, h->envL[k].p);
-        spk::gather(s, P.xmap.p, site_ptr(h, k), h->Xd.p, P.Xd_size);
-        P.t_left.launch(s, b, P.coef.p, P.xmap.p);
-        P.mixl.launch(s, b, P.coef.p);
-        P.t_envl.launch(s, b, P.coef.p, P.xmap.p);
+        env_chain(h, k, P.c_envl, P.mix_l, h->envL[k - 1].p, h->env[k - 1].size, h->envL[k].p, h->env[k].size);
     }
     if (reduced(h))
         spk::to_f32(s, h->envL[k].p, h->envL32[k].p, (long long)h->G * h->env[k].size);
@@ -2269,11 +2661,7 @@ void env_right(sp_handle* h, int k) {
         P.mixr.launch(s, b, P.coef.p);
         P.envr_out.launch(s, b, P.coef.p);
     } else {
-        const spk::BufSet b = bufset(h, k, h->Xd.p, nullptr, nullptr, h->envR[k - 1].p);
-        spk::gather(s, P.xmap.p, site_ptr(h, k), h->Xd.p, P.Xd_size);
-        P.t_zr.launch(s, b, P.coef.p, P.xmap.p);
-        P.mixr.launch(s, b, P.coef.p);
-        P.t_envr.launch(s, b, P.coef.p, P.xmap.p);
+        env_chain(h, k, P.c_envr, P.mix_r, h->envR[k].p, h->env[k].size, h->envR[k - 1].p, h->env[k - 1].size);
     }
     if (reduced(h))
         spk::to_f32(s, h->envR[k - 1].p, h->envR32[k - 1].p, (long long)h->G * h->env[k - 1].size);
@@ -3666,6 +4054,7 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         long long Tmax = 0, Vmax = 0, qrs = 0, qrr = 0, LTmax = 0;
         for (int k = 1; k <= h->L; ++k) {
             build_plan(h.get(), k);
+            if (h->path == SP_PATH_TILED) build_chain(h.get(), k);
             if (h->path == SP_PATH_TILED && !build_fused(h.get(), k)) build_fused(h.get(), k, kHeffLdsMax);
             if (h->path == SP_PATH_TILED && h->plan[k - 1].h_rows == 1) {
                 // one row per task re-reads the right environment once per
@@ -3681,7 +4070,7 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
             const long long dgT = (long long)P.dg_nzl * h->bonds[k - 1].D + (long long)P.dg_nzr * h->bonds[k].D;
             Tmax = std::max({Tmax, P.Tsize, P.Zsize, dgT});
             Vmax = std::max({Vmax, P.Vsize, P.Ztsize, (long long)P.dg_mix.size() * h->bonds[k - 1].D});
-            LTmax = std::max(LTmax, P.LTsize);
+            LTmax = std::max({LTmax, P.LTsize, P.mix_l.size, P.mix_r.size});
             qrs = std::max({qrs, P.qr_scratch, P.lq_scratch});
             qrr = std::max({qrr, P.qr_rsize, P.lq_rsize});
         }
@@ -3692,6 +4081,7 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         h->qr_r_cap = std::max(1LL, qrr);
         for (int k = 1; k <= h->L; ++k) {
             h->Xd_cap = std::max(h->Xd_cap, h->plan[k - 1].Xd_size);
+            h->Xr_cap = std::max(h->Xr_cap, h->G * (long long)h->plan[k - 1].rmap_h.size());
             h->tr_split_max = std::max(h->tr_split_max, h->plan[k - 1].tr_split);
         }
         h->Xd_cap = std::max(1LL, h->Xd_cap);
@@ -3702,14 +4092,15 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         for (int k = 1; k <= h->L; ++k) upload_plan(h.get(), k);
         h->T.alloc(h->T_cap);
         h->V.alloc(h->V_cap);
-        h->LT.alloc(h->LT_cap);
+        h->LT.alloc(h->LT_cap + read_pad(h.get()));
         h->diag_part.alloc(size_t(spk::kDiagSplitMax) * std::max(1LL, h->max_site));
         h->qr_scratch.alloc(h->qr_scratch_cap);
         h->qr_r.alloc(h->qr_r_cap);
         h->tmp_site.alloc(h->max_site);
         h->mps.alloc(h->mps_size);
         if (h->path == SP_PATH_TILED) {
-            h->Xd.alloc(h->Xd_cap);
+            h->Xd.alloc(h->Xd_cap + read_pad(h.get()));
+            h->Xr.alloc(h->Xr_cap + read_pad(h.get()));
             h->ypart.alloc(size_t(h->G) * h->tr_split_max * h->max_site);
             h->nypart.alloc(size_t(h->G) * h->tr_split_max * h->max_site);
         }

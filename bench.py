@@ -40,16 +40,15 @@ def fused_kernel_sha256():
     layout, which key the committed hardware-counter summaries."""
     import hashlib
     hs = hashlib.sha256()
-    for f in ("heff3.hip", "kernels.h"):
+    for f in ("chain.hip", "kernels.h"):
         hs.update(open(os.path.join(ROOT, "paper_1703_04789_amd", "csrc", f), "rb").read())
     return hs.hexdigest()
 
 
-def measured_traffic(rows):
+def measured_traffic():
     """HBM bytes per launch of the fused kernel from the committed rocprofv3
     summary (FETCH_SIZE and WRITE_SIZE, calibrated on a 64 MiB copy), or None
-    when the kernel source has changed since those counters were taken or
-    no counters were taken on this plan (rows per task) of the site."""
+    when the kernel source has changed since those counters were taken."""
     import hashlib
     import re
     path = os.path.join(ROOT, "profiles", "heff_hubbard_L32_D256_G9_fused_fp64_hbm_traffic.md")
@@ -58,8 +57,8 @@ def measured_traffic(rows):
         now = fused_kernel_sha256()
     except OSError:
         return None
-    m_b = re.search(r"traffic_bytes_per_launch\[rows_per_task=%d\]: (\d+)" % rows, txt)
-    m_h = re.search(r"heff3.hip\+kernels.h sha256: ([0-9a-f]+)", txt)
+    m_b = re.search(r"traffic_bytes_per_launch: (\d+)", txt)
+    m_h = re.search(r"chain.hip\+kernels.h sha256: ([0-9a-f]+)", txt)
     if not m_b or not m_h or m_h.group(1) != now:
         return None
     return float(m_b.group(1))
@@ -679,10 +678,10 @@ def main():
         achieved = dom["bytes"] / (dom["ms"] * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": achieved / PEAK_HBM_GBS, "traffic": None}
-    roof["kernel"] = f"{'k_bgemm' if args.path == 'plain' else 'k_heff3'} ({dom_name}) at site {kc}"
+    roof["kernel"] = f"{'k_bgemm' if args.path == 'plain' else 'k_chain'} ({dom_name}) at site {kc}"
     roof["plan"] = {"rows_per_task": main_run["plan"][0], "lds_doubles": main_run["plan"][1]}
     if args.path == "tiled" and dom_name == "fused_heff":
-        roof["traffic"] = measured_traffic(main_run["plan"][0])
+        roof["traffic"] = measured_traffic()
         roof["traffic_unit"] = "B per launch (HBM, rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated)"
     roof["per_launch"] = {k: {"ms": v["ms"], "flops": v["flops"], "bytes": v["bytes"]} for k, v in prof.items()}
 
@@ -703,7 +702,7 @@ def main():
                    "twoM": wl.twoM, "D": wl.D, "G": wl.G, "seed": wl.seed, "path": f"{args.path} FP64",
                    "davidson": {"tol": args.tol, "max_iter": args.max_iter, "max_sub": args.max_sub,
                                 "keep": args.keep},
-                   "fused_plans": "autotuned per site (sp_autotune: the fused kernel at each LDS budget or the tiled block products, 5 repetitions each)"
+                   "fused_plans": "autotuned per site (sp_autotune, 5 repetitions each)"
                    if main_run["tuned"] is not None else "default LDS budget"},
         "site_steps": n_site_steps,
         "matvecs_per_site_step": mv,

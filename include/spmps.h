@@ -56,8 +56,8 @@ extern "C" {
                              orthogonalisation and subspace solve, and a
                              final FP64 Rayleigh quotient per site step
                              (the reported energy) stay FP64           */
-#define SP_BF16X3 2       /* as SP_FP32, and the LDS-tiled block products of
-                             sites too wide for the fused kernel run in
+#define SP_BF16X3 2       /* as SP_FP32, and the block products of sites too
+                             wide for a fused plan run in
                              split BF16 on the matrix cores: each operand
                              value v ~ hi + lo (two bf16, round to nearest
                              even), three products hi hi + hi lo + lo hi
@@ -68,18 +68,19 @@ extern "C" {
 #define SP_SOLVER_HOST 1
 #define SP_SOLVER_DEVICE 2
 
-#define SP_PATH_TILED 0   /* environment updates as LDS-tiled block products
-                             over particle-number blocks (FP64 matrix
-                             cores); H_eff x per site either in one fused
-                             launch with per-g partial outputs, or as block
-                             products from the left environment with the
-                             rotated MPO mixed in (formed once per L[site-1])
-                             - the latter where a particle-number block is
-                             too wide for the fused kernel's LDS, where the
-                             fused plan has one row per task, or where
-                             sp_autotune / sp_set_heff_plan choose it.  The
-                             block products are FP64 in SP_FP64 and SP_FP32
-                             and split BF16 in SP_BF16X3                  */
+#define SP_PATH_TILED 0   /* chained block products over particle-number
+                             blocks on the matrix cores: H_eff x and each
+                             environment update are one launch over all
+                             quadrature points, with the MPO mixed into the
+                             environment first where it is wide.  A site's
+                             H_eff plan sets the arithmetic of its products
+                             in the reduced precisions: FP32 at a site with
+                             a fused plan; FP64 (SP_FP32) or split BF16
+                             (SP_BF16X3) as block products, which run where
+                             a particle-number block is too wide for the
+                             plan's LDS, where the plan has one row per
+                             task, or where sp_autotune /
+                             sp_set_heff_plan choose them                 */
 #define SP_PATH_PLAIN 1   /* one work-group per (N, M) block product, the
                              plain FP64 reference path                      */
 
@@ -207,7 +208,7 @@ int sp_heff_apply(sp_handle* h, int site, const double* x, double* y, double* ny
  * until the process ends) instead of the handle's buffers.  The call
  * allocates nothing.  Tiled path only (SP_EINVAL otherwise); SP_EINVAL when
  * the site needs more than 2^21 partial slots per output (G x site size on
- * a fused site, G x the channel split x site size on the block products).
+ * a fused site, G x the channel split x site size on the others).
  * Every handle on one GPU shares that GPU's array: calls that overlap on one
  * GPU (on different streams, or from several threads) race and must be
  * ordered by the caller.  Its contents after a call are undefined. */
@@ -227,35 +228,34 @@ int sp_sweep(sp_handle* h, const sp_sweep_opts* o, sp_sweep_report* r);
 /* Sweeps of n states together (each as sp_sweep would run them, same
  * results to rounding): every round advances each unfinished state by one
  * site step; the Davidson iterations of the states run in lockstep, with one
- * fused H_eff launch (per row count) covering every state and quadrature
- * point, batched Davidson passes, and the subspace solves on host threads.
+ * fused H_eff launch (per tile shape and arithmetic) covering every state and
+ * quadrature point, batched Davidson passes, and the subspace solves on host threads.
  * All handles: tiled path, one precision, one device and one stream,
- * centre at site 1, each listed once.  Sites without a fused plan run their
- * tiled products per state in the same round.  r: n reports (or NULL).  The ability to
+ * centre at site 1, each listed once.  r: n reports (or NULL).  The ability to
  * run many states at once follows the paper's use of several
  * broken-symmetry starting guesses (Sec. 3). */
 int sp_sweep_batch(sp_handle** hs, int n, const sp_sweep_opts* o, sp_sweep_report* r);
 
 /* Autotuner of the H_eff plans (tiled path): for every site, time `reps`
- * applications of the fused kernel for each LDS budget of the work-group
- * (36, 72, 108 and 144 KB, which set the rows per task) and of the LDS-tiled
- * block products, and keep the fastest.  The products are the same to
- * rounding whatever the choice.  Optional outputs (L entries each): the
+ * applications under the smallest LDS budget that has a fused plan (36, 72,
+ * 108 and 144 KB) and, where the choice changes the products (reduced
+ * precisions) or none has, as block products, and keep the fastest.  In FP64
+ * the products are the same whatever the choice.  Optional outputs (L entries each): the
  * budget in doubles (0: block products), the rows per task (0: block
  * products) and the time per application in microseconds.  Synchronises. */
 int sp_autotune(sp_handle* h, int reps, int* budget_out, int* rows_out, double* usec_out);
 
-/* Current H_eff plan of a site: rows per task of the fused kernel and its
+/* Current H_eff plan of a site: rows per task of the fused plan and its
  * LDS in doubles, or 0 and 0 (plain path, or a tiled-path site that runs the
  * tiled block products).  Host only. */
 int sp_heff_plan(const sp_handle* h, int site, int* rows, int* lds_doubles);
 
-/* Choose the H_eff plan of one site (tiled path): the fused kernel with an
- * LDS budget of `lds_budget` doubles per work-group (1..18432; it sets the
- * rows per task), or 0 for the LDS-tiled block products.  A budget that no
+/* Choose the H_eff plan of one site (tiled path): a fused plan with an LDS
+ * budget of `lds_budget` doubles per work-group (1..18432; it sets the rows
+ * per task), or 0 for the block products.  A budget that no
  * particle-number block of the site fits also selects the tiled products.
  * *rows (optional) receives the rows per task, 0 for the tiled products.
- * The products are the same to rounding either way.  Synchronises. */
+ * In FP64 the products are the same either way.  Synchronises. */
 int sp_set_heff_plan(sp_handle* h, int site, int lds_budget, int* rows);
 
 /* Excited states (Sec. 2.3, Eq. [orthoB]): later sp_sweep calls on h keep
@@ -369,11 +369,10 @@ int sp_heff_flops(const sp_handle* h, int site, double* flops);
 
 /* Timing of the phases of sp_heff_apply at `site`, each averaged over
  * `reps` launches.  Plain path: left product, W r mixing, right product.
- * Tiled path: the fused launch (left product, mixing and right product in
- * one kernel) or, at a site without a fused plan, the tiled block-product
- * lists; then the pre-mixing of the left environment that the block
- * products build once per local problem (timed once, before the products,
- * and not part of their time; 0 at a fused site); then the g sum.  Phases
+ * Tiled path: the site vectors and the chained product; then the
+ * pre-mixing of the left environment that wide MPOs build once per local
+ * problem (timed once, before the products, and not part of their time; 0
+ * where nothing is mixed); then the g sum.  Phases
  * are timed with HIP events on the handle's stream.  out[0..2]: mean
  * milliseconds per launch; out[3..5]: algorithmic flops per launch (tiled
  * path: the product, the pre-mixing's scaled adds, the g sum);

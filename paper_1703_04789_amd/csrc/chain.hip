@@ -13,6 +13,16 @@
 //   right environment: P = the bra tensor, A = R(c'), B = the rotated ket tensor
 // One work-group of four wavefronts per output tile; the steps of a tile are
 // dealt to the wavefronts, whose sums are added through LDS in a fixed order.
+// What bounds it: at narrow MPOs the latency of a wavefront's chain of loads
+// (matrix cores 22 % busy at the L = 32, D = 256, G = 9 Hubbard centre); at
+// wide ones the L2 (39 % busy, 12 TB/s of L2 reads at the K = 12, D = 128,
+// G = 11 ab-initio centre).  The next chunk's loads are issued before the
+// current chunk's products; deeper prefetch and tiles of 48 x 48 were slower
+// (registers, so fewer wavefronts).  Calls of H_eff x and N_eff x, before
+// (FP64 FMAs through LDS; block products with intermediates in memory) and now:
+// Hubbard L = 32, D = 256 45 -> 24 us, L = 48, D = 512 145 -> 63, ab-initio
+// K = 12, D = 128 496 -> 227; an environment update at L = 32, D = 256 (four
+// launches of block products before) 75 -> 26 us.
 #include "kernels.h"
 
 #include <type_traits>
@@ -27,18 +37,21 @@ typedef short s4_t __attribute__((ext_vector_type(4)));
 typedef double d2u_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
 
-__device__ inline unsigned short bf16_rne(float f) {
-    unsigned int u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-// v ~ hi + lo, both bf16 rounded to nearest even (about 16 significant bits)
+typedef __bf16 bf4_t __attribute__((ext_vector_type(4)));
+// v ~ hi + lo, both bf16 rounded to nearest even (about 16 significant bits;
+// the residue of the FP32 value, which is exact, so the split is off by 2^-18
+// of v as with an FP64 residue)
 template <class V>
-__device__ inline void split_bf16(V v, short& hi, short& lo) {
-    const unsigned short h = bf16_rne(float(v));
-    const V hv = V(__uint_as_float((unsigned int)h << 16));
-    hi = short(h);
-    lo = short(bf16_rne(float(v - hv)));
+__device__ inline void split_bf16(const V* v, s4_t& hi, s4_t& lo) {
+    f4_t f, r;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) f[t] = float(v[t]);
+    const bf4_t h = __builtin_convertvector(f, bf4_t);
+    const f4_t hf = __builtin_convertvector(h, f4_t);
+    r = f - hf;
+    const bf4_t l = __builtin_convertvector(r, bf4_t);
+    hi = __builtin_bit_cast(s4_t, h);
+    lo = __builtin_bit_cast(s4_t, l);
 }
 
 // the value at element i of a block: a uniform base and a 32-bit byte offset
@@ -87,14 +100,18 @@ struct Frag {
 // both operands share it).  Rows past an extent re-read its last one, kj and
 // kc values past a range are read from what follows (the buffers end in
 // read_pad values) and set to zero in both operands.
-template <int MODE, int LAY, int NM, int NI, int NN, bool BATCH>
-__global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const KInst* __restrict__ insts, KInst one) {
+template <int MODE, int LAY, int NM, int NI, int NN, int W, bool BATCH>
+__global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* __restrict__ insts, KInst one) {
     typedef typename std::conditional<MODE == kChainF32, float, double>::type E;         // operands
     typedef typename std::conditional<MODE == kChainF64, d4_t, f4_t>::type A4;           // accumulators
     typedef typename std::conditional<MODE == kChainF64, double, float>::type AE;
-    constexpr int KL = MODE == kChainF64 ? 2 : 4, KC = 4 * KL, W = kChainThreads / 64;
+    // sums over steps in the FP32 mode are FP64: a step's part is added to them
+    typedef typename std::conditional<MODE == kChainBF3, float, double>::type SE;
+    constexpr bool kFold = MODE == kChainF32;
+    constexpr int KL = MODE == kChainF64 ? 2 : 4, KC = 4 * KL, NE = NM * NN * 4;
     typedef Frag<E, NI, NN, KL> F;
-    __shared__ AE red[W][NM * NN * 4][64];
+    // the sums of the wavefronts, and that of N_eff x
+    __shared__ SE red[W + (LAY == kChainHeff ? 1 : 0)][W == 1 ? 1 : NE][64];
     const KInst& I = BATCH ? insts[blockIdx.y] : one;
     if (I.gate && *I.gate == 0) return;
     // work-group w runs on XCD w mod 8: contiguous runs of the g-major list of
@@ -102,7 +119,8 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
     const int T = I.ntile * I.G, per = (T + 7) / 8, pos = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (int(blockIdx.x >> 3) >= per || pos >= T) return;
     const int g = pos / I.ntile;
-    const KTile tk = I.tiles[pos - g * I.ntile];
+    const KTile* __restrict__ tp = I.tiles + (pos - g * I.ntile);
+    const KTile& tk = *tp;
     const double* __restrict__ coef = I.coef + (long long)g * I.nc;
     const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const int li = lane % 16, lk = lane / 16;
@@ -117,10 +135,14 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
     for (int i = 0; i < NN; ++i) bn[i] = min(tk.n0 + 16 * i + li, tk.n1 - 1);
     const int nm = (tk.m1 - tk.m0 + 15) / 16;
     A4 acc[NM][NN], in[NI][NN];
+    d4_t sum64[kFold ? NM : 1][kFold ? NN : 1];
 #pragma unroll
     for (int i = 0; i < NM; ++i)
 #pragma unroll
-        for (int j = 0; j < NN; ++j) acc[i][j] = A4{0, 0, 0, 0};
+        for (int j = 0; j < NN; ++j) {
+            acc[i][j] = A4{0, 0, 0, 0};
+            if constexpr (kFold) sum64[i][j] = d4_t{0, 0, 0, 0};
+        }
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -128,21 +150,31 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
 
     // the chunks of this wavefront's steps as one sequence: every step holds
     // a segment and every segment a kj value (checked with the lists)
-    int st = tk.s0 + wave;
+    const bool metric = LAY == kChainHeff && wave == W - 1 && tk.e1 > tk.e0;
+    const int y0 = tk.s[wave], y1 = tk.s[wave + 1];
+    int st = metric ? tk.e0 : y0, s1 = metric ? tk.e1 : y1;
+    auto base = [&](int b) { return static_cast<const E*>(I.in[b].p) + g * I.in[b].gs; };
+    const E* __restrict__ x0 = base(K_X);
+    const E* __restrict__ x1 = base(K_XR);
+    const E* __restrict__ e0 = base(LAY == kChainEnvR ? K_R : K_L);
+    const E* __restrict__ e1 = base(K_LT);
+    const E* __restrict__ pb = LAY == kChainHeff ? base(K_R) : x0;
     KStep fs{};
     KSeg sg{};
     int s = 0, kb = 0;
-    if (st < tk.s1) {
+    if (st < s1) {
         fs = I.steps[st];
         s = fs.g0;
         sg = I.segs[s];
         kb = sg.k0;
     }
     auto fetch = [&](F& f) {
-        f.cf = E(coef[sg.cidx]);
+        f.cf = E(sg.cf);
         f.nk = sg.k1 - kb;
-        const E* __restrict__ A = static_cast<const E*>(I.in[sg.a_buf].p) + g * I.in[sg.a_buf].gs + sg.a_off;
-        const E* __restrict__ B = static_cast<const E*>(I.in[sg.b_buf].p) + g * I.in[sg.b_buf].gs + sg.b_off;
+        const E* __restrict__ X = sg.alt_x ? x1 : x0;
+        const E* __restrict__ V = sg.alt_e ? e1 : e0;
+        const E* __restrict__ A = (LAY == kChainHeff ? X : V) + sg.a_off;
+        const E* __restrict__ B = (LAY == kChainHeff ? V : X) + sg.b_off;
         if constexpr (LAY == kChainHeff) {  // A(kc, kj) at kj * lda + kc
             A += (long long)kb * sg.lda;
 #pragma unroll
@@ -179,21 +211,19 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
             ++s;
             if (s >= fs.g1) {
                 f.last = true;
-                st += W;
-                if (st < tk.s1) {
+                ++st;
+                if (st < s1) {
                     fs = I.steps[st];
                     s = fs.g0;
                 }
             }
-            if (st < tk.s1) {
-                sg = I.segs[s];
-                kb = sg.k0;
-            }
+            if (st < s1) sg = I.segs[s];
+            kb = sg.k0;
         }
     };
     KStep cs{};  // the step whose inner product is being formed
     int cst = st;
-    if (cst < tk.s1) cs = fs;
+    if (cst < s1) cs = fs;
     auto products = [&](F& f) {
         if (f.nk < KC) {
 #pragma unroll
@@ -213,25 +243,12 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
         if constexpr (MODE == kChainBF3) {
             s4_t bh[NN], bl[NN];
 #pragma unroll
-            for (int j = 0; j < NN; ++j)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    short h, l;
-                    split_bf16(f.b[j][t], h, l);
-                    bh[j][t] = h;
-                    bl[j][t] = l;
-                }
+            for (int j = 0; j < NN; ++j) split_bf16(f.b[j], bh[j], bl[j]);
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 if (i >= ni) break;
                 s4_t ah, al;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    short h, l;
-                    split_bf16(f.a[i][t], h, l);
-                    ah[t] = h;
-                    al[t] = l;
-                }
+                split_bf16(f.a[i], ah, al);
 #pragma unroll
                 for (int j = 0; j < NN; ++j) {
                     in[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh[j], in[i][j], 0, 0, 0);
@@ -244,9 +261,9 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
             for (int i = 0; i < NI; ++i) {
                 if (i >= ni) break;
 #pragma unroll
-                for (int j = 0; j < NN; ++j)
+                for (int t = 0; t < KL; ++t)
 #pragma unroll
-                    for (int t = 0; t < KL; ++t) {
+                    for (int j = 0; j < NN; ++j) {
                         if constexpr (MODE == kChainF64)
                             in[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[i][t], f.b[j][t], in[i][j], 0, 0, 0);
                         else
@@ -256,7 +273,7 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
         }
         if (!f.last) return;
         // O += P I, 16 kc values at a time
-        const E* __restrict__ P = static_cast<const E*>(I.in[cs.p_buf].p) + g * I.in[cs.p_buf].gs + cs.p_off;
+        const E* __restrict__ P = pb + cs.p_off;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             if (i >= ni) break;
@@ -287,25 +304,15 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
             if constexpr (MODE == kChainBF3) {
                 s4_t ih[NN], il[NN];
 #pragma unroll
-                for (int j = 0; j < NN; ++j)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        short h, l;
-                        split_bf16(in[i][j][v], h, l);
-                        ih[j][v] = h;
-                        il[j][v] = l;
-                    }
+                for (int j = 0; j < NN; ++j) {
+                    float v[4] = {in[i][j][0], in[i][j][1], in[i][j][2], in[i][j][3]};
+                    split_bf16(v, ih[j], il[j]);
+                }
 #pragma unroll
                 for (int a = 0; a < NM; ++a) {
                     if (a >= nm) break;
                     s4_t ph, pl;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        short h, l;
-                        split_bf16(p[a][v], h, l);
-                        ph[v] = h;
-                        pl[v] = l;
-                    }
+                    split_bf16(p[a], ph, pl);
 #pragma unroll
                     for (int j = 0; j < NN; ++j) {
                         acc[a][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pl, ih[j], acc[a][j], 0, 0, 0);
@@ -318,9 +325,9 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
                 for (int a = 0; a < NM; ++a) {
                     if (a >= nm) break;
 #pragma unroll
-                    for (int j = 0; j < NN; ++j)
+                    for (int v = 0; v < 4; ++v)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
+                        for (int j = 0; j < NN; ++j) {
                             if constexpr (MODE == kChainF64)
                                 acc[a][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[a][v], in[i][j][v], acc[a][j], 0, 0, 0);
                             else
@@ -331,49 +338,100 @@ __global__ __launch_bounds__(kChainThreads, NM > 4 ? 1 : 2) void k_chain(const K
 #pragma unroll
             for (int j = 0; j < NN; ++j) in[i][j] = A4{0, 0, 0, 0};
         }
-        cst += W;
-        if (cst < tk.s1) cs = I.steps[cst];
+        if constexpr (kFold) {
+#pragma unroll
+            for (int a = 0; a < NM; ++a)
+#pragma unroll
+                for (int j = 0; j < NN; ++j) {
+                    sum64[a][j] += __builtin_convertvector(acc[a][j], d4_t);
+                    acc[a][j] = A4{0, 0, 0, 0};
+                }
+        }
+        ++cst;
+        if (cst < s1) cs = I.steps[cst];
     };
-    if (st < tk.s1) {
+    auto total = [&](int a, int j, int v) {
+        if constexpr (kFold) return sum64[a][j][v];
+        else return acc[a][j][v];
+    };
+    for (int pass = metric ? 0 : 1; pass < 2; ++pass) {
+        if (pass == 1 && metric) {  // N_eff x is done: its sum to LDS, then this wavefront's own steps
+#pragma unroll
+            for (int a = 0; a < NM; ++a)
+#pragma unroll
+                for (int j = 0; j < NN; ++j) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if constexpr (LAY == kChainHeff) red[W][(a * NN + j) * 4 + v][lane] = total(a, j, v);
+                    acc[a][j] = A4{0, 0, 0, 0};
+                    if constexpr (kFold) sum64[a][j] = d4_t{0, 0, 0, 0};
+                }
+            st = cst = y0;
+            s1 = y1;
+            if (st < s1) {
+                cs = fs = I.steps[st];
+                s = fs.g0;
+                sg = I.segs[s];
+                kb = sg.k0;
+            }
+        }
+        if (st >= s1) continue;
+        // the loads of the next chunk are issued whether there is one or not
+        // (past the end the last segment's first chunk again): behind a branch
+        // the wait for the current chunk would have to take them in as well
         F f0, f1;
         fetch(f0);
         for (;;) {
-            const bool m1 = st < tk.s1;
-            if (m1) fetch(f1);
+            const bool m1 = st < s1;
+            fetch(f1);
             products(f0);
             if (!m1) break;
-            const bool m0 = st < tk.s1;
-            if (m0) fetch(f0);
+            const bool m0 = st < s1;
+            fetch(f0);
             products(f1);
             if (!m0) break;
         }
     }
-    // the wavefronts' sums in wavefront order
-    const int nw = min(W, tk.s1 - tk.s0);
-    if (wave < nw || wave == 0) {
+    const double scale = tk.cidx < 0 ? 1.0 : coef[tk.cidx];
+    double* __restrict__ out = I.out[0] + g * I.ogs + tk.o_off;
+    if constexpr (W == 1) {
 #pragma unroll
         for (int a = 0; a < NM; ++a)
 #pragma unroll
             for (int j = 0; j < NN; ++j)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) red[wave][(a * NN + j) * 4 + v][lane] = acc[a][j][v];
-    }
-    __syncthreads();
-    const double cs_out = tk.cidx < 0 ? 1.0 : coef[tk.cidx];
-    double* __restrict__ out = I.out[tk.out] + g * I.ogs + tk.o_off;
-    const int nelem = nm * NN * 4;
-    for (int e = wave; e < nelem; e += W) {
-        const int v = e % 4, j = (e / 4) % NN, a = e / (4 * NN);
-        const int m = tk.m0 + 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = tk.n0 + 16 * j + li;
-        if (m >= tk.m1 || n >= tk.n1) continue;
-        AE sum = red[0][e][lane];
-        for (int w = 1; w < nw; ++w) sum += red[w][e][lane];
-        const double val = cs_out * double(sum);
-        if constexpr (LAY == kChainHeff) {
-            const int q = I.map[tk.map_off + n * tk.o_ns + m];
-            if (q >= 0) out[q] = val;
-        } else {
-            out[(long long)m * tk.o_ms + n] = val;
+                for (int v = 0; v < 4; ++v) {
+                    const int m = tk.m0 + 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = tk.n0 + 16 * j + li;
+                    if (m < tk.m1 && n < tk.n1) out[(long long)m * tk.ldo + n] = scale * double(total(a, j, v));
+                }
+        return;
+    } else {
+        // the wavefronts' sums in wavefront order
+#pragma unroll
+        for (int a = 0; a < NM; ++a)
+#pragma unroll
+            for (int j = 0; j < NN; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[wave][(a * NN + j) * 4 + v][lane] = total(a, j, v);
+        __syncthreads();
+        double* __restrict__ out2 = I.out[1] + g * I.ogs;
+        const bool both = LAY == kChainHeff && tk.e1 > tk.e0;
+        for (int e = wave; e < nm * NN * 4; e += W) {
+            const int v = e % 4, j = (e / 4) % NN, a = e / (4 * NN);
+            const int m = tk.m0 + 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = tk.n0 + 16 * j + li;
+            if (m >= tk.m1 || n >= tk.n1) continue;
+            double sum = red[0][e][lane];
+#pragma unroll
+            for (int w = 1; w < W; ++w) sum += double(red[w][e][lane]);
+            if constexpr (LAY == kChainHeff) {
+                const int q = I.map[tk.map_off + n * tk.ldo + m];
+                if (q >= 0) {
+                    out[q] = scale * sum;
+                    if (both) out2[q] = scale * double(red[W][e][lane]);
+                }
+            } else {
+                out[(long long)m * tk.ldo + n] = scale * sum;
+            }
         }
     }
 }
@@ -402,79 +460,96 @@ __global__ __launch_bounds__(256) void k_xprep(const KPrep* __restrict__ insts, 
     out[I.nr + e] = E(r[4 * 2 + 1] * a + r[4 * 2 + 2] * b);
 }
 
-template <int MODE, int LAY>
+template <int MODE, int LAY, int W>
 void launch_shape(hipStream_t s, int shape, dim3 grid, const KInst* insts, const KInst& one) {
-#define SPK_CHAIN(NM, NI, NN)                                                                                      \
+#define SPK_CHAIN(NM, NN)                                                                                          \
     if (LAY == kChainHeff && insts)                                                                                \
-        hipLaunchKernelGGL((k_chain<MODE, LAY, NM, NI, NN, LAY == kChainHeff>), grid, dim3(kChainThreads), 0, s, insts, one); \
+        hipLaunchKernelGGL((k_chain<MODE, LAY, NM, 2, NN, W, LAY == kChainHeff>), grid, dim3(64 * W), 0, s, insts, one); \
     else                                                                                                           \
-        hipLaunchKernelGGL((k_chain<MODE, LAY, NM, NI, NN, false>), grid, dim3(kChainThreads), 0, s, insts, one)
+        hipLaunchKernelGGL((k_chain<MODE, LAY, NM, 2, NN, W, false>), grid, dim3(64 * W), 0, s, insts, one)
     switch (shape) {
-        case 0: SPK_CHAIN(2, 2, 1); break;
-        case 1: SPK_CHAIN(4, 4, 1); break;
-        default: SPK_CHAIN(8, 4, 1); break;
+        case 0: SPK_CHAIN(2, 1); return;
+        case 1: SPK_CHAIN(3, 1); return;
+        case 2: SPK_CHAIN(4, 1); return;
+        case 3: SPK_CHAIN(6, 1); return;
+        case 4: SPK_CHAIN(8, 1); return;
+        default: break;
+    }
+    if constexpr (LAY == kChainHeff) {  // environments use the narrow shapes
+        switch (shape) {
+            case 5: SPK_CHAIN(2, 2); break;
+            case 6: SPK_CHAIN(3, 2); break;
+            default: SPK_CHAIN(4, 2); break;
+        }
     }
 #undef SPK_CHAIN
 }
 
-// out(g, e) = sum over the task's terms of coef[cidx] * in(g, a_off + e): the
-// environment of one side with the unrotated MPO mixed in, for every g.  The
-// terms are staged in LDS 64 at a time, so that the loads of the sum are
-// independent of each other; every element adds its terms in list order.
+// The pre-mixed environment of one side, blockIdx.y = g.  Wide MPOs sum tens
+// of blocks into one and use every block in hundreds of sums, so the sources
+// are staged in LDS, and since a sum's sources are set by its channel and
+// operator type, whole groups of blocks share them: one LDS read serves up to
+// kMixGroup sums (the LDS gives 16 values per clock and CU, the FMAs take 64).
+// K = 12, D = 128, site 7, G = 11: 261 us, of which writing the 700 MB of
+// mixed blocks takes about 160; a work-group per 64 elements of one block with
+// terms read from memory 870, one block at a time from LDS 650.
 template <class E>
-__global__ __launch_bounds__(256) void k_premix(const MTask* __restrict__ tasks, const MTerm* __restrict__ terms,
-                                                const E* __restrict__ in, long long igs, E* __restrict__ out,
-                                                long long ogs, const double* __restrict__ coef) {
-    constexpr int kAtOnce = 64, kPer = 4;
-    __shared__ const E* sp[kAtOnce];
-    __shared__ double sc[kAtOnce];
-    const MTask tk = tasks[blockIdx.x];
-    in += blockIdx.y * igs;
-    out += blockIdx.y * ogs + tk.o_off;
-    for (int eb = 0; eb < tk.n; eb += kPer * 256) {
-        double acc[kPer] = {0.0, 0.0, 0.0, 0.0};
-        for (int tb = tk.t0; tb < tk.t1; tb += kAtOnce) {
-            const int nt = min(kAtOnce, tk.t1 - tb);
-            __syncthreads();
-            if ((int)threadIdx.x < nt) {
-                const MTerm tm = terms[tb + threadIdx.x];
-                sp[threadIdx.x] = in + tm.a_off;
-                sc[threadIdx.x] = coef[tm.cidx];
-            }
-            __syncthreads();
-            for (int t = 0; t < nt; ++t) {
-                const E* __restrict__ a = sp[t];
-                const double c = sc[t];
+__global__ __launch_bounds__(kMixThreads) void k_premix(MixLists m, const E* __restrict__ in, long long igs,
+                                                        E* __restrict__ out, long long ogs) {
+    __shared__ E src[kMixTile][64];
+    constexpr int NW = kMixThreads / 64;
+    const MixWork* __restrict__ w = m.work + blockIdx.x;
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const bool on = w->e0 + lane < w->n;
+    in += blockIdx.y * igs + w->e0 + lane;
+    out += blockIdx.y * ogs + w->e0 + lane;
+    for (int t = w->tile0; t < w->tile1; ++t) {
+        const MixTileRec* __restrict__ tl = m.tiles + t;
+        const int s0 = tl->s0, ns = tl->s1 - s0;
+#pragma unroll 4
+        for (int q = wave; q < ns; q += NW) src[q][lane] = on ? in[m.src[s0 + q]] : E(0);
+        __syncthreads();
+        for (int i = tl->i0 + wave; i < tl->i1; i += NW) {
+            const MixGroup* __restrict__ it = m.groups + i;
+            const int t1 = it->t1, n = it->n;
+            double acc[kMixGroup];
 #pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const int e = eb + threadIdx.x + u * 256;
-                    if (e < tk.n) acc[u] = fma(c, double(a[e]), acc[u]);
-                }
-            }
-        }
+            for (int b = 0; b < kMixGroup; ++b) acc[b] = it->first || b >= n || !on ? 0.0 : double(out[it->o[b]]);
+#pragma unroll 4
+            for (int q = it->t0; q < t1; ++q) {
+                const double v = double(src[m.at[q]][lane]);
+                const double* __restrict__ c = m.cf + kMixGroup * (long long)q;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int e = eb + threadIdx.x + u * 256;
-            if (e < tk.n) out[e] = E(acc[u]);
+                for (int b = 0; b < kMixGroup; ++b) acc[b] = fma(c[b], v, acc[b]);
+            }
+            if (on)
+#pragma unroll
+                for (int b = 0; b < kMixGroup; ++b)
+                    if (b < n) out[it->o[b]] = E(acc[b]);
         }
+        __syncthreads();
     }
 }
 
 }  // namespace
 
-const KShape kChainShapes[kNumChainShapes] = {{2, 2, 1}, {4, 4, 1}, {8, 4, 1}};
+const KShape kChainShapes[kNumChainShapes] = {{2, 2, 1}, {3, 2, 1}, {4, 2, 1}, {6, 2, 1}, {8, 2, 1},
+                                               {2, 2, 2}, {3, 2, 2}, {4, 2, 2}};
 
-void chain(hipStream_t s, int mode, int lay, int shape, int max_tiles, int ninst, const KInst* insts, const KInst& one) {
+void chain(hipStream_t s, int mode, int lay, int shape, int waves, int max_tiles, int ninst, const KInst* insts,
+           const KInst& one) {
     if (max_tiles <= 0 || ninst <= 0) return;
     const dim3 grid((max_tiles + 7) / 8 * 8, ninst);
     if (lay == kChainHeff) {
-        if (mode == kChainF64) launch_shape<kChainF64, kChainHeff>(s, shape, grid, insts, one);
-        else if (mode == kChainF32) launch_shape<kChainF32, kChainHeff>(s, shape, grid, insts, one);
-        else launch_shape<kChainBF3, kChainHeff>(s, shape, grid, insts, one);
+        if (mode == kChainF64) launch_shape<kChainF64, kChainHeff, kChainWaves>(s, shape, grid, insts, one);
+        else if (mode == kChainF32) launch_shape<kChainF32, kChainHeff, kChainWaves>(s, shape, grid, insts, one);
+        else launch_shape<kChainBF3, kChainHeff, kChainWaves>(s, shape, grid, insts, one);
     } else if (lay == kChainEnvL) {
-        launch_shape<kChainF64, kChainEnvL>(s, shape, grid, insts, one);
+        if (waves == 1) launch_shape<kChainF64, kChainEnvL, 1>(s, shape, grid, insts, one);
+        else launch_shape<kChainF64, kChainEnvL, kChainWaves>(s, shape, grid, insts, one);
     } else {
-        launch_shape<kChainF64, kChainEnvR>(s, shape, grid, insts, one);
+        if (waves == 1) launch_shape<kChainF64, kChainEnvR, 1>(s, shape, grid, insts, one);
+        else launch_shape<kChainF64, kChainEnvR, kChainWaves>(s, shape, grid, insts, one);
     }
 }
 
@@ -487,16 +562,13 @@ void xprep(hipStream_t s, bool f32, int max_n, int max_G, int ninst, const KPrep
     else hipLaunchKernelGGL((k_xprep<double, false>), grid, dim3(256), 0, s, insts, one);
 }
 
-void premix(hipStream_t s, bool f32, const MTask* tasks, int ntask, const MTerm* terms, const void* in, long long igs,
-            void* out, long long ogs, const double* coef, int G) {
-    if (ntask <= 0) return;
+void premix(hipStream_t s, bool f32, const MixLists& m, const void* in, long long igs, void* out, long long ogs, int G) {
+    if (m.nwork <= 0) return;
+    const dim3 grid(m.nwork, G), wg(kMixThreads);
     if (f32)
-        hipLaunchKernelGGL(k_premix<float>, dim3(ntask, G), dim3(256), 0, s, tasks, terms, static_cast<const float*>(in), igs,
-                           static_cast<float*>(out), ogs, coef);
+        hipLaunchKernelGGL(k_premix<float>, grid, wg, 0, s, m, static_cast<const float*>(in), igs, static_cast<float*>(out), ogs);
     else
-        hipLaunchKernelGGL(k_premix<double>, dim3(ntask, G), dim3(256), 0, s, tasks, terms, static_cast<const double*>(in),
-                           igs, static_cast<double*>(out), ogs, coef);
+        hipLaunchKernelGGL(k_premix<double>, grid, wg, 0, s, m, static_cast<const double*>(in), igs, static_cast<double*>(out), ogs);
 }
 
 }  // namespace spk
-

@@ -85,40 +85,16 @@ struct QrPiece {
     int transposed, row0;  // row offset in the gathered matrix
 };
 
-// Dense tile product: one 64x64 output tile C[r0:r0+64, c0:c0+64] of an
-// M x N block = sum over segments of coef[cidx] * A[:, k0:k1] B[k0:k1, :].
-// ta/tb = 1 read A (resp. B) transposed: A(r, k) = A[k*lda + r],
-// B(k, c) = B[c*ldb + k].  mode 0 stores C[c_off + r*ldc + c]; mode 1 stores
-// element (r, c) at C[c_off + map[pack_off + r*N + c]] when that index is
-// >= 0 (scatter of a particle-number block into the packed (N, M) layout).
-struct TTask {
-    long long c_off, pack_off;
-    int c_buf, ldc, M, N, r0, c0, s0, s1, mode, pad;
-};
-struct TSeg {
-    long long a_off, b_off;
-    int a_buf, b_buf, lda, ldb, ta, tb, k0, k1, cidx, pad;
-};
-constexpr int kTile = 64;  // the wide tile; 32 is the narrow one
-
-// tile: 64 or 32 (the task grid of the list was built for that tile)
-void tgemm(hipStream_t s, const TTask* tasks, int ntasks, const TSeg* segs, BufSet bufs, const double* coef,
-           const int* map, int tile);
-// the same products in split BF16 (hi + lo per operand, three matrix-core
-// products, FP32 accumulation); relative error of order 1e-5
-void tgemm_bf3(hipStream_t s, const TTask* tasks, int ntasks, const TSeg* segs, BufSet bufs, const double* coef,
-               const int* map, int tile);
-// dst[e] = map[e] >= 0 ? src[map[e]] : 0, e < n
-void gather(hipStream_t s, const int* map, const double* src, double* dst, long long n);
-// out[e] = sum_{g < G} part[g*stride + e] in ascending g, for two arrays at once
-void gsum2(hipStream_t s, const double* pa, const double* pb, long long stride, int G, int n, double* outa,
+// outa[e] = sum over Ga slots of pa[slot * stride + e], outb likewise over Gb,
+// in a fixed order
+void gsum2(hipStream_t s, const double* pa, const double* pb, long long stride, int Ga, int Gb, int n, double* outa,
            double* outb);
 
 // Chained block products (chain.hip): the lists of one launch, the same for
 // every quadrature point; a buffer's values of point g start at g * gs.
 constexpr int kChainF64 = 0, kChainF32 = 1, kChainBF3 = 2;     // arithmetic
 constexpr int kChainHeff = 0, kChainEnvL = 1, kChainEnvR = 2;  // operand layouts
-constexpr int kChainThreads = 256;
+constexpr int kChainWaves = 4;  // wavefronts of a tile, at most
 // operand buffers: the environments left and right of the site, the dense
 // site tensor, its rotated singly occupied blocks, the pre-mixed environment
 enum KBufId { K_L = 0, K_R = 1, K_X = 2, K_XR = 3, K_LT = 4, K_NBUF = 5 };
@@ -126,22 +102,28 @@ struct KBuf {
     const void* p;
     long long gs;
 };
-// one product of the inner sum: A(kc, kj) B(kj, n) over kj in [k0, k1)
+// one product of the inner sum: cf A(kc, kj) B(kj, n) over kj in [k0, k1).
+// Each operand is one of two buffers: the site tensor's is K_X or (alt_x)
+// K_XR, the environment's K_L (right updates: K_R) or (alt_e) K_LT
 struct KSeg {
     long long a_off, b_off;
-    int a_buf, b_buf, lda, ldb, k0, k1, cidx, pad;
+    double cf;
+    int lda, ldb, k0, k1, alt_x, alt_e;
 };
-// kc values [kc0, kc1) of P and the segments [g0, g1) of the inner sum
+// kc values [kc0, kc1) of P (H_eff x: of K_R, environments: of K_X) and the
+// segments [g0, g1) of the inner sum
 struct KStep {
     long long p_off;
-    int p_buf, ldp, kc0, kc1, g0, g1;
+    int ldp, kc0, kc1, g0, g1, pad;
 };
-// output tile [m0, m1) x [n0, n1) of a block, steps [s0, s1), the sum times
-// coef[cidx] (cidx < 0: 1).  Environments: element (m, n) at o_off + m * o_ms
-// + n; H_eff x: at o_off + map[map_off + n * o_ns + m] where that is >= 0
+// output tile [m0, m1) x [n0, n1) of a block, the steps [s[w], s[w + 1]) of
+// wavefront w, the sum times coef[cidx] (cidx < 0: 1).  Environments: element
+// (m, n) at o_off + m * ldo + n; H_eff x: at o_off + map[map_off + n * ldo + m]
+// where that is >= 0, and the steps [e0, e1) of N_eff x (second output, no
+// o_off), taken by the last wavefront before its own
 struct KTile {
     long long o_off, map_off;
-    int out, m0, m1, n0, n1, o_ms, o_ns, s0, s1, cidx;
+    int m0, m1, n0, n1, ldo, cidx, s[5], e0, e1, pad;
 };
 struct KInst {
     const KTile* tiles;
@@ -171,113 +153,42 @@ struct KPrep {
 struct KShape {
     int nm, ni, nn;
 };
-constexpr int kNumChainShapes = 3;
+constexpr int kNumChainShapes = 8, kNarrowShapes = 5;  // the first kNarrowShapes have nn = 1
 extern const KShape kChainShapes[kNumChainShapes];
 // values that may be read past the end of an operand buffer of blocks at most
 // ld wide
 inline long long read_pad(int ld) { return 16LL * ld + 64; }
-// one block of a pre-mixed environment and its terms
-struct MTask {
-    long long o_off;
-    int n, t0, t1, pad;
+// Pre-mixed environments: blocks that are sums of environment blocks of one
+// shape (bra and ket particle number).  A work item sums 64 consecutive
+// elements of every such block; its sources are staged in LDS kMixTile at a
+// time, and up to kMixGroup blocks of the same sources are summed together.
+constexpr int kMixTile = 160, kMixThreads = 1024, kMixGroup = 8;
+struct MixWork {
+    int tile0, tile1, e0, n;  // tiles of the shape, elements [e0, min(e0 + 64, n))
 };
-struct MTerm {
-    long long a_off;
-    int cidx, pad;
+struct MixTileRec {
+    int s0, s1, i0, i1;  // sources, groups
 };
-void premix(hipStream_t s, bool f32, const MTask* tasks, int ntask, const MTerm* terms, const void* in, long long igs,
-            void* out, long long ogs, const double* coef, int G);
+struct MixGroup {
+    long long o[kMixGroup];
+    int t0, t1, n, first;  // terms, blocks; first: the first tile of these blocks (they start from zero)
+};
+struct MixLists {
+    const MixWork* work;
+    const MixTileRec* tiles;
+    const long long* src;  // environment block of every source
+    const MixGroup* groups;
+    const double* cf;  // term t of a group: kMixGroup coefficients
+    const int* at;     // and the source within the tile
+    int nwork, pad;
+};
+void premix(hipStream_t s, bool f32, const MixLists& m, const void* in, long long igs, void* out, long long ogs, int G);
+// waves: wavefronts per tile (1 or kChainWaves; H_eff x: kChainWaves);
 // max_tiles: the largest tile count times G of the instances; insts = null:
 // the one instance `one`
-void chain(hipStream_t s, int mode, int lay, int shape, int max_tiles, int ninst, const KInst* insts, const KInst& one);
+void chain(hipStream_t s, int mode, int lay, int shape, int waves, int max_tiles, int ninst, const KInst* insts, const KInst& one);
 void xprep(hipStream_t s, bool f32, int max_n, int max_G, int ninst, const KPrep* insts, const KPrep& one);
 
-// Fused H_eff x / N_eff x (all quadrature points in one launch).  One
-// work-group per (g, bra particle-number block i of the left bond, rows
-// [r0, r0 + rows)), rows <= RC (a compile-time row count, 1..8).
-//  phase A: the chunk's rows of every left-environment block L_g(c, i, .)
-//           are staged in LDS; then every product T(c, s') = L_g(c, i) x[s']
-//           (x block-sparse in M, so each T column runs over the ket rows of
-//           one (N, M) sector) is formed one column per thread, all rows at
-//           once, and kept in LDS column-major (RC rows per column);
-//  per output sigma: V(c') = sum_terms coef * T for every right channel c'
-//           of sigma (the W r mixing with coef_g; the identity channel gives
-//           N_eff), then every allowed (N, M) output
-//           y[sigma](r, b) = sum_c' sum_k V(c')(r, k) R_g(c')(b, k) is formed
-//           by a group of lanes that split k and add their partial sums
-//           with cross-lane shuffles (right environment read coalesced from
-//           global memory).
-// Per-g partials go to ypart/nypart[g*n + packed index].  All LDS offsets in
-// the descriptors are in doubles and already include the RC factors.
-struct H3Blk {
-    int c0, c1;        // T columns (H3Col list)
-    int l0, l1;        // left-environment blocks staged per chunk (H3LSrc list)
-    int s0[4], s1[4];  // right-channel segments per output sigma (H3Seg list)
-};
-struct H3Col {
-    int x_off, x_ld, K;  // x entries x_off + kk * x_ld, kk < K
-    int l_lds, l_ld;     // staged L entry (rr, kk) at l_lds + rr * l_ld + kk
-    int t_pos;           // T entry (rr) at t_pos + rr
-    int pad0, pad1;
-};
-struct H3LSrc {
-    int l_off, ld, lds, pad;  // rows of ld entries (within one g) -> LDS at lds + rr * ld
-};
-struct H3Seg {
-    int r_off, K;  // right-environment block (within one g): row b at r_off + b * K
-    int v_off;     // V entry (rr, k) at v_off + k * RC + rr
-    int t0, t1;    // mixing terms
-    int is_ny, pad0, pad1;
-};
-struct H3Term {
-    int t_base, cidx;  // T block in LDS (entry (rr, k) at t_base + k * RC + rr), coefficient index
-};
-struct H3Piece {
-    int rlo, rhi;         // chunk-relative rows of one left (N, M) sector
-    int b0, nb;           // right-block rows of the output columns
-    int out_off, out_ld;  // output (rr, b) at out_off + (rr - rlo) * out_ld + b
-    int pad0, pad1;
-};
-struct H3Task {
-    int g, blk, r0, rows;  // blk < 0: an empty task (padding)
-    int p0[4], p1[4];      // output pieces per sigma
-    int inst, pad0, pad1, pad2;  // instance of a batched launch (0 otherwise)
-};
-// Everything a task needs besides its own descriptor: the plan lists of its
-// site, the environments, x and the outputs of one SP-MPS instance.  Lenv and
-// Renv point to FP64 or FP32 data according to the launch.
-struct H3Inst {
-    const H3Blk* blks;
-    const H3Col* cols;
-    const H3LSrc* lsrc;
-    const H3Seg* segs;
-    const H3Term* terms;
-    const H3Piece* pieces;
-    const void* Lenv;
-    const void* Renv;
-    long long Lsz, Rsz;
-    const double* x;
-    const double* coef;
-    double* ypart;
-    double* nypart;
-    long long n;
-    int nc, pad;
-    const int* gate;  // when set, tasks of this instance return at once while *gate == 0
-};
-constexpr int kH3MaxRC = 8;
-constexpr int kH3Threads = 256;  // threads per work-group of the fused kernel
-constexpr int kH3SlMax = 16;     // lanes per output column (at most)
-// lds_elems: LDS elements (of the environment type) per work-group.  One
-// instance (I, passed by value) or, with insts != nullptr, every task reads
-// its instance from insts[task.inst] (many SP-MPS states in one launch; all
-// tasks of a launch share RC).
-void heff3(hipStream_t s, int RC, int lds_elems, const H3Task* tasks, int ntasks, const H3Inst& I,
-           const H3Inst* insts = nullptr);
-// the same contraction with FP32 environments, FP32 LDS tiles and FP32
-// accumulation (x, the coefficients and the partial outputs stay FP64 in
-// memory and are converted on the fly)
-void heff3_f32(hipStream_t s, int RC, int lds_elems, const H3Task* tasks, int ntasks, const H3Inst& I,
-               const H3Inst* insts = nullptr);
 // out = float(in), n elements
 void to_f32(hipStream_t s, const double* in, float* out, long long n);
 
@@ -336,11 +247,11 @@ void dav_normalize(hipStream_t s, const double* part, int nchunk, const double* 
 // HV_j.V_m (j<m), NV_j.V_m (j<m).  With t != nullptr, V_m = t / |t| where
 // |t|^2 = the sum of the npn partials pn (|t| -> *tnorm) and H_eff t, N_eff t
 // are scaled by 1/|t| (t needs ypart); with ypart != nullptr they are the
-// sums over the G quadrature partials (stride gstride) and V_m (if t), HV_m
-// and NV_m are stored, else they are read from HV_m, NV_m.
+// sums over the partials (G slots of H_eff, Gn of N_eff, stride gstride) and
+// V_m (if t), HV_m and NV_m are stored, else they are read from HV_m, NV_m.
 void dav_gram(hipStream_t s, double* V, double* HV, double* NV, long long ld, int m, int n, const double* t,
               const double* pn, int npn, double* tnorm, const double* ypart, const double* nypart, long long gstride,
-              int G, double* part);
+              int G, int Gn, double* part);
 
 // One instance of the batched Davidson passes (many SP-MPS states advanced
 // together): the arguments of the single-instance passes above, with the
@@ -367,7 +278,7 @@ struct DavInst {
     const double* ypart;
     const double* nypart;
     long long gstride;
-    int G, m, n, active, from_t, mr;  // mr: subspace size of the Ritz pass
+    int G, Gn, m, n, active, from_t, mr;  // mr: subspace size of the Ritz pass
     int ext;  // the search space grows this iteration (CGS, H_eff and Gram passes run)
     // device-resident iteration (davdev.hip): the state the host-driven
     // solver keeps on the host, here in this record on the device

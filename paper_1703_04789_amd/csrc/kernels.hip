@@ -513,399 +513,44 @@ __global__ __launch_bounds__(kThreads) void k_basis_rotate(const double* __restr
     }
 }
 
-// TILE x TILE output tile per work-group of (TILE/4)^2 threads, i.e.
-// (TILE/32)^2 wavefronts; each wavefront owns a 32 x 32 quarter (TILE = 64)
-// or the whole tile (TILE = 32) as 2 x 2 FP64 matrix-core blocks of 16 x 16
-// (v_mfma_f64_16x16x4: lane l supplies A(l % 16, l / 16) and B(l / 16, l % 16)
-// of a 16 x 4 by 4 x 16 step and holds D(4 v + l / 16, l % 16), v < 4).  K is
-// staged through LDS in chunks of kKC with coalesced global loads for either
-// operand layout, zero-padded past the segment and the tile edge.  The chunk
-// is short (8) so that a 64-thread work-group needs 4 KB of LDS and a CU can
-// hold as many of these latency-bound work-groups as it has wave slots (a
-// chunk of 16 halves that and is 1.3x slower at the ab-initio centre, 32 is
-// 1.8x slower); the chunk size does not change the sequence of 4-deep steps,
-// so results are the same bits for any chunk.  The chunks of all segments
-// run as one sequence in which each chunk's global loads are issued before
-// the products of the previous one: 1.14x faster than a plain load-then-
-// multiply loop at the K = 12 ab-initio centre in the 64-thread tile, and
-// 1.16-1.23x at K = 16-24 in the 256-thread tile (36 VGPRs, 7 waves per
-// SIMD; an earlier form of that tile had needed enough registers to halve
-// its occupancy and was slower).  TILE = 64
-// (256 threads) for wide particle-number blocks, 32 (64 threads) for narrow
-// ones; every output accumulates the same sequence of 4-deep matrix-core
-// steps for either tile, so both tiles give the same bits.
-constexpr int kKC = 8;
-typedef double d4_t __attribute__((ext_vector_type(4)));
-
-template <int TILE>
-__global__ __launch_bounds__((TILE / 4) * (TILE / 4)) void k_tgemm(const TTask* __restrict__ tasks,
-                                                                  const TSeg* __restrict__ segs, BufSet bufs,
-                                                                  const double* __restrict__ coef,
-                                                                  const int* __restrict__ map) {
-    constexpr int NT = (TILE / 4) * (TILE / 4), WPR = TILE / 32;
-    static_assert(NT == 64 * WPR * WPR, "one wavefront per 32 x 32 quarter");
-    __shared__ double As[kKC][TILE + 1];
-    __shared__ double Bs[kKC][TILE + 1];
-    const TTask tk = tasks[blockIdx.x];
-    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const int wr = (wave / WPR) * 32, wc = (wave % WPR) * 32;
-    // the 16 x 16 blocks of the wavefront's quarter that hold outputs of the
-    // task: a tile at the edge of a narrow block skips the rest's products
-    bool live[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) live[i][j] = tk.r0 + wr + 16 * i < tk.M && tk.c0 + wc + 16 * j < tk.N;
-    const int li = lane % 16, lk = lane / 16;
-    d4_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
-    // the chunks of all segments in order; the global loads of the next
-    // chunk are issued before the products of the current one
-    constexpr int PER = TILE * kKC / NT;
-    static_assert(PER * NT == TILE * kKC, "a chunk is PER values per thread and operand");
-    int s = tk.s0, kb = 0;
-    TSeg sg{};
-    while (s < tk.s1) {
-        sg = segs[s];
-        if (sg.k0 < sg.k1) {
-            kb = sg.k0;
-            break;
-        }
-        ++s;
-    }
-    double ra[PER], rb[PER];
-    int cta = 0, ctb = 0;
-    auto fetch = [&]() {
-        const double cf = coef[sg.cidx];
-        const double* __restrict__ A = bufs.p[sg.a_buf] + sg.a_off;
-        const double* __restrict__ B = bufs.p[sg.b_buf] + sg.b_off;
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int idx = threadIdx.x + p * NT;
-            int r, k;
-            if (sg.ta == 0) {
-                r = idx / kKC;
-                k = idx % kKC;
-            } else {
-                k = idx / TILE;
-                r = idx % TILE;
-            }
-            const int gr = tk.r0 + r, gk = kb + k;
-            double v = 0.0;
-            if (gr < tk.M && gk < sg.k1)
-                v = (sg.ta == 0) ? A[(long long)gr * sg.lda + gk] : A[(long long)gk * sg.lda + gr];
-            ra[p] = cf * v;
-        }
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int idx = threadIdx.x + p * NT;
-            int c, k;
-            if (sg.tb == 0) {
-                k = idx / TILE;
-                c = idx % TILE;
-            } else {
-                c = idx / kKC;
-                k = idx % kKC;
-            }
-            const int gc = tk.c0 + c, gk = kb + k;
-            double v = 0.0;
-            if (gc < tk.N && gk < sg.k1)
-                v = (sg.tb == 0) ? B[(long long)gk * sg.ldb + gc] : B[(long long)gc * sg.ldb + gk];
-            rb[p] = v;
-        }
-        cta = sg.ta;
-        ctb = sg.tb;
-    };
-    if (s < tk.s1) fetch();
-    while (s < tk.s1) {
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int idx = threadIdx.x + p * NT;
-            if (cta == 0) As[idx % kKC][idx / kKC] = ra[p];
-            else As[idx / TILE][idx % TILE] = ra[p];
-            if (ctb == 0) Bs[idx / TILE][idx % TILE] = rb[p];
-            else Bs[idx % kKC][idx / kKC] = rb[p];
-        }
-        __syncthreads();
-        kb += kKC;
-        if (kb >= sg.k1) {
-            ++s;
-            while (s < tk.s1) {
-                sg = segs[s];
-                if (sg.k0 < sg.k1) {
-                    kb = sg.k0;
-                    break;
-                }
-                ++s;
-            }
-        }
-        if (s < tk.s1) fetch();
-#pragma unroll
-        for (int ks = 0; ks < kKC; ks += 4) {
-            const double a0 = As[ks + lk][wr + li], a1 = As[ks + lk][wr + 16 + li];
-            const double b0 = Bs[ks + lk][wc + li], b1 = Bs[ks + lk][wc + 16 + li];
-            if (live[0][0]) acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-            if (live[0][1]) acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-            if (live[1][0]) acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-            if (live[1][1]) acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    double* C = bufs.p[tk.c_buf] + tk.c_off;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = tk.r0 + wr + 16 * i + 4 * v + lk;
-            if (r >= tk.M) continue;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int c = tk.c0 + wc + 16 * j + li;
-                if (c >= tk.N) continue;
-                if (tk.mode == 0) {
-                    C[(long long)r * tk.ldc + c] = acc[i][j][v];
-                } else {
-                    const int p = map[tk.pack_off + (long long)r * tk.N + c];
-                    if (p >= 0) C[p] = acc[i][j][v];
-                }
-            }
-        }
-    }
-}
-
-// The same block products in split BF16 (three matrix-core products per
-// step, FP32 accumulation).  Every operand value v (FP64, the A operand
-// already times its segment coefficient) is split as v ~ hi + lo with
-// hi = bf16(v) and lo = bf16(v - hi), round to nearest even, and
-// A B ~ hi_A hi_B + hi_A lo_B + lo_A hi_B (the lo lo term is dropped): about
-// 16 significant bits per operand, so products carry a relative error of
-// order 1e-5.  K is staged in chunks of 16 as bf16 pairs, k contiguous per
-// row of A and per column of B, so that a lane fetches its four k values of
-// a v_mfma_f32_16x16x16_bf16 step with one 8-byte LDS read (lane l supplies
-// A(l % 16, 4 (l / 16) + t) and B(4 (l / 16) + t, l % 16), t < 4, and holds
-// D(4 (l / 16) + v, l % 16), v < 4).  The 16-deep steps keep a 64-thread
-// work-group at 5 KB of LDS and 48 VGPRs, so a CU holds as many as it has
-// wave slots (the 32-deep v_mfma_f32_16x16x32_bf16 with chunks of 32 needed
-// 10 KB and 97 VGPRs and was 1.5x slower at the K = 12 ab-initio centre).
-// The chunk loads are pipelined as in k_tgemm (1.4x faster in the 64-thread
-// tile, 1.2-1.25x in the 256-thread tile at K = 16-24).  Tiles, wavefront
-// layout and output addressing as in k_tgemm;
-// values must lie in the FP32 range.
-constexpr int kKC3 = 16;
-constexpr int kKC3Pad = kKC3 + 4;  // bf16 per LDS row (8-byte aligned rows)
-typedef float f4_t __attribute__((ext_vector_type(4)));
-typedef short s4_t __attribute__((ext_vector_type(4)));
-
-__device__ inline unsigned short bf16_rne(float f) {
-    unsigned int u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-__device__ inline void split_bf16(double v, unsigned short& hi, unsigned short& lo) {
-    hi = bf16_rne(float(v));
-    const double h = double(__uint_as_float((unsigned int)hi << 16));
-    lo = bf16_rne(float(v - h));
-}
-
-template <int TILE>
-__global__ __launch_bounds__((TILE / 4) * (TILE / 4)) void k_tgemm_bf3(const TTask* __restrict__ tasks,
-                                                                      const TSeg* __restrict__ segs, BufSet bufs,
-                                                                      const double* __restrict__ coef,
-                                                                      const int* __restrict__ map) {
-    constexpr int NT = (TILE / 4) * (TILE / 4), WPR = TILE / 32;
-    static_assert(NT == 64 * WPR * WPR, "one wavefront per 32 x 32 quarter");
-    __shared__ __align__(16) unsigned short Ah[TILE][kKC3Pad], Al[TILE][kKC3Pad];
-    __shared__ __align__(16) unsigned short Bh[TILE][kKC3Pad], Bl[TILE][kKC3Pad];
-    const TTask tk = tasks[blockIdx.x];
-    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const int wr = (wave / WPR) * 32, wc = (wave % WPR) * 32;
-    // the 16 x 16 blocks of the wavefront's quarter that hold outputs of the
-    // task: a tile at the edge of a narrow block skips the rest's products
-    bool live[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) live[i][j] = tk.r0 + wr + 16 * i < tk.M && tk.c0 + wc + 16 * j < tk.N;
-    const int li = lane % 16, lk = lane / 16;
-    f4_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f4_t{0.f, 0.f, 0.f, 0.f};
-    // as in k_tgemm: the chunks of all segments in order, each chunk's
-    // global loads issued before the products of the previous one
-    constexpr int PER = TILE * kKC3 / NT;
-    static_assert(PER * NT == TILE * kKC3, "a chunk is PER values per thread and operand");
-    int s = tk.s0, kb = 0;
-    TSeg sg{};
-    while (s < tk.s1) {
-        sg = segs[s];
-        if (sg.k0 < sg.k1) {
-            kb = sg.k0;
-            break;
-        }
-        ++s;
-    }
-    double ra[PER], rb[PER];
-    int cta = 0, ctb = 0;
-    auto fetch = [&]() {
-        const double cf = coef[sg.cidx];
-        const double* __restrict__ A = bufs.p[sg.a_buf] + sg.a_off;
-        const double* __restrict__ B = bufs.p[sg.b_buf] + sg.b_off;
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int idx = threadIdx.x + p * NT;
-            int r, k;
-            if (sg.ta == 0) {
-                r = idx / kKC3;
-                k = idx % kKC3;
-            } else {
-                k = idx / TILE;
-                r = idx % TILE;
-            }
-            const int gr = tk.r0 + r, gk = kb + k;
-            double v = 0.0;
-            if (gr < tk.M && gk < sg.k1)
-                v = (sg.ta == 0) ? A[(long long)gr * sg.lda + gk] : A[(long long)gk * sg.lda + gr];
-            ra[p] = cf * v;
-        }
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int idx = threadIdx.x + p * NT;
-            int c, k;
-            if (sg.tb == 0) {
-                k = idx / TILE;
-                c = idx % TILE;
-            } else {
-                c = idx / kKC3;
-                k = idx % kKC3;
-            }
-            const int gc = tk.c0 + c, gk = kb + k;
-            double v = 0.0;
-            if (gc < tk.N && gk < sg.k1)
-                v = (sg.tb == 0) ? B[(long long)gk * sg.ldb + gc] : B[(long long)gc * sg.ldb + gk];
-            rb[p] = v;
-        }
-        cta = sg.ta;
-        ctb = sg.tb;
-    };
-    if (s < tk.s1) fetch();
-    while (s < tk.s1) {
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int idx = threadIdx.x + p * NT;
-            const int ar = cta == 0 ? idx / kKC3 : idx % TILE, ak = cta == 0 ? idx % kKC3 : idx / TILE;
-            const int bc = ctb == 0 ? idx % TILE : idx / kKC3, bk = ctb == 0 ? idx / TILE : idx % kKC3;
-            split_bf16(ra[p], Ah[ar][ak], Al[ar][ak]);
-            split_bf16(rb[p], Bh[bc][bk], Bl[bc][bk]);
-        }
-        __syncthreads();
-        kb += kKC3;
-        if (kb >= sg.k1) {
-            ++s;
-            while (s < tk.s1) {
-                sg = segs[s];
-                if (sg.k0 < sg.k1) {
-                    kb = sg.k0;
-                    break;
-                }
-                ++s;
-            }
-        }
-        if (s < tk.s1) fetch();
-        s4_t ah[2], al[2], bh[2], bl[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            ah[i] = *reinterpret_cast<const s4_t*>(&Ah[wr + 16 * i + li][4 * lk]);
-            al[i] = *reinterpret_cast<const s4_t*>(&Al[wr + 16 * i + li][4 * lk]);
-            bh[i] = *reinterpret_cast<const s4_t*>(&Bh[wc + 16 * i + li][4 * lk]);
-            bl[i] = *reinterpret_cast<const s4_t*>(&Bl[wc + 16 * i + li][4 * lk]);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (!live[i][j]) continue;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al[i], bh[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah[i], bl[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah[i], bh[j], acc[i][j], 0, 0, 0);
-            }
-        __syncthreads();
-    }
-    double* C = bufs.p[tk.c_buf] + tk.c_off;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = tk.r0 + wr + 16 * i + 4 * lk + v;
-            if (r >= tk.M) continue;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int c = tk.c0 + wc + 16 * j + li;
-                if (c >= tk.N) continue;
-                if (tk.mode == 0) {
-                    C[(long long)r * tk.ldc + c] = double(acc[i][j][v]);
-                } else {
-                    const int p = map[tk.pack_off + (long long)r * tk.N + c];
-                    if (p >= 0) C[p] = double(acc[i][j][v]);
-                }
-            }
-        }
-    }
-}
-
 __global__ __launch_bounds__(kThreads) void k_to_f32(const double* __restrict__ in, float* __restrict__ out,
                                                        long long n) {
     const long long e = (long long)blockIdx.x * kThreads + threadIdx.x;
     if (e < n) out[e] = float(in[e]);
 }
 
-__global__ __launch_bounds__(kThreads) void k_gather(const int* __restrict__ map, const double* __restrict__ src,
-                                                       double* __restrict__ dst, long long n) {
-    const long long e = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= n) return;
-    const int p = map[e];
-    dst[e] = p >= 0 ? src[p] : 0.0;
-}
-
-// sa += pa[g stride + e], sb += pb[g stride + e] for g = 0..G-1 in order,
-// the loads of U slots issued together (wide sums: the tiled products leave
-// G x tr_split slots, over a hundred)
+// the sum of p[g stride + e] over g = 0..G-1 in order, U slots' loads issued
+// together
 template <int U>
-__device__ inline void sum_slots(const double* __restrict__ pa, const double* __restrict__ pb, long long stride,
-                                 int G, long long e, double& sa, double& sb) {
+__device__ inline double sum_slots(const double* __restrict__ p, long long stride, int G, long long e) {
+    double s = 0.0;
     int g = 0;
     for (; g + U <= G; g += U) {
-        double a[U], b[U];
+        double a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = pa[(g + u) * stride + e];
-            b[u] = pb[(g + u) * stride + e];
-        }
+        for (int u = 0; u < U; ++u) a[u] = p[(g + u) * stride + e];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            sa += a[u];
-            sb += b[u];
-        }
+        for (int u = 0; u < U; ++u) s += a[u];
     }
-    for (; g < G; ++g) {
-        sa += pa[g * stride + e];
-        sb += pb[g * stride + e];
-    }
+    for (; g < G; ++g) s += p[g * stride + e];
+    return s;
 }
 
+// 64 elements per work-group (a wavefront's width: the vectors are short, so
+// wider groups leave most of the chip idle); wavefront w adds its quarter of
+// the slots, then the four sums are added in order.  blockIdx.y: the output.
 __global__ __launch_bounds__(kThreads) void k_gsum2(const double* __restrict__ pa, const double* __restrict__ pb,
-                                                      long long stride, int G, int n, double* __restrict__ outa,
-                                                      double* __restrict__ outb) {
-    const int e = blockIdx.x * kThreads + threadIdx.x;
-    if (e >= n) return;
-    double sa = 0.0, sb = 0.0;
-    sum_slots<16>(pa, pb, stride, G, e, sa, sb);
-    outa[e] = sa;
-    outb[e] = sb;
+                                                      long long stride, int Ga, int Gb, int n,
+                                                      double* __restrict__ outa, double* __restrict__ outb) {
+    __shared__ double red[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lane, G = blockIdx.y ? Gb : Ga;
+    const int g0 = G * wave / 4, g1 = G * (wave + 1) / 4;
+    const double* __restrict__ p = blockIdx.y ? pb : pa;
+    red[wave][lane] = e < n ? sum_slots<8>(p + g0 * stride, stride, g1 - g0, e) : 0.0;
+    __syncthreads();
+    if (wave == 0 && e < n)
+        (blockIdx.y ? outb : outa)[e] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
 // ---- grid-parallel Davidson passes ----------------------------------------
@@ -1169,7 +814,7 @@ __device__ inline void dav_gram_body(double* __restrict__ V, double* __restrict_
                                                          const double* __restrict__ pn, int npn,
                                                          double* __restrict__ tnorm,
                                                          const double* __restrict__ ypart,
-                                                         const double* __restrict__ nypart, long long gstride, int G,
+                                                         const double* __restrict__ nypart, long long gstride, int G, int Gn,
                                                          double* __restrict__ part, int chunk, int grp) {
     __shared__ double vs[kDavChunk], hs[kDavChunk], ns[kDavChunk];
     __shared__ double wred[4][64];
@@ -1191,7 +836,8 @@ __device__ inline void dav_gram_body(double* __restrict__ V, double* __restrict_
         const long long o = (long long)m * ld + e;
         vm = t ? t[e] * inv : V[o];
         if (ypart) {
-            sum_slots<8>(ypart, nypart, gstride, G, e, hm, nm);
+            hm = sum_slots<8>(ypart, gstride, G, e);
+            nm = sum_slots<8>(nypart, gstride, Gn, e);
         } else {
             hm = HV[o];
             nm = NV[o];
@@ -1287,9 +933,9 @@ __global__ __launch_bounds__(kThreads) void k_dav_gram(double* __restrict__ V, d
                                                          const double* __restrict__ pn, int npn,
                                                          double* __restrict__ tnorm,
                                                          const double* __restrict__ ypart,
-                                                         const double* __restrict__ nypart, long long gstride, int G,
+                                                         const double* __restrict__ nypart, long long gstride, int G, int Gn,
                                                          double* __restrict__ part) {
-    dav_gram_body(V, HV, NV, ld, m, n, t, pn, npn, tnorm, ypart, nypart, gstride, G, part, blockIdx.x, blockIdx.y);
+    dav_gram_body(V, HV, NV, ld, m, n, t, pn, npn, tnorm, ypart, nypart, gstride, G, Gn, part, blockIdx.x, blockIdx.y);
 }
 
 // batched passes: blockIdx.y (blockIdx.z for the Gram pass) is the instance;
@@ -1315,40 +961,20 @@ __global__ __launch_bounds__(kThreads) void k_bdav_gram(const DavInst* __restric
     const int nd = 4 * I.m + 2;
     if (!I.active || !I.ext || (int)blockIdx.x >= dav_chunks(I.n) || (int)blockIdx.y * kGramGroup >= nd) return;
     dav_gram_body(I.V, I.HV, I.NV, I.ld, I.m, I.n, I.from_t ? I.t : nullptr, I.pn, dav_chunks(I.n), I.tnorm,
-                  I.ypart, I.nypart, I.gstride, I.G, I.pg, blockIdx.x, blockIdx.y);
+                  I.ypart, I.nypart, I.gstride, I.G, I.Gn, I.pg, blockIdx.x, blockIdx.y);
 }
 
 inline int nblk(int n) { return (n + kThreads - 1) / kThreads; }
 
 }  // namespace
 
-void tgemm_bf3(hipStream_t s, const TTask* tasks, int ntasks, const TSeg* segs, BufSet bufs, const double* coef,
-               const int* map, int tile) {
-    if (ntasks <= 0) return;
-    if (tile == 32)
-        hipLaunchKernelGGL(k_tgemm_bf3<32>, dim3(ntasks), dim3(64), 0, s, tasks, segs, bufs, coef, map);
-    else
-        hipLaunchKernelGGL(k_tgemm_bf3<64>, dim3(ntasks), dim3(256), 0, s, tasks, segs, bufs, coef, map);
-}
-
-void tgemm(hipStream_t s, const TTask* tasks, int ntasks, const TSeg* segs, BufSet bufs, const double* coef,
-           const int* map, int tile) {
-    if (ntasks <= 0) return;
-    if (tile == 32)
-        hipLaunchKernelGGL(k_tgemm<32>, dim3(ntasks), dim3(64), 0, s, tasks, segs, bufs, coef, map);
-    else
-        hipLaunchKernelGGL(k_tgemm<64>, dim3(ntasks), dim3(256), 0, s, tasks, segs, bufs, coef, map);
-}
 void to_f32(hipStream_t s, const double* in, float* out, long long n) {
     if (n > 0)
         hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, in, out, n);
 }
-void gather(hipStream_t s, const int* map, const double* src, double* dst, long long n) {
-    if (n > 0) hipLaunchKernelGGL(k_gather, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, map, src, dst, n);
-}
-void gsum2(hipStream_t s, const double* pa, const double* pb, long long stride, int G, int n, double* outa,
+void gsum2(hipStream_t s, const double* pa, const double* pb, long long stride, int Ga, int Gb, int n, double* outa,
            double* outb) {
-    hipLaunchKernelGGL(k_gsum2, dim3(nblk(n)), dim3(kThreads), 0, s, pa, pb, stride, G, n, outa, outb);
+    hipLaunchKernelGGL(k_gsum2, dim3((n + 63) / 64, 2), dim3(kThreads), 0, s, pa, pb, stride, Ga, Gb, n, outa, outb);
 }
 void bgemm(hipStream_t s, const BTask* tasks, int ntasks, const BTerm* terms, BufSet bufs,
            const double* coef) {
@@ -1420,10 +1046,10 @@ void dav_normalize(hipStream_t s, const double* part, int nchunk, const double* 
 }
 void dav_gram(hipStream_t s, double* V, double* HV, double* NV, long long ld, int m, int n, const double* t,
               const double* pn, int npn, double* tnorm, const double* ypart, const double* nypart, long long gstride,
-              int G, double* part) {
+              int G, int Gn, double* part) {
     const int nd = 4 * m + 2;
     hipLaunchKernelGGL(k_dav_gram, dim3(dav_chunks(n), (nd + kGramGroup - 1) / kGramGroup), dim3(kThreads), 0, s, V, HV,
-                       NV, ld, m, n, t, pn, npn, tnorm, ypart, nypart, gstride, G, part);
+                       NV, ld, m, n, t, pn, npn, tnorm, ypart, nypart, gstride, G, Gn, part);
 }
 
 void bdav_ritz(hipStream_t s, const DavInst* insts, int ninst, int max_n) {

@@ -14,6 +14,9 @@
 //   L_g[k] = A^T V_g                          (left environment update)
 //   right pass mirrors it for R_g[k].
 //
+// These are the plain path's passes; the tiled path runs each line's products
+// as one chained launch (y and ny together) that keeps T and V in registers.
+//
 // The environments are blocked by particle number only: the rotation
 // exp(-i beta S_y) mixes M, so every (N_bra, N_ket) block is dense in M
 // (the subduction described in Sec. 2.3).  Site tensors and H_eff vectors
@@ -33,6 +36,7 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <numeric>
 #include <memory>
 #include <mutex>
 #include <set>
@@ -245,81 +249,66 @@ struct CList {
     }
 };
 
-struct TList {
-    std::vector<spk::TTask> tasks;
-    std::vector<spk::TSeg> segs;
-    int tile = spk::kTile;  // output tile of every task (64 or 32)
-    DArr<spk::TTask> dtasks;
-    DArr<spk::TSeg> dsegs;
-    void add_task(int c_buf, long long c_off, int ldc, int M, int N, int r0, int c0, int mode, long long pack_off) {
-        spk::TTask t{};
-        t.c_off = c_off;
-        t.pack_off = pack_off;
-        t.c_buf = c_buf;
-        t.ldc = ldc;
-        t.M = M;
-        t.N = N;
-        t.r0 = r0;
-        t.c0 = c0;
-        t.s0 = t.s1 = int(segs.size());
-        t.mode = mode;
-        tasks.push_back(t);
-    }
-    void add_seg(int a_buf, long long a_off, int lda, int ta, int b_buf, long long b_off, int ldb, int tb, int k0,
-                 int k1, int cidx) {
-        spk::TSeg g{};
-        g.a_off = a_off;
-        g.b_off = b_off;
-        g.a_buf = a_buf;
-        g.b_buf = b_buf;
-        g.lda = lda;
-        g.ldb = ldb;
-        g.ta = ta;
-        g.tb = tb;
-        g.k0 = k0;
-        g.k1 = k1;
-        g.cidx = cidx;
-        segs.push_back(g);
-        tasks.back().s1 = int(segs.size());
-    }
-    void upload(hipStream_t s) {
-        dtasks.upload(tasks, s);
-        dsegs.upload(segs, s);
-    }
-    void launch(hipStream_t s, const spk::BufSet& b, const double* coef, const int* map, bool bf3 = false) const {
-        if (bf3) spk::tgemm_bf3(s, dtasks.p, int(tasks.size()), dsegs.p, b, coef, map, tile);
-        else spk::tgemm(s, dtasks.p, int(tasks.size()), dsegs.p, b, coef, map, tile);
-    }
-};
-
 // lists of a chained product (the same for every quadrature point)
 struct ChainList {
-    int lay = spk::kChainHeff, shape = 0;
+    int lay = spk::kChainHeff, shape = 0, waves = spk::kChainWaves;
     std::vector<spk::KTile> tiles;
     std::vector<spk::KStep> steps;
     std::vector<spk::KSeg> segs;
     DArr<spk::KTile> dtiles;
     DArr<spk::KStep> dsteps;
     DArr<spk::KSeg> dsegs;
-    void begin_tile(spk::KTile t) {
-        t.s0 = t.s1 = int(steps.size());
-        tiles.push_back(t);
+    // the steps of the tile being built: of the sum, and of N_eff x
+    std::vector<spk::KStep> own, metric;
+    void begin_step(long long p_off, int ldp, int kc0, int kc1, bool of_metric = false) {
+        (of_metric ? metric : own).push_back(spk::KStep{p_off, ldp, kc0, kc1, int(segs.size()), int(segs.size()), 0});
     }
-    // opens a step of the last tile; a step left without segments is dropped
-    void begin_step(int p_buf, long long p_off, int ldp, int kc0, int kc1) {
-        drop_empty();
-        steps.push_back(spk::KStep{p_off, p_buf, ldp, kc0, kc1, int(segs.size()), int(segs.size())});
-        tiles.back().s1 = int(steps.size());
+    // alt_x: the rotated site tensor, alt_e: the mixed environment
+    void add_seg(long long a_off, int lda, long long b_off, int ldb, int k0, int k1, double cf, bool alt_x, bool alt_e,
+                 bool of_metric = false) {
+        segs.push_back(spk::KSeg{a_off, b_off, cf, lda, ldb, k0, k1, alt_x, alt_e});
+        (of_metric ? metric : own).back().g1 = int(segs.size());
     }
-    void add_seg(int a_buf, long long a_off, int lda, int b_buf, long long b_off, int ldb, int k0, int k1, int cidx) {
-        segs.push_back(spk::KSeg{a_off, b_off, a_buf, b_buf, lda, ldb, k0, k1, cidx, 0});
-        steps.back().g1 = int(segs.size());
+    // matrix-core steps of a step (blocks of 16 kc values times the 8-deep
+    // chunks of its segments, then the outer product), plus its latency
+    int weight(const spk::KStep& p, int nm) const {
+        const int ni = (p.kc1 - p.kc0 + 15) / 16;
+        int w = 12 + 4 * ni * nm;
+        for (int g = p.g0; g < p.g1; ++g) w += 2 * ni * ((segs[g].k1 - segs[g].k0 + 7) / 8);
+        return w;
     }
-    void drop_empty() {
-        if (!steps.empty() && tiles.back().s1 > tiles.back().s0 && steps.back().g0 == steps.back().g1) {
-            steps.pop_back();
-            --tiles.back().s1;
+    // closes the tile: steps without segments are dropped, the others dealt to
+    // the wavefronts, the heaviest first to the least loaded
+    void end_tile(spk::KTile t) {
+        auto has = [](const spk::KStep& p) { return p.g1 > p.g0; };
+        const int nm = (t.m1 - t.m0 + 15) / 16;
+        t.e0 = int(steps.size());
+        int load[spk::kChainWaves] = {};
+        for (const spk::KStep& p : metric)
+            if (has(p)) {
+                steps.push_back(p);
+                load[waves - 1] += weight(p, nm);
+            }
+        t.e1 = int(steps.size());
+        std::vector<std::pair<int, int>> order;
+        for (int i = 0; i < int(own.size()); ++i)
+            if (has(own[i])) order.push_back({-weight(own[i], nm), i});
+        std::sort(order.begin(), order.end());
+        std::vector<int> of[spk::kChainWaves];
+        for (const auto& o : order) {
+            const int w = int(std::min_element(load, load + waves) - load);
+            load[w] -= o.first;
+            of[w].push_back(o.second);
         }
+        t.s[0] = int(steps.size());
+        for (int w = 0; w < spk::kChainWaves; ++w) {
+            std::sort(of[w].begin(), of[w].end());
+            for (int i : of[w]) steps.push_back(own[i]);
+            t.s[w + 1] = int(steps.size());
+        }
+        own.clear();
+        metric.clear();
+        tiles.push_back(t);
     }
     void upload(hipStream_t s) {
         dtiles.upload(tiles, s);
@@ -329,31 +318,117 @@ struct ChainList {
 };
 // one side's environment with the unrotated MPO mixed in
 struct MixList {
-    std::vector<spk::MTask> tasks;
-    std::vector<spk::MTerm> terms;
-    DArr<spk::MTask> dtasks;
-    DArr<spk::MTerm> dterms;
-    long long size = 0;   // values per quadrature point
-    double flops = 0.0;   // per quadrature point
-    void add_task(int n) {
-        tasks.push_back(spk::MTask{size, n, int(terms.size()), int(terms.size()), 0});
+    std::vector<spk::MixWork> work;
+    std::vector<spk::MixTileRec> tiles;
+    std::vector<long long> src;
+    std::vector<spk::MixGroup> groups;
+    std::vector<double> cf;
+    std::vector<int> at;
+    DArr<spk::MixWork> dwork;
+    DArr<spk::MixTileRec> dtiles;
+    DArr<long long> dsrc;
+    DArr<spk::MixGroup> dgroups;
+    DArr<double> dcf;
+    DArr<int> dat;
+    long long size = 0;  // values per quadrature point
+    double flops = 0.0;  // per quadrature point
+    // blocks to be mixed by shape (bra block, ket block): offset, then the
+    // terms (environment block, coefficient)
+    struct Block {
+        long long off;
+        std::vector<std::pair<int, double>> terms;
+    };
+    std::map<std::pair<int, int>, std::vector<Block>> shapes;
+    long long add(int i, int j, int n, std::vector<std::pair<int, double>> t) {
+        flops += 2.0 * n * t.size();
+        std::sort(t.begin(), t.end());
+        shapes[{i, j}].push_back({size, std::move(t)});
         size += n;
+        return size - n;
     }
-    void add_term(long long a_off, int cidx) {
-        terms.push_back(spk::MTerm{a_off, cidx, 0});
-        tasks.back().t1 = int(terms.size());
-        flops += 2.0 * tasks.back().n;
+    bool empty() const { return shapes.empty(); }
+    void finish(const EnvLayout& env) {
+        std::vector<int> weight;
+        for (const auto& sh : shapes) {
+            std::set<int> used;
+            for (const Block& b : sh.second)
+                for (const auto& t : b.terms) used.insert(t.first);
+            const std::vector<int> blk(used.begin(), used.end());
+            // blocks of the same sources
+            std::map<std::vector<int>, std::vector<const Block*>> alike;
+            for (const Block& b : sh.second) {
+                std::vector<int> from;
+                for (const auto& t : b.terms) from.push_back(t.first);
+                alike[from].push_back(&b);
+            }
+            const int tile0 = int(tiles.size());
+            for (size_t s0 = 0; s0 < blk.size(); s0 += spk::kMixTile) {
+                const size_t s1 = std::min(blk.size(), s0 + spk::kMixTile);
+                spk::MixTileRec tr{int(src.size()), 0, int(groups.size()), 0};
+                for (size_t q = s0; q < s1; ++q) src.push_back(env.blk[blk[q]].off);
+                tr.s1 = int(src.size());
+                for (const auto& al : alike) {
+                    const std::vector<int>& from = al.first;
+                    const size_t q0 = std::lower_bound(from.begin(), from.end(), blk[s0]) - from.begin(),
+                                 q1 = std::upper_bound(from.begin(), from.end(), blk[s1 - 1]) - from.begin();
+                    if (q0 == q1) continue;
+                    for (size_t b0 = 0; b0 < al.second.size(); b0 += spk::kMixGroup) {
+                        spk::MixGroup gr{};
+                        gr.n = int(std::min<size_t>(spk::kMixGroup, al.second.size() - b0));
+                        gr.first = q0 == 0;
+                        gr.t0 = int(at.size());
+                        for (int b = 0; b < gr.n; ++b) gr.o[b] = al.second[b0 + b]->off;
+                        for (size_t q = q0; q < q1; ++q) {
+                            at.push_back(int(std::lower_bound(blk.begin(), blk.end(), from[q]) - blk.begin() - s0));
+                            for (int b = 0; b < spk::kMixGroup; ++b)
+                                cf.push_back(b < gr.n ? al.second[b0 + b]->terms[q].second : 0.0);
+                        }
+                        gr.t1 = int(at.size());
+                        groups.push_back(gr);
+                    }
+                }
+                tr.i1 = int(groups.size());
+                // the longest sums first
+                std::stable_sort(groups.begin() + tr.i0, groups.end(), [](const spk::MixGroup& a, const spk::MixGroup& b) {
+                    return a.t1 - a.t0 > b.t1 - b.t0;
+                });
+                tiles.push_back(tr);
+            }
+            const EnvBlk& e = env.blk[blk[0]];
+            const int n = e.rows * e.cols;
+            for (int e0 = 0; e0 < n; e0 += 64) work.push_back(spk::MixWork{tile0, int(tiles.size()), e0, n});
+            weight.resize(work.size(), terms_of(work.back()));
+        }
+        // the shapes with the most terms first
+        std::vector<int> ord(work.size());
+        std::iota(ord.begin(), ord.end(), 0);
+        std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return weight[a] > weight[b]; });
+        std::vector<spk::MixWork> by(work.size());
+        for (size_t i = 0; i < ord.size(); ++i) by[i] = work[ord[i]];
+        work.swap(by);
+    }
+    int terms_of(const spk::MixWork& w) const {
+        int n = 0;
+        for (int i = tiles[w.tile0].i0; i < tiles[w.tile1 - 1].i1; ++i) n += groups[i].t1 - groups[i].t0;
+        return n;
     }
     void upload(hipStream_t s) {
-        dtasks.upload(tasks, s);
-        dterms.upload(terms, s);
+        dwork.upload(work, s);
+        dtiles.upload(tiles, s);
+        dsrc.upload(src, s);
+        dgroups.upload(groups, s);
+        dcf.upload(cf, s);
+        dat.upload(at, s);
+    }
+    spk::MixLists lists() const {
+        return spk::MixLists{dwork.p, dtiles.p, dsrc.p, dgroups.p, dcf.p, dat.p, int(work.size()), 0};
     }
 };
 
 // buffer slots of a launch; B_BRA is the site tensor on the bra side of the
 // plain-path environment updates (the same as B_X except for the mixed
 // environments of an orthogonality constraint)
-enum Buf { B_ENVL = 0, B_ENVR = 1, B_X = 2, B_T = 3, B_V = 4, B_Y = 5, B_NY = 6, B_OUT = 7, B_BRA = 8, B_LT = 9 };
+enum Buf { B_ENVL = 0, B_ENVR = 1, B_X = 2, B_T = 3, B_V = 4, B_Y = 5, B_NY = 6, B_OUT = 7, B_BRA = 8 };
 
 struct SitePlan {
     // coefficient table [G][nc]
@@ -371,7 +446,6 @@ struct SitePlan {
     int nWr = 0;
     int c_wr(int e) const { return 2 * nW + 18 + e; }
     int c_r(int s, int u) const { return 2 * nW + 18 + nWr + 4 * s + u; }
-    int c_minus() const { return 2 * nW + 18 + nWr + 16; }
     // scratch sizes per quadrature point
     long long Tsize = 0, Vsize = 0, Zsize = 0, Ztsize = 0;
     BList p1, yout, envl_out, p1r, envr_out;
@@ -400,44 +474,23 @@ struct SitePlan {
     std::vector<long long> lq_roff;  // per left sector of bond k-1
     BList absorb_right;  // R of site k into site k+1
     BList absorb_left;   // L of site k into site k-1
-    // tiled path: dense particle-number layout of the site and its tile lists
+    // tiled path: dense particle-number layout of the site
     long long Xd_size = 0;
     std::vector<int> xmap_h;  // dense element -> packed index or -1
     DArr<int> xmap;
-    TList t_left, t_right, t_envl, t_zr, t_envr;
-    // H_eff x of the tiled block products from the pre-mixed left
-    // environment Lt(sigma, c', sigma', i) = sum_c W~_g[c, c', sigma, sigma'] L_g(c, i)
-    // (premix, once per local problem), V = sum_sigma' Lt Xd(sigma') (t_leftv)
-    // and the identity-channel products T(0, i, sigma') for N_eff (t_left0)
     // chained products: the environment updates, the pre-mixed environments
     // they (and H_eff x at wide MPOs) use, the packed indices of the rotated
     // site vector's two states
     std::vector<std::array<int, 4>> wr_ent;  // unrotated MPO entries (a, b, s, s')
-    ChainList c_envl, c_envr;
+    ChainList c_heff, c_envl, c_envr;
+    int y_split = 1;                         // channel chunks of H_eff x (partials of y: y_split * G)
     MixList mix_l, mix_r;                    // empty: the products read the environment itself
     std::vector<int> rmap_h;
     DArr<int> rmap;
-    CList premix, xrmix;
-    TList t_leftv, t_left0;
-    long long LTsize = 0;
-    int tr_split = 1;  // channel chunks of the tiled right product (partials: tr_split * G)
-    // fused H_eff x
-    int h_rows = 0;         // rows per task (RC); 0: no fused plan
-    int h_lds = 0;          // dynamic LDS per work-group (doubles)
-    std::vector<spk::H3Task> h_tasks;
-    std::vector<spk::H3Blk> h_blks;
-    std::vector<spk::H3Col> h_cols;
-    std::vector<spk::H3LSrc> h_lsrc;
-    std::vector<spk::H3Seg> h_segs;
-    std::vector<spk::H3Term> h_terms;
-    std::vector<spk::H3Piece> h_pieces;
-    DArr<spk::H3Task> dh_tasks;
-    DArr<spk::H3Blk> dh_blks;
-    DArr<spk::H3Col> dh_cols;
-    DArr<spk::H3LSrc> dh_lsrc;
-    DArr<spk::H3Seg> dh_segs;
-    DArr<spk::H3Term> dh_terms;
-    DArr<spk::H3Piece> dh_pieces;
+    // fused plan of H_eff x: rows per task and LDS (doubles) of the row-chunk
+    // form; 0: the site's MPO is too wide for one
+    int h_rows = 0;
+    int h_lds = 0;
 };
 
 }  // namespace
@@ -478,9 +531,10 @@ struct sp_handle {
     std::vector<long long> Lgen;
     int lt_site = -1;   // -1: none (the scratch holds a right environment, or nothing)
     long long lt_gen = -1;
+    bool lt_f32 = false;
     long long Xr_cap = 0;
     long long Xd_cap = 0;
-    int tr_split_max = 1;  // partial slots per quadrature point (tiled lists)
+    int y_split_max = 1;  // partial slots of y per quadrature point
     long long T_cap = 0, V_cap = 0, qr_scratch_cap = 0, qr_r_cap = 0;
     int center = 1;
     // Davidson workspace
@@ -804,11 +858,9 @@ void build_plan(sp_handle* h, int k) {
         byR[size_t(q[2]) * wl + q[0]].push_back({q[1], q[3], e});
         if (q[2] == q[3]) byD[q[2]].push_back({q[0], q[1], e});
     }
-    // the unrotated entries W[a, b, s, s'] of the blocks in the pattern, by
-    // (s, b) as (a, s', entry) in ascending order: the block products
-    // pre-mix the left environment with them and apply the rotation to the
-    // site vector instead (Eq. [expSy] acts on s' only)
-    std::vector<std::vector<std::array<int, 3>>> byWr(size_t(4) * wr);
+    // the unrotated entries W[a, b, s, s'] of the blocks in the pattern: the
+    // chained products rotate the site vector instead (Eq. [expSy] acts on s'
+    // only)
     std::vector<double> wr_val;
     {
         std::set<std::pair<int, int>> blocks;
@@ -818,14 +870,13 @@ void build_plan(sp_handle* h, int k) {
             for (int s2 = 0; s2 < 4; ++s2)
                 for (int v = 0; v < 4; ++v)
                     if (op[s2 * 4 + v] != 0.0) {
-                        byWr[size_t(s2) * wr + ab.second].push_back({ab.first, v, int(wr_val.size())});
                         wr_val.push_back(op[s2 * 4 + v]);
                         P.wr_ent.push_back({ab.first, ab.second, s2, v});
                     }
         }
     }
     P.nWr = int(wr_val.size());
-    P.nc = 2 * P.nW + 18 + P.nWr + 17;
+    P.nc = 2 * P.nW + 18 + P.nWr + 16;
     P.coef_h.assign(size_t(G) * P.nc, 0.0);
     for (int g = 0; g < G; ++g) {
         double* cf = &P.coef_h[size_t(g) * P.nc];
@@ -841,7 +892,6 @@ void build_plan(sp_handle* h, int k) {
         for (int s = 0; s < 4; ++s)
             for (int u = 0; u < 4; ++u) cf[P.c_gr(s, u)] = h->qcoef[g] * rot_value(s, u, h->qc[g], h->qs[g]);
         cf[P.c_one()] = 1.0;
-        cf[P.c_minus()] = -1.0;
         for (int e = 0; e < P.nWr; ++e) cf[P.c_wr(e)] = wr_val[e];
         for (int s = 0; s < 4; ++s)
             for (int u = 0; u < 4; ++u) cf[P.c_r(s, u)] = rot_value(s, u, h->qc[g], h->qs[g]);
@@ -1257,327 +1307,14 @@ void build_plan(sp_handle* h, int k) {
             for (int c = 0; c < X.cols; ++c)
                 P.xmap_h[base + (long long)(SA.ro + r) * ldb + SB.ro + c] = int(X.off + (long long)r * X.cols + c);
     }
-    auto xdoff = [&](int j, int q) { return Xdoff[size_t(j) * 4 + q]; };
-    // rows of N-block j (bond k-1) that columns [c0, c1) of N-block jb (bond k)
-    // reach through sigma, as one contiguous range
-    auto k_from_cols = [&](int jb, int q, int c0, int c1, int& k0, int& k1) {
-        k0 = INT32_MAX;
-        k1 = -1;
-        const NBlock& NB = br.nb[jb];
-        for (int sb = NB.s0; sb < NB.s1; ++sb) {
-            const Sector& SB = br.sec[sb];
-            if (SB.ro + SB.dim <= c0 || SB.ro >= c1) continue;
-            const int sa = bl.sector(SB.n - kSigmaN[q], SB.m2 - kSigma2M[q]);
-            if (sa < 0) continue;
-            k0 = std::min(k0, bl.sec[sa].ro);
-            k1 = std::max(k1, bl.sec[sa].ro + bl.sec[sa].dim);
-        }
-        return k1 > k0;
-    };
-    // columns of N-block jb (bond k) that rows [r0, r1) of N-block j reach
-    auto k_from_rows = [&](int j, int q, int r0, int r1, int& k0, int& k1) {
-        k0 = INT32_MAX;
-        k1 = -1;
-        const NBlock& NA = bl.nb[j];
-        for (int sa = NA.s0; sa < NA.s1; ++sa) {
-            const Sector& SA = bl.sec[sa];
-            if (SA.ro + SA.dim <= r0 || SA.ro >= r1) continue;
-            const int sb = br.sector(SA.n + kSigmaN[q], SA.m2 + kSigma2M[q]);
-            if (sb < 0) continue;
-            k0 = std::min(k0, br.sec[sb].ro);
-            k1 = std::max(k1, br.sec[sb].ro + br.sec[sb].dim);
-        }
-        return k1 > k0;
-    };
-    // output tile of the site's lists: 32 when the particle-number blocks of
-    // both bonds are narrow (dimension-weighted mean <= 32), else 64
-    int TT = spk::kTile;
-    {
-        double wsum = 0.0, dsum = 0.0;
-        for (const Bond* bd : {&bl, &br})
-            for (const NBlock& nb : bd->nb) {
-                wsum += double(nb.dim) * nb.dim;
-                dsum += nb.dim;
-            }
-        if (dsum > 0 && wsum / dsum <= 32.0) TT = 32;
-    }
-    for (TList* tl : {&P.t_left, &P.t_right, &P.t_envl, &P.t_zr, &P.t_envr}) tl->tile = TT;
-    // left product: T(eb, sigma') = L_g(eb) Xd(j, sigma', jb)
-    for (int g = 0; g < G; ++g)
-        for (size_t e = 0; e < el.blk.size(); ++e)
-            for (int q = 0; q < 4; ++q) {
-                if (Toff[e * 4 + q] < 0) continue;
-                const EnvBlk& eb = el.blk[e];
-                const int jb = br.nblock(bl.nb[eb.j].n + kSigmaN[q]);
-                const int ncol = br.nb[jb].dim;
-                for (int r0 = 0; r0 < eb.rows; r0 += TT)
-                    for (int c0 = 0; c0 < ncol; c0 += TT) {
-                        P.t_left.add_task(B_T, g * P.Tsize + Toff[e * 4 + q], ncol, eb.rows, ncol, r0, c0, 0, 0);
-                        int k0, k1;
-                        if (k_from_cols(jb, q, c0, std::min(ncol, c0 + TT), k0, k1))
-                            P.t_left.add_seg(B_ENVL, g * Lsz + eb.off, eb.cols, 0, B_X, xdoff(eb.j, q), ncol, 0, k0, k1,
-                                             g * P.nc + P.c_one());
-                    }
-            }
-    // Pre-mixed left environment with the unrotated MPO, Lt(sigma, c', i,
-    // sigma'') = sum_c W[c, c', sigma, sigma''] L(c, i) (rows of bra N-block i
-    // x ket N-block j, the same j for every channel c of the group), and the
-    // rotated site vector Xr(sigma'', j) = sum_sigma' r_g(sigma'', sigma')
-    // Xd(j, sigma') (Eq. [expSy]: it mixes the two singly occupied states
-    // only, so Xr = Xd for the empty and doubly occupied states), so that
-    // V(sigma, c', i) = sum_sigma'' Lt(sigma, c', i, sigma'') Xr(sigma'', j).
-    // The rotation acts on the site vector, which is small, instead of
-    // multiplying the environment blocks: fewer and smaller Lt blocks.  The
-    // Lt blocks are built once per local problem, the Xr blocks with every
-    // product; both live in the pre-mixed scratch (Lt first, then Xr).
-    for (TList* tl : {&P.t_leftv, &P.t_left0}) tl->tile = TT;
-    {
-        struct LtBlk {
-            int j;
-            long long off;
-            std::vector<std::pair<int, int>> terms;  // (env block e, unrotated entry)
-        };
-        std::vector<LtBlk> lts;
-        std::map<std::array<int, 4>, int> ltidx;  // (sigma, c', i, sigma'')
-        long long lto = 0;
-        for (int sig = 0; sig < 4; ++sig)
-            for (int cp = 0; cp < wr; ++cp)
-                for (int i = 0; i < int(bl.nb.size()); ++i) {
-                    if (!Voff.count({sig, cp, i})) continue;
-                    for (const auto& ent : byWr[size_t(sig) * wr + cp]) {
-                        const int c = ent[0], s2 = ent[1];
-                        const int e = el.find(c, i);
-                        if (e < 0) continue;
-                        const EnvBlk& eb = el.blk[e];
-                        if (xdoff(eb.j, s2) < 0) continue;
-                        auto it = ltidx.find({sig, cp, i, s2});
-                        if (it == ltidx.end()) {
-                            it = ltidx.emplace(std::array<int, 4>{sig, cp, i, s2}, int(lts.size())).first;
-                            lts.push_back(LtBlk{eb.j, lto, {}});
-                            lto += (long long)eb.rows * eb.cols;
-                        }
-                        LtBlk& lb = lts[it->second];
-                        SP_REQUIRE(lb.j == eb.j, "internal: inconsistent particle numbers in the pre-mixed environment");
-                        lb.terms.push_back({e, ent[2]});
-                    }
-                }
-        // rotated site-vector blocks of the singly occupied states
-        std::map<std::array<int, 2>, long long> xroff;  // (sigma'' in {1, 2}, j)
-        long long xro = lto;
-        for (int j = 0; j < int(bl.nb.size()); ++j)
-            for (int s2 = 1; s2 <= 2; ++s2) {
-                if (xdoff(j, s2) < 0) continue;
-                xroff[{s2, j}] = xro;
-                xro += (long long)bl.nb[j].dim * br.nb[br.nblock(bl.nb[j].n + kSigmaN[s2])].dim;
-            }
-        P.LTsize = xro;
-        for (int g = 0; g < G; ++g)
-            for (const LtBlk& lb : lts) {
-                const EnvBlk& e0 = el.blk[lb.terms[0].first];
-                P.premix.add_task(B_LT, g * P.LTsize + lb.off, e0.rows * e0.cols);
-                for (const auto& tm : lb.terms)
-                    P.premix.add_term(B_ENVL, g * Lsz + el.blk[tm.first].off, g * P.nc + P.c_wr(tm.second));
-            }
-        for (int g = 0; g < G; ++g)
-            for (const auto& kv : xroff) {
-                const int s2 = kv.first[0], j = kv.first[1];
-                const int ncol = br.nb[br.nblock(bl.nb[j].n + kSigmaN[s2])].dim;
-                P.xrmix.add_task(B_LT, g * P.LTsize + kv.second, bl.nb[j].dim * ncol);
-                for (int q = 1; q <= 2; ++q) P.xrmix.add_term(B_X, xdoff(j, q), g * P.nc + P.c_r(s2, q));
-            }
-        // V(sigma, c', i) = sum over sigma'' (ascending) of Lt(sigma, c', i, sigma'') Xr(sigma'', j)
-        for (int g = 0; g < G; ++g)
-            for (int sig = 0; sig < 4; ++sig)
-                for (int cp = 0; cp < wr; ++cp)
-                    for (int i = 0; i < int(bl.nb.size()); ++i) {
-                        auto vo = Voff.find({sig, cp, i});
-                        if (vo == Voff.end()) continue;
-                        const int ncol = Vcols[{sig, cp, i}];
-                        const int nbk = br.nblock(bl.nb[i].n + kSigmaN[sig]);
-                        const int nbp = br.nblock(br.nb[nbk].n - h->dn[k][cp]);
-                        const int M = bl.nb[i].dim;
-                        for (int r0 = 0; r0 < M; r0 += TT)
-                            for (int c0 = 0; c0 < ncol; c0 += TT) {
-                                P.t_leftv.add_task(B_V, g * P.Vsize + vo->second, ncol, M, ncol, r0, c0, 0, 0);
-                                for (int s2 = 0; s2 < 4; ++s2) {
-                                    auto li = ltidx.find({sig, cp, i, s2});
-                                    if (li == ltidx.end()) continue;
-                                    const LtBlk& lb = lts[li->second];
-                                    SP_REQUIRE(br.nblock(bl.nb[lb.j].n + kSigmaN[s2]) == nbp,
-                                               "internal: pre-mixed product columns");
-                                    // rows of Xr reached by the tile's columns: those of
-                                    // every state the rotation mixes into sigma''
-                                    int k0 = INT32_MAX, k1 = -1;
-                                    for (int q = 0; q < 4; ++q) {
-                                        int a0, a1;
-                                        if (rot_nonzero(s2, q) && k_from_cols(nbp, q, c0, std::min(ncol, c0 + TT), a0, a1)) {
-                                            k0 = std::min(k0, a0);
-                                            k1 = std::max(k1, a1);
-                                        }
-                                    }
-                                    if (k1 <= k0) continue;
-                                    if (s2 == 1 || s2 == 2)
-                                        P.t_leftv.add_seg(B_LT, g * P.LTsize + lb.off, bl.nb[lb.j].dim, 0, B_LT,
-                                                          g * P.LTsize + xroff.at({s2, lb.j}), ncol, 0, k0, k1,
-                                                          g * P.nc + P.c_one());
-                                    else
-                                        P.t_leftv.add_seg(B_LT, g * P.LTsize + lb.off, bl.nb[lb.j].dim, 0, B_X,
-                                                          xdoff(lb.j, s2), ncol, 0, k0, k1, g * P.nc + P.c_one());
-                                }
-                            }
-                    }
-        // T of the identity channel (c = 0) only, for N_eff
-        for (int g = 0; g < G; ++g)
-            for (size_t e = 0; e < el.blk.size(); ++e) {
-                if (el.blk[e].c != 0) continue;
-                for (int q = 0; q < 4; ++q) {
-                    if (Toff[e * 4 + q] < 0) continue;
-                    const EnvBlk& eb = el.blk[e];
-                    const int jb = br.nblock(bl.nb[eb.j].n + kSigmaN[q]);
-                    const int ncol = br.nb[jb].dim;
-                    for (int r0 = 0; r0 < eb.rows; r0 += TT)
-                        for (int c0 = 0; c0 < ncol; c0 += TT) {
-                            P.t_left0.add_task(B_T, g * P.Tsize + Toff[e * 4 + q], ncol, eb.rows, ncol, r0, c0, 0, 0);
-                            int k0, k1;
-                            if (k_from_cols(jb, q, c0, std::min(ncol, c0 + TT), k0, k1))
-                                P.t_left0.add_seg(B_ENVL, g * Lsz + eb.off, eb.cols, 0, B_X, xdoff(eb.j, q), ncol, 0, k0,
-                                                  k1, g * P.nc + P.c_one());
-                        }
-                }
-            }
-    }
-    // right product: per g partial y and ny, scattered into the packed layout.
-    // An output tile sums over every right channel; wide MPOs have hundreds,
-    // so the channel list of a tile is cut into up to tr_split chunks, each
-    // its own work-group writing partial slot (chunk * G + g): the consumers
-    // add all tr_split * G slots in a fixed order (slots a tile has no chunk
-    // for are zero-filled before the launch).  tr_split aims at about 16384
-    // work-groups (two per wave slot of the GPU for the 64-thread tiles: a
-    // work-group's channels run as a chain of dependent chunk loads, so the
-    // chains are cut short; 8192 was 9% and 32768 1% slower at the K = 12
-    // ab-initio centre), each with at least 4 channels, so that the extra
-    // partial slots stay few.
-    const long long xs = si.size;
-    struct TSegD {
-        int a_buf;
-        long long a_off;
-        int lda, ta, b_buf;
-        long long b_off;
-        int ldb, tb, k0, k1, cidx;
-    };
-    struct TOut {
-        int c_buf, g, Nn, M, r0, c0;
-        long long pack;
-        std::vector<TSegD> segs;
-    };
-    std::vector<TOut> outs;
-    for (int g = 0; g < G; ++g)
-        for (int i = 0; i < int(bl.nb.size()); ++i)
-            for (int sig = 0; sig < 4; ++sig) {
-                const int nbb = br.nblock(bl.nb[i].n + kSigmaN[sig]);
-                if (nbb < 0) continue;
-                const int M = bl.nb[i].dim, Nn = br.nb[nbb].dim;
-                for (int r0 = 0; r0 < M; r0 += TT)
-                    for (int c0 = 0; c0 < Nn; c0 += TT) {
-                        int k0, k1;
-                        if (!k_from_rows(i, sig, r0, std::min(M, r0 + TT), k0, k1)) continue;
-                        if (k1 <= c0 || k0 >= std::min(Nn, c0 + TT)) continue;  // no (N, M) block in the tile
-                        TOut oy{B_Y, g, Nn, M, r0, c0, xdoff(i, sig), {}};
-                        for (int cp = 0; cp < wr; ++cp) {
-                            auto it = Voff.find({sig, cp, i});
-                            if (it == Voff.end()) continue;
-                            const int re = er.find(cp, nbb);
-                            if (re < 0) continue;
-                            const EnvBlk& RB = er.blk[re];
-                            oy.segs.push_back(TSegD{B_V, g * P.Vsize + it->second, RB.cols, 0, B_ENVR,
-                                                    g * Rsz + RB.off, RB.cols, 1, 0, RB.cols, g * P.nc + P.c_g()});
-                        }
-                        outs.push_back(std::move(oy));
-                        TOut on{B_NY, g, Nn, M, r0, c0, xdoff(i, sig), {}};
-                        const int e0 = el.find(0, i);
-                        const int re = er.find(lastR, nbb);
-                        if (e0 >= 0 && re >= 0)
-                            for (int q = 0; q < 4; ++q) {
-                                if (!rot_nonzero(sig, q)) continue;
-                                const long long to = Toff[size_t(e0) * 4 + q];
-                                if (to < 0) continue;
-                                const EnvBlk& RB = er.blk[re];
-                                on.segs.push_back(TSegD{B_T, g * P.Tsize + to, Tcols[size_t(e0) * 4 + q], 0, B_ENVR,
-                                                        g * Rsz + RB.off, RB.cols, 1, 0, RB.cols,
-                                                        g * P.nc + P.c_gr(sig, q)});
-                            }
-                        outs.push_back(std::move(on));
-                    }
-            }
-    size_t max_segs = 1;
-    for (const TOut& o : outs) max_segs = std::max(max_segs, o.segs.size());
-    const int want = int(std::max<size_t>(1, (16384 + outs.size() - 1) / std::max<size_t>(1, outs.size())));
-    const int kSegChunk = int(std::max<size_t>(4, (max_segs + want - 1) / want));
-    P.tr_split = 1;
-    for (const TOut& o : outs)
-        P.tr_split = std::max(P.tr_split, int((o.segs.size() + kSegChunk - 1) / kSegChunk));
-    for (const TOut& o : outs) {
-        const int nchunk = std::max(1, int((o.segs.size() + kSegChunk - 1) / kSegChunk));
-        for (int c = 0; c < nchunk; ++c) {
-            P.t_right.add_task(o.c_buf, ((long long)c * G + o.g) * xs, o.Nn, o.M, o.Nn, o.r0, o.c0, 1, o.pack);
-            const size_t s0 = size_t(c) * kSegChunk, s1 = std::min(o.segs.size(), s0 + kSegChunk);
-            for (size_t q = s0; q < s1; ++q) {
-                const TSegD& d = o.segs[q];
-                P.t_right.add_seg(d.a_buf, d.a_off, d.lda, d.ta, d.b_buf, d.b_off, d.ldb, d.tb, d.k0, d.k1, d.cidx);
-            }
-        }
-    }
-    // left environment: L[k](c', b, b') = sum_sigma Xd(a, sigma, b)^T V(sigma, c', a)
-    for (int g = 0; g < G; ++g)
-        for (const EnvBlk& OB : er.blk)
-            for (int r0 = 0; r0 < OB.rows; r0 += TT)
-                for (int c0 = 0; c0 < OB.cols; c0 += TT) {
-                    P.t_envl.add_task(B_OUT, g * Rsz + OB.off, OB.cols, OB.rows, OB.cols, r0, c0, 0, 0);
-                    for (int q = 0; q < 4; ++q) {
-                        const int a = bl.nblock(br.nb[OB.i].n - kSigmaN[q]);
-                        if (a < 0) continue;
-                        auto it = Voff.find({q, OB.c, a});
-                        if (it == Voff.end()) continue;
-                        int k0, k1;
-                        if (!k_from_cols(OB.i, q, r0, std::min(OB.rows, r0 + TT), k0, k1)) continue;
-                        P.t_envl.add_seg(B_X, xdoff(a, q), OB.rows, 1, B_V, g * P.Vsize + it->second, OB.cols, 0, k0,
-                                         k1, g * P.nc + P.c_one());
-                    }
-                }
-    // right pass: Z(rb, sigma') = Xd(i, sigma', b') R_g(rb)^T
-    for (int g = 0; g < G; ++g)
-        for (size_t e = 0; e < er.blk.size(); ++e)
-            for (int q = 0; q < 4; ++q) {
-                if (Zoff[e * 4 + q] < 0) continue;
-                const EnvBlk& rb = er.blk[e];
-                const int i = bl.nblock(br.nb[rb.j].n - kSigmaN[q]);
-                const int M = bl.nb[i].dim;
-                for (int r0 = 0; r0 < M; r0 += TT)
-                    for (int c0 = 0; c0 < rb.rows; c0 += TT) {
-                        P.t_zr.add_task(B_T, g * P.Zsize + Zoff[e * 4 + q], rb.rows, M, rb.rows, r0, c0, 0, 0);
-                        int k0, k1;
-                        if (k_from_rows(i, q, r0, std::min(M, r0 + TT), k0, k1))
-                            P.t_zr.add_seg(B_X, xdoff(i, q), rb.cols, 0, B_ENVR, g * Rsz + rb.off, rb.cols, 1, k0, k1,
-                                           g * P.nc + P.c_one());
-                    }
-            }
-    // right environment: R(c, a, a') = sum_sigma Xd(a, sigma, b) Zt(sigma, c, a')^T
-    for (int g = 0; g < G; ++g)
-        for (const EnvBlk& OB : el.blk)
-            for (int r0 = 0; r0 < OB.rows; r0 += TT)
-                for (int c0 = 0; c0 < OB.cols; c0 += TT) {
-                    P.t_envr.add_task(B_OUT, g * Lsz + OB.off, OB.cols, OB.rows, OB.cols, r0, c0, 0, 0);
-                    for (int q = 0; q < 4; ++q) {
-                        auto it = Ztoff.find({q, OB.c, OB.j});
-                        if (it == Ztoff.end()) continue;
-                        const int nbb = br.nblock(bl.nb[OB.i].n + kSigmaN[q]);
-                        int k0, k1;
-                        if (!k_from_rows(OB.i, q, r0, std::min(OB.rows, r0 + TT), k0, k1)) continue;
-                        P.t_envr.add_seg(B_X, xdoff(OB.i, q), br.nb[nbb].dim, 0, B_V, g * P.Ztsize + it->second,
-                                         br.nb[nbb].dim, 1, k0, k1, g * P.nc + P.c_one());
-                    }
-                }
 }
+
+// partial slots of sp_heff_apply_noalloc, doubles per output (y, ny): 16 MiB each
+constexpr long long kNoAllocSlots = 1LL << 21;
+
+// H_eff x of a wide MPO: work-groups aimed at, and the fewest channels of one
+constexpr long long kChainGroups = 8192;
+constexpr int kChainMinChannels = 8;
 
 // chained-product lists of site k (tiled path)
 void build_chain(sp_handle* h, int k) {
@@ -1612,7 +1349,7 @@ void build_chain(sp_handle* h, int k) {
         }
     for (int j = 0; j < nl; ++j)
         if (xr[size_t(j) * 4 + 1] >= 0) xr[size_t(j) * 4 + 2] = nr + xr[size_t(j) * 4 + 1];
-    auto xbuf = [&](int q) { return q == 1 || q == 2 ? spk::K_XR : spk::K_X; };
+    auto rotates = [](int q) { return q == 1 || q == 2; };
     auto xoff = [&](int j, int q) { return (q == 1 || q == 2 ? xr : xd)[size_t(j) * 4 + q]; };
     // the rows of N-block j that columns [c0, c1) of N-block jb reach through
     // the rotated state q (every state the rotation mixes into q), and the
@@ -1672,7 +1409,9 @@ void build_chain(sp_handle* h, int k) {
     // V(sigma, c', i) = sum of (block, coefficient, ket block j, sigma') terms
     // of the left environment, Zt(sigma, c, b) likewise of the right one
     struct Src {
-        int buf, cols, j, q, cidx;
+        bool mixed;
+        int cols, j, q;
+        double cf;
         long long off;
     };
     std::map<std::array<int, 3>, std::vector<Src>> vsrc, zsrc;
@@ -1699,8 +1438,8 @@ void build_chain(sp_handle* h, int k) {
                         const EnvBlk& b0 = e.blk[g.second[0].first];
                         if (!(side ? mixed_r : mixed_l) || g.second.size() == 1) {
                             for (const auto& t : g.second)
-                                src[{sig, c, i}].push_back(Src{side ? spk::K_R : spk::K_L, b0.cols, g.first.first, g.first.second,
-                                                               P.c_wr(t.second), e.blk[t.first].off});
+                                src[{sig, c, i}].push_back(Src{false, b0.cols, g.first.first, g.first.second, wval[t.second],
+                                                               e.blk[t.first].off});
                             continue;
                         }
                         const double sgn = wval[g.second[0].second] < 0.0 ? -1.0 : 1.0;
@@ -1708,24 +1447,128 @@ void build_chain(sp_handle* h, int k) {
                         for (const auto& t : g.second) key.push_back({t.first, sgn * wval[t.second]});
                         auto it = same.find(key);
                         if (it == same.end()) {
-                            it = same.emplace(key, std::make_pair(mix.size, sgn)).first;
-                            mix.add_task(b0.rows * b0.cols);
-                            for (const auto& t : g.second) mix.add_term(e.blk[t.first].off, P.c_wr(t.second));
+                            std::vector<std::pair<int, double>> terms;
+                            for (const auto& t : g.second) terms.push_back({t.first, wval[t.second]});
+                            it = same.emplace(key, std::make_pair(mix.add(b0.i, b0.j, b0.rows * b0.cols, terms), sgn)).first;
                         }
-                        src[{sig, c, i}].push_back(Src{spk::K_LT, b0.cols, g.first.first, g.first.second,
-                                                       it->second.second == sgn ? P.c_one() : P.c_minus(), it->second.first});
+                        src[{sig, c, i}].push_back(Src{true, b0.cols, g.first.first, g.first.second,
+                                                       it->second.second == sgn ? 1.0 : -1.0, it->second.first});
                     }
                 }
     }
-    auto shape_for = [](int m) { return m <= 32 ? 0 : (m <= 64 ? 1 : 2); };
+    P.mix_l.finish(el);
+    P.mix_r.finish(er);
+    auto shape_for = [](int m, bool wide) {  // the smallest tile that takes m, or the largest
+        int sh = wide ? spk::kNarrowShapes : 0;
+        const int end = wide ? spk::kNumChainShapes : spk::kNarrowShapes;
+        while (sh + 1 < end && 16 * spk::kChainShapes[sh].nm < m) ++sh;
+        return sh;
+    };
+    // Two blocks in n halve the reads of A and P per product.  The BF16 matrix
+    // cores wait for reads and splits, and gain (K = 14, D = 181: 538 us
+    // against 635); FP64 needs its registers for wavefronts in flight (K = 12,
+    // D = 128, site 7: 300 us against 293 with one)
+    const bool wide_h = mixed_l && h->precision == SP_BF16X3;
+    // Environment updates: an output block is a sum over few steps with a
+    // narrow MPO, split over four wavefronts (L = 32, D = 256: 25 us against
+    // 50 with one); a wide MPO has thousands of blocks of many steps each, and
+    // a wavefront per tile saves the LDS sums (K = 12, D = 128: 226 and 405 us
+    // for left and right against 264 and 416)
+    if (mixed_l || mixed_r) P.c_envl.waves = P.c_envr.waves = 1;
     int dl = 1, dr = 1;
     for (const NBlock& nb : bl.nb) dl = std::max(dl, nb.dim);
     for (const NBlock& nb : br.nb) dr = std::max(dr, nb.dim);
+    // H_eff x, transposed: y(a, sigma, b) = sum_c' sum_k R(c')(b, k) V(sigma, c', i)(a, k)
+    // in tiles of 16 rows a by the columns b that those rows reach; N_eff x
+    // from the identity strings, V = L(0) X and R of the last channel
+    {
+        ChainList& C = P.c_heff;
+        C.lay = spk::kChainHeff;
+        const int lastR = wr - 1, TN = 16 * spk::kChainShapes[shape_for(1, wide_h)].nn;
+        struct Tile {
+            int i, q, b, n0, n1, m0, m1;
+        };
+        std::vector<Tile> rows, tiles;
+        int widest = 1;
+        for (int i = 0; i < nl; ++i)
+            for (int q = 0; q < 4; ++q) {
+                const int b = right_nb(i, q);
+                if (b < 0) continue;
+                for (int n0 = 0; n0 < bl.nb[i].dim; n0 += TN) {
+                    const int n1 = std::min(bl.nb[i].dim, n0 + TN);
+                    int c0, c1;
+                    if (!cols_of(i, q, n0, n1, false, c0, c1)) continue;
+                    rows.push_back({i, q, b, n0, n1, c0, c1});
+                    widest = std::max(widest, c1 - c0);
+                }
+            }
+        C.shape = shape_for(widest, wide_h);
+        const int TM = 16 * spk::kChainShapes[C.shape].nm, TI = 16 * spk::kChainShapes[C.shape].ni;
+        for (const Tile& t : rows)
+            for (int m0 = t.m0; m0 < t.m1; m0 += TM) tiles.push_back({t.i, t.q, t.b, t.n0, t.n1, m0, std::min(t.m1, m0 + TM)});
+        // the widest first: the launch ends with the short ones
+        std::stable_sort(tiles.begin(), tiles.end(), [&](const Tile& x, const Tile& y) { return br.nb[x.b].dim > br.nb[y.b].dim; });
+        // channels of a tile in chunks, each its own work-group and partial
+        // slot, where the tiles alone leave the chip short of work-groups
+        std::vector<int> nch(tiles.size(), 0);
+        long long total = 0;
+        int most = 1;
+        for (const Tile& t : tiles) {
+            int n = 0;
+            for (int cp = 0; cp < wr; ++cp) n += vsrc.count({t.q, cp, t.i}) && er.find(cp, t.b) >= 0;
+            total += n;
+            most = std::max(most, n);
+        }
+        long long want = std::max<long long>(1, kChainGroups / std::max<long long>(1, (long long)tiles.size() * h->G));
+        // a site with a fused plan keeps to the fixed slots wherever one slot
+        // per g does
+        const long long per = std::max<long long>(1, h->G * si.size);
+        if (P.h_rows > 0 && per <= kNoAllocSlots) want = std::min(want, kNoAllocSlots / per);
+        const int chunk = int(std::max<long long>(kChainMinChannels, (most + want - 1) / want));
+        P.y_split = std::max(1, (most + chunk - 1) / chunk);
+        for (const Tile& t : tiles) {
+            const long long mo = xd[size_t(t.i) * 4 + t.q];
+            const int nn = br.nb[t.b].dim;
+            int n = 0, slot = 0;
+            auto end = [&]() {
+                C.end_tile(spk::KTile{(long long)slot * h->G * si.size, mo, t.m0, t.m1, t.n0, t.n1, nn, P.c_g(), {}, 0, 0, 0});
+                ++slot;
+            };
+            const int e0 = el.find(0, t.i), rl = er.find(lastR, t.b);
+            SP_REQUIRE(e0 >= 0 && rl >= 0 && el.blk[e0].j == t.i && er.blk[rl].j == t.b, "internal: identity channels must conserve N");
+            for (int c0 = 0; c0 < nn; c0 += TI) {  // N_eff x, with the first chunk
+                const int c1 = std::min(nn, c0 + TI);
+                int k0, k1;
+                C.begin_step(er.blk[rl].off, nn, c0, c1, true);
+                if (rows_of(t.b, t.q, c0, c1, true, k0, k1))
+                    C.add_seg(xoff(t.i, t.q), nn, el.blk[e0].off, el.blk[e0].cols, k0, k1, 1.0, rotates(t.q), false, true);
+            }
+            for (int cp = 0; cp < wr; ++cp) {
+                auto it = vsrc.find({t.q, cp, t.i});
+                const int re = er.find(cp, t.b);
+                if (it == vsrc.end() || re < 0) continue;
+                if (n > 0 && n % chunk == 0) end();
+                ++n;
+                const EnvBlk& RB = er.blk[re];
+                for (int c0 = 0; c0 < RB.cols; c0 += TI) {
+                    const int c1 = std::min(RB.cols, c0 + TI);
+                    C.begin_step(RB.off, RB.cols, c0, c1);
+                    for (const Src& v : it->second) {
+                        int k0, k1;
+                        SP_REQUIRE(right_nb(v.j, v.q) == RB.j, "internal: H_eff particle numbers");
+                        if (rows_of(RB.j, v.q, c0, c1, true, k0, k1))
+                            C.add_seg(xoff(v.j, v.q), RB.cols, v.off, v.cols, k0, k1, v.cf, rotates(v.q), v.mixed);
+                    }
+                }
+            }
+            while (slot < P.y_split) end();  // slots without channels: zeros
+        }
+    }
     // left environment L[k](c', b, b') = sum_sigma X(a, sigma, b)^T V(sigma, c', a)(a, b')
     P.c_envl.lay = spk::kChainEnvL;
-    P.c_envl.shape = shape_for(dr);
+    P.c_envl.shape = shape_for(dr, false);
     P.c_envr.lay = spk::kChainEnvR;
-    P.c_envr.shape = shape_for(dl);
+    P.c_envr.shape = shape_for(dl, false);
     for (int side = 0; side < 2; ++side) {
         ChainList& C = side ? P.c_envr : P.c_envl;
         const spk::KShape sh = spk::kChainShapes[C.shape];
@@ -1734,7 +1577,6 @@ void build_chain(sp_handle* h, int k) {
             for (int m0 = 0; m0 < OB.rows; m0 += TM)
                 for (int n0 = 0; n0 < OB.cols; n0 += TN) {
                     const int m1 = std::min(OB.rows, m0 + TM), n1 = std::min(OB.cols, n0 + TN);
-                    C.begin_tile(spk::KTile{OB.off, 0, 0, m0, m1, n0, n1, OB.cols, 0, 0, 0, -1});
                     for (int q = 0; q < 4; ++q) {
                         int b0, b1;
                         if (side == 0) {  // X(a, q)^T: b = OB.i, a on the left bond
@@ -1743,12 +1585,12 @@ void build_chain(sp_handle* h, int k) {
                             auto it = vsrc.find({q, OB.c, a});
                             if (it == vsrc.end() || !rows_of(OB.i, q, m0, m1, false, b0, b1)) continue;
                             for (int c0 = b0; c0 < b1; c0 += TI) {
-                                C.begin_step(spk::K_X, xd[size_t(a) * 4 + q], OB.rows, c0, std::min(b1, c0 + TI));
+                                C.begin_step(xd[size_t(a) * 4 + q], OB.rows, c0, std::min(b1, c0 + TI));
                                 for (const Src& v : it->second) {
                                     int k0, k1;
                                     SP_REQUIRE(right_nb(v.j, v.q) == OB.j, "internal: left environment particle numbers");
                                     if (rows_of(OB.j, v.q, n0, n1, true, k0, k1))
-                                        C.add_seg(v.buf, v.off, v.cols, xbuf(v.q), xoff(v.j, v.q), OB.cols, k0, k1, v.cidx);
+                                        C.add_seg(v.off, v.cols, xoff(v.j, v.q), OB.cols, k0, k1, v.cf, rotates(v.q), v.mixed);
                                 }
                             }
                         } else {  // X(a, q): a = OB.i, b on the right bond
@@ -1757,293 +1599,78 @@ void build_chain(sp_handle* h, int k) {
                             auto it = zsrc.find({q, OB.c, b});
                             if (it == zsrc.end() || !cols_of(OB.i, q, m0, m1, false, b0, b1)) continue;
                             for (int c0 = b0; c0 < b1; c0 += TI) {
-                                C.begin_step(spk::K_X, xd[size_t(OB.i) * 4 + q], br.nb[b].dim, c0, std::min(b1, c0 + TI));
+                                C.begin_step(xd[size_t(OB.i) * 4 + q], br.nb[b].dim, c0, std::min(b1, c0 + TI));
                                 for (const Src& v : it->second) {
                                     int k0, k1;
                                     SP_REQUIRE(right_nb(OB.j, v.q) == v.j, "internal: right environment particle numbers");
                                     if (cols_of(OB.j, v.q, n0, n1, true, k0, k1))
-                                        C.add_seg(v.buf, v.off, v.cols, xbuf(v.q), xoff(OB.j, v.q), br.nb[v.j].dim, k0, k1, v.cidx);
+                                        C.add_seg(v.off, v.cols, xoff(OB.j, v.q), br.nb[v.j].dim, k0, k1, v.cf, rotates(v.q), v.mixed);
                                 }
                             }
                         }
                     }
-                    C.drop_empty();
+                    C.end_tile(spk::KTile{OB.off, 0, m0, m1, n0, n1, OB.cols, -1, {}, 0, 0, 0});
                 }
     }
 }
 
-// fused H_eff x plan: column descriptors, products per bra block, channels
-// per output sigma, output lists and row-chunk tasks
-// LDS budget of the fused H_eff kernel per work-group (doubles): the default,
-// and the largest the autotuner tries (the 160 KB of a CU less the static
-// arrays)
+// LDS budget of a row-chunk plan of H_eff x (doubles): the default, and the
+// largest the autotuner tries (the 160 KB of a CU less static arrays)
 constexpr int kHeffLdsBudget = 9216;
 constexpr int kHeffLdsMax = 18432;
+constexpr int kHeffMaxRows = 8;
 
-// Returns false (and leaves the site without a fused plan, h_rows = 0) when
-// a particle-number block is too wide for the budget: the site then runs
-// the LDS-tiled block-product lists.
+// The fused plan of site k for an LDS budget: rows per task RC such that RC
+// rows of every left-environment block, of every product L(c) x[sigma'] and
+// of the right channels of one sigma fit.  It decides which sites run H_eff x
+// as one fused contraction in the precision of the local solves (RC >= 1) and
+// which as block products (RC = 0: the MPO is too wide, or the caller chose
+// so); the kernel itself keeps its intermediates in registers.  Returns false
+// where no row fits.
 bool build_fused(sp_handle* h, int k, int lds_budget = kHeffLdsBudget) {
     SitePlan& P = h->plan[k - 1];
-    const int G = h->G;
     const Bond& bl = h->bonds[k - 1];
     const Bond& br = h->bonds[k];
-    const SiteInfo& si = h->sites[k - 1];
     const EnvLayout& el = h->env[k - 1];
     const EnvLayout& er = h->env[k];
     const int wl = h->w[k - 1], wr = h->w[k];
-    const int lastR = wr - 1;
-    // rotated-MPO entries by (sigma, right channel): (left channel, sigma', entry)
-    std::vector<std::vector<std::array<int, 3>>> byL(size_t(4) * wr);
-    for (int e = 0; e < P.nW; ++e) {
-        const auto& q = P.went[e];
-        byL[size_t(q[2]) * wr + q[1]].push_back({q[0], q[3], e});
-    }
-    const int nb = int(bl.nb.size());
-
-    // RC-independent description of one bra block
-    struct TCol {
-        int x_off, x_ld, K, src, ro;  // src: local L source, ro: its first column
-    };
-    struct TBlk {
-        int ncol;
-        std::vector<TCol> cols;
-    };
-    struct SegD {
-        long long r_off;
-        int K, is_ny;
-        std::vector<std::pair<int, int>> terms;  // (local T block, coefficient)
-    };
-    struct BlkD {
-        std::vector<std::pair<long long, int>> lsrc;  // (L offset, ld)
-        std::vector<TBlk> T;
-        std::array<std::vector<SegD>, 4> seg;
+    std::vector<std::vector<std::array<int, 2>>> by(size_t(4) * wr);  // (left channel, sigma') by (sigma, right channel)
+    for (const auto& q : P.went) by[size_t(q[2]) * wr + q[1]].push_back({q[0], q[3]});
+    auto right_nb = [&](int j, int q) { return br.nblock(bl.nb[j].n + kSigmaN[q]); };
+    int need1 = 1;
+    for (int i = 0; i < int(bl.nb.size()); ++i) {
         int lsum = 0, tsum = 0, vmax = 0;
-    };
-    std::vector<BlkD> bd(nb);
-    for (int i = 0; i < nb; ++i) {
-        const NBlock& NA = bl.nb[i];
-        BlkD& D = bd[i];
-        std::map<std::pair<int, int>, int> tloc;  // (c, s') -> local T block
         for (int c = 0; c < wl; ++c) {
             const int e = el.find(c, i);
             if (e < 0) continue;
-            const EnvBlk& EB = el.blk[e];
-            const int src = int(D.lsrc.size());
-            D.lsrc.push_back({EB.off, EB.cols});
-            D.lsum += EB.cols;
-            const int j = EB.j;
-            for (int q = 0; q < 4; ++q) {
-                const int jb = br.nblock(bl.nb[j].n + kSigmaN[q]);
-                if (jb < 0) continue;
-                const NBlock& NB = br.nb[jb];
-                TBlk T;
-                T.ncol = NB.dim;
-                for (int sb = NB.s0; sb < NB.s1; ++sb) {
-                    const Sector& SB = br.sec[sb];
-                    const int sa = bl.sector(SB.n - kSigmaN[q], SB.m2 - kSigma2M[q]);
-                    const int xb = sa >= 0 ? si.find(sa, q) : -1;
-                    for (int c2 = 0; c2 < SB.dim; ++c2) {
-                        if (xb < 0) {
-                            T.cols.push_back(TCol{0, 0, 0, src, 0});
-                        } else {
-                            const XBlk& X = si.blk[xb];
-                            SP_REQUIRE(bl.sec[sa].n == bl.nb[j].n, "internal: fused ket sector");
-                            T.cols.push_back(TCol{int(X.off + c2), X.cols, X.rows, src, bl.sec[sa].ro});
-                        }
-                    }
-                }
-                tloc[{c, q}] = int(D.T.size());
-                D.tsum += T.ncol;
-                D.T.push_back(std::move(T));
-            }
+            lsum += el.blk[e].cols;
+            for (int q = 0; q < 4; ++q)
+                if (right_nb(el.blk[e].j, q) >= 0) tsum += br.nb[right_nb(el.blk[e].j, q)].dim;
         }
         for (int sig = 0; sig < 4; ++sig) {
-            const int nbb = br.nblock(NA.n + kSigmaN[sig]);
+            const int nbb = right_nb(i, sig);
             if (nbb < 0) continue;
-            auto add_seg = [&](int re, int is_ny, const std::vector<std::pair<int, int>>& tl) {
-                if (tl.empty()) return;
-                const EnvBlk& RB = er.blk[re];
-                for (auto& pr : tl)
-                    SP_REQUIRE(D.T[pr.first].ncol == RB.cols, "internal: fused H_eff particle numbers");
-                D.seg[sig].push_back(SegD{RB.off, RB.cols, is_ny, tl});
-            };
+            int v = 0;
             for (int cp = 0; cp < wr; ++cp) {
                 const int re = er.find(cp, nbb);
                 if (re < 0) continue;
-                std::vector<std::pair<int, int>> tl;
-                for (const auto& ent : byL[size_t(sig) * wr + cp]) {  // ascending (c, s'), as tloc
-                    auto it = tloc.find({ent[0], ent[1]});
-                    if (it != tloc.end()) tl.push_back({it->second, P.c_cwt(ent[2])});
+                for (const auto& ent : by[size_t(sig) * wr + cp]) {
+                    const int e = el.find(ent[0], i);
+                    if (e < 0 || right_nb(el.blk[e].j, ent[1]) < 0) continue;
+                    v += er.blk[re].cols;
+                    break;
                 }
-                add_seg(re, 0, tl);
             }
-            const int re = er.find(lastR, nbb);
-            if (re >= 0) {
-                std::vector<std::pair<int, int>> tl;
-                for (int q = 0; q < 4; ++q) {
-                    if (!rot_nonzero(sig, q)) continue;
-                    auto it = tloc.find({0, q});
-                    if (it == tloc.end()) continue;
-                    SP_REQUIRE(el.blk[el.find(0, i)].j == i, "internal: identity channel must conserve N");
-                    tl.push_back({it->second, P.c_gr(sig, q)});
-                }
-                add_seg(re, 1, tl);
-            }
-            int v = 0;
-            for (auto& sd : D.seg[sig]) v += sd.K;
-            D.vmax = std::max(D.vmax, v);
+            const int e0 = el.find(0, i), re = er.find(wr - 1, nbb);
+            if (re >= 0 && e0 >= 0) v += er.blk[re].cols;  // N_eff
+            vmax = std::max(vmax, v);
         }
+        need1 = std::max(need1, lsum + tsum + vmax);
     }
-    // rows per task: the largest RC <= 8 whose LDS fits the budget
-    int need1 = 1;
-    for (auto& D : bd) need1 = std::max(need1, D.lsum + D.tsum + D.vmax);
-    const int RC = std::min(spk::kH3MaxRC, lds_budget / need1);
-    P.h_blks.clear();
-    P.h_cols.clear();
-    P.h_lsrc.clear();
-    P.h_segs.clear();
-    P.h_terms.clear();
-    P.h_pieces.clear();
-    P.h_tasks.clear();
-    if (RC < 1) {
-        P.h_rows = 0;
-        P.h_lds = 0;
-        return false;
-    }
-    P.h_rows = RC;
-    P.h_lds = RC * need1;
-    for (int i = 0; i < nb; ++i) {
-        BlkD& D = bd[i];
-        spk::H3Blk B{};
-        B.l0 = int(P.h_lsrc.size());
-        std::vector<int> lds_src(D.lsrc.size());
-        int pos = 0;
-        for (size_t q = 0; q < D.lsrc.size(); ++q) {
-            SP_REQUIRE(D.lsrc[q].first < INT32_MAX, "environment too large for 32-bit offsets");
-            lds_src[q] = pos;
-            P.h_lsrc.push_back(spk::H3LSrc{int(D.lsrc[q].first), D.lsrc[q].second, pos, 0});
-            pos += RC * D.lsrc[q].second;
-        }
-        B.l1 = int(P.h_lsrc.size());
-        B.c0 = int(P.h_cols.size());
-        std::vector<int> tbase(D.T.size());
-        for (size_t t = 0; t < D.T.size(); ++t) {
-            tbase[t] = pos;
-            for (int c2 = 0; c2 < D.T[t].ncol; ++c2) {
-                const TCol& tc = D.T[t].cols[c2];
-                P.h_cols.push_back(spk::H3Col{tc.x_off, tc.x_ld, tc.K, lds_src[tc.src] + tc.ro,
-                                              D.lsrc[tc.src].second, pos + c2 * RC, 0, 0});
-            }
-            pos += RC * D.T[t].ncol;
-        }
-        B.c1 = int(P.h_cols.size());
-        // columns that read the same x column (channels with the same ket
-        // block) next to each other: the kernel pairs neighbours and loads a
-        // shared x column once; empty columns last
-        std::stable_sort(P.h_cols.begin() + B.c0, P.h_cols.begin() + B.c1,
-                         [](const spk::H3Col& a, const spk::H3Col& b) {
-                             if ((a.K == 0) != (b.K == 0)) return b.K == 0;
-                             return std::tie(a.x_off, a.x_ld, a.K) < std::tie(b.x_off, b.x_ld, b.K);
-                         });
-        const int vbase = pos;
-        for (int sig = 0; sig < 4; ++sig) {
-            B.s0[sig] = int(P.h_segs.size());
-            int v = vbase;
-            for (auto& sd : D.seg[sig]) {
-                SP_REQUIRE(sd.r_off < INT32_MAX, "environment too large for 32-bit offsets");
-                spk::H3Seg S{};
-                S.r_off = int(sd.r_off);
-                S.K = sd.K;
-                S.v_off = v;
-                S.t0 = int(P.h_terms.size());
-                for (auto& pr : sd.terms) P.h_terms.push_back(spk::H3Term{tbase[pr.first], pr.second});
-                S.t1 = int(P.h_terms.size());
-                S.is_ny = sd.is_ny;
-                P.h_segs.push_back(S);
-                v += RC * sd.K;
-            }
-            B.s1[sig] = int(P.h_segs.size());
-        }
-        P.h_blks.push_back(B);
-    }
-    // tasks of one quadrature point: chunks of RC rows per bra block, with the
-    // output pieces (rows of one left sector x the columns its sigma allows)
-    std::vector<spk::H3Task> one;
-    for (int i = 0; i < nb; ++i) {
-        const NBlock& NA = bl.nb[i];
-        for (int r0 = 0; r0 < NA.dim; r0 += RC) {
-            spk::H3Task t{};
-            t.g = 0;
-            t.blk = i;
-            t.r0 = r0;
-            t.rows = std::min(RC, NA.dim - r0);
-            bool any = false;
-            for (int sig = 0; sig < 4; ++sig) {
-                t.p0[sig] = t.p1[sig] = int(P.h_pieces.size());
-                if (br.nblock(NA.n + kSigmaN[sig]) < 0) continue;
-                for (int sa = NA.s0; sa < NA.s1; ++sa) {
-                    const Sector& SA = bl.sec[sa];
-                    const int lo = std::max(r0, SA.ro), hi = std::min(r0 + t.rows, SA.ro + SA.dim);
-                    if (lo >= hi) continue;
-                    const int sb = br.sector(SA.n + kSigmaN[sig], SA.m2 + kSigma2M[sig]);
-                    if (sb < 0) continue;
-                    const int xb = si.find(sa, sig);
-                    SP_REQUIRE(xb >= 0, "internal: missing site block");
-                    const XBlk& X = si.blk[xb];
-                    spk::H3Piece pc{};
-                    pc.rlo = lo - r0;
-                    pc.rhi = hi - r0;
-                    pc.b0 = br.sec[sb].ro;
-                    pc.nb = br.sec[sb].dim;
-                    pc.out_off = int(X.off + (long long)(lo - SA.ro) * X.cols);
-                    pc.out_ld = X.cols;
-                    P.h_pieces.push_back(pc);
-                }
-                t.p1[sig] = int(P.h_pieces.size());
-                any = any || t.p1[sig] > t.p0[sig];
-            }
-            if (any) one.push_back(t);
-        }
-    }
-    // all quadrature points, dealt to the eight XCDs in contiguous runs of the
-    // g-ordered list (work-group w runs on XCD w mod 8), so that each XCD's L2
-    // holds the environments of about G/8 quadrature points
-    std::vector<spk::H3Task> all;
-    for (int g = 0; g < G; ++g)
-        for (spk::H3Task t : one) {
-            t.g = g;
-            all.push_back(t);
-        }
-    const int T = int(all.size()), nq = 8;
-    const int rounds = (T + nq - 1) / nq;
-    P.h_tasks.assign(size_t(rounds) * nq, spk::H3Task{0, -1, 0, 0, {0, 0, 0, 0}, {0, 0, 0, 0}});
-    for (int q = 0; q < nq; ++q) {
-        const int a0 = int((long long)T * q / nq), a1 = int((long long)T * (q + 1) / nq);
-        for (int r = 0; r < a1 - a0; ++r) P.h_tasks[size_t(r) * nq + q] = all[a0 + r];
-    }
-    while (!P.h_tasks.empty() && P.h_tasks.back().blk < 0) P.h_tasks.pop_back();
-    return true;
-}
-
-void upload_fused(sp_handle* h, int k) {
-    SitePlan& P = h->plan[k - 1];
-    hipStream_t s = h->stream;
-    P.dh_tasks.upload(P.h_tasks, s);
-    P.dh_blks.upload(P.h_blks, s);
-    P.dh_cols.upload(P.h_cols, s);
-    P.dh_lsrc.upload(P.h_lsrc, s);
-    P.dh_segs.upload(P.h_segs, s);
-    P.dh_terms.upload(P.h_terms, s);
-    P.dh_pieces.upload(P.h_pieces, s);
-    // every list the fused kernel reads must be on the device, whole
-    SP_REQUIRE(P.dh_tasks.n == P.h_tasks.size() && P.dh_blks.n == P.h_blks.size() &&
-                   P.dh_cols.n == P.h_cols.size() && P.dh_lsrc.n == P.h_lsrc.size() &&
-                   P.dh_segs.n == P.h_segs.size() && P.dh_terms.n == P.h_terms.size() &&
-                   P.dh_pieces.n == P.h_pieces.size(),
-               "internal: fused plan upload");
-    SP_REQUIRE(P.h_tasks.empty() || (P.dh_tasks.p && P.dh_blks.p && P.dh_cols.p && P.dh_lsrc.p && P.dh_pieces.p),
-               "internal: fused plan upload");
+    const int RC = std::min(kHeffMaxRows, lds_budget / need1);
+    P.h_rows = std::max(0, RC);
+    P.h_lds = P.h_rows * need1;
+    return RC >= 1;
 }
 
 void upload_plan(sp_handle* h, int k) {
@@ -2069,21 +1696,12 @@ void upload_plan(sp_handle* h, int k) {
     P.absorb_right.upload(s);
     P.absorb_left.upload(s);
     P.xmap.upload(P.xmap_h, s);
-    P.t_left.upload(s);
-    P.t_leftv.upload(s);
-    P.t_left0.upload(s);
-    P.premix.upload(s);
-    P.xrmix.upload(s);
-    P.t_right.upload(s);
-    P.t_envl.upload(s);
-    P.t_zr.upload(s);
-    P.t_envr.upload(s);
+    P.c_heff.upload(s);
     P.c_envl.upload(s);
     P.c_envr.upload(s);
     P.mix_l.upload(s);
     P.mix_r.upload(s);
     P.rmap.upload(P.rmap_h, s);
-    upload_fused(h, k);
 }
 
 // ---------------------------------------------------------------------------
@@ -2123,33 +1741,6 @@ void validate(const CList& b, const Sizes& sz, long long ncoef, const char* what
     }
 }
 
-void validate(const TList& b, const Sizes& sz, long long ncoef, long long map_size, long long packed_max,
-              const char* what) {
-    const int TT = b.tile;
-    if (TT != 32 && TT != 64) throw SpError(SP_EINVAL, std::string("internal tile size: ") + what);
-    for (const spk::TTask& t : b.tasks) {
-        if (t.r0 < 0 || t.c0 < 0 || t.r0 >= t.M || t.c0 >= t.N) throw SpError(SP_EINVAL, std::string("internal tile: ") + what);
-        const int rl = std::min(t.M, t.r0 + TT) - 1, cl = std::min(t.N, t.c0 + TT) - 1;
-        if (t.mode == 0) {
-            check_span(t.c_off + (long long)t.r0 * t.ldc + t.c0, t.c_off + (long long)rl * t.ldc + cl, sz[t.c_buf], what);
-        } else {
-            check_span(t.pack_off, t.pack_off + (long long)(t.M - 1) * t.N + (t.N - 1), map_size, what);
-            check_span(t.c_off, t.c_off + packed_max - 1, sz[t.c_buf], what);
-        }
-        for (int i = t.s0; i < t.s1; ++i) {
-            const spk::TSeg& g = b.segs[i];
-            if (g.k0 < 0 || g.k1 <= g.k0) throw SpError(SP_EINVAL, std::string("internal segment: ") + what);
-            const long long a_first = g.ta ? g.a_off + (long long)g.k0 * g.lda + t.r0 : g.a_off + (long long)t.r0 * g.lda + g.k0;
-            const long long a_last = g.ta ? g.a_off + (long long)(g.k1 - 1) * g.lda + rl : g.a_off + (long long)rl * g.lda + (g.k1 - 1);
-            const long long b_first = g.tb ? g.b_off + (long long)t.c0 * g.ldb + g.k0 : g.b_off + (long long)g.k0 * g.ldb + t.c0;
-            const long long b_last = g.tb ? g.b_off + (long long)cl * g.ldb + (g.k1 - 1) : g.b_off + (long long)(g.k1 - 1) * g.ldb + cl;
-            check_span(a_first, a_last, sz[g.a_buf], what);
-            check_span(b_first, b_last, sz[g.b_buf], what);
-            check_span(g.cidx, g.cidx, ncoef, what);
-        }
-    }
-}
-
 // bounds of a chained product: in[] the values per quadrature point of every
 // operand buffer, nout of the output, npart the outputs a tile may scatter to
 void validate(const ChainList& C, const std::array<long long, spk::K_NBUF>& in, long long nout, long long map_size,
@@ -2158,116 +1749,63 @@ void validate(const ChainList& C, const std::array<long long, spk::K_NBUF>& in, 
     const spk::KShape sh = spk::kChainShapes[C.shape];
     for (const spk::KTile& t : C.tiles) {
         if (t.m0 < 0 || t.n0 < 0 || t.m1 <= t.m0 || t.n1 <= t.n0 || t.m1 - t.m0 > 16 * sh.nm || t.n1 - t.n0 > 16 * sh.nn ||
-            t.s0 < 0 || t.s1 < t.s0 || t.s1 > int(C.steps.size()) || t.out < 0 || t.out > 1)
+            t.e0 < 0 || t.e1 < t.e0 || (C.lay != spk::kChainHeff && t.e1 > t.e0) || t.s[0] < t.e1 ||
+            !std::is_sorted(t.s, t.s + 5) || t.s[4] > int(C.steps.size()) || t.s[C.waves] != t.s[4])
             throw SpError(SP_EINVAL, std::string("internal tile: ") + what);
         if (t.cidx >= 0) check_span(t.cidx, t.cidx, ncoef, what);
         if (C.lay == spk::kChainHeff) {
-            check_span(t.map_off + (long long)t.n0 * t.o_ns + t.m0, t.map_off + (long long)(t.n1 - 1) * t.o_ns + t.m1 - 1, map_size, what);
+            check_span(t.map_off + (long long)t.n0 * t.ldo + t.m0, t.map_off + (long long)(t.n1 - 1) * t.ldo + t.m1 - 1, map_size, what);
             check_span(t.o_off, t.o_off + npart - 1, nout, what);
         } else {
-            check_span(t.o_off + (long long)t.m0 * t.o_ms + t.n0, t.o_off + (long long)(t.m1 - 1) * t.o_ms + t.n1 - 1, nout, what);
+            check_span(t.o_off + (long long)t.m0 * t.ldo + t.n0, t.o_off + (long long)(t.m1 - 1) * t.ldo + t.n1 - 1, nout, what);
         }
-        for (int q = t.s0; q < t.s1; ++q) {
+        for (int q = t.e0; q < t.s[4]; ++q) {
+            if (q >= t.e1 && q < t.s[0]) continue;
             const spk::KStep& p = C.steps[q];
             if (p.kc0 < 0 || p.kc1 <= p.kc0 || p.kc1 - p.kc0 > 16 * sh.ni || p.g0 < 0 || p.g1 <= p.g0 || p.g1 > int(C.segs.size()))
                 throw SpError(SP_EINVAL, std::string("internal step: ") + what);
             const bool pt = C.lay == spk::kChainEnvL;
             check_span(p.p_off + (pt ? (long long)p.kc0 * p.ldp + t.m0 : (long long)t.m0 * p.ldp + p.kc0),
                        p.p_off + (pt ? (long long)(p.kc1 - 1) * p.ldp + t.m1 - 1 : (long long)(t.m1 - 1) * p.ldp + p.kc1 - 1),
-                       in[p.p_buf], what);
+                       in[C.lay == spk::kChainHeff ? spk::K_R : spk::K_X], what);
             for (int i = p.g0; i < p.g1; ++i) {
                 const spk::KSeg& g = C.segs[i];
                 if (g.k0 < 0 || g.k1 <= g.k0) throw SpError(SP_EINVAL, std::string("internal segment: ") + what);
                 const bool at = C.lay == spk::kChainHeff, bt = C.lay == spk::kChainEnvL;
+                const long long nx = in[g.alt_x ? spk::K_XR : spk::K_X];
+                const long long ne = in[g.alt_e ? spk::K_LT : (C.lay == spk::kChainEnvR ? spk::K_R : spk::K_L)];
                 check_span(g.a_off + (at ? (long long)g.k0 * g.lda + p.kc0 : (long long)p.kc0 * g.lda + g.k0),
                            g.a_off + (at ? (long long)(g.k1 - 1) * g.lda + p.kc1 - 1 : (long long)(p.kc1 - 1) * g.lda + g.k1 - 1),
-                           in[g.a_buf], what);
+                           at ? nx : ne, what);
                 check_span(g.b_off + (bt ? (long long)g.k0 * g.ldb + t.n0 : (long long)t.n0 * g.ldb + g.k0),
                            g.b_off + (bt ? (long long)(g.k1 - 1) * g.ldb + t.n1 - 1 : (long long)(t.n1 - 1) * g.ldb + g.k1 - 1),
-                           in[g.b_buf], what);
-                check_span(g.cidx, g.cidx, ncoef, what);
+                           at ? ne : nx, what);
             }
         }
     }
 }
 
-void validate(const MixList& m, long long nin, long long nout, long long ncoef, const char* what) {
-    for (const spk::MTask& t : m.tasks) {
-        check_span(t.o_off, t.o_off + t.n - 1, nout, what);
-        for (int i = t.t0; i < t.t1; ++i) {
-            check_span(m.terms[i].a_off, m.terms[i].a_off + t.n - 1, nin, what);
-            check_span(m.terms[i].cidx, m.terms[i].cidx, ncoef, what);
-        }
-    }
-}
-
-// bounds of every list of the fused H_eff plan of site k (host side)
-void validate_fused(sp_handle* h, int k) {
-    const SitePlan& P = h->plan[k - 1];
-    const long long xs = h->sites[k - 1].size;
-    if (P.h_rows == 0) {  // no fused plan: the site runs the plain lists
-        if (!P.h_tasks.empty() || P.h_lds != 0) throw SpError(SP_EINVAL, "internal: fused plan state");
-        return;
-    }
-    const long long Lg = h->env[k - 1].size, Rg = h->env[k].size;
-    const int RC = P.h_rows, lmax = P.h_lds;
-    const int nblk = int(P.h_blks.size());
-    auto in_lds = [&](long long a0, long long a1, const char* what) { check_span(a0, a1, lmax, what); };
-    if (RC < 1 || RC > spk::kH3MaxRC || lmax > kHeffLdsMax) throw SpError(SP_EINVAL, "internal: fused shape");
-    std::vector<int> seen(size_t(xs) * h->G, 0);
-    for (const spk::H3Task& t : P.h_tasks) {
-        if (t.blk < 0) continue;
-        if (t.g < 0 || t.g >= h->G || t.blk >= nblk || t.rows < 1 || t.rows > RC)
-            throw SpError(SP_EINVAL, "internal: fused task");
-        const spk::H3Blk& B = P.h_blks[t.blk];
-        check_span(B.l0, B.l1 - 1, (long long)P.h_lsrc.size(), "fused L sources");
-        for (int q = B.l0; q < B.l1; ++q) {
-            const spk::H3LSrc& L = P.h_lsrc[q];
-            check_span(L.l_off + (long long)t.r0 * L.ld, L.l_off + (long long)(t.r0 + t.rows) * L.ld - 1, Lg,
-                       "fused L rows");
-            in_lds(L.lds, L.lds + (long long)RC * L.ld - 1, "fused staged L");
-        }
-        if (B.c1 > B.c0) check_span(B.c0, B.c1 - 1, (long long)P.h_cols.size(), "fused columns");
-        for (int ci = B.c0; ci < B.c1; ++ci) {
-            const spk::H3Col& c = P.h_cols[ci];
-            if (c.K > 0) {
-                check_span(c.x_off, c.x_off + (long long)(c.K - 1) * c.x_ld, xs, "fused x column");
-                in_lds(c.l_lds, c.l_lds + (long long)(RC - 1) * c.l_ld + c.K - 1, "fused L entries");
-            }
-            in_lds(c.t_pos, c.t_pos + RC - 1, "fused T column");
-        }
-        for (int sig = 0; sig < 4; ++sig) {
-            if (B.s1[sig] > B.s0[sig]) check_span(B.s0[sig], B.s1[sig] - 1, (long long)P.h_segs.size(), "fused segments");
-            if (t.p1[sig] > t.p0[sig]) check_span(t.p0[sig], t.p1[sig] - 1, (long long)P.h_pieces.size(), "fused pieces");
-            for (int p = t.p0[sig]; p < t.p1[sig]; ++p) {
-                const spk::H3Piece& pc = P.h_pieces[p];
-                if (pc.rlo < 0 || pc.rhi > t.rows || pc.rlo >= pc.rhi || pc.nb < 1)
-                    throw SpError(SP_EINVAL, "internal: fused piece");
-                for (int rr = pc.rlo; rr < pc.rhi; ++rr)
-                    for (int b = 0; b < pc.nb; ++b) {
-                        const long long o = pc.out_off + (long long)(rr - pc.rlo) * pc.out_ld + b;
-                        check_span(o, o, xs, "fused output");
-                        if (seen[size_t(t.g) * xs + o]++) throw SpError(SP_EINVAL, "internal: fused output written twice");
-                    }
-                for (int si = B.s0[sig]; si < B.s1[sig]; ++si) {
-                    const spk::H3Seg& S = P.h_segs[si];
-                    check_span(S.r_off + (long long)pc.b0 * S.K, S.r_off + (long long)(pc.b0 + pc.nb) * S.K - 1, Rg,
-                               "fused R rows");
-                }
-            }
-            for (int si = B.s0[sig]; si < B.s1[sig]; ++si) {
-                const spk::H3Seg& S = P.h_segs[si];
-                in_lds(S.v_off, S.v_off + (long long)RC * S.K - 1, "fused V");
-                if (S.t1 > S.t0) check_span(S.t0, S.t1 - 1, (long long)P.h_terms.size(), "fused terms");
-                for (int tm = S.t0; tm < S.t1; ++tm) {
-                    in_lds(P.h_terms[tm].t_base, P.h_terms[tm].t_base + (long long)RC * S.K - 1, "fused T block");
-                    check_span(P.h_terms[tm].cidx, P.h_terms[tm].cidx, P.nc, "fused coefficient");
-                }
+void validate(const MixList& m, long long nin, long long nout, const char* what) {
+    for (const spk::MixWork& w : m.work) {
+        if (w.tile0 < 0 || w.tile1 <= w.tile0 || w.tile1 > int(m.tiles.size()) || w.e0 < 0 || w.e0 >= w.n)
+            throw SpError(SP_EINVAL, std::string("internal work: ") + what);
+        if (w.e0 > 0) continue;  // the first chunk of a shape stands for all
+        for (int t = w.tile0; t < w.tile1; ++t) {
+            const spk::MixTileRec& r = m.tiles[t];
+            if (r.s0 < 0 || r.s1 < r.s0 || r.s1 - r.s0 > spk::kMixTile || r.s1 > int(m.src.size()) || r.i0 < 0 || r.i1 < r.i0 ||
+                r.i1 > int(m.groups.size()))
+                throw SpError(SP_EINVAL, std::string("internal tile: ") + what);
+            for (int q = r.s0; q < r.s1; ++q) check_span(m.src[q], m.src[q] + w.n - 1, nin, what);
+            for (int i = r.i0; i < r.i1; ++i) {
+                const spk::MixGroup& it = m.groups[i];
+                if (it.n < 1 || it.n > spk::kMixGroup || it.t0 < 0 || it.t1 <= it.t0 || it.t1 > int(m.at.size()) ||
+                    m.cf.size() != m.at.size() * spk::kMixGroup)
+                    throw SpError(SP_EINVAL, std::string("internal terms: ") + what);
+                for (int b = 0; b < it.n; ++b) check_span(it.o[b], it.o[b] + w.n - 1, nout, what);
+                for (int q = it.t0; q < it.t1; ++q) check_span(m.at[q], m.at[q], r.s1 - r.s0, what);
             }
         }
     }
-    for (long long o = 0; o < (long long)xs * h->G; ++o)
-        if (seen[o] != 1) throw SpError(SP_EINVAL, "internal: fused outputs do not cover the site");
 }
 
 // bounds of the lists of the diagonals of site k
@@ -2335,46 +1873,25 @@ void validate_plans(sp_handle* h) {
         validate(P.envl_out, z, nco, "left environment");
         z[B_OUT] = Lb;
         validate(P.envr_out, z, nco, "right environment");
-        // tiled lists: B_X is the dense site layout, B_Y/B_NY the per-g partials
         {
-            Sizes t = z;
-            t[B_X] = h->Xd_cap;
-            t[B_Y] = G * h->tr_split_max * h->max_site;
-            t[B_NY] = G * h->tr_split_max * h->max_site;
             for (int e : P.xmap_h)
                 if (e >= xs) throw SpError(SP_EINVAL, "internal: packed map out of range");
             const long long ms = (long long)P.xmap_h.size();
-            validate(P.t_left, t, nco, ms, xs, "tiled left product");
-            if (h->path == SP_PATH_TILED) {  // the plain path has no pre-mixed environment buffer
-                t[B_LT] = h->LT_cap;
-                if (G * P.LTsize > h->LT_cap)
-                    throw SpError(SP_EINVAL, "internal: pre-mixed environment scratch too small");
-                validate(P.t_leftv, t, nco, ms, xs, "tiled product of the pre-mixed environment");
-                validate(P.t_left0, t, nco, ms, xs, "tiled identity-channel product");
-                validate(P.premix, t, nco, "pre-mixed left environment");
-                validate(P.xrmix, t, nco, "rotated site vector");
-            }
-            validate(P.t_right, t, nco, ms, xs, "tiled right product");
-            validate(P.t_zr, t, nco, ms, xs, "tiled right-pass product");
-            t[B_OUT] = Rb;
-            validate(P.t_envl, t, nco, ms, xs, "tiled left environment");
-            t[B_OUT] = Lb;
-            validate(P.t_envr, t, nco, ms, xs, "tiled right environment");
             if (h->path == SP_PATH_TILED) {
                 const long long Lg = h->env[k - 1].size, Rg = h->env[k].size;
                 if (G * std::max(P.mix_l.size, P.mix_r.size) > h->LT_cap || G * (long long)P.rmap_h.size() > h->Xr_cap)
                     throw SpError(SP_EINVAL, "internal: scratch of the chained products too small");
                 for (int e : P.rmap_h)
                     if (e >= xs) throw SpError(SP_EINVAL, "internal: packed map out of range");
-                validate(P.mix_l, Lg, P.mix_l.size, P.nc, "pre-mixed left environment");
-                validate(P.mix_r, Rg, P.mix_r.size, P.nc, "pre-mixed right environment");
+                validate(P.mix_l, Lg, P.mix_l.size, "pre-mixed left environment");
+                validate(P.mix_r, Rg, P.mix_r.size, "pre-mixed right environment");
                 const long long nxr = (long long)P.rmap_h.size();
+                validate(P.c_heff, {Lg, Rg, P.Xd_size, nxr, P.mix_l.size}, P.y_split * G * xs, ms, xs, P.nc, "H_eff x");
                 validate(P.c_envl, {Lg, 0, P.Xd_size, nxr, P.mix_l.size}, Rg, 0, 0, P.nc, "left environment update");
                 validate(P.c_envr, {0, Rg, P.Xd_size, nxr, P.mix_r.size}, Lg, 0, 0, P.nc, "right environment update");
             }
             if (P.Xd_size > h->Xd_cap) throw SpError(SP_EINVAL, "internal: dense site scratch too small");
         }
-        validate_fused(h, k);
         if (k < h->L) {
             Sizes a{};
             a.fill(0);
@@ -2468,111 +1985,10 @@ spk::BufSet bufset(sp_handle* h, int k, const double* x, double* y, double* ny, 
     b.p[B_NY] = ny;
     b.p[B_OUT] = out;
     b.p[B_BRA] = const_cast<double*>(x);
-    b.p[B_LT] = h->LT.p;
     return b;
 }
 
 void check_site(const sp_handle* h, int k) { SP_REQUIRE(k >= 1 && k <= h->L, "site out of range"); }
-
-// the fused-kernel instance descriptor of site k applied to x
-// (yp, nyp: the per-g partial slots; null = the handle's own)
-spk::H3Inst heff_inst(sp_handle* h, int k, const double* x, bool f32, double* yp = nullptr, double* nyp = nullptr) {
-    SitePlan& P = h->plan[k - 1];
-    spk::H3Inst I{};
-    I.blks = P.dh_blks.p;
-    I.cols = P.dh_cols.p;
-    I.lsrc = P.dh_lsrc.p;
-    I.segs = P.dh_segs.p;
-    I.terms = P.dh_terms.p;
-    I.pieces = P.dh_pieces.p;
-    if (f32) {
-        I.Lenv = h->envL32[k - 1].p;
-        I.Renv = h->envR32[k].p;
-    } else {
-        I.Lenv = h->envL[k - 1].p;
-        I.Renv = h->envR[k].p;
-    }
-    I.Lsz = h->env[k - 1].size;
-    I.Rsz = h->env[k].size;
-    I.x = x;
-    I.coef = P.coef.p;
-    I.ypart = yp ? yp : h->ypart.p;
-    I.nypart = nyp ? nyp : h->nypart.p;
-    I.n = h->sites[k - 1].size;
-    I.nc = P.nc;
-    return I;
-}
-
-// H_eff x at a tiled-path site without a fused plan (a particle-number block
-// too wide for its LDS): the LDS-tiled block-product lists (FP64, or split
-// BF16 in that mode), leaving the same per-g partials as the fused kernel.
-// The MPO is mixed into the left environment instead of into the products
-// L_g x, and the rotation r_g into the site vector: the pre-mixed
-// environment depends only on L[k-1] and is built once per local problem
-// (the first product after L[k-1] changes), the rotated site vector (two
-// small blocks per particle-number block) with every product, so each
-// product is one small mixing launch and two block-product launches.
-void heff_tiled(sp_handle* h, int k, const double* x, bool bf3 = false, double* yp = nullptr,
-                double* nyp = nullptr) {
-    SitePlan& P = h->plan[k - 1];
-    hipStream_t s = h->stream;
-    if (!yp) yp = h->ypart.p;
-    if (!nyp) nyp = h->nypart.p;
-    const spk::BufSet b = bufset(h, k, h->Xd.p, yp, nyp, nullptr);
-    spk::gather(s, P.xmap.p, x, h->Xd.p, P.Xd_size);
-    if (h->lt_site != k || h->lt_gen != h->Lgen[k - 1]) {  // once per left environment and site
-        P.premix.launch(s, b, P.coef.p);
-        h->lt_site = k;
-        h->lt_gen = h->Lgen[k - 1];
-    }
-    P.xrmix.launch(s, b, P.coef.p);
-    P.t_left0.launch(s, b, P.coef.p, P.xmap.p, bf3);
-    P.t_leftv.launch(s, b, P.coef.p, P.xmap.p, bf3);
-    if (P.tr_split > 1) {  // slots without a chunk of some tile stay zero
-        const long long nslot = (long long)P.tr_split * h->G * h->sites[k - 1].size;
-        spk::fill(s, yp, nslot, 0.0);
-        spk::fill(s, nyp, nslot, 0.0);
-    }
-    P.t_right.launch(s, b, P.coef.p, P.xmap.p, bf3);
-}
-
-// number of per-site partial outputs H_eff x leaves (in G * n blocks of n)
-int heff_parts(const sp_handle* h, int k) {
-    return (h->path == SP_PATH_TILED && h->plan[k - 1].h_rows == 0) ? h->G * h->plan[k - 1].tr_split : h->G;
-}
-
-// With defer_gsum on the tiled path only the per-quadrature-point partials
-// (h->ypart, h->nypart) are produced and the function returns true: the
-// caller adds them (the Davidson Gram pass does).
-// yp, nyp: where the partials go (null = the handle's own slots)
-bool heff_apply(sp_handle* h, int k, const double* x, double* y, double* ny, bool defer_gsum = false,
-                bool force_fp64 = false, double* yp = nullptr, double* nyp = nullptr) {
-    if (!h->Lvalid[k - 1] || !h->Rvalid[k])
-        throw SpError(SP_ESTATE, "H_eff needs L[site-1] and R[site+1]; build them with sp_env_update");
-    SitePlan& P = h->plan[k - 1];
-    hipStream_t s = h->stream;
-    if (h->path == SP_PATH_PLAIN) {
-        const spk::BufSet b = bufset(h, k, x, y, ny, nullptr);
-        P.p1.launch(s, b, P.coef.p);
-        P.mixl.launch(s, b, P.coef.p);
-        P.yout.launch(s, b, P.coef.p);
-        return false;
-    }
-    const int n = int(h->sites[k - 1].size);
-    if (!yp) yp = h->ypart.p;
-    if (!nyp) nyp = h->nypart.p;
-    if (P.h_rows == 0) {
-        heff_tiled(h, k, x, h->precision == SP_BF16X3 && !force_fp64, yp, nyp);
-    } else {
-        const bool f32 = reduced(h) && !force_fp64;
-        const spk::H3Inst I = heff_inst(h, k, x, f32, yp, nyp);
-        if (f32) spk::heff3_f32(s, P.h_rows, P.h_lds, P.dh_tasks.p, int(P.h_tasks.size()), I);
-        else spk::heff3(s, P.h_rows, P.h_lds, P.dh_tasks.p, int(P.h_tasks.size()), I);
-    }
-    if (defer_gsum) return true;
-    spk::gsum2(s, yp, nyp, n, heff_parts(h, k), n, y, ny);
-    return false;
-}
 
 // operands of a chained product at site k (x prepared by site_vectors)
 spk::KInst chain_inst(sp_handle* h, int k, const ChainList& C, const MixList& mix) {
@@ -2611,9 +2027,144 @@ spk::KPrep prep_inst(sp_handle* h, int k, const double* x) {
     I.G = h->G;
     return I;
 }
-void site_vectors(sp_handle* h, int k, const double* x) {
+void site_vectors(sp_handle* h, int k, const double* x, bool f32 = false) {
     const spk::KPrep I = prep_inst(h, k, x);
-    spk::xprep(h->stream, false, std::max(I.nd, I.nr), h->G, 1, nullptr, I);
+    spk::xprep(h->stream, f32, std::max(I.nd, I.nr), h->G, 1, nullptr, I);
+}
+
+// arithmetic of H_eff x at site k: fused plans follow the precision of the
+// local solves, block products are FP64 or split BF16
+int heff_mode(const sp_handle* h, int k, bool force_fp64) {
+    if (force_fp64 || !reduced(h)) return spk::kChainF64;
+    if (h->plan[k - 1].h_rows > 0) return spk::kChainF32;
+    return h->precision == SP_BF16X3 ? spk::kChainBF3 : spk::kChainF64;
+}
+
+// partial slots of y that H_eff x leaves (of ny: G), in units of the site size
+int heff_parts(const sp_handle* h, int k) {
+    return h->path == SP_PATH_TILED ? h->G * h->plan[k - 1].y_split : h->G;
+}
+
+// the left environment with the MPO mixed in, once per local problem: it
+// depends on L[k-1] only
+void premix_left(sp_handle* h, int k, int mode) {
+    const SitePlan& P = h->plan[k - 1];
+    const MixList& m = P.mix_l;
+    const bool f32 = mode == spk::kChainF32;
+    if (m.empty() || (h->lt_site == k && h->lt_gen == h->Lgen[k - 1] && h->lt_f32 == f32)) return;
+    const void* env = f32 ? (const void*)h->envL32[k - 1].p : (const void*)h->envL[k - 1].p;
+    spk::premix(h->stream, f32, m.lists(), env, h->env[k - 1].size, h->LT.p, m.size, h->G);
+    h->lt_site = k;
+    h->lt_gen = h->Lgen[k - 1];
+    h->lt_f32 = f32;
+}
+
+// H_eff x as a chained product into the partial slots yp, nyp
+spk::KInst heff_inst(sp_handle* h, int k, int mode, double* yp, double* nyp) {
+    const SitePlan& P = h->plan[k - 1];
+    spk::KInst I = chain_inst(h, k, P.c_heff, P.mix_l);
+    if (mode == spk::kChainF32) {
+        I.in[spk::K_L].p = h->envL32[k - 1].p;
+        I.in[spk::K_R].p = h->envR32[k].p;
+    }
+    I.out[0] = yp;
+    I.out[1] = nyp;
+    I.ogs = h->sites[k - 1].size;
+    return I;
+}
+
+void need_envs(const sp_handle* h, int k) {
+    if (!h->Lvalid[k - 1] || !h->Rvalid[k])
+        throw SpError(SP_ESTATE, "H_eff needs L[site-1] and R[site+1]; build them with sp_env_update");
+}
+
+// H_eff x of several states as one launch per arithmetic and tile shape: the
+// instances in launch order and the launches over them
+struct HeffBatch {
+    struct Launch {
+        int mode, shape, first, count, max_tiles, max_n, max_G;
+    };
+    std::vector<spk::KInst> insts;
+    std::vector<spk::KPrep> preps;
+    std::vector<Launch> launches;
+    std::vector<std::tuple<int, int, spk::KInst, spk::KPrep>> items;  // (mode, shape, ..)
+    // adds x at site k of h (mixing its left environment if it is due); gate:
+    // see KInst
+    void add(sp_handle* h, int k, const double* x, const int* gate) {
+        const int mode = heff_mode(h, k, false);
+        need_envs(h, k);
+        premix_left(h, k, mode);
+        spk::KInst I = heff_inst(h, k, mode, h->ypart.p, h->nypart.p);
+        spk::KPrep q = prep_inst(h, k, x);
+        I.gate = q.gate = gate;
+        items.push_back({mode, h->plan[k - 1].c_heff.shape, I, q});
+    }
+    void finish() {
+        std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) {
+            return std::tie(std::get<0>(a), std::get<1>(a)) < std::tie(std::get<0>(b), std::get<1>(b));
+        });
+        for (const auto& it : items) {
+            const spk::KInst& I = std::get<2>(it);
+            const spk::KPrep& q = std::get<3>(it);
+            if (launches.empty() || launches.back().mode != std::get<0>(it) || launches.back().shape != std::get<1>(it))
+                launches.push_back({std::get<0>(it), std::get<1>(it), int(insts.size()), 0, 0, 0, 0});
+            Launch& l = launches.back();
+            ++l.count;
+            l.max_tiles = std::max(l.max_tiles, I.ntile * I.G);
+            l.max_n = std::max(l.max_n, std::max(q.nd, q.nr));
+            l.max_G = std::max(l.max_G, I.G);
+            insts.push_back(I);
+            preps.push_back(q);
+        }
+    }
+    size_t bytes() const { return insts.size() * (sizeof(spk::KInst) + sizeof(spk::KPrep)); }
+    // the records as one block: the instances, then the site vectors
+    void pack(void* dst) const {
+        std::memcpy(dst, insts.data(), insts.size() * sizeof(spk::KInst));
+        std::memcpy(static_cast<char*>(dst) + insts.size() * sizeof(spk::KInst), preps.data(), preps.size() * sizeof(spk::KPrep));
+    }
+    void launch(hipStream_t s, const void* dev) const {
+        const spk::KInst* di = static_cast<const spk::KInst*>(dev);
+        const spk::KPrep* dp = reinterpret_cast<const spk::KPrep*>(di + insts.size());
+        for (const Launch& l : launches) {
+            spk::xprep(s, l.mode == spk::kChainF32, l.max_n, l.max_G, l.count, dp + l.first, preps[l.first]);
+            spk::chain(s, l.mode, spk::kChainHeff, l.shape, spk::kChainWaves, l.max_tiles, l.count, di + l.first, insts[l.first]);
+        }
+    }
+};
+
+// H_eff x at site k into the partial slots, whatever the environments hold
+void heff_partials(sp_handle* h, int k, const double* x, int mode, double* yp, double* nyp) {
+    const SitePlan& P = h->plan[k - 1];
+    premix_left(h, k, mode);
+    site_vectors(h, k, x, mode == spk::kChainF32);
+    const spk::KInst I = heff_inst(h, k, mode, yp, nyp);
+    spk::chain(h->stream, mode, spk::kChainHeff, P.c_heff.shape, spk::kChainWaves, I.ntile * I.G, 1, nullptr, I);
+}
+
+// With defer_gsum on the tiled path only the per-quadrature-point partials
+// (h->ypart, h->nypart) are produced and the function returns true: the
+// caller adds them (the Davidson Gram pass does).
+// yp, nyp: where the partials go (null = the handle's own slots)
+bool heff_apply(sp_handle* h, int k, const double* x, double* y, double* ny, bool defer_gsum = false,
+                bool force_fp64 = false, double* yp = nullptr, double* nyp = nullptr) {
+    need_envs(h, k);
+    SitePlan& P = h->plan[k - 1];
+    hipStream_t s = h->stream;
+    if (h->path == SP_PATH_PLAIN) {
+        const spk::BufSet b = bufset(h, k, x, y, ny, nullptr);
+        P.p1.launch(s, b, P.coef.p);
+        P.mixl.launch(s, b, P.coef.p);
+        P.yout.launch(s, b, P.coef.p);
+        return false;
+    }
+    const int n = int(h->sites[k - 1].size);
+    if (!yp) yp = h->ypart.p;
+    if (!nyp) nyp = h->nypart.p;
+    heff_partials(h, k, x, heff_mode(h, k, force_fp64), yp, nyp);
+    if (defer_gsum) return true;
+    spk::gsum2(s, yp, nyp, n, heff_parts(h, k), h->G, n, y, ny);
+    return false;
 }
 
 // one environment update as a chained product: out, of the given values per g
@@ -2621,14 +2172,16 @@ void env_chain(sp_handle* h, int k, const ChainList& C, const MixList& mix, cons
                long long osize) {
     const SitePlan& P = h->plan[k - 1];
     site_vectors(h, k, site_ptr(h, k));
-    if (!mix.tasks.empty()) {
-        spk::premix(h->stream, false, mix.dtasks.p, int(mix.tasks.size()), mix.dterms.p, env, esize, h->LT.p, mix.size, P.coef.p, h->G);
+    if (&mix == &P.mix_l) {
+        premix_left(h, k, spk::kChainF64);  // there already if H_eff was applied at this site
+    } else if (!mix.empty()) {
+        spk::premix(h->stream, false, mix.lists(), env, esize, h->LT.p, mix.size, h->G);
         h->lt_site = -1;
     }
     spk::KInst I = chain_inst(h, k, C, mix);
     I.out[0] = out;
     I.ogs = osize;
-    spk::chain(h->stream, spk::kChainF64, C.lay, C.shape, I.ntile * I.G, 1, nullptr, I);
+    spk::chain(h->stream, spk::kChainF64, C.lay, C.shape, C.waves, I.ntile * I.G, 1, nullptr, I);
 }
 
 void env_left(sp_handle* h, int k) {
@@ -2969,12 +2522,12 @@ DavOut davidson(sp_handle* h, int k, const sp_sweep_opts& o) {
         if (h->path == SP_PATH_PLAIN) {
             if (from_t) spk::dav_normalize(s, sm + lay.pn, nch, h->dt.p, vm, n, tn);
             heff_apply(h, k, vm, HV + size_t(mm) * ld, NV + size_t(mm) * ld);
-            spk::dav_gram(s, V, HV, NV, ld, mm, n, nullptr, nullptr, 0, nullptr, nullptr, nullptr, n, h->G,
+            spk::dav_gram(s, V, HV, NV, ld, mm, n, nullptr, nullptr, 0, nullptr, nullptr, nullptr, n, h->G, h->G,
                           dn_dev + (lay.pg - lay.out));
         } else {
             heff_apply(h, k, from_t ? h->dt.p : vm, nullptr, nullptr, true);
             spk::dav_gram(s, V, HV, NV, ld, mm, n, from_t ? h->dt.p : nullptr, sm + lay.pn, nch, tn, h->ypart.p,
-                          h->nypart.p, n, heff_parts(h, k), dn_dev + (lay.pg - lay.out));
+                          h->nypart.p, n, heff_parts(h, k), h->G, dn_dev + (lay.pg - lay.out));
         }
         // constrained pencil (Q H Q, Q N Q): the Gram rows above are the same
         // for the projected products, since every V_j is orthogonal to C
@@ -3286,8 +2839,7 @@ struct BatchState {
 };
 
 struct BatchBufs {
-    DArr<spk::H3Task> tasks;
-    DArr<spk::H3Inst> insts;
+    DArr<char> insts;
     DArr<spk::DavInst> dav;
     double* pin = nullptr;  // staging of the per-round uploads
     size_t pin_n = 0;
@@ -3313,50 +2865,14 @@ struct BatchBufs {
 void batch_heff_mixed(std::vector<BatchState>& B, const std::vector<int>& idx, const std::vector<int>& from_v0,
                       BatchBufs& bb, hipStream_t s) {
     if (idx.empty()) return;
-    std::vector<spk::H3Inst> insts(idx.size());
-    std::map<int, std::vector<spk::H3Task>> by_rc;
-    std::map<int, int> lds_by_rc;
-    const bool f32 = reduced(B[idx[0]].h);
-    for (size_t q = 0; q < idx.size(); ++q) {
-        BatchState& st = B[idx[q]];
-        sp_handle* h = st.h;
-        const double* x = from_v0[idx[q]] ? h->dV.p : h->dt.p;
-        insts[q] = heff_inst(h, st.k, x, f32);
-        const SitePlan& P = h->plan[st.k - 1];
-        if (P.h_rows == 0) {  // no fused plan: this state's tiled lists, same partials
-            heff_tiled(h, st.k, x, h->precision == SP_BF16X3);
-            continue;
-        }
-        auto& v = by_rc[P.h_rows];
-        for (spk::H3Task t : P.h_tasks) {
-            if (t.blk < 0) continue;
-            t.inst = int(q);
-            v.push_back(t);
-        }
-        lds_by_rc[P.h_rows] = std::max(lds_by_rc[P.h_rows], P.h_lds);
-    }
-    size_t ntask = 0;
-    for (auto& kv : by_rc) ntask += kv.second.size();
-    const size_t bytes = insts.size() * sizeof(spk::H3Inst) + ntask * sizeof(spk::H3Task);
-    char* stage = reinterpret_cast<char*>(bb.staging(bytes));
-    std::memcpy(stage, insts.data(), insts.size() * sizeof(spk::H3Inst));
-    size_t off = insts.size() * sizeof(spk::H3Inst);
-    for (auto& kv : by_rc) {
-        std::memcpy(stage + off, kv.second.data(), kv.second.size() * sizeof(spk::H3Task));
-        off += kv.second.size() * sizeof(spk::H3Task);
-    }
-    if (bb.insts.n < insts.size()) bb.insts.alloc(insts.size());
-    if (bb.tasks.n < ntask) bb.tasks.alloc(ntask);
-    HIPCK(hipMemcpyAsync(bb.insts.p, stage, insts.size() * sizeof(spk::H3Inst), hipMemcpyHostToDevice, s));
-    HIPCK(hipMemcpyAsync(bb.tasks.p, stage + insts.size() * sizeof(spk::H3Inst), ntask * sizeof(spk::H3Task),
-                         hipMemcpyHostToDevice, s));
-    size_t t0 = 0;
-    for (auto& kv : by_rc) {
-        const int nt = int(kv.second.size());
-        if (f32) spk::heff3_f32(s, kv.first, lds_by_rc[kv.first], bb.tasks.p + t0, nt, insts[0], bb.insts.p);
-        else spk::heff3(s, kv.first, lds_by_rc[kv.first], bb.tasks.p + t0, nt, insts[0], bb.insts.p);
-        t0 += nt;
-    }
+    HeffBatch hb;
+    for (int i : idx) hb.add(B[i].h, B[i].k, from_v0[i] ? B[i].h->dV.p : B[i].h->dt.p, nullptr);
+    hb.finish();
+    void* stage = bb.staging(hb.bytes());
+    hb.pack(stage);
+    if (bb.insts.n < hb.bytes()) bb.insts.alloc(hb.bytes());
+    HIPCK(hipMemcpyAsync(bb.insts.p, stage, hb.bytes(), hipMemcpyHostToDevice, s));
+    hb.launch(s, bb.insts.p);
 }
 
 void batch_dav_upload(std::vector<spk::DavInst>& D, BatchBufs& bb, hipStream_t s) {
@@ -3391,6 +2907,7 @@ spk::DavInst dav_inst(BatchState& st) {
     I.nypart = h->nypart.p;
     I.gstride = st.n;
     I.G = heff_parts(h, st.k);
+    I.Gn = h->G;
     I.m = st.m;
     I.mr = st.m;
     I.n = st.n;
@@ -3433,7 +2950,6 @@ int sweep_batch(std::vector<BatchState>& B, const sp_sweep_opts& o, std::vector<
     // phase: 0 = start a step, 1 = Davidson iterations, 2 = done
     std::vector<int> phase(B.size());
     for (size_t i = 0; i < B.size(); ++i) phase[i] = B[i].order.empty() ? 2 : 0;
-    std::vector<spk::H3Inst> hinst;
     for (;;) {
         std::vector<int> starting, iterating;
         for (size_t i = 0; i < B.size(); ++i) {
@@ -3733,6 +3249,7 @@ spk::DavInst dev_inst(BatchState& st, const sp_sweep_opts& o, int max_sub, int k
     I.nypart = h->nypart.p;
     I.gstride = st.n;
     I.G = heff_parts(h, st.k);
+    I.Gn = h->G;
     I.m = 0;  // the first Gram pass (V_0, products read from the partials)
     I.mr = 0;
     I.n = st.n;
@@ -3779,8 +3296,7 @@ int sweep_rounds(std::vector<BatchState>& B, const sp_sweep_opts& o, std::vector
     } cleanup{stat, stage, gs};
     DArr<spk::DavInst> dinst;
     dinst.alloc(nb);
-    DArr<spk::H3Inst> ginst;
-    DArr<spk::H3Task> gtask;
+    DArr<char> ginst;
     int status = SP_OK;
     const int poll = 4;  // replays between two looks at the status
     for (;;) {
@@ -3814,49 +3330,23 @@ int sweep_rounds(std::vector<BatchState>& B, const sp_sweep_opts& o, std::vector
         HIPCK(hipMemcpyAsync(dinst.p, D, size_t(na) * sizeof(spk::DavInst), hipMemcpyHostToDevice, s));
         spk::bdav_gram(s, dinst.p, na, max_n, 0);
         spk::bdav_start(s, dinst.p, na);
-        // the fused H_eff of the corrections: instance records and tasks on
-        // the device for the whole round, each instance gated by its record
-        std::vector<spk::H3Inst> hi(na);
-        std::map<int, std::vector<spk::H3Task>> by_rc;
-        std::map<int, int> lds_by_rc;
-        std::vector<int> tiled;
-        const bool f32 = reduced(B[idx[0]].h);
-        for (int q = 0; q < na; ++q) {
-            BatchState& st = B[idx[q]];
-            sp_handle* h = st.h;
-            hi[q] = heff_inst(h, st.k, h->dt.p, f32);
-            hi[q].gate = reinterpret_cast<const int*>(reinterpret_cast<const char*>(dinst.p + q) +
-                                                     offsetof(spk::DavInst, ext));
-            const SitePlan& P = h->plan[st.k - 1];
-            if (P.h_rows == 0) {
-                tiled.push_back(q);
-                continue;
-            }
-            for (spk::H3Task t : P.h_tasks) {
-                if (t.blk < 0) continue;
-                t.inst = q;
-                by_rc[P.h_rows].push_back(t);
-            }
-            lds_by_rc[P.h_rows] = std::max(lds_by_rc[P.h_rows], P.h_lds);
+        // H_eff x of the corrections: the instance records on the device for
+        // the whole round, each instance gated by its record
+        HeffBatch hb;
+        for (int q = 0; q < na; ++q)
+            hb.add(B[idx[q]].h, B[idx[q]].k, B[idx[q]].h->dt.p,
+                   reinterpret_cast<const int*>(reinterpret_cast<const char*>(dinst.p + q) + offsetof(spk::DavInst, ext)));
+        hb.finish();
+        if (ginst.n < hb.bytes()) ginst.alloc(hb.bytes());
+        {
+            std::vector<char> rec(hb.bytes());
+            hb.pack(rec.data());
+            HIPCK(hipMemcpy(ginst.p, rec.data(), rec.size(), hipMemcpyHostToDevice));
         }
-        std::vector<spk::H3Task> all;
-        std::vector<std::pair<int, std::pair<size_t, int>>> groups;
-        for (auto& kv : by_rc) {
-            groups.push_back({kv.first, {all.size(), int(kv.second.size())}});
-            all.insert(all.end(), kv.second.begin(), kv.second.end());
-        }
-        if (ginst.n < size_t(na)) ginst.alloc(na);
-        if (gtask.n < all.size()) gtask.alloc(all.size());
-        HIPCK(hipMemcpy(ginst.p, hi.data(), size_t(na) * sizeof(spk::H3Inst), hipMemcpyHostToDevice));
-        if (!all.empty())
-            HIPCK(hipMemcpy(gtask.p, all.data(), all.size() * sizeof(spk::H3Task), hipMemcpyHostToDevice));
         HIPCK(hipStreamSynchronize(s));
         // one iteration of every state, captured on the private stream
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
-        std::vector<hipStream_t> saved;
-        for (int q : tiled) saved.push_back(B[idx[q]].h->stream);
-        for (int q : tiled) B[idx[q]].h->stream = gs;  // their block products launch on the capture stream
         hipError_t ce = hipStreamBeginCapture(gs, hipStreamCaptureModeThreadLocal);
         if (ce == hipSuccess) {
             spk::bdav_solve(gs, dinst.p, na, max_sub);
@@ -3865,20 +3355,11 @@ int sweep_rounds(std::vector<BatchState>& B, const sp_sweep_opts& o, std::vector
             spk::bdav_cgs(gs, dinst.p, na, max_n, 2);
             spk::bdav_cgs(gs, dinst.p, na, max_n, 0);
             spk::bdav_cgs(gs, dinst.p, na, max_n, 1);
-            for (auto& gr : groups) {
-                const spk::H3Task* tp = gtask.p + gr.second.first;
-                if (f32) spk::heff3_f32(gs, gr.first, lds_by_rc[gr.first], tp, gr.second.second, hi[0], ginst.p);
-                else spk::heff3(gs, gr.first, lds_by_rc[gr.first], tp, gr.second.second, hi[0], ginst.p);
-            }
-            for (int q : tiled) {
-                BatchState& st = B[idx[q]];
-                heff_tiled(st.h, st.k, st.h->dt.p, st.h->precision == SP_BF16X3);
-            }
+            hb.launch(gs, ginst.p);
             spk::bdav_gram(gs, dinst.p, na, max_n, max_sub);
             spk::bdav_update(gs, dinst.p, na);
             ce = hipStreamEndCapture(gs, &graph);
         }
-        for (size_t j = 0; j < tiled.size(); ++j) B[idx[tiled[j]]].h->stream = saved[j];
         hip_check(ce, "capture of the Davidson iteration");
         HIPCK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
         int replays = 0;
@@ -3956,7 +3437,6 @@ int sweep_rounds(std::vector<BatchState>& B, const sp_sweep_opts& o, std::vector
 // device comes from hipGetSymbolAddress, taken once per device at
 // sp_init_mps with that device current.
 
-constexpr long long kNoAllocSlots = 1LL << 21;  // doubles per output (y, ny): 16 MiB each
 static __device__ __align__(256) double scratch[2 * kNoAllocSlots];
 
 namespace {
@@ -4054,23 +3534,23 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         long long Tmax = 0, Vmax = 0, qrs = 0, qrr = 0, LTmax = 0;
         for (int k = 1; k <= h->L; ++k) {
             build_plan(h.get(), k);
-            if (h->path == SP_PATH_TILED) build_chain(h.get(), k);
-            if (h->path == SP_PATH_TILED && !build_fused(h.get(), k)) build_fused(h.get(), k, kHeffLdsMax);
+            if (h->path == SP_PATH_TILED) {
+                if (!build_fused(h.get(), k)) build_fused(h.get(), k, kHeffLdsMax);
+                build_chain(h.get(), k);
+            }
             if (h->path == SP_PATH_TILED && h->plan[k - 1].h_rows == 1) {
-                // one row per task re-reads the right environment once per
-                // row (wide MPOs): the tiled block products are faster there
-                // (3.6 ms against about 1 ms at the K = 12 ab-initio sites)
+                // wide MPOs: block products, in the reduced precisions FP64
+                // or split BF16
                 SitePlan& P1 = h->plan[k - 1];
                 P1.h_rows = 0;
                 P1.h_lds = 0;
-                P1.h_tasks.clear();
             }
             const SitePlan& P = h->plan[k - 1];
             // the diagonals use the same scratch
             const long long dgT = (long long)P.dg_nzl * h->bonds[k - 1].D + (long long)P.dg_nzr * h->bonds[k].D;
             Tmax = std::max({Tmax, P.Tsize, P.Zsize, dgT});
             Vmax = std::max({Vmax, P.Vsize, P.Ztsize, (long long)P.dg_mix.size() * h->bonds[k - 1].D});
-            LTmax = std::max({LTmax, P.LTsize, P.mix_l.size, P.mix_r.size});
+            LTmax = std::max({LTmax, P.mix_l.size, P.mix_r.size});
             qrs = std::max({qrs, P.qr_scratch, P.lq_scratch});
             qrr = std::max({qrr, P.qr_rsize, P.lq_rsize});
         }
@@ -4082,7 +3562,7 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         for (int k = 1; k <= h->L; ++k) {
             h->Xd_cap = std::max(h->Xd_cap, h->plan[k - 1].Xd_size);
             h->Xr_cap = std::max(h->Xr_cap, h->G * (long long)h->plan[k - 1].rmap_h.size());
-            h->tr_split_max = std::max(h->tr_split_max, h->plan[k - 1].tr_split);
+            h->y_split_max = std::max(h->y_split_max, h->plan[k - 1].y_split);
         }
         h->Xd_cap = std::max(1LL, h->Xd_cap);
         validate_plans(h.get());
@@ -4101,8 +3581,8 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         if (h->path == SP_PATH_TILED) {
             h->Xd.alloc(h->Xd_cap + read_pad(h.get()));
             h->Xr.alloc(h->Xr_cap + read_pad(h.get()));
-            h->ypart.alloc(size_t(h->G) * h->tr_split_max * h->max_site);
-            h->nypart.alloc(size_t(h->G) * h->tr_split_max * h->max_site);
+            h->ypart.alloc(size_t(h->G) * h->y_split_max * h->max_site);
+            h->nypart.alloc(size_t(h->G) * h->max_site);
         }
         HIPCK(hipMemcpyAsync(h->mps.p, init_blocks, h->mps_size * sizeof(double), hipMemcpyHostToDevice, h->stream));
         // right-canonical form of sites L..2 and the right environments
@@ -4291,27 +3771,12 @@ int sp_autotune(sp_handle* h, int reps, int* budget_out, int* rows_out, double* 
         for (int k = 1; k <= h->L; ++k) {
             SitePlan& P = h->plan[k - 1];
             const double* x = site_ptr(h, k);
-            int best_b = 0, best_rc = 0, last_rc = -1;
+            int best_b = 0, best_rc = 0;
             float best = 1e30f;
-            for (int b : candidates) {
-                if (!build_fused(h, k, b)) continue;  // a block too wide for this budget
-                if (P.h_rows == last_rc) continue;  // same plan as the previous budget
-                last_rc = P.h_rows;
-                validate_fused(h, k);
-                upload_fused(h, k);
-                HIPCK(hipStreamSynchronize(s));
-                const bool f32 = reduced(h);
-                const spk::H3Inst I = heff_inst(h, k, x, f32);
-                auto launch = [&]() {
-                    if (f32) spk::heff3_f32(s, P.h_rows, P.h_lds, P.dh_tasks.p, int(P.h_tasks.size()), I);
-                    else spk::heff3(s, P.h_rows, P.h_lds, P.dh_tasks.p, int(P.h_tasks.size()), I);
-                };
-                (void)hipGetLastError();
-                launch();  // warm-up
-                if (hipGetLastError() != hipSuccess) {  // this LDS size does not launch here
-                    HIPCK(hipStreamSynchronize(s));
-                    continue;
-                }
+            auto time_plan = [&](int budget) {
+                const int mode = heff_mode(h, k, false);
+                auto launch = [&]() { heff_partials(h, k, x, mode, h->ypart.p, h->nypart.p); };
+                launch();  // warm-up (also mixes the left environment)
                 HIPCK(hipEventRecord(e0, s));
                 for (int r = 0; r < reps; ++r) launch();
                 HIPCK(hipEventRecord(e1, s));
@@ -4321,45 +3786,23 @@ int sp_autotune(sp_handle* h, int reps, int* budget_out, int* rows_out, double* 
                 HIPCK(hipGetLastError());
                 if (ms < best) {
                     best = ms;
-                    best_b = b;
+                    best_b = budget;
                     best_rc = P.h_rows;
                 }
-            }
-            {
-                // the LDS-tiled block products are a candidate too: for wide
-                // MPOs a fused plan of one or two rows per task re-reads the
-                // right environment once per row and can lose to them
-                P.h_rows = 0;
-                P.h_lds = 0;
-                P.h_tasks.clear();
-                validate_fused(h, k);
-                upload_fused(h, k);
-                HIPCK(hipStreamSynchronize(s));
-                const bool bf3 = h->precision == SP_BF16X3;
-                heff_tiled(h, k, x, bf3);  // warm-up (also forms the pre-mixed environment)
-                HIPCK(hipEventRecord(e0, s));
-                for (int r = 0; r < reps; ++r) heff_tiled(h, k, x, bf3);
-                HIPCK(hipEventRecord(e1, s));
-                HIPCK(hipEventSynchronize(e1));
-                float ms = 0.f;
-                HIPCK(hipEventElapsedTime(&ms, e0, e1));
-                HIPCK(hipGetLastError());
-                if (ms < best) {
-                    best = ms;
-                    best_b = 0;
-                    best_rc = 0;
+            };
+            // a site's products run the same lists whatever the plan; it sets
+            // their arithmetic in the reduced precisions, so the first budget
+            // that fits stands for all and in FP64 for the block products too
+            for (int b : candidates)
+                if (build_fused(h, k, b)) {
+                    time_plan(b);
+                    break;
                 }
+            if (best_b == 0 || reduced(h)) {
+                P.h_rows = P.h_lds = 0;
+                time_plan(0);
             }
-            if (best_b > 0) {
-                build_fused(h, k, best_b);
-            } else {  // the tiled block products were fastest, or no budget fits
-                P.h_rows = 0;
-                P.h_lds = 0;
-                P.h_tasks.clear();
-            }
-            validate_fused(h, k);
-            upload_fused(h, k);
-            HIPCK(hipStreamSynchronize(s));
+            if (best_b > 0) build_fused(h, k, best_b);
             if (budget_out) budget_out[k - 1] = best_b;
             if (rows_out) rows_out[k - 1] = best_rc;
             if (usec_out) usec_out[k - 1] = 1e3 * double(best) / reps;
@@ -4389,14 +3832,7 @@ int sp_set_heff_plan(sp_handle* h, int site, int lds_budget, int* rows) {
                    "LDS budget outside 0..18432 doubles");
         SitePlan& P = h->plan[site - 1];
         HIPCK(hipStreamSynchronize(h->stream));  // the old plan may still be in use
-        if (lds_budget == 0 || !build_fused(h, site, lds_budget)) {
-            P.h_rows = 0;
-            P.h_lds = 0;
-            P.h_tasks.clear();
-        }
-        validate_fused(h, site);
-        upload_fused(h, site);
-        HIPCK(hipStreamSynchronize(h->stream));
+        if (lds_budget == 0 || !build_fused(h, site, lds_budget)) P.h_rows = P.h_lds = 0;
         if (rows) *rows = P.h_rows;
         return SP_OK;
     });
@@ -4737,9 +4173,8 @@ int sp_heff_batch_profile(sp_handle** hs, int n, const int* sites, int reps, dou
     return guarded([&]() -> int {
         SP_REQUIRE(hs && sites && out && n >= 1 && reps >= 1, "bad arguments");
         hipStream_t s = hs[0]->stream;
-        std::vector<spk::H3Inst> insts(n);
-        std::map<int, std::vector<spk::H3Task>> by_rc;
-        std::map<int, int> lds_by_rc;
+        HeffBatch hb;
+        double groups = 0.0;
         double flops = 0.0, bytes = 0.0;
         for (int i = 0; i < n; ++i) {
             sp_handle* h = hs[i];
@@ -4751,38 +4186,20 @@ int sp_heff_batch_profile(sp_handle** hs, int n, const int* sites, int reps, dou
                        "one device, stream and precision");
             SP_REQUIRE(h->Lvalid[k - 1] && h->Rvalid[k], "environments are not built");
             for (int j = 0; j < i; ++j) SP_REQUIRE(hs[j] != h, "a handle appears twice");
-            insts[i] = heff_inst(h, k, site_ptr(h, k), reduced(h));
+            hb.add(h, k, site_ptr(h, k), nullptr);
             const SitePlan& P = h->plan[k - 1];
-            for (spk::H3Task t : P.h_tasks) {
-                if (t.blk < 0) continue;
-                t.inst = i;
-                by_rc[P.h_rows].push_back(t);
-            }
-            lds_by_rc[P.h_rows] = std::max(lds_by_rc[P.h_rows], P.h_lds);
+            groups += double(P.c_heff.tiles.size()) * h->G;
             flops += P.heff_flops;
             const double G = h->G, xs = double(h->sites[k - 1].size);
             bytes += 8.0 * (G * h->env[k - 1].size + G * h->env[k].size + xs + 2.0 * G * xs);
         }
-        std::vector<spk::H3Task> all;
-        std::vector<std::pair<int, std::pair<size_t, int>>> groups;  // rc -> (first, count)
-        for (auto& kv : by_rc) {
-            groups.push_back({kv.first, {all.size(), int(kv.second.size())}});
-            all.insert(all.end(), kv.second.begin(), kv.second.end());
-        }
-        DArr<spk::H3Inst> dinst;
-        DArr<spk::H3Task> dtask;
-        dinst.upload(insts, s);
-        dtask.upload(all, s);
+        hb.finish();
+        std::vector<char> rec(hb.bytes());
+        hb.pack(rec.data());
+        DArr<char> dinst;
+        dinst.upload(rec, s);
         HIPCK(hipStreamSynchronize(s));
-        const bool f32 = reduced(hs[0]);
-        auto launch_on = [&](hipStream_t st) {
-            for (auto& gr : groups) {
-                const int rc = gr.first;
-                const spk::H3Task* tp = dtask.p + gr.second.first;
-                if (f32) spk::heff3_f32(st, rc, lds_by_rc[rc], tp, gr.second.second, insts[0], dinst.p);
-                else spk::heff3(st, rc, lds_by_rc[rc], tp, gr.second.second, insts[0], dinst.p);
-            }
-        };
+        auto launch_on = [&](hipStream_t st) { hb.launch(st, dinst.p); };
         auto launch = [&]() { launch_on(s); };
         launch();  // warm-up
         hipEvent_t e0, e1;
@@ -4798,7 +4215,7 @@ int sp_heff_batch_profile(sp_handle** hs, int n, const int* sites, int reps, dou
         out[0] = 1e3 * double(ms) / reps;
         out[1] = flops;
         out[2] = bytes;
-        out[3] = double(all.size());
+        out[3] = groups;
 
         // The same launches captured once in a HIP graph (on a private
         // stream: the handles' stream may be the null stream) and replayed.
@@ -4807,10 +4224,10 @@ int sp_heff_batch_profile(sp_handle** hs, int n, const int* sites, int reps, dou
         std::vector<std::vector<double>> ref(n), got(n);
         auto partials = [&](std::vector<std::vector<double>>& dst) {
             for (int i = 0; i < n; ++i) {
-                const size_t m = size_t(hs[i]->G) * hs[i]->sites[sites[i] - 1].size;
-                dst[i].resize(2 * m);
+                const size_t xs = hs[i]->sites[sites[i] - 1].size, m = heff_parts(hs[i], sites[i]) * xs, mn = hs[i]->G * xs;
+                dst[i].resize(m + mn);
                 HIPCK(hipMemcpy(dst[i].data(), hs[i]->ypart.p, m * sizeof(double), hipMemcpyDeviceToHost));
-                HIPCK(hipMemcpy(dst[i].data() + m, hs[i]->nypart.p, m * sizeof(double), hipMemcpyDeviceToHost));
+                HIPCK(hipMemcpy(dst[i].data() + m, hs[i]->nypart.p, mn * sizeof(double), hipMemcpyDeviceToHost));
             }
         };
         launch();
@@ -4827,9 +4244,9 @@ int sp_heff_batch_profile(sp_handle** hs, int n, const int* sites, int reps, dou
         double maxdiff = 0.0;
         for (int c = 0; c < 3; ++c) {
             for (int i = 0; i < n; ++i) {
-                const long long m = (long long)hs[i]->G * hs[i]->sites[sites[i] - 1].size;
-                spk::fill(s, hs[i]->ypart.p, m, 0.0);
-                spk::fill(s, hs[i]->nypart.p, m, 0.0);
+                const long long xs = hs[i]->sites[sites[i] - 1].size;
+                spk::fill(s, hs[i]->ypart.p, heff_parts(hs[i], sites[i]) * xs, 0.0);
+                spk::fill(s, hs[i]->nypart.p, hs[i]->G * xs, 0.0);
             }
             HIPCK(hipStreamSynchronize(s));
             HIPCK(hipGraphLaunch(exec, gs));
@@ -4865,8 +4282,7 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
         SitePlan& P = h->plan[site - 1];
         hipStream_t s = h->stream;
         const bool plain = h->path == SP_PATH_PLAIN;
-        const spk::BufSet b = plain ? bufset(h, site, x, y, ny, nullptr)
-                                    : bufset(h, site, h->Xd.p, h->ypart.p, h->nypart.p, nullptr);
+        const spk::BufSet b = bufset(h, site, x, y, ny, nullptr);
         const int n = int(h->sites[site - 1].size);
         hipEvent_t ev[4];
         for (auto& e : ev) HIPCK(hipEventCreate(&e));
@@ -4876,15 +4292,14 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
             // the pre-mixed left environment of the block products is built
             // once per local problem and reused by every product of the
             // solve: timed on its own, outside the products
+            h->lt_site = -1;
             HIPCK(hipEventRecord(ev[0], s));
-            P.premix.launch(s, b, P.coef.p);
+            premix_left(h, site, heff_mode(h, site, false));
             HIPCK(hipEventRecord(ev[1], s));
             HIPCK(hipEventSynchronize(ev[1]));
             float t = 0.f;
             HIPCK(hipEventElapsedTime(&t, ev[0], ev[1]));
             premix_ms = t;
-            h->lt_site = site;
-            h->lt_gen = h->Lgen[site - 1];
         }
         for (int r = 0; r < reps; ++r) {
             HIPCK(hipEventRecord(ev[0], s));
@@ -4899,7 +4314,7 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
             if (plain) {
                 P.yout.launch(s, b, P.coef.p);
             } else {
-                spk::gsum2(s, h->ypart.p, h->nypart.p, n, heff_parts(h, site), n, y, ny);
+                spk::gsum2(s, h->ypart.p, h->nypart.p, n, heff_parts(h, site), h->G, n, y, ny);
             }
             HIPCK(hipEventRecord(ev[3], s));
             HIPCK(hipEventSynchronize(ev[3]));
@@ -4926,7 +4341,7 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
             // once, per-g partials written
             out[1] = premix_ms;
             out[3] = P.p1.flops + P.mixl.flops + P.yout.flops;
-            out[4] = P.h_rows == 0 ? P.premix.flops : 0.0;
+            out[4] = P.h_rows == 0 ? G * P.mix_l.flops : 0.0;
             out[5] = 2.0 * G * xs;
             out[6] = 8.0 * (Lb + Rb + xs + 2.0 * G * xs);
             out[7] = 0.0;

@@ -158,17 +158,73 @@ __global__ __launch_bounds__(1024) void k_sumsq(const double* __restrict__ v, in
     if (threadIdx.x == 0) *out = s;
 }
 
-__global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const float* __restrict__ w, int H,
-                                                             const float* __restrict__ F, long long n,
-                                                             float* __restrict__ y) {
-    extern __shared__ double sw[];
-    load_weights(w, H, sw);
-    const long long i = (long long)blockIdx.x * kMlpThreads + threadIdx.x;
-    if (i >= n) return;
-    double f[kMlpIn];
+// A tile of up to kTileRows rows (features in LDS as f(row, c) at
+// row * kRow + c, rows past ns zero): the model's outputs without b2 in eight
+// parts, one per wavefront.  Wavefront v takes hidden units [v H / 8, ..), a
+// lane the rows lane + 64 i, so a weight read from LDS serves four rows (with
+// one row per thread the reads, 16 values per clock and CU, take four times
+// as long as the FMAs).
+constexpr int kTileThreads = 512, kTileRows = 256, kTileWaves = kTileThreads / 64;
+constexpr int kRow = 6, kUnit = 8;  // doubles per row (features, target) and per hidden unit (W1, b1, w2)
+
+__device__ inline void load_units(const float* __restrict__ w, int H, double* su) {
+    for (int p = threadIdx.x; p < H * (kMlpIn + 2); p += kTileThreads) {
+        const int j = p < H * kMlpIn ? p / kMlpIn : (p - H * kMlpIn) % H;
+        const int c = p < H * kMlpIn ? p % kMlpIn : kMlpIn + (p - H * kMlpIn) / H;
+        su[j * kUnit + c] = double(w[p]);
+    }
+}
+
+__device__ inline void tile_outputs(const double* __restrict__ su, int H, const double* __restrict__ sf, int ns,
+                                    double (*__restrict__ part)[kTileRows]) {
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, ng = (ns + 63) / 64;
+    const int j0 = wave * H / kTileWaves, j1 = (wave + 1) * H / kTileWaves;
+    double f[4][kMlpIn], y[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < kMlpIn; ++c) f[c] = F[i * kMlpIn + c];
-    y[i] = float(mlp_eval(sw, H, f));
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < kMlpIn; ++c) f[i][c] = sf[(lane + 64 * i) * kRow + c];
+    auto unit = [&](int j, int i) {
+        const double* u = su + j * kUnit;
+        double z = u[kMlpIn];
+#pragma unroll
+        for (int c = 0; c < kMlpIn; ++c) z = fma(u[c], f[i][c], z);
+        y[i] = fma(u[kMlpIn + 1], fmax(z, 0.0), y[i]);
+    };
+    if (ng > 2) {
+#pragma unroll 2
+        for (int j = j0; j < j1; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) unit(j, i);
+    } else {
+#pragma unroll 2
+        for (int j = j0; j < j1; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) unit(j, i);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) part[wave][lane + 64 * i] = y[i];
+}
+
+__global__ __launch_bounds__(kTileThreads) void k_mlp_forward(const float* __restrict__ w, int H,
+                                                              const float* __restrict__ F, long long n, int rows,
+                                                              float* __restrict__ y) {
+    __shared__ double su[kMlpMaxHidden * kUnit], sf[kTileRows * kRow], part[kTileWaves][kTileRows];
+    const long long q0 = (long long)blockIdx.x * rows;
+    const int ns = int(min((long long)rows, n - q0));
+    load_units(w, H, su);
+    for (int e = threadIdx.x; e < kTileRows * kMlpIn; e += kTileThreads)
+        sf[e / kMlpIn * kRow + e % kMlpIn] = e < ns * kMlpIn ? double(F[q0 * kMlpIn + e]) : 0.0;
+    __syncthreads();
+    tile_outputs(su, H, sf, ns, part);
+    __syncthreads();
+    const int r = threadIdx.x;
+    if (r < ns) {
+        double v = double(w[H * (kMlpIn + 2)]);
+#pragma unroll
+        for (int q = 0; q < kTileWaves; ++q) v += part[q][r];
+        y[q0 + r] = float(v);
+    }
 }
 
 // one work-group per recorded iteration j: Y_j = sign(r_j) e_j / rms(e_j),
@@ -252,116 +308,138 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_targets_grouped(const doubl
     }
 }
 
-// gradient partials of 0.5 * sum (y - Y)^2 over rows row0 + q*stride,
-// q in this work-group's share of [0, count): thread j owns hidden unit j;
-// four rows per reduction round
-__global__ __launch_bounds__(kMlpThreads) void k_mlp_grad(const float* __restrict__ w, int H,
-                                                          const float* __restrict__ F, const float* __restrict__ Y,
-                                                          long long row0, long long stride, long long count,
-                                                          double* __restrict__ gpart) {
-    __shared__ double sf[4][kMlpIn + 1];
-    __shared__ double sred[4][kMlpThreads / 64];
-    __shared__ double sy[4];
-    const int j = threadIdx.x;
-    const bool own = j < H;
-    double W1[kMlpIn] = {}, b1 = 0.0, w2 = 0.0;
-    if (own) {
-#pragma unroll
-        for (int c = 0; c < kMlpIn; ++c) W1[c] = w[j * kMlpIn + c];
-        b1 = w[H * kMlpIn + j];
-        w2 = w[H * kMlpIn + H + j];
-    }
+// gradient partials of 0.5 * sum (y - Y)^2 over rows row0 + q * stride, q in
+// this work-group's share of [0, count), a tile of kTileRows at a time: the
+// outputs as above, then thread (column, split) owns hidden units column and
+// column + ncol for every nsplit-th row, so that a row read from LDS serves
+// two units; the splits' sums are added in order at the end.  FP64 FMAs bound
+// it (7 us for 60001 rows of 256 units); four rows per work-group-wide
+// reduction took 585 us, this form 27.
+__global__ __launch_bounds__(kTileThreads) void k_mlp_grad(const float* __restrict__ w, int H,
+                                                           const float* __restrict__ F, const float* __restrict__ Y,
+                                                           long long row0, long long stride, long long count,
+                                                           double* __restrict__ gpart) {
+    constexpr int NG = kMlpIn + 2;  // gradients per unit: W1, b1, w2
+    __shared__ double su[kMlpMaxHidden * kUnit], sf[kTileRows * kRow], red[kTileThreads / 64];
+    __shared__ double sums[NG][2 * kTileThreads];
+    double(*part)[kTileRows] = reinterpret_cast<double(*)[kTileRows]>(&sums[0][0]);
+    static_assert(kTileWaves * kTileRows <= NG * 2 * kTileThreads, "outputs fit the sums' LDS");
+    load_units(w, H, su);
     const double b2 = w[H * (kMlpIn + 2)];
-    double gW1[kMlpIn] = {}, gb1 = 0.0, gw2 = 0.0, gb2 = 0.0, loss = 0.0;
+    const int ncol = 64 * ((H + 127) / 128), nsplit = kTileThreads / ncol;
+    const int col = threadIdx.x % ncol, split = threadIdx.x / ncol;
+    __syncthreads();
+    double W[2][NG], g[2][NG];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int c = 0; c < NG; ++c) {
+            const int j = col + u * ncol;
+            W[u][c] = j < H ? su[j * kUnit + c] : 0.0;
+            g[u][c] = 0.0;
+        }
+    double gb2 = 0.0, loss = 0.0;
     const long long per = (count + gridDim.x - 1) / gridDim.x;
     const long long q0 = (long long)blockIdx.x * per, q1 = min(count, q0 + per);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (long long q = q0; q < q1; q += 4) {
-        const int ns = int(min(4LL, q1 - q));
-        __syncthreads();
-        if (threadIdx.x < 4 * (kMlpIn + 1)) {
-            const int s = threadIdx.x / (kMlpIn + 1), c = threadIdx.x % (kMlpIn + 1);
-            double v = 0.0;
-            if (s < ns) {
-                const long long row = row0 + (q + s) * stride;
-                v = (c < kMlpIn) ? double(F[row * kMlpIn + c]) : double(Y[row]);
-            }
-            sf[s][c] = v;
+    for (long long q = q0; q < q1; q += kTileRows) {
+        const int ns = int(min((long long)kTileRows, q1 - q));
+        for (int e = threadIdx.x; e < kTileRows * kRow; e += kTileThreads) {
+            const int r = e / kRow, c = e % kRow;
+            const long long row = row0 + (q + r) * stride;
+            sf[e] = r < ns ? double(c < kMlpIn ? F[row * kMlpIn + c] : Y[row]) : 0.0;
         }
         __syncthreads();
-        double z[4], h[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            double zz = b1;
-#pragma unroll
-            for (int c = 0; c < kMlpIn; ++c) zz = fma(W1[c], sf[s][c], zz);
-            z[s] = zz;
-            h[s] = own ? fmax(zz, 0.0) : 0.0;
-            const double p = wsum(w2 * h[s]);
-            if (lane == 0) sred[s][wave] = p;
-        }
+        tile_outputs(su, H, sf, ns, part);
         __syncthreads();
-        if (threadIdx.x < 4) {
+        if (threadIdx.x < unsigned(ns)) {
             double y = b2;
-            for (int v = 0; v < kMlpThreads / 64; ++v) y += sred[threadIdx.x][v];
-            sy[threadIdx.x] = y;
+#pragma unroll
+            for (int v = 0; v < kTileWaves; ++v) y += part[v][threadIdx.x];
+            const double dy = y - sf[threadIdx.x * kRow + kMlpIn];
+            sf[threadIdx.x * kRow + kMlpIn] = dy;
+            gb2 += dy;
+            loss = fma(dy, dy, loss);
         }
         __syncthreads();
-        for (int s = 0; s < ns; ++s) {
-            const double dy = sy[s] - sf[s][kMlpIn];
-            if (own) {
-                gw2 = fma(dy, h[s], gw2);
-                if (z[s] > 0.0) {
-                    const double dz = dy * w2;
-                    gb1 += dz;
+        for (int r = split; r < ns; r += nsplit) {
+            double f[kRow];
 #pragma unroll
-                    for (int c = 0; c < kMlpIn; ++c) gW1[c] = fma(dz, sf[s][c], gW1[c]);
+            for (int c = 0; c < kRow; ++c) f[c] = sf[r * kRow + c];
+            const double dy = f[kMlpIn];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                double z = W[u][kMlpIn];
+#pragma unroll
+                for (int c = 0; c < kMlpIn; ++c) z = fma(W[u][c], f[c], z);
+                g[u][kMlpIn + 1] = fma(dy, fmax(z, 0.0), g[u][kMlpIn + 1]);
+                if (z > 0.0) {
+                    const double dz = dy * W[u][kMlpIn + 1];
+                    g[u][kMlpIn] += dz;
+#pragma unroll
+                    for (int c = 0; c < kMlpIn; ++c) g[u][c] = fma(dz, f[c], g[u][c]);
                 }
             }
-            if (threadIdx.x == 0) {
-                gb2 += dy;
-                loss = fma(dy, dy, loss);
-            }
         }
+        __syncthreads();
     }
-    const long long P = mlp_size(H) + 1;
-    double* g = gpart + (long long)blockIdx.x * P;
-    if (own) {
 #pragma unroll
-        for (int c = 0; c < kMlpIn; ++c) g[j * kMlpIn + c] = gW1[c];
-        g[H * kMlpIn + j] = gb1;
-        g[H * kMlpIn + H + j] = gw2;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int c = 0; c < NG; ++c) sums[c][u * kTileThreads + threadIdx.x] = g[u][c];
+    gb2 = group_sum(gb2, red);
+    loss = group_sum(loss, red);
+    const long long P = mlp_size(H) + 1;
+    double* out = gpart + (long long)blockIdx.x * P;
+    for (int p = threadIdx.x; p < H * NG; p += kTileThreads) {
+        const int j = p < H * kMlpIn ? p / kMlpIn : (p - H * kMlpIn) % H;
+        const int c = p < H * kMlpIn ? p % kMlpIn : kMlpIn + (p - H * kMlpIn) / H;
+        const double* v = &sums[c][j < ncol ? j : kTileThreads + j - ncol];
+        double t = 0.0;
+        for (int q = 0; q < nsplit; ++q) t += v[q * ncol];
+        out[p] = t;
     }
     if (threadIdx.x == 0) {
-        g[H * (kMlpIn + 2)] = gb2;
-        g[P - 1] = loss;
+        out[H * NG] = gb2;
+        out[P - 1] = loss;
     }
 }
 
-// Adam step: gradient = scale * (sum of the partials in work-group order)
+// Adam step: gradient = scale * (sum of the partials, 16 interleaved runs of
+// work-groups added in order).  A work-group takes 16 neighbouring parameters,
+// so that the partials are read as whole lines by many CUs (one work-group for
+// all of them took 109 us for 1793 parameters, this 6).
+constexpr int kAdamPar = 16, kAdamRun = kMlpThreads / kAdamPar;
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_adam(float* __restrict__ w, double* __restrict__ m,
                                                           double* __restrict__ v, int H,
                                                           const double* __restrict__ gpart, int nparts,
                                                           double scale, double lr, int step,
                                                           double* __restrict__ loss_out) {
+    __shared__ double run[kAdamRun][kAdamPar];
     const long long P = mlp_size(H) + 1;
+    const int i = threadIdx.x % kAdamPar, r = threadIdx.x / kAdamPar;
+    const long long p = (long long)blockIdx.x * kAdamPar + i;
+    double g = 0.0;
+    if (p < P)
+#pragma unroll 8
+        for (int b = r; b < nparts; b += kAdamRun) g += gpart[b * P + p];
+    run[r][i] = g;
+    __syncthreads();
+    if (r > 0 || p >= P) return;
+    g = 0.0;
+#pragma unroll
+    for (int q = 0; q < kAdamRun; ++q) g += run[q][i];
+    if (p == P - 1) {
+        if (loss_out) *loss_out = 0.5 * g * scale;
+        return;
+    }
     const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
     const double c1 = 1.0 - pow(b1, step), c2 = 1.0 - pow(b2, step);
-    for (long long p = threadIdx.x; p < P - 1; p += kMlpThreads) {
-        double g = 0.0;
-        for (int b = 0; b < nparts; ++b) g += gpart[b * P + p];
-        g *= scale;
-        const double mm = b1 * m[p] + (1.0 - b1) * g;
-        const double vv = b2 * v[p] + (1.0 - b2) * g * g;
-        m[p] = mm;
-        v[p] = vv;
-        w[p] = float(double(w[p]) - lr * (mm / c1) / (sqrt(vv / c2) + eps));
-    }
-    if (threadIdx.x == 0 && loss_out) {
-        double l = 0.0;
-        for (int b = 0; b < nparts; ++b) l += gpart[b * P + P - 1];
-        *loss_out = 0.5 * l * scale;
-    }
+    g *= scale;
+    const double mm = b1 * m[p] + (1.0 - b1) * g;
+    const double vv = b2 * v[p] + (1.0 - b2) * g * g;
+    m[p] = mm;
+    v[p] = vv;
+    w[p] = float(double(w[p]) - lr * (mm / c1) / (sqrt(vv / c2) + eps));
 }
 
 inline int blocks_for(long long n) { return int((n + kMlpThreads - 1) / kMlpThreads); }
@@ -399,8 +477,9 @@ void sumsq(hipStream_t s, const double* v, int n, double* out) {
 
 void mlp_forward(hipStream_t s, const float* w, int H, const float* F, long long n, float* y) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_mlp_forward, dim3(blocks_for(n)), dim3(kMlpThreads), size_t(mlp_size(H)) * sizeof(double), s,
-                       w, H, F, n, y);
+    // few rows: smaller tiles, more work-groups
+    const int rows = n > 64LL * 256 ? kTileRows : 64;
+    hipLaunchKernelGGL(k_mlp_forward, dim3(int((n + rows - 1) / rows)), dim3(kTileThreads), 0, s, w, H, F, n, rows, y);
 }
 
 void mlp_targets(hipStream_t s, const double* X, long long ldx, int nrec, const double* xstar, int n, float* Y) {
@@ -417,12 +496,13 @@ void mlp_targets_grouped(hipStream_t s, const double* X, long long ldx, int nrec
 
 void mlp_grad(hipStream_t s, const float* w, int H, const float* F, const float* Y, long long row0, long long stride,
               long long count, double* gpart, int nparts) {
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nparts), dim3(kMlpThreads), 0, s, w, H, F, Y, row0, stride, count, gpart);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(nparts), dim3(kTileThreads), 0, s, w, H, F, Y, row0, stride, count, gpart);
 }
 
 void mlp_adam(hipStream_t s, float* w, double* m, double* v, int H, const double* gpart, int nparts, double scale,
               double lr, int step, double* loss_out) {
-    hipLaunchKernelGGL(k_mlp_adam, dim3(1), dim3(kMlpThreads), 0, s, w, m, v, H, gpart, nparts, scale, lr, step,
+    const int groups = int((mlp_size(H) + 1 + kAdamPar - 1) / kAdamPar);
+    hipLaunchKernelGGL(k_mlp_adam, dim3(groups), dim3(kMlpThreads), 0, s, w, m, v, H, gpart, nparts, scale, lr, step,
                        loss_out);
 }
 

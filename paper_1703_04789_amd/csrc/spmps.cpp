@@ -4037,7 +4037,7 @@ int sp_mlp_train_step(sp_mlp* m, const float* F, const float* Y, long long n, do
     return guarded([&]() -> int {
         SP_REQUIRE(m && F && Y && n >= 1 && lr > 0.0, "bad arguments");
         hipStream_t s = static_cast<hipStream_t>(stream);
-        const int parts = int(std::min<long long>(m->nparts, std::max<long long>(1, n / 1024)));
+        const int parts = int(std::min<long long>(m->nparts, (n + 63) / 64));
         spk::mlp_grad(s, m->w.p, m->hidden, F, Y, 0, 1, n, m->gpart.p, parts);
         m->step++;
         spk::mlp_adam(s, m->w.p, m->m.p, m->v.p, m->hidden, m->gpart.p, parts, 1.0 / double(n), lr, m->step,
@@ -4061,7 +4061,7 @@ int sp_mlp_train(sp_mlp* m, int epochs, long long batch, double lr, double* loss
             // batch b: rows b, b + nb, b + 2 nb, ... (interleaves the solves)
             for (long long b = 0; b < nb; ++b) {
                 const long long count = (rows - b + nb - 1) / nb;
-                const int parts = int(std::min<long long>(m->nparts, std::max<long long>(1, count / 1024)));
+                const int parts = int(std::min<long long>(m->nparts, (count + 63) / 64));
                 spk::mlp_grad(s, m->w.p, m->hidden, m->F.p, m->Y.p, b, nb, count, m->gpart.p, parts);
                 m->step++;
                 spk::mlp_adam(s, m->w.p, m->m.p, m->v.p, m->hidden, m->gpart.p, parts, 1.0 / double(count), lr,

@@ -10,7 +10,9 @@ torch = pytest.importorskip("torch")
 
 from gpu_util import make_pair, rel_err  # noqa: E402
 
+import paper_1703_04789_amd as sp  # noqa: E402
 import workloads as W  # noqa: E402
+from oracle import precond as pre  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -133,3 +135,31 @@ def test_premixed_environments_of_several_lds_tiles():
         for h in (a, b):
             if k < K:
                 h.env_update(k, +1)
+
+
+@pytest.mark.parametrize("hidden", [1, 64, 65, 128, 129, 256])
+@pytest.mark.parametrize("rows", [1, 63, 65, 257, 16385])
+def test_model_training_at_tile_edges(hidden, rows):
+    # two Adam steps and a forward pass; tolerances as for the other training
+    # tests (loss 1e-9 relative, FP32 weights 2e-7, FP32 outputs 1e-6)
+    p = W.mlp_init(hidden, 11)
+    m = sp.MLP(p)
+    rng = np.random.default_rng(12)
+    F = rng.standard_normal((rows, 5)).astype(np.float32)
+    Y = rng.standard_normal(rows).astype(np.float32)
+    Fd, Yd = torch.tensor(F, device="cuda"), torch.tensor(Y, device="cuda")
+    ref = {k: np.asarray(np.asarray(v, np.float32), np.float64) if np.ndim(v) else float(np.float32(v)) for k, v in p.items()}
+    state = {}
+    for _ in range(2):
+        loss = m.train_step(Fd, Yd, 1e-3)
+        lref, g = pre.loss_and_grads(ref, F.astype(np.float64), Y.astype(np.float64))
+        assert abs(loss - lref) < 1e-9 * lref
+        ref = pre.adam_step(ref, g, state, 1e-3)
+        ref = {k: np.asarray(np.asarray(v, np.float32), np.float64) if np.ndim(v) else float(np.float32(v))
+               for k, v in ref.items()}
+        got = m.params()
+        for k in ("W1", "b1", "w2", "b2"):
+            assert np.abs(np.asarray(got[k], np.float64) - ref[k]).max() < 2e-7, k
+    y = m.forward(Fd).cpu().numpy()
+    want = pre.forward({k: np.asarray(v, np.float64) for k, v in got.items()}, F.astype(np.float64))
+    assert np.abs(y - want).max() < 1e-6 * np.abs(want).max()

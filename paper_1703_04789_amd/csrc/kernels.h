@@ -208,12 +208,25 @@ void diag_mix(hipStream_t s, const DiagMix* mix, int nmix, const DiagMixTerm* te
 void diag_blocks(hipStream_t s, const DiagBlk* blks, int nblk, const int* zlist, const double* M, int nmix, int Dl,
                  const double* Rd, int nzr, int Dr, int G, double* dh, double* dn, int nsplit, double* part,
                  long long ntot);
-// Per-sector positive-diagonal QR.  Tasks whose two rows x cols matrices
-// fit kQrLdsMax doubles run in LDS (lds_doubles = the largest 2 rows cols
-// of the list); otherwise they use the scratch buffer in global memory.
-constexpr int kQrLdsMax = 12288;
+// Per-sector positive-diagonal QR.  A list whose sectors fit kQrRegRows x
+// kQrRegCols (every configuration up to D = 512) keeps its columns in
+// registers; one whose two rows x cols matrices fit kQrLdsMax doubles runs in
+// LDS; others use the scratch buffer in global memory.
+constexpr int kQrLdsMax = 12288, kQrRegCols = 64, kQrRegRows = 256;
+// the largest rows, cols, rows (rounded up to 16) * cols and 2 rows cols of a
+// list's tasks
+struct QrShape {
+    int rows = 0, cols = 0, area = 0, lds = 0;
+    void add(int r, int c) {
+        auto up = [](int& a, long long b) { a = int(b > a ? (b < INT32_MAX ? b : INT32_MAX) : a); };
+        up(rows, r);
+        up(cols, c);
+        up(area, (r + 15) / 16 * 16LL * c);
+        up(lds, 2LL * r * c);
+    }
+};
 void qr_sectors(hipStream_t s, const QrTask* tasks, int ntasks, const QrPiece* pieces, double* site,
-                double* scratch, double* rout, int lds_doubles);
+                double* scratch, double* rout, const QrShape& shape);
 
 // Davidson vector kernels (n = vector length, ld = stride between vectors)
 void normalize(hipStream_t s, const double* in, double* out, int n, double* norm_out);

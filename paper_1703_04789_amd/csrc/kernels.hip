@@ -9,6 +9,8 @@
 // floating-point atomics), so repeated calls give bitwise-identical results.
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace spk {
 
 namespace {
@@ -448,6 +450,132 @@ __global__ __launch_bounds__(kThreads) void k_qr_lds(const QrTask* __restrict__ 
             if (diag_s[cc] < 0.0) v = -v;
             if (pc.transposed) site[pc.off + (long long)cc * pc.pcol + rr] = v;
             else site[pc.off + (long long)rr * pc.pcol + cc] = v;
+        }
+    }
+}
+
+// Sum over rows q + 16 i of a column in 16 lanes (acc[i % 4] adds them for
+// ascending i / 4), the same bits in every lane: the order of wave_sum64 over
+// rows dealt to 64 lanes, whichever row the lanes start at.
+__device__ inline double column_sum(const double (&acc)[4]) {
+    auto ror = [](double x, auto n) {
+        constexpr int ctrl = 0x120 + decltype(n)::value;  // row_ror
+        const long long b = __builtin_bit_cast(long long, x);
+        const int lo = __builtin_amdgcn_mov_dpp(int(b), ctrl, 0xf, 0xf, false);
+        const int hi = __builtin_amdgcn_mov_dpp(int(b >> 32), ctrl, 0xf, 0xf, false);
+        return __builtin_bit_cast(double, (long long)((unsigned long long)(unsigned)lo | (unsigned long long)(unsigned)hi << 32));
+    };
+    double v = (acc[0] + acc[2]) + (acc[1] + acc[3]);
+    v += ror(v, std::integral_constant<int, 8>{});
+    v += ror(v, std::integral_constant<int, 4>{});
+    v += ror(v, std::integral_constant<int, 2>{});
+    v += ror(v, std::integral_constant<int, 1>{});
+    return v;
+}
+
+// The same factorisation with a column per 16 lanes, its rows lane + 16 i
+// in registers; only the Householder vectors are in LDS (zero above their
+// diagonal and past the last row).  Latency bounds it: a chain of one LDS
+// read, dot product, update, norm, square root and division per column, one
+// barrier each -- the lanes of column j + 1 form their vector as soon as
+// vector j is applied to it -- and no barrier at all in the Q pass.  Sums run
+// in the order of k_qr_lds: the two give the same bits (near-dependent columns
+// amplify any rounding).  With S
+// and Q in LDS and a wavefront per column a gauge move at L = 32, D = 256 took
+// 102 us on average, this 23; at D = 512 (S and Q in memory, a thread per
+// column) 2.8 ms, this 71 us.
+template <int RV>
+__global__ __launch_bounds__(16 * kQrRegCols) void k_qr_reg(const QrTask* __restrict__ tasks,
+                                                           const QrPiece* __restrict__ pieces,
+                                                           double* __restrict__ site, double* __restrict__ rout) {
+    extern __shared__ double sh[];  // Householder vectors, 16 nv values each
+    __shared__ double tau_s[kQrRegCols], diag_s[kQrRegCols];
+    const QrTask tk = tasks[blockIdx.x];
+    const int rows = tk.rows, cols = tk.cols, nv = (rows + 15) / 16, ldv = 16 * nv;
+    const int q = threadIdx.x % 16, c = threadIdx.x / 16;
+    const int cw = __builtin_amdgcn_readfirstlane(c);  // first column of the wavefront
+    double s[RV], v[RV];
+#pragma unroll
+    for (int i = 0; i < RV; ++i) s[i] = 0.0;
+    if (c < cols)
+        for (int p = tk.p0; p < tk.p1; ++p) {
+            const QrPiece pc = pieces[p];
+            const int nr = pc.transposed ? pc.pcol : pc.prow;
+#pragma unroll
+            for (int i = 0; i < RV; ++i) {
+                const int rr = q + 16 * i - pc.row0;
+                if (rr >= 0 && rr < nr)
+                    s[i] = site[pc.off + (pc.transposed ? (long long)c * pc.pcol + rr : (long long)rr * pc.pcol + c)];
+            }
+        }
+    // the Householder vector of column j = c from its rows >= j
+    auto reflect = [&](int j) {
+        double sq[4] = {}, top[4] = {};
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            const int r = q + 16 * i;
+            if (r >= j) sq[i % 4] = fma(s[i], s[i], sq[i % 4]);
+            if (r == j) top[0] = s[i];
+        }
+        const double ss = column_sum(sq), x0 = column_sum(top);
+        const double nrm = sqrt(ss);
+        const double alpha = (x0 >= 0.0) ? -nrm : nrm;
+        const double v0 = x0 - alpha;
+        const double vv = ss - x0 * x0 + v0 * v0;
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            const int r = q + 16 * i;
+            if (i < nv) sh[j * ldv + r] = r > j ? s[i] : (r == j ? v0 : 0.0);
+        }
+        if (q == 0) {
+            tau_s[j] = (vv > 0.0) ? 2.0 / vv : 0.0;
+            diag_s[j] = alpha;
+        }
+    };
+    // s -= tau (v_j . s) v_j
+    auto apply = [&](int j) {
+        const double tau = tau_s[j];
+        double d[4] = {};
+#pragma unroll
+        for (int i = 0; i < RV; ++i) v[i] = i < nv ? sh[j * ldv + q + 16 * i] : 0.0;
+#pragma unroll
+        for (int i = 0; i < RV; ++i) d[i % 4] = fma(v[i], s[i], d[i % 4]);
+        const double f = tau * column_sum(d);
+#pragma unroll
+        for (int i = 0; i < RV; ++i) s[i] = fma(-f, v[i], s[i]);
+    };
+    if (c == 0) reflect(0);
+    __syncthreads();
+    for (int j = 0; j + 1 < cols; ++j) {
+        if (cw + 3 > j) {
+            if (c > j && c < cols) apply(j);
+            if (c == j + 1) reflect(j + 1);
+        }
+        __syncthreads();
+    }
+    if (c >= cols) return;
+    double* R = rout + tk.r_off;
+#pragma unroll
+    for (int i = 0; i < RV; ++i) {
+        const int r = q + 16 * i;
+        if (r < cols) {
+            const double dg = diag_s[r], x = r < c ? s[i] : (r == c ? dg : 0.0);
+            R[r * cols + c] = dg < 0.0 ? -x : x;
+        }
+    }
+    // column c of H_0 .. H_{cols-1} [I; 0]; vectors j > c leave it alone
+#pragma unroll
+    for (int i = 0; i < RV; ++i) s[i] = q + 16 * i == c ? 1.0 : 0.0;
+    for (int j = min(cw + 3, cols - 1); j >= 0; --j) apply(j);
+    const double sign = diag_s[c] < 0.0 ? -1.0 : 1.0;
+    for (int p = tk.p0; p < tk.p1; ++p) {
+        const QrPiece pc = pieces[p];
+        const int nr = pc.transposed ? pc.pcol : pc.prow;
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            const int rr = q + 16 * i - pc.row0;
+            if (rr >= 0 && rr < nr)
+                site[pc.off + (pc.transposed ? (long long)c * pc.pcol + rr : (long long)rr * pc.pcol + c)] = sign * s[i];
         }
     }
 }
@@ -1006,13 +1134,23 @@ void diag_blocks(hipStream_t s, const DiagBlk* blks, int nb, const int* zlist, c
                            nsplit, ntot, dh);
 }
 void qr_sectors(hipStream_t s, const QrTask* tasks, int ntasks, const QrPiece* pieces, double* site,
-                double* scratch, double* rout, int lds_doubles) {
+                double* scratch, double* rout, const QrShape& shape) {
     if (ntasks <= 0) return;
-    if (lds_doubles > 0 && lds_doubles <= kQrLdsMax)
-        hipLaunchKernelGGL(k_qr_lds, dim3(ntasks), dim3(kThreads), size_t(lds_doubles) * sizeof(double), s, tasks,
+    if (shape.cols <= kQrRegCols && shape.rows <= kQrRegRows) {
+        const dim3 wg(64 * ((shape.cols + 3) / 4));
+        const size_t lds = size_t(shape.area) * sizeof(double);
+        if (shape.rows <= 64)
+            hipLaunchKernelGGL(k_qr_reg<4>, dim3(ntasks), wg, lds, s, tasks, pieces, site, rout);
+        else if (shape.rows <= 128)
+            hipLaunchKernelGGL(k_qr_reg<8>, dim3(ntasks), wg, lds, s, tasks, pieces, site, rout);
+        else
+            hipLaunchKernelGGL(k_qr_reg<16>, dim3(ntasks), wg, lds, s, tasks, pieces, site, rout);
+    } else if (shape.lds <= kQrLdsMax) {
+        hipLaunchKernelGGL(k_qr_lds, dim3(ntasks), dim3(kThreads), size_t(shape.lds) * sizeof(double), s, tasks,
                            pieces, site, rout);
-    else
+    } else {
         hipLaunchKernelGGL(k_qr, dim3(ntasks), dim3(kThreads), 0, s, tasks, pieces, site, scratch, rout);
+    }
 }
 void fill(hipStream_t s, double* p, long long n, double value) {
     if (n <= 0) return;

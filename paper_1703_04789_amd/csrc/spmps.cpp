@@ -469,7 +469,7 @@ struct SitePlan {
     DArr<spk::QrTask> dqr_tasks, dlq_tasks;
     DArr<spk::QrPiece> dqr_pieces, dlq_pieces;
     long long qr_scratch = 0, lq_scratch = 0, qr_rsize = 0, lq_rsize = 0;
-    int qr_lds = 0, lq_lds = 0;  // largest 2 * rows * cols of a task (doubles)
+    spk::QrShape qr_shape, lq_shape;
     std::vector<long long> qr_roff;  // per right sector of bond k
     std::vector<long long> lq_roff;  // per left sector of bond k-1
     BList absorb_right;  // R of site k into site k+1
@@ -1227,7 +1227,7 @@ void build_plan(sp_handle* h, int k) {
         P.qr_roff[sb] = ro;
         sc += 2LL * rows * t.cols;
         ro += (long long)t.cols * t.cols;
-        P.qr_lds = int(std::min<long long>(INT32_MAX, std::max<long long>(P.qr_lds, 2LL * rows * t.cols)));
+        P.qr_shape.add(t.rows, t.cols);
         P.qr_tasks.push_back(t);
     }
     P.qr_scratch = sc;
@@ -1255,7 +1255,7 @@ void build_plan(sp_handle* h, int k) {
         P.lq_roff[sa] = ro;
         sc += 2LL * rows * t.cols;
         ro += (long long)t.cols * t.cols;
-        P.lq_lds = int(std::min<long long>(INT32_MAX, std::max<long long>(P.lq_lds, 2LL * rows * t.cols)));
+        P.lq_shape.add(t.rows, t.cols);
         P.lq_tasks.push_back(t);
     }
     P.lq_scratch = sc;
@@ -2245,7 +2245,7 @@ void diag(sp_handle* h, int k, double* dh, double* dn) {
 void move_right(sp_handle* h, int k) {
     SitePlan& P = h->plan[k - 1];
     spk::qr_sectors(h->stream, P.dqr_tasks.p, int(P.qr_tasks.size()), P.dqr_pieces.p, site_ptr(h, k),
-                    h->qr_scratch.p, h->qr_r.p, P.qr_lds);
+                    h->qr_scratch.p, h->qr_r.p, P.qr_shape);
     if (k < h->L) {
         spk::BufSet b{};
         b.p[B_V] = h->qr_r.p;
@@ -2261,7 +2261,7 @@ void move_right(sp_handle* h, int k) {
 void move_left(sp_handle* h, int k) {
     SitePlan& P = h->plan[k - 1];
     spk::qr_sectors(h->stream, P.dlq_tasks.p, int(P.lq_tasks.size()), P.dlq_pieces.p, site_ptr(h, k),
-                    h->qr_scratch.p, h->qr_r.p, P.lq_lds);
+                    h->qr_scratch.p, h->qr_r.p, P.lq_shape);
     if (k > 1) {
         spk::BufSet b{};
         b.p[B_V] = h->qr_r.p;

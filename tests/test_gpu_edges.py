@@ -163,3 +163,17 @@ def test_model_training_at_tile_edges(hidden, rows):
     y = m.forward(Fd).cpu().numpy()
     want = pre.forward({k: np.asarray(v, np.float64) for k, v in got.items()}, F.astype(np.float64))
     assert np.abs(y - want).max() < 1e-6 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("K,D", [(8, 16), (8, 64), (10, 200), (16, 256), (16, 480), (16, 700)])
+def test_gauge_moves_at_register_tile_edges(K, D):
+    # sectors of 1 to more than 64 columns and 1 to more than 256 rows (odd
+    # remainders of 16 on the way): the right-canonical form of random tensors.
+    # Single tensors are conditioned like their QR; their orthonormality and
+    # the centre, which collects every R, are not
+    tab, gpu, orc = _pair(K, D, 2)
+    for k in range(2, K + 1):
+        a = orc.mps.dense_site(k, gpu.get_site(k))  # (sigma, left, right)
+        m = np.tensordot(a, a, axes=([0, 2], [0, 2]))
+        assert np.abs(m - np.eye(len(m))).max() < 1e-11, k
+    assert rel_err(gpu.get_site(1), orc.mps.site_packed(1)) < 1e-11

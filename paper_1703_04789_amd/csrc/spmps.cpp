@@ -34,6 +34,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <exception>
 #include <functional>
 #include <map>
 #include <numeric>
@@ -117,6 +118,30 @@ struct DRef {  // view of device memory owned elsewhere
     T* p = nullptr;
 };
 
+// Many small host arrays as one device block and one copy: the lists of a
+// state's sites are about forty arrays each, and an allocation, a copy and a
+// free apiece cost 9 us (10.7 of the 31 ms of an expectation value at L = 32).
+struct Upload {
+    std::vector<char> host;
+    std::vector<std::pair<void**, size_t>> views;
+    template <class T>
+    void add(DRef<T>& d, const std::vector<T>& v) {
+        d.p = nullptr;
+        if (v.empty()) return;
+        const size_t off = (host.size() + 255) / 256 * 256;
+        host.resize(off + v.size() * sizeof(T));
+        std::memcpy(host.data() + off, v.data(), v.size() * sizeof(T));
+        views.push_back({reinterpret_cast<void**>(&d.p), off});
+    }
+    void finish(DArr<char>& mem, hipStream_t s) {
+        mem.alloc(host.size());
+        if (host.empty()) return;
+        HIPCK(hipMemcpyAsync(mem.p, host.data(), host.size(), hipMemcpyHostToDevice, s));
+        for (const auto& v : views) *v.first = mem.p + v.second;
+        HIPCK(hipStreamSynchronize(s));
+    }
+};
+
 struct Sector {
     int n, m2, dim, off, nb, ro;
 };
@@ -178,8 +203,8 @@ struct EnvLayout {
 struct BList {
     std::vector<spk::BTask> tasks;
     std::vector<spk::BTerm> terms;
-    DArr<spk::BTask> dtasks;
-    DArr<spk::BTerm> dterms;
+    DRef<spk::BTask> dtasks;
+    DRef<spk::BTerm> dterms;
     double flops = 0.0;
     void add_task(int c_buf, long long c_off, int M, int N, int ldc, int accumulate = 0) {
         spk::BTask t{};
@@ -209,9 +234,9 @@ struct BList {
         tasks.back().t1 = int(terms.size());
         flops += 2.0 * tasks.back().M * tasks.back().N * K;
     }
-    void upload(hipStream_t s) {
-        dtasks.upload(tasks, s);
-        dterms.upload(terms, s);
+    void upload(Upload& u) {
+        u.add(dtasks, tasks);
+        u.add(dterms, terms);
     }
     void launch(hipStream_t s, const spk::BufSet& b, const double* coef) const {
         spk::bgemm(s, dtasks.p, int(tasks.size()), dterms.p, b, coef);
@@ -220,8 +245,8 @@ struct BList {
 struct CList {
     std::vector<spk::CTask> tasks;
     std::vector<spk::CTerm> terms;
-    DArr<spk::CTask> dtasks;
-    DArr<spk::CTerm> dterms;
+    DRef<spk::CTask> dtasks;
+    DRef<spk::CTerm> dterms;
     double flops = 0.0;
     void add_task(int c_buf, long long c_off, int n) {
         spk::CTask t{};
@@ -240,9 +265,9 @@ struct CList {
         tasks.back().t1 = int(terms.size());
         flops += 2.0 * tasks.back().n;
     }
-    void upload(hipStream_t s) {
-        dtasks.upload(tasks, s);
-        dterms.upload(terms, s);
+    void upload(Upload& u) {
+        u.add(dtasks, tasks);
+        u.add(dterms, terms);
     }
     void launch(hipStream_t s, const spk::BufSet& b, const double* coef) const {
         spk::combine(s, dtasks.p, int(tasks.size()), dterms.p, b, coef);
@@ -255,9 +280,9 @@ struct ChainList {
     std::vector<spk::KTile> tiles;
     std::vector<spk::KStep> steps;
     std::vector<spk::KSeg> segs;
-    DArr<spk::KTile> dtiles;
-    DArr<spk::KStep> dsteps;
-    DArr<spk::KSeg> dsegs;
+    DRef<spk::KTile> dtiles;
+    DRef<spk::KStep> dsteps;
+    DRef<spk::KSeg> dsegs;
     // the steps of the tile being built: of the sum, and of N_eff x
     std::vector<spk::KStep> own, metric;
     void begin_step(long long p_off, int ldp, int kc0, int kc1, bool of_metric = false) {
@@ -310,10 +335,10 @@ struct ChainList {
         metric.clear();
         tiles.push_back(t);
     }
-    void upload(hipStream_t s) {
-        dtiles.upload(tiles, s);
-        dsteps.upload(steps, s);
-        dsegs.upload(segs, s);
+    void upload(Upload& u) {
+        u.add(dtiles, tiles);
+        u.add(dsteps, steps);
+        u.add(dsegs, segs);
     }
 };
 // one side's environment with the unrotated MPO mixed in
@@ -324,12 +349,12 @@ struct MixList {
     std::vector<spk::MixGroup> groups;
     std::vector<double> cf;
     std::vector<int> at;
-    DArr<spk::MixWork> dwork;
-    DArr<spk::MixTileRec> dtiles;
-    DArr<long long> dsrc;
-    DArr<spk::MixGroup> dgroups;
-    DArr<double> dcf;
-    DArr<int> dat;
+    DRef<spk::MixWork> dwork;
+    DRef<spk::MixTileRec> dtiles;
+    DRef<long long> dsrc;
+    DRef<spk::MixGroup> dgroups;
+    DRef<double> dcf;
+    DRef<int> dat;
     long long size = 0;  // values per quadrature point
     double flops = 0.0;  // per quadrature point
     // blocks to be mixed by shape (bra block, ket block): offset, then the
@@ -412,13 +437,13 @@ struct MixList {
         for (int i = tiles[w.tile0].i0; i < tiles[w.tile1 - 1].i1; ++i) n += groups[i].t1 - groups[i].t0;
         return n;
     }
-    void upload(hipStream_t s) {
-        dwork.upload(work, s);
-        dtiles.upload(tiles, s);
-        dsrc.upload(src, s);
-        dgroups.upload(groups, s);
-        dcf.upload(cf, s);
-        dat.upload(at, s);
+    void upload(Upload& u) {
+        u.add(dwork, work);
+        u.add(dtiles, tiles);
+        u.add(dsrc, src);
+        u.add(dgroups, groups);
+        u.add(dcf, cf);
+        u.add(dat, at);
     }
     spk::MixLists lists() const {
         return spk::MixLists{dwork.p, dtiles.p, dsrc.p, dgroups.p, dcf.p, dat.p, int(work.size()), 0};
@@ -435,7 +460,7 @@ struct SitePlan {
     int nW = 0, nc = 0;
     std::vector<std::array<int, 4>> went;  // (a, b, s, u) of the rotated MPO pattern
     std::vector<double> coef_h;
-    DArr<double> coef;
+    DRef<double> coef;
     int c_wt(int e) const { return e; }
     int c_cwt(int e) const { return nW + e; }
     int c_g() const { return 2 * nW; }
@@ -458,16 +483,16 @@ struct SitePlan {
     std::vector<spk::DiagMix> dg_mix;
     std::vector<spk::DiagMixTerm> dg_term;
     std::vector<spk::DiagBlk> dg_blk;
-    DArr<spk::DiagSrc> ddg_src;
-    DArr<int> ddg_idx;
-    DArr<spk::DiagMix> ddg_mix;
-    DArr<spk::DiagMixTerm> ddg_term;
-    DArr<spk::DiagBlk> ddg_blk;
+    DRef<spk::DiagSrc> ddg_src;
+    DRef<int> ddg_idx;
+    DRef<spk::DiagMix> ddg_mix;
+    DRef<spk::DiagMixTerm> ddg_term;
+    DRef<spk::DiagBlk> ddg_blk;
     // gauge moves
     std::vector<spk::QrTask> qr_tasks, lq_tasks;
     std::vector<spk::QrPiece> qr_pieces, lq_pieces;
-    DArr<spk::QrTask> dqr_tasks, dlq_tasks;
-    DArr<spk::QrPiece> dqr_pieces, dlq_pieces;
+    DRef<spk::QrTask> dqr_tasks, dlq_tasks;
+    DRef<spk::QrPiece> dqr_pieces, dlq_pieces;
     long long qr_scratch = 0, lq_scratch = 0, qr_rsize = 0, lq_rsize = 0;
     spk::QrShape qr_shape, lq_shape;
     std::vector<long long> qr_roff;  // per right sector of bond k
@@ -477,7 +502,7 @@ struct SitePlan {
     // tiled path: dense particle-number layout of the site
     long long Xd_size = 0;
     std::vector<int> xmap_h;  // dense element -> packed index or -1
-    DArr<int> xmap;
+    DRef<int> xmap;
     // chained products: the environment updates, the pre-mixed environments
     // they (and H_eff x at wide MPOs) use, the packed indices of the rotated
     // site vector's two states
@@ -486,7 +511,7 @@ struct SitePlan {
     int y_split = 1;                         // channel chunks of H_eff x (partials of y: y_split * G)
     MixList mix_l, mix_r;                    // empty: the products read the environment itself
     std::vector<int> rmap_h;
-    DArr<int> rmap;
+    DRef<int> rmap;
     // fused plan of H_eff x: rows per task and LDS (doubles) of the row-chunk
     // form; 0: the site's MPO is too wide for one
     int h_rows = 0;
@@ -511,6 +536,7 @@ struct sp_handle {
     // buffer for both sides: a sweep builds L[k] only after its last use of
     // R[k] and the other way round, so at most one of the two is valid at a
     // time (Lvalid/Rvalid); the boundary bonds 0 and L keep both.
+    DArr<char> plan_mem;  // the lists of every site
     std::vector<DArr<double>> envmem;
     std::vector<DArr<float>> envmem32;     // FP32 copies (reduced precisions)
     std::vector<DRef<double>> envL, envR;
@@ -823,6 +849,10 @@ double rot_value(int t, int u, double c, double s) {
 void build_plan(sp_handle* h, int k) {
     SitePlan& P = h->plan[k - 1];
     const int G = h->G;
+    // the tiled path runs the chained lists and only counts the passes below:
+    // one quadrature point stands for all
+    const bool plain = h->path == SP_PATH_PLAIN;
+    const int Gl = plain ? G : 1;
     const Bond& bl = h->bonds[k - 1];
     const Bond& br = h->bonds[k];
     const SiteInfo& si = h->sites[k - 1];
@@ -912,7 +942,7 @@ void build_plan(sp_handle* h, int k) {
             toff += (long long)eb.rows * br.nb[jb].dim;
         }
     P.Tsize = toff;
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < Gl; ++g) {
         for (size_t e = 0; e < el.blk.size(); ++e)
             for (int q = 0; q < 4; ++q) {
                 if (Toff[e * 4 + q] < 0) continue;
@@ -962,7 +992,7 @@ void build_plan(sp_handle* h, int k) {
                 voff += (long long)bl.nb[i].dim * br.nb[nbp].dim;
             }
     P.Vsize = voff;
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < Gl; ++g) {
         size_t t = 0;
         while (t < vterms.size()) {
             const VTerm& v0 = vterms[t];
@@ -981,7 +1011,7 @@ void build_plan(sp_handle* h, int k) {
         const Sector& SA = bl.sec[X.sa];
         const Sector& SB = br.sec[X.sb];
         P.yout.add_task(B_Y, X.off, X.rows, X.cols, X.cols);
-        for (int g = 0; g < G; ++g)
+        for (int g = 0; g < Gl; ++g)
             for (int cp = 0; cp < wr; ++cp) {
                 auto it = Voff.find({X.s, cp, SA.nb});
                 if (it == Voff.end()) continue;
@@ -1002,7 +1032,7 @@ void build_plan(sp_handle* h, int k) {
         const int re = er.find(lastR, SB.nb);
         if (e0 < 0 || re < 0) continue;
         SP_REQUIRE(el.blk[e0].j == SA.nb && er.blk[re].j == SB.nb, "internal: identity channels must conserve N");
-        for (int g = 0; g < G; ++g)
+        for (int g = 0; g < Gl; ++g)
             for (int q = 0; q < 4; ++q) {
                 if (!rot_nonzero(X.s, q)) continue;
                 const long long to = Toff[size_t(e0) * 4 + q];
@@ -1016,7 +1046,7 @@ void build_plan(sp_handle* h, int k) {
             }
     }
     // ---- left environment update: L[k](c', b, b') rows of sector s_b = sum_sigma A^T V
-    for (int g = 0; g < G; ++g)
+    for (int g = 0; g < Gl; ++g)
         for (const EnvBlk& OB : er.blk) {
             const NBlock& NB = br.nb[OB.i];
             for (int sb = NB.s0; sb < NB.s1; ++sb) {
@@ -1049,7 +1079,7 @@ void build_plan(sp_handle* h, int k) {
             zoff += (long long)bl.nb[i].dim * rb.rows;
         }
     P.Zsize = zoff;
-    for (int g = 0; g < G; ++g)
+    for (int g = 0; g < Gl; ++g)
         for (size_t e = 0; e < er.blk.size(); ++e)
             for (int q = 0; q < 4; ++q) {
                 if (Zoff[e * 4 + q] < 0) continue;
@@ -1096,7 +1126,7 @@ void build_plan(sp_handle* h, int k) {
                 ztoff += (long long)bl.nb[ip].dim * br.nb[nbb].dim;
             }
     P.Ztsize = ztoff;
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < Gl; ++g) {
         size_t t = 0;
         while (t < zterms.size()) {
             const VTerm& v0 = zterms[t];
@@ -1110,7 +1140,7 @@ void build_plan(sp_handle* h, int k) {
         }
     }
     // ---- right environment update: R(c, a, a') rows of sector s_a = sum_sigma A Zt^T
-    for (int g = 0; g < G; ++g)
+    for (int g = 0; g < Gl; ++g)
         for (const EnvBlk& OB : el.blk) {
             const NBlock& NA = bl.nb[OB.i];
             for (int sa = NA.s0; sa < NA.s1; ++sa) {
@@ -1282,7 +1312,11 @@ void build_plan(sp_handle* h, int k) {
     }
     // algorithmic flops of one H_eff x: per g the left product, the mixing and
     // the right product for y, and the right product of ny
-    P.heff_flops = P.p1.flops + P.mixl.flops + P.yout.flops;
+    P.heff_flops = (P.p1.flops + P.mixl.flops + P.yout.flops) * (plain ? 1 : G);
+    if (!plain) {
+        P.p1 = P.p1r = P.yout = P.envl_out = P.envr_out = BList{};
+        P.mixl = P.mixr = CList{};
+    }
 
     // ================= tiled path =================
     // dense particle-number blocks Xd(j, sigma, jb) of the site (zero outside
@@ -1673,35 +1707,60 @@ bool build_fused(sp_handle* h, int k, int lds_budget = kHeffLdsBudget) {
     return RC >= 1;
 }
 
-void upload_plan(sp_handle* h, int k) {
+// f(1) .. f(L) on up to eight threads (sites only write their own plan); the
+// error of the lowest site, if any
+template <class F>
+void for_sites(int L, F f) {
+    std::vector<std::exception_ptr> err(L);
+    std::atomic<int> next{0};
+    auto work = [&]() {
+        for (int k = next++; k < L; k = next++) try {
+                f(k + 1);
+            } catch (...) {
+                err[k] = std::current_exception();
+            }
+    };
+    const int nt = std::min({8, L / 2, int(std::thread::hardware_concurrency())});
+    std::vector<std::thread> threads;
+    try {
+        threads.reserve(std::max(nt, 1));
+        for (int t = 1; t < nt; ++t) threads.emplace_back(work);
+    } catch (...) {  // no more threads: those there, and this one, do the work
+    }
+    work();
+    for (auto& t : threads) t.join();
+    for (const auto& e : err)
+        if (e) std::rethrow_exception(e);
+}
+
+void upload_plan(sp_handle* h, int k, Upload& u) {
     SitePlan& P = h->plan[k - 1];
-    hipStream_t s = h->stream;
-    P.coef.upload(P.coef_h, s);
-    P.p1.upload(s);
-    P.mixl.upload(s);
-    P.yout.upload(s);
-    P.envl_out.upload(s);
-    P.p1r.upload(s);
-    P.mixr.upload(s);
-    P.envr_out.upload(s);
-    P.ddg_src.upload(P.dg_src, s);
-    P.ddg_idx.upload(P.dg_idx, s);
-    P.ddg_mix.upload(P.dg_mix, s);
-    P.ddg_term.upload(P.dg_term, s);
-    P.ddg_blk.upload(P.dg_blk, s);
-    P.dqr_tasks.upload(P.qr_tasks, s);
-    P.dlq_tasks.upload(P.lq_tasks, s);
-    P.dqr_pieces.upload(P.qr_pieces, s);
-    P.dlq_pieces.upload(P.lq_pieces, s);
-    P.absorb_right.upload(s);
-    P.absorb_left.upload(s);
-    P.xmap.upload(P.xmap_h, s);
-    P.c_heff.upload(s);
-    P.c_envl.upload(s);
-    P.c_envr.upload(s);
-    P.mix_l.upload(s);
-    P.mix_r.upload(s);
-    P.rmap.upload(P.rmap_h, s);
+    u.add(P.coef, P.coef_h);
+    P.p1.upload(u);
+    P.mixl.upload(u);
+    P.yout.upload(u);
+    P.envl_out.upload(u);
+    P.p1r.upload(u);
+    P.mixr.upload(u);
+    P.envr_out.upload(u);
+    u.add(P.ddg_src, P.dg_src);
+    u.add(P.ddg_idx, P.dg_idx);
+    u.add(P.ddg_mix, P.dg_mix);
+    u.add(P.ddg_term, P.dg_term);
+    u.add(P.ddg_blk, P.dg_blk);
+    u.add(P.dqr_tasks, P.qr_tasks);
+    u.add(P.dlq_tasks, P.lq_tasks);
+    u.add(P.dqr_pieces, P.qr_pieces);
+    u.add(P.dlq_pieces, P.lq_pieces);
+    P.absorb_right.upload(u);
+    P.absorb_left.upload(u);
+    u.add(P.xmap, P.xmap_h);
+    P.c_heff.upload(u);
+    P.c_envl.upload(u);
+    P.c_envr.upload(u);
+    P.mix_l.upload(u);
+    P.mix_r.upload(u);
+    u.add(P.rmap, P.rmap_h);
 }
 
 // ---------------------------------------------------------------------------
@@ -3532,7 +3591,7 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         build_env_layouts(h.get());
         h->plan.resize(h->L);
         long long Tmax = 0, Vmax = 0, qrs = 0, qrr = 0, LTmax = 0;
-        for (int k = 1; k <= h->L; ++k) {
+        for_sites(h->L, [&](int k) {
             build_plan(h.get(), k);
             if (h->path == SP_PATH_TILED) {
                 if (!build_fused(h.get(), k)) build_fused(h.get(), k, kHeffLdsMax);
@@ -3545,6 +3604,8 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
                 P1.h_rows = 0;
                 P1.h_lds = 0;
             }
+        });
+        for (int k = 1; k <= h->L; ++k) {
             const SitePlan& P = h->plan[k - 1];
             // the diagonals use the same scratch
             const long long dgT = (long long)P.dg_nzl * h->bonds[k - 1].D + (long long)P.dg_nzr * h->bonds[k].D;
@@ -3569,7 +3630,11 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         // every host-side check is done; device work starts here
         HIPCK(hipGetDevice(&h->device));
         alloc_envs(h.get());
-        for (int k = 1; k <= h->L; ++k) upload_plan(h.get(), k);
+        {
+            Upload u;
+            for (int k = 1; k <= h->L; ++k) upload_plan(h.get(), k, u);
+            u.finish(h->plan_mem, h->stream);
+        }
         h->T.alloc(h->T_cap);
         h->V.alloc(h->V_cap);
         h->LT.alloc(h->LT_cap + read_pad(h.get()));
@@ -4340,8 +4405,8 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
             // lists at a site without a fused plan): environments and x read
             // once, per-g partials written
             out[1] = premix_ms;
-            out[3] = P.p1.flops + P.mixl.flops + P.yout.flops;
-            out[4] = P.h_rows == 0 ? G * P.mix_l.flops : 0.0;
+            out[3] = P.heff_flops;
+            out[4] = G * P.mix_l.flops;
             out[5] = 2.0 * G * xs;
             out[6] = 8.0 * (Lb + Rb + xs + 2.0 * G * xs);
             out[7] = 0.0;

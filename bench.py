@@ -27,8 +27,6 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP64_TFLOPS = 78.6
 PEAK_HBM_GBS = 8000.0
-# the fused-kernel LDS budgets (doubles per work-group) that sp_autotune tries
-AUTOTUNE_BUDGETS = (4608, 9216, 13824, 18432)
 
 
 def log(msg):
@@ -558,24 +556,11 @@ def main():
         log(f"[bench] --heff-only: left environments up to site {kc} built")
         x = torch.tensor(gpu.get_site(kc), dtype=torch.float64, device="cuda")
         y, ny = torch.empty_like(x), torch.empty_like(x)
-        # the Hubbard centre runs every fused plan the autotuner can choose
-        # (one per distinct row count), so counters exist for whichever plan
-        # a timed run picks; the ab-initio centre keeps its tuned plan
-        budgets = [0]
-        if args.path == "tiled" and args.heff_workload == "hubbard":
-            budgets = list(AUTOTUNE_BUDGETS)
-        seen = set()
-        for b in budgets:
-            if b:
-                rows = gpu.set_heff_plan(kc, b)
-                if rows in seen:
-                    continue
-                seen.add(rows)
-            for _ in range(args.heff_only):
-                gpu.heff_apply(kc, x, y, ny)
-            torch.cuda.synchronize()
-            log(f"[bench] {args.heff_only} H_eff x applications at site {kc} ({args.path}); "
-                f"site size {x.numel()}, algorithmic flops {gpu.heff_flops(kc):.4e}, plan {gpu.heff_plan(kc)}")
+        for _ in range(args.heff_only):
+            gpu.heff_apply(kc, x, y, ny)
+        torch.cuda.synchronize()
+        log(f"[bench] {args.heff_only} H_eff x applications at site {kc} ({args.path}); "
+            f"site size {x.numel()}, algorithmic flops {gpu.heff_flops(kc):.4e}, plan {gpu.heff_plan(kc)}")
         if args.heff_workload != "hubbard":
             prof = gpu.heff_profile(kc, x, y, ny, reps=5)
             ms = product_ms(prof)

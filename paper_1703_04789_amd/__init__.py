@@ -528,7 +528,7 @@ class SPMPS:
         return np.array([self.expect(mpo_abinitio_component(h, eri, p))[0] for p in range(1, self.L + 1)])
 
     def autotune(self, reps=5):
-        """Pick the fused-kernel LDS budget (rows per task) of every site by
+        """Pick the LDS budget (rows per task) of every site's fused plan by
         timing; returns per-site (budget in doubles, rows, microseconds)."""
         b = np.zeros(self.L, dtype=np.int32)
         r = np.zeros(self.L, dtype=np.int32)
@@ -567,8 +567,8 @@ class SPMPS:
         return rows.value, lds.value
 
     def set_heff_plan(self, site, lds_budget):
-        """Fused kernel with this LDS budget (doubles) at ``site``, or 0 for
-        the tiled block products; returns the rows per task (0: tiled)."""
+        """Fused plan with this LDS budget (doubles) at ``site``, or 0 for
+        the block products; returns the rows per task (0: tiled)."""
         rows = ctypes.c_int(0)
         _check(lib().sp_set_heff_plan(self._h, site, lds_budget, ctypes.byref(rows)))
         return rows.value

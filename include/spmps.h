@@ -206,7 +206,8 @@ int sp_heff_apply(sp_handle* h, int site, const double* x, double* y, double* ny
  * bits), with the per-quadrature-point partial outputs held in a fixed
  * device array of the library (2 x 2^21 doubles, 32 MiB per device, kept
  * until the process ends) instead of the handle's buffers.  The call
- * allocates nothing.  Tiled path only (SP_EINVAL otherwise); SP_EINVAL when
+ * allocates nothing.  Recorded into a graph, it reads the environments as they
+ * are at each replay.  Tiled path only (SP_EINVAL otherwise); SP_EINVAL when
  * the site needs more than 2^21 partial slots per output (G x site size on
  * a fused site, G x the channel split x site size on the others).
  * Every handle on one GPU shares that GPU's array: calls that overlap on one

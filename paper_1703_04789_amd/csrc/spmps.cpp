@@ -558,6 +558,11 @@ struct sp_handle {
     int lt_site = -1;   // -1: none (the scratch holds a right environment, or nothing)
     long long lt_gen = -1;
     bool lt_f32 = false;
+    // the caller's capture that recorded it (0: it was launched), and whether
+    // calls were ever recorded: their replays, which the handle does not see,
+    // write the scratch and the environments
+    unsigned long long lt_capture = 0;
+    bool recorded = false;
     long long Xr_cap = 0;
     long long Xd_cap = 0;
     int y_split_max = 1;  // partial slots of y per quadrature point
@@ -2104,18 +2109,40 @@ int heff_parts(const sp_handle* h, int k) {
     return h->path == SP_PATH_TILED ? h->G * h->plan[k - 1].y_split : h->G;
 }
 
+// the capture that the handle's stream is under, 0 if none
+unsigned long long capture_of(sp_handle* h) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(h->stream, &st, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    if (st == hipStreamCaptureStatusNone) return 0;
+    h->recorded = true;
+    return id;
+}
+// start of a public call that mixes environments: after a replay the scratch
+// may hold another site's, or the environment it was mixed from may be new
+void forget_mix(sp_handle* h) {
+    if (h->recorded && capture_of(h) == 0) h->lt_site = -1;
+}
+
 // the left environment with the MPO mixed in, once per local problem: it
-// depends on L[k-1] only
+// depends on L[k-1] only.  A capture records its own, so that every replay
+// mixes the environment of the moment
 void premix_left(sp_handle* h, int k, int mode) {
     const SitePlan& P = h->plan[k - 1];
     const MixList& m = P.mix_l;
     const bool f32 = mode == spk::kChainF32;
-    if (m.empty() || (h->lt_site == k && h->lt_gen == h->Lgen[k - 1] && h->lt_f32 == f32)) return;
+    if (m.empty()) return;
+    const unsigned long long capture = capture_of(h);
+    if (h->lt_site == k && h->lt_gen == h->Lgen[k - 1] && h->lt_f32 == f32 && h->lt_capture == capture) return;
     const void* env = f32 ? (const void*)h->envL32[k - 1].p : (const void*)h->envL[k - 1].p;
     spk::premix(h->stream, f32, m.lists(), env, h->env[k - 1].size, h->LT.p, m.size, h->G);
     h->lt_site = k;
     h->lt_gen = h->Lgen[k - 1];
     h->lt_f32 = f32;
+    h->lt_capture = capture;
 }
 
 // H_eff x as a chained product into the partial slots yp, nyp
@@ -2230,6 +2257,7 @@ bool heff_apply(sp_handle* h, int k, const double* x, double* y, double* ny, boo
 void env_chain(sp_handle* h, int k, const ChainList& C, const MixList& mix, const double* env, long long esize, double* out,
                long long osize) {
     const SitePlan& P = h->plan[k - 1];
+    (void)capture_of(h);  // a recorded update writes an environment when it is replayed
     site_vectors(h, k, site_ptr(h, k));
     if (&mix == &P.mix_l) {
         premix_left(h, k, spk::kChainF64);  // there already if H_eff was applied at this site
@@ -3678,6 +3706,7 @@ int sp_env_update(sp_handle* h, int site, int dir) {
         SP_REQUIRE(h, "null handle");
         check_site(h, site);
         SP_REQUIRE(dir == 1 || dir == -1, "dir must be +1 or -1");
+        forget_mix(h);
         if (dir > 0) env_left(h, site);
         else env_right(h, site);
         HIPCK(hipGetLastError());
@@ -3690,6 +3719,7 @@ int sp_heff_apply(sp_handle* h, int site, const double* x, double* y, double* ny
         SP_REQUIRE(h && x && y && ny, "null argument");
         check_site(h, site);
         SP_REQUIRE(x != y && x != ny && y != ny, "x, y and ny must not alias");
+        forget_mix(h);
         heff_apply(h, site, x, y, ny);
         HIPCK(hipGetLastError());
         return SP_OK;
@@ -3712,6 +3742,7 @@ int sp_heff_apply_noalloc(sp_handle* h, int site, const double* x, double* y, do
         SP_REQUIRE(it != g_scratch_ptr.end(), "internal: scratch address of the device not resolved");
         double* base = it->second;
         lk.unlock();
+        forget_mix(h);
         heff_apply(h, site, x, y, ny, false, false, base, base + kNoAllocSlots);
         HIPCK(hipGetLastError());
         return SP_OK;
@@ -3734,6 +3765,7 @@ int sp_sweep(sp_handle* h, const sp_sweep_opts* o, sp_sweep_report* r) {
         SP_REQUIRE(o->n_sweeps >= 0 && o->max_iter >= 1 && o->max_sub >= 2 && o->keep >= 1 && o->tol >= 0,
                    "bad sweep options");
         SP_REQUIRE(h->center == 1, "sweeps start with the canonical centre at site 1");
+        forget_mix(h);
         if (r) r->n_steps = 0;
         SP_REQUIRE(o->solver >= SP_SOLVER_AUTO && o->solver <= SP_SOLVER_DEVICE, "unknown solver");
         if (device_solver_ok(h, *o, 1)) {
@@ -3804,6 +3836,7 @@ int sp_sweep_batch(sp_handle** hs, int n, const sp_sweep_opts* o, sp_sweep_repor
             SP_REQUIRE(h->precision == hs[0]->precision, "batched handles must share the precision");
             SP_REQUIRE(h->center == 1, "sweeps start with the canonical centre at site 1");
             for (int j = 0; j < i; ++j) SP_REQUIRE(hs[j] != h, "a handle appears twice in the batch");
+            forget_mix(h);
             B[i].h = h;
             const int L = h->L;
             std::vector<std::pair<int, int>> one;
@@ -3828,6 +3861,7 @@ int sp_autotune(sp_handle* h, int reps, int* budget_out, int* rows_out, double* 
     return guarded([&]() -> int {
         SP_REQUIRE(h && reps >= 1, "bad arguments");
         SP_REQUIRE(h->path == SP_PATH_TILED, "the autotuner tunes the fused kernel of the tiled path");
+        forget_mix(h);
         const int candidates[] = {4608, 9216, 13824, kHeffLdsMax};
         hipStream_t s = h->stream;
         hipEvent_t e0, e1;
@@ -4165,6 +4199,7 @@ int sp_energy(sp_handle* h, double* E, double* normP) {
         const int k = h->center;
         const int n = int(h->sites[k - 1].size);
         ensure_davidson(h, std::max(h->dav_sub, 2));
+        forget_mix(h);
         // always FP64 (also with SP_FP32)
         heff_apply(h, k, site_ptr(h, k), h->dHV.p, h->dNV.p, false, true);
         double* sm = h->dsmall.p;
@@ -4251,6 +4286,7 @@ int sp_heff_batch_profile(sp_handle** hs, int n, const int* sites, int reps, dou
                        "one device, stream and precision");
             SP_REQUIRE(h->Lvalid[k - 1] && h->Rvalid[k], "environments are not built");
             for (int j = 0; j < i; ++j) SP_REQUIRE(hs[j] != h, "a handle appears twice");
+            forget_mix(h);
             hb.add(h, k, site_ptr(h, k), nullptr);
             const SitePlan& P = h->plan[k - 1];
             groups += double(P.c_heff.tiles.size()) * h->G;
@@ -4344,6 +4380,7 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
         SP_REQUIRE(h && x && y && ny && out && reps >= 1, "bad arguments");
         check_site(h, site);
         if (!h->Lvalid[site - 1] || !h->Rvalid[site]) throw SpError(SP_ESTATE, "environments are not built");
+        forget_mix(h);
         SitePlan& P = h->plan[site - 1];
         hipStream_t s = h->stream;
         const bool plain = h->path == SP_PATH_PLAIN;

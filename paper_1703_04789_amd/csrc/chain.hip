@@ -38,9 +38,9 @@ typedef double d2u_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
 
 typedef __bf16 bf4_t __attribute__((ext_vector_type(4)));
-// v ~ hi + lo, both bf16 rounded to nearest even (about 16 significant bits;
-// the residue of the FP32 value, which is exact, so the split is off by 2^-18
-// of v as with an FP64 residue)
+// v ~ hi + lo, both bf16 rounded to nearest even, off by at most 2^-17 of v.
+// The residue of an FP64 value is formed in FP64: what FP32 drops of v can
+// decide how it rounds
 template <class V>
 __device__ inline void split_bf16(const V* v, s4_t& hi, s4_t& lo) {
     f4_t f, r;
@@ -48,7 +48,8 @@ __device__ inline void split_bf16(const V* v, s4_t& hi, s4_t& lo) {
     for (int t = 0; t < 4; ++t) f[t] = float(v[t]);
     const bf4_t h = __builtin_convertvector(f, bf4_t);
     const f4_t hf = __builtin_convertvector(h, f4_t);
-    r = f - hf;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) r[t] = float(v[t] - V(hf[t]));
     const bf4_t l = __builtin_convertvector(r, bf4_t);
     hi = __builtin_bit_cast(s4_t, h);
     lo = __builtin_bit_cast(s4_t, l);

@@ -55,8 +55,8 @@ __device__ inline void split_bf16(const V* v, s4_t& hi, s4_t& lo) {
     lo = __builtin_bit_cast(s4_t, l);
 }
 
-// the value at element i of a block: a uniform base and a 32-bit byte offset
-// per lane (a block holds fewer than 2^28 values)
+// the value at element i from a tile's first: a uniform base and a 32-bit
+// byte offset per lane
 template <class E>
 __device__ inline E at(const E* __restrict__ p, unsigned i) {
     return *reinterpret_cast<const E*>(reinterpret_cast<const char*>(p) + unsigned(sizeof(E)) * i);
@@ -101,8 +101,12 @@ struct Frag {
 // both operands share it).  Rows past an extent re-read its last one, kj and
 // kc values past a range are read from what follows (the buffers end in
 // read_pad values) and set to zero in both operands.
+// Wavefronts per SIMD: as many as the registers of a tile leave without spills.
+constexpr int chain_waves_per_simd(int lay, int nm) {
+    return lay == kChainHeff ? (nm <= 4 ? 3 : 2) : (nm == 2 ? 5 : nm == 3 ? 4 : nm <= 6 ? 3 : 2);
+}
 template <int MODE, int LAY, int NM, int NI, int NN, int W, bool BATCH>
-__global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* __restrict__ insts, KInst one) {
+__global__ __launch_bounds__(64 * W, chain_waves_per_simd(LAY, NM)) void k_chain(const KInst* __restrict__ insts, KInst one) {
     typedef typename std::conditional<MODE == kChainF32, float, double>::type E;         // operands
     typedef typename std::conditional<MODE == kChainF64, d4_t, f4_t>::type A4;           // accumulators
     typedef typename std::conditional<MODE == kChainF64, double, float>::type AE;
@@ -131,10 +135,10 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
     const int ai = MODE == kChainF64 ? 4 * (li % 4) + li / 4 : li;
     int pm[NM], bn[NN];
 #pragma unroll
-    for (int i = 0; i < NM; ++i) pm[i] = min(tk.m0 + 16 * i + li, tk.m1 - 1);
+    for (int i = 0; i < NM; ++i) pm[i] = min(16 * i + li, tk.m - 1);
 #pragma unroll
-    for (int i = 0; i < NN; ++i) bn[i] = min(tk.n0 + 16 * i + li, tk.n1 - 1);
-    const int nm = (tk.m1 - tk.m0 + 15) / 16;
+    for (int i = 0; i < NN; ++i) bn[i] = min(16 * i + li, tk.n - 1);
+    const int nm = (tk.m + 15) / 16;
     A4 acc[NM][NN], in[NI][NN];
     d4_t sum64[kFold ? NM : 1][kFold ? NN : 1];
 #pragma unroll
@@ -167,11 +171,10 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
         fs = I.steps[st];
         s = fs.g0;
         sg = I.segs[s];
-        kb = sg.k0;
     }
     auto fetch = [&](F& f) {
         f.cf = E(sg.cf);
-        f.nk = sg.k1 - kb;
+        f.nk = sg.nk - kb;
         const E* __restrict__ X = sg.alt_x ? x1 : x0;
         const E* __restrict__ V = sg.alt_e ? e1 : e0;
         const E* __restrict__ A = (LAY == kChainHeff ? X : V) + sg.a_off;
@@ -182,7 +185,7 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
             for (int t = 0; t < KL; ++t) {
 #pragma unroll
                 for (int i = 0; i < NI; ++i) {
-                    const int r = min(fs.kc0 + 16 * i + ai, fs.kc1 - 1);
+                    const int r = 16 * i + min(ai, fs.nkc - 1 - 16 * i);
                     f.a[i][t] = at(A, unsigned(KL * lk * sg.lda + r));
                 }
                 A += sg.lda;
@@ -190,7 +193,7 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
         } else {  // A(kc, kj) at kc * lda + kj
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                const int r = min(fs.kc0 + 16 * i + ai, fs.kc1 - 1);
+                const int r = 16 * i + min(ai, fs.nkc - 1 - 16 * i);
                 read_run(A + kb, unsigned(r * sg.lda + KL * lk), f.a[i]);
             }
         }
@@ -208,7 +211,7 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
         }
         kb += KC;
         f.last = false;
-        if (kb >= sg.k1) {
+        if (kb >= sg.nk) {
             ++s;
             if (s >= fs.g1) {
                 f.last = true;
@@ -219,7 +222,7 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
                 }
             }
             if (st < s1) sg = I.segs[s];
-            kb = sg.k0;
+            kb = 0;
         }
     };
     KStep cs{};  // the step whose inner product is being formed
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
         for (int j = 0; j < NN; ++j)
 #pragma unroll
             for (int t = 0; t < KL; ++t) f.b[j][t] *= f.cf;
-        const int ni = (cs.kc1 - cs.kc0 + 15) / 16;
+        const int ni = (cs.nkc + 15) / 16;
         if constexpr (MODE == kChainBF3) {
             s4_t bh[NN], bl[NN];
 #pragma unroll
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             if (i >= ni) break;
-            const int k0 = cs.kc0 + 16 * i;
+            const int k0 = 16 * i;
             E p[NM][4];
             if constexpr (LAY == kChainEnvL) {  // P(m, kc) at kc * ldp + m
                 const E* __restrict__ q = P + (long long)k0 * cs.ldp;
@@ -292,10 +295,10 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
 #pragma unroll
                 for (int a = 0; a < NM; ++a) read_run(P + k0, unsigned(pm[a] * cs.ldp + 4 * lk), p[a]);
             }
-            if (k0 + 16 > cs.kc1) {
+            if (k0 + 16 > cs.nkc) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const bool on = k0 + 4 * lk + v < cs.kc1;
+                    const bool on = k0 + 4 * lk + v < cs.nkc;
 #pragma unroll
                     for (int a = 0; a < NM; ++a) p[a][v] = on ? p[a][v] : E(0);
 #pragma unroll
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
                 cs = fs = I.steps[st];
                 s = fs.g0;
                 sg = I.segs[s];
-                kb = sg.k0;
+                kb = 0;
             }
         }
         if (st >= s1) continue;
@@ -402,8 +405,8 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
             for (int j = 0; j < NN; ++j)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int m = tk.m0 + 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = tk.n0 + 16 * j + li;
-                    if (m < tk.m1 && n < tk.n1) out[(long long)m * tk.ldo + n] = scale * double(total(a, j, v));
+                    const int m = 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = 16 * j + li;
+                    if (m < tk.m && n < tk.n) out[(long long)m * tk.ldo + n] = scale * double(total(a, j, v));
                 }
         return;
     } else {
@@ -419,13 +422,13 @@ __global__ __launch_bounds__(64 * W, NM <= 4 ? 3 : 2) void k_chain(const KInst* 
         const bool both = LAY == kChainHeff && tk.e1 > tk.e0;
         for (int e = wave; e < nm * NN * 4; e += W) {
             const int v = e % 4, j = (e / 4) % NN, a = e / (4 * NN);
-            const int m = tk.m0 + 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = tk.n0 + 16 * j + li;
-            if (m >= tk.m1 || n >= tk.n1) continue;
+            const int m = 16 * a + (MODE == kChainF64 ? 4 * v + lk : 4 * lk + v), n = 16 * j + li;
+            if (m >= tk.m || n >= tk.n) continue;
             double sum = red[0][e][lane];
 #pragma unroll
             for (int w = 1; w < W; ++w) sum += double(red[w][e][lane]);
             if constexpr (LAY == kChainHeff) {
-                const int q = I.map[tk.map_off + n * tk.ldo + m];
+                const int q = I.map[tk.map_off + (long long)n * tk.ldo + m];
                 if (q >= 0) {
                     out[q] = scale * sum;
                     if (both) out2[q] = scale * double(red[W][e][lane]);
@@ -444,7 +447,7 @@ template <class E, bool BATCH>
 __global__ __launch_bounds__(256) void k_xprep(const KPrep* __restrict__ insts, KPrep one) {
     const KPrep& I = BATCH ? insts[blockIdx.z] : one;
     if (I.gate && *I.gate == 0) return;
-    const int e = blockIdx.x * 256 + threadIdx.x;
+    const long long e = blockIdx.x * 256LL + threadIdx.x;
     if (blockIdx.y == 0) {
         if (e >= I.nd) return;
         const int q = I.map[e];
@@ -456,7 +459,7 @@ __global__ __launch_bounds__(256) void k_xprep(const KPrep* __restrict__ insts, 
     const int qa = I.rmap[2 * e], qb = I.rmap[2 * e + 1];
     const double a = qa >= 0 ? I.x[qa] : 0.0, b = qb >= 0 ? I.x[qb] : 0.0;
     const double* __restrict__ r = I.coef + (long long)g * I.nc + I.crot;  // r(s, u) at 4 s + u
-    E* __restrict__ out = static_cast<E*>(I.xr) + (long long)g * 2 * I.nr;
+    E* __restrict__ out = static_cast<E*>(I.xr) + g * 2 * I.nr;
     out[e] = E(r[4 * 1 + 1] * a + r[4 * 1 + 2] * b);
     out[I.nr + e] = E(r[4 * 2 + 1] * a + r[4 * 2 + 2] * b);
 }
@@ -554,9 +557,9 @@ void chain(hipStream_t s, int mode, int lay, int shape, int waves, int max_tiles
     }
 }
 
-void xprep(hipStream_t s, bool f32, int max_n, int max_G, int ninst, const KPrep* insts, const KPrep& one) {
+void xprep(hipStream_t s, bool f32, long long max_n, int max_G, int ninst, const KPrep* insts, const KPrep& one) {
     if (max_n <= 0 || ninst <= 0) return;
-    const dim3 grid((max_n + 255) / 256, max_G + 1, ninst);
+    const dim3 grid(unsigned((max_n + 255) / 256), max_G + 1, ninst);
     if (f32 && insts) hipLaunchKernelGGL((k_xprep<float, true>), grid, dim3(256), 0, s, insts, one);
     else if (f32) hipLaunchKernelGGL((k_xprep<float, false>), grid, dim3(256), 0, s, insts, one);
     else if (insts) hipLaunchKernelGGL((k_xprep<double, true>), grid, dim3(256), 0, s, insts, one);

@@ -102,29 +102,43 @@ struct KBuf {
     const void* p;
     long long gs;
 };
-// one product of the inner sum: cf A(kc, kj) B(kj, n) over kj in [k0, k1).
+// Offsets of a tile, a step and a segment are those of their first element
+// (first row, column, kc and kj value), 64 bits wide and the same for every
+// lane; a lane adds the rows and values of its tile alone, 32 bits of bytes.
+// one product of the inner sum: cf A(kc, kj) B(kj, n) over nk values of kj.
 // Each operand is one of two buffers: the site tensor's is K_X or (alt_x)
 // K_XR, the environment's K_L (right updates: K_R) or (alt_e) K_LT
 struct KSeg {
     long long a_off, b_off;
     double cf;
-    int lda, ldb, k0, k1, alt_x, alt_e;
+    int lda, ldb, nk, alt_x, alt_e, pad;
 };
-// kc values [kc0, kc1) of P (H_eff x: of K_R, environments: of K_X) and the
+// nkc values of kc of P (H_eff x: of K_R, environments: of K_X) and the
 // segments [g0, g1) of the inner sum
 struct KStep {
     long long p_off;
-    int ldp, kc0, kc1, g0, g1, pad;
+    int ldp, nkc, g0, g1;
 };
-// output tile [m0, m1) x [n0, n1) of a block, the steps [s[w], s[w + 1]) of
-// wavefront w, the sum times coef[cidx] (cidx < 0: 1).  Environments: element
-// (m, n) at o_off + m * ldo + n; H_eff x: at o_off + map[map_off + n * ldo + m]
-// where that is >= 0, and the steps [e0, e1) of N_eff x (second output, no
-// o_off), taken by the last wavefront before its own
+// output tile of m x n elements, the steps [s[w], s[w + 1]) of wavefront w,
+// the sum times coef[cidx] (cidx < 0: 1).  Environments: element (m, n) at
+// o_off + m * ldo + n; H_eff x: at o_off + map[map_off + n * ldo + m] where
+// that is >= 0, and the steps [e0, e1) of N_eff x (second output, no o_off),
+// taken by the last wavefront before its own
 struct KTile {
     long long o_off, map_off;
-    int m0, m1, n0, n1, ldo, cidx, s[5], e0, e1, pad;
+    int m, n, ldo, cidx, s[5], e0, e1, pad;
 };
+// first elements in blocks at off with rows ld apart: of P from row m0, value
+// kc0, of A from kc0, kj0, of B from kj0, column n0, and of an output tile
+inline long long chain_p(int lay, long long off, int ld, long long m0, long long kc0) {
+    return off + (lay == kChainEnvL ? kc0 * ld + m0 : m0 * ld + kc0);
+}
+inline long long chain_a(int lay, long long off, int ld, long long kc0, long long kj0) {
+    return off + (lay == kChainHeff ? kj0 * ld + kc0 : kc0 * ld + kj0);
+}
+inline long long chain_b(int lay, long long off, int ld, long long kj0, long long n0) {
+    return off + (lay == kChainEnvL ? kj0 * ld + n0 : n0 * ld + kj0);
+}
 struct KInst {
     const KTile* tiles;
     const KStep* steps;
@@ -147,7 +161,8 @@ struct KPrep {
     void* xd;
     void* xr;
     const int* gate;
-    int nd, nr, nc, crot, G, pad;
+    long long nd, nr;
+    int nc, crot, G, pad;
 };
 // blocks of 16 of a tile in m, of kc values formed at once, in n
 struct KShape {
@@ -155,6 +170,11 @@ struct KShape {
 };
 constexpr int kNumChainShapes = 8, kNarrowShapes = 5;  // the first kNarrowShapes have nn = 1
 extern const KShape kChainShapes[kNumChainShapes];
+// a lane stays within kLaneRows rows of its tile's or chunk's first element,
+// and within that many values of the last of them: rows ld apart have to be
+// few enough for 32 bits of bytes, whatever the block's size
+constexpr int kLaneRows = 128;
+inline bool chain_lanes_fit(int ld) { return 8 * (kLaneRows * (long long)ld + kLaneRows) < (1LL << 32); }
 // values that may be read past the end of an operand buffer of blocks at most
 // ld wide
 inline long long read_pad(int ld) { return 16LL * ld + 64; }
@@ -187,7 +207,7 @@ void premix(hipStream_t s, bool f32, const MixLists& m, const void* in, long lon
 // max_tiles: the largest tile count times G of the instances; insts = null:
 // the one instance `one`
 void chain(hipStream_t s, int mode, int lay, int shape, int waves, int max_tiles, int ninst, const KInst* insts, const KInst& one);
-void xprep(hipStream_t s, bool f32, int max_n, int max_G, int ninst, const KPrep* insts, const KPrep& one);
+void xprep(hipStream_t s, bool f32, long long max_n, int max_G, int ninst, const KPrep* insts, const KPrep& one);
 
 // out = float(in), n elements
 void to_f32(hipStream_t s, const double* in, float* out, long long n);

@@ -285,28 +285,37 @@ struct ChainList {
     DRef<spk::KSeg> dsegs;
     // the steps of the tile being built: of the sum, and of N_eff x
     std::vector<spk::KStep> own, metric;
+    int tile_m0 = 0, tile_n0 = 0, step_kc0 = 0;
+    // the tile from row m0 and column n0 of its block
+    void begin_tile(int m0, int n0) {
+        tile_m0 = m0;
+        tile_n0 = n0;
+    }
     void begin_step(long long p_off, int ldp, int kc0, int kc1, bool of_metric = false) {
-        (of_metric ? metric : own).push_back(spk::KStep{p_off, ldp, kc0, kc1, int(segs.size()), int(segs.size()), 0});
+        step_kc0 = kc0;
+        (of_metric ? metric : own)
+            .push_back(spk::KStep{spk::chain_p(lay, p_off, ldp, tile_m0, kc0), ldp, kc1 - kc0, int(segs.size()), int(segs.size())});
     }
     // alt_x: the rotated site tensor, alt_e: the mixed environment
     void add_seg(long long a_off, int lda, long long b_off, int ldb, int k0, int k1, double cf, bool alt_x, bool alt_e,
                  bool of_metric = false) {
-        segs.push_back(spk::KSeg{a_off, b_off, cf, lda, ldb, k0, k1, alt_x, alt_e});
+        segs.push_back(spk::KSeg{spk::chain_a(lay, a_off, lda, step_kc0, k0), spk::chain_b(lay, b_off, ldb, k0, tile_n0), cf,
+                                 lda, ldb, k1 - k0, alt_x, alt_e, 0});
         (of_metric ? metric : own).back().g1 = int(segs.size());
     }
     // matrix-core steps of a step (blocks of 16 kc values times the 8-deep
     // chunks of its segments, then the outer product), plus its latency
     int weight(const spk::KStep& p, int nm) const {
-        const int ni = (p.kc1 - p.kc0 + 15) / 16;
+        const int ni = (p.nkc + 15) / 16;
         int w = 12 + 4 * ni * nm;
-        for (int g = p.g0; g < p.g1; ++g) w += 2 * ni * ((segs[g].k1 - segs[g].k0 + 7) / 8);
+        for (int g = p.g0; g < p.g1; ++g) w += 2 * ni * ((segs[g].nk + 7) / 8);
         return w;
     }
     // closes the tile: steps without segments are dropped, the others dealt to
     // the wavefronts, the heaviest first to the least loaded
     void end_tile(spk::KTile t) {
         auto has = [](const spk::KStep& p) { return p.g1 > p.g0; };
-        const int nm = (t.m1 - t.m0 + 15) / 16;
+        const int nm = (t.m + 15) / 16;
         t.e0 = int(steps.size());
         int load[spk::kChainWaves] = {};
         for (const spk::KStep& p : metric)
@@ -1570,11 +1579,13 @@ void build_chain(sp_handle* h, int k) {
             const int nn = br.nb[t.b].dim;
             int n = 0, slot = 0;
             auto end = [&]() {
-                C.end_tile(spk::KTile{(long long)slot * h->G * si.size, mo, t.m0, t.m1, t.n0, t.n1, nn, P.c_g(), {}, 0, 0, 0});
+                C.end_tile(spk::KTile{(long long)slot * h->G * si.size, mo + (long long)t.n0 * nn + t.m0, t.m1 - t.m0, t.n1 - t.n0,
+                                      nn, P.c_g(), {}, 0, 0, 0});
                 ++slot;
             };
             const int e0 = el.find(0, t.i), rl = er.find(lastR, t.b);
             SP_REQUIRE(e0 >= 0 && rl >= 0 && el.blk[e0].j == t.i && er.blk[rl].j == t.b, "internal: identity channels must conserve N");
+            C.begin_tile(t.m0, t.n0);
             for (int c0 = 0; c0 < nn; c0 += TI) {  // N_eff x, with the first chunk
                 const int c1 = std::min(nn, c0 + TI);
                 int k0, k1;
@@ -1616,6 +1627,7 @@ void build_chain(sp_handle* h, int k) {
             for (int m0 = 0; m0 < OB.rows; m0 += TM)
                 for (int n0 = 0; n0 < OB.cols; n0 += TN) {
                     const int m1 = std::min(OB.rows, m0 + TM), n1 = std::min(OB.cols, n0 + TN);
+                    C.begin_tile(m0, n0);
                     for (int q = 0; q < 4; ++q) {
                         int b0, b1;
                         if (side == 0) {  // X(a, q)^T: b = OB.i, a on the left bond
@@ -1648,7 +1660,7 @@ void build_chain(sp_handle* h, int k) {
                             }
                         }
                     }
-                    C.end_tile(spk::KTile{OB.off, 0, m0, m1, n0, n1, OB.cols, -1, {}, 0, 0, 0});
+                    C.end_tile(spk::KTile{OB.off + (long long)m0 * OB.cols + n0, 0, m1 - m0, n1 - n0, OB.cols, -1, {}, 0, 0, 0});
                 }
     }
 }
@@ -1812,38 +1824,37 @@ void validate(const ChainList& C, const std::array<long long, spk::K_NBUF>& in, 
     if (C.shape < 0 || C.shape >= spk::kNumChainShapes) throw SpError(SP_EINVAL, std::string("internal shape: ") + what);
     const spk::KShape sh = spk::kChainShapes[C.shape];
     for (const spk::KTile& t : C.tiles) {
-        if (t.m0 < 0 || t.n0 < 0 || t.m1 <= t.m0 || t.n1 <= t.n0 || t.m1 - t.m0 > 16 * sh.nm || t.n1 - t.n0 > 16 * sh.nn ||
-            t.e0 < 0 || t.e1 < t.e0 || (C.lay != spk::kChainHeff && t.e1 > t.e0) || t.s[0] < t.e1 ||
-            !std::is_sorted(t.s, t.s + 5) || t.s[4] > int(C.steps.size()) || t.s[C.waves] != t.s[4])
+        if (t.m < 1 || t.n < 1 || t.m > 16 * sh.nm || t.n > 16 * sh.nn || t.e0 < 0 || t.e1 < t.e0 ||
+            (C.lay != spk::kChainHeff && t.e1 > t.e0) || t.s[0] < t.e1 || !std::is_sorted(t.s, t.s + 5) ||
+            t.s[4] > int(C.steps.size()) || t.s[C.waves] != t.s[4])
             throw SpError(SP_EINVAL, std::string("internal tile: ") + what);
         if (t.cidx >= 0) check_span(t.cidx, t.cidx, ncoef, what);
         if (C.lay == spk::kChainHeff) {
-            check_span(t.map_off + (long long)t.n0 * t.ldo + t.m0, t.map_off + (long long)(t.n1 - 1) * t.ldo + t.m1 - 1, map_size, what);
+            check_span(t.map_off, t.map_off + (t.n - 1LL) * t.ldo + t.m - 1, map_size, what);
             check_span(t.o_off, t.o_off + npart - 1, nout, what);
         } else {
-            check_span(t.o_off + (long long)t.m0 * t.ldo + t.n0, t.o_off + (long long)(t.m1 - 1) * t.ldo + t.n1 - 1, nout, what);
+            check_span(t.o_off, t.o_off + (t.m - 1LL) * t.ldo + t.n - 1, nout, what);
         }
         for (int q = t.e0; q < t.s[4]; ++q) {
             if (q >= t.e1 && q < t.s[0]) continue;
             const spk::KStep& p = C.steps[q];
-            if (p.kc0 < 0 || p.kc1 <= p.kc0 || p.kc1 - p.kc0 > 16 * sh.ni || p.g0 < 0 || p.g1 <= p.g0 || p.g1 > int(C.segs.size()))
+            if (p.nkc < 1 || p.nkc > 16 * sh.ni || p.g0 < 0 || p.g1 <= p.g0 || p.g1 > int(C.segs.size()))
                 throw SpError(SP_EINVAL, std::string("internal step: ") + what);
             const bool pt = C.lay == spk::kChainEnvL;
-            check_span(p.p_off + (pt ? (long long)p.kc0 * p.ldp + t.m0 : (long long)t.m0 * p.ldp + p.kc0),
-                       p.p_off + (pt ? (long long)(p.kc1 - 1) * p.ldp + t.m1 - 1 : (long long)(t.m1 - 1) * p.ldp + p.kc1 - 1),
-                       in[C.lay == spk::kChainHeff ? spk::K_R : spk::K_X], what);
+            // the last element from the first, rows ld apart
+            auto span = [&](long long off, long long rows, int ld, int run, long long size) {
+                if (!spk::chain_lanes_fit(ld)) throw SpError(SP_EINVAL, std::string("block too wide: ") + what);
+                check_span(off, off + (rows - 1) * ld + run - 1, size, what);
+            };
+            span(p.p_off, pt ? p.nkc : t.m, p.ldp, pt ? t.m : p.nkc, in[C.lay == spk::kChainHeff ? spk::K_R : spk::K_X]);
             for (int i = p.g0; i < p.g1; ++i) {
                 const spk::KSeg& g = C.segs[i];
-                if (g.k0 < 0 || g.k1 <= g.k0) throw SpError(SP_EINVAL, std::string("internal segment: ") + what);
+                if (g.nk < 1) throw SpError(SP_EINVAL, std::string("internal segment: ") + what);
                 const bool at = C.lay == spk::kChainHeff, bt = C.lay == spk::kChainEnvL;
                 const long long nx = in[g.alt_x ? spk::K_XR : spk::K_X];
                 const long long ne = in[g.alt_e ? spk::K_LT : (C.lay == spk::kChainEnvR ? spk::K_R : spk::K_L)];
-                check_span(g.a_off + (at ? (long long)g.k0 * g.lda + p.kc0 : (long long)p.kc0 * g.lda + g.k0),
-                           g.a_off + (at ? (long long)(g.k1 - 1) * g.lda + p.kc1 - 1 : (long long)(p.kc1 - 1) * g.lda + g.k1 - 1),
-                           at ? nx : ne, what);
-                check_span(g.b_off + (bt ? (long long)g.k0 * g.ldb + t.n0 : (long long)t.n0 * g.ldb + g.k0),
-                           g.b_off + (bt ? (long long)(g.k1 - 1) * g.ldb + t.n1 - 1 : (long long)(t.n1 - 1) * g.ldb + g.k1 - 1),
-                           at ? ne : nx, what);
+                span(g.a_off, at ? g.nk : p.nkc, g.lda, at ? p.nkc : g.nk, at ? nx : ne);
+                span(g.b_off, bt ? g.nk : t.n, g.ldb, bt ? t.n : g.nk, at ? ne : nx);
             }
         }
     }
@@ -2084,8 +2095,8 @@ spk::KPrep prep_inst(sp_handle* h, int k, const double* x) {
     I.coef = P.coef.p;
     I.xd = h->Xd.p;
     I.xr = h->Xr.p;
-    I.nd = int(P.Xd_size);
-    I.nr = int(P.rmap_h.size() / 2);
+    I.nd = P.Xd_size;
+    I.nr = (long long)P.rmap_h.size() / 2;
     I.nc = P.nc;
     I.crot = P.c_r(0, 0);
     I.G = h->G;
@@ -2168,7 +2179,8 @@ void need_envs(const sp_handle* h, int k) {
 // instances in launch order and the launches over them
 struct HeffBatch {
     struct Launch {
-        int mode, shape, first, count, max_tiles, max_n, max_G;
+        int mode, shape, first, count, max_tiles, max_G;
+        long long max_n;
     };
     std::vector<spk::KInst> insts;
     std::vector<spk::KPrep> preps;

@@ -480,7 +480,7 @@ struct SitePlan {
     int nWr = 0;
     int c_wr(int e) const { return 2 * nW + 18 + e; }
     int c_r(int s, int u) const { return 2 * nW + 18 + nWr + 4 * s + u; }
-    // scratch sizes per quadrature point
+    // scratch of the plain path's passes per quadrature point
     long long Tsize = 0, Vsize = 0, Zsize = 0, Ztsize = 0;
     BList p1, yout, envl_out, p1r, envr_out;
     CList mixl, mixr;
@@ -1330,6 +1330,7 @@ void build_plan(sp_handle* h, int k) {
     if (!plain) {
         P.p1 = P.p1r = P.yout = P.envl_out = P.envr_out = BList{};
         P.mixl = P.mixr = CList{};
+        P.Tsize = P.Vsize = P.Zsize = P.Ztsize = 0;
     }
 
     // ================= tiled path =================
@@ -2329,7 +2330,7 @@ void diag(sp_handle* h, int k, double* dh, double* dn) {
     const Bond& br = h->bonds[k];
     const int* idx = P.ddg_idx.p;
     const int nnbl = int(bl.nb.size()), nnbr = int(br.nb.size()), nmix = int(P.dg_mix.size());
-    double* Ld = h->T.p;  // scratch of the block products, idle here
+    double* Ld = h->T.p;  // on the plain path scratch of the block products, idle here
     double* Rd = h->T.p + (long long)h->G * P.dg_nzl * bl.D;
     const spk::DiagSide left{P.ddg_src.p, idx, idx + bl.D, h->envL[k - 1].p, h->env[k - 1].size, Ld, P.dg_nzl, bl.D, nnbl, 0};
     const spk::DiagSide right{P.ddg_src.p + (size_t)P.dg_nzl * nnbl, idx + 2 * bl.D, idx + 2 * bl.D + br.D, h->envR[k].p,
@@ -3647,7 +3648,8 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
         });
         for (int k = 1; k <= h->L; ++k) {
             const SitePlan& P = h->plan[k - 1];
-            // the diagonals use the same scratch
+            // the diagonals use the scratch of the plain path's passes; a tiled
+            // state has it for them alone
             const long long dgT = (long long)P.dg_nzl * h->bonds[k - 1].D + (long long)P.dg_nzr * h->bonds[k].D;
             Tmax = std::max({Tmax, P.Tsize, P.Zsize, dgT});
             Vmax = std::max({Vmax, P.Vsize, P.Ztsize, (long long)P.dg_mix.size() * h->bonds[k - 1].D});

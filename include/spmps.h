@@ -208,8 +208,8 @@ int sp_heff_apply(sp_handle* h, int site, const double* x, double* y, double* ny
  * until the process ends) instead of the handle's buffers.  The call
  * allocates nothing.  Recorded into a graph, it reads the environments as they
  * are at each replay.  Tiled path only (SP_EINVAL otherwise); SP_EINVAL when
- * the site needs more than 2^21 partial slots per output (G x site size on
- * a fused site, G x the channel split x site size on the others).
+ * the site needs more than 2^21 partial slots per output (G x the parts that
+ * its channels are summed in x site size).
  * Every handle on one GPU shares that GPU's array: calls that overlap on one
  * GPU (on different streams, or from several threads) race and must be
  * ordered by the caller.  Its contents after a call are undefined. */

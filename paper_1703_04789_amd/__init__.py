@@ -479,7 +479,7 @@ class SPMPS:
         """Per-launch timing of H_eff x at site k: dict of (ms, flops, bytes)
         for the left product, the mixing and the right product (plain path),
         or for the product, the once-per-local-problem pre-mixing of the left
-        environment (block-product sites; not part of the product's time)
+        environment (wide MPOs; not part of the product's time)
         and the g sum (tiled path)."""
         out = np.zeros(9)
         _check(lib().sp_heff_profile(self._h, k, reps, _dev(x), _dev(y), _dev(ny), _dptr(out)))

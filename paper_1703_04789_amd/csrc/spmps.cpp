@@ -4404,10 +4404,10 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
         for (auto& e : ev) HIPCK(hipEventCreate(&e));
         double ms[3] = {0, 0, 0};
         double premix_ms = 0.0;
-        if (!plain && P.h_rows == 0) {
-            // the pre-mixed left environment of the block products is built
-            // once per local problem and reused by every product of the
-            // solve: timed on its own, outside the products
+        if (!plain && !P.mix_l.empty()) {
+            // the pre-mixed left environment is built once per local problem
+            // and reused by every product of the solve: timed on its own,
+            // outside the products
             h->lt_site = -1;
             HIPCK(hipEventRecord(ev[0], s));
             premix_left(h, site, heff_mode(h, site, false));

@@ -34,8 +34,9 @@ struct BufSet {
     double* p[kMaxBufs];
 };
 
-// Diagonal of H_eff / N_eff, in three launches (the spin-diagonal part of
-// the rotated MPO acts on the diagonals of the environments alone):
+// Diagonal of H_eff / N_eff (the spin-diagonal part of the rotated MPO acts on
+// the diagonals of the environments alone).  Narrow MPOs sum every term in
+// one launch (DiagTerm); wide ones take three:
 //   gather  Ld(g, z, p), Rd(g, z, p): the diagonals of the environment
 //           blocks of the particle-conserving channels z, state p of the bond
 //   mix     M(g, row, p) = sum over terms of coef * Ld(g, z, p)
@@ -69,7 +70,15 @@ struct DiagBlk {
     int row0, nrow;        // units: M rows row0 .. row0 + nrow
     int p0, q0;            // first state of the tile on the left, right bond
     int zl0;               // Rd channel of unit u: zlist[zl0 + u]
-    int is_n, pad0, pad1;  // 1: N_eff
+    int is_n;              // 1: N_eff
+    int t0, t1;            // one launch: the terms of the tile's (N, M) block
+    int r0, c0;            // and the tile's first row and column in it
+};
+// coef[cidx] L(r, r) R(c, c): the diagonals of an (N, M) block's rows and
+// columns, elements ld + 1 apart
+struct DiagTerm {
+    long long l_off, r_off;
+    int l_ld, r_ld, cidx, pad;
 };
 
 // QR of one gathered sector matrix: pieces are row-major blocks of a packed
@@ -222,6 +231,14 @@ void combine(hipStream_t s, const CTask* tasks, int ntasks, const CTerm* terms, 
 // doubles, ntot = the site size); nsplit = 1 sums straight into dh
 constexpr int kDiagTile = 32;
 constexpr int kDiagSplitMax = 8;
+// One launch up to so many terms of an (N, M) block, times G: its cost grows
+// with them (4 us, and 0.12 for each), that of three launches starts at 9.5.
+// 5: 4.3 us against 9.7 (L = 8, D = 64, G = 5); 27: 7.0 against 11.4 (L = 32,
+// D = 256, G = 9); 75: 17.9 against 18.3 (the same, G = 25); 114: 32.6 against
+// 26.8 (D = 400, G = 38), 15.5 against 17.8 at the second site of it
+constexpr int kDiagDirectMax = 80;
+void diag_direct(hipStream_t s, const DiagBlk* blks, int nblk, const DiagTerm* terms, const double* lenv, long long lsize,
+                 const double* renv, long long rsize, const double* coef, int ncoef, int G, double* dh, double* dn);
 void diag_gather(hipStream_t s, const DiagSide& left, const DiagSide& right, int G);
 void diag_mix(hipStream_t s, const DiagMix* mix, int nmix, const DiagMixTerm* terms, const double* Ld, int nzl, int Dl,
               const double* coef, int ncoef, int G, double* M);

@@ -185,29 +185,16 @@ __global__ __launch_bounds__(kThreads) void k_diag_mix(const DiagMix* __restrict
     }
 }
 
-// One tile of the diagonal of H_eff or N_eff.  Its units u = (g, row) are an
-// outer-product sum out(r, c) += M(u, r) Rd(u, c), staged through LDS 32
-// units at a time with the next chunk's loads issued before the products of
-// the current one; a thread owns column tid % 32 and rows tid / 32 + 8 i.
-// Every environment value is read once per tile instead of once per element,
-// and a right channel's terms are mixed once per bond state: the centre of
-// the K = 12, D = 128, G = 11 ab-initio state has 8600 terms per sigma but 250
-// rows, and its three launches take the diagonal from 3.8 ms (one work-group
-// summing every term of every element of a block) to under 0.1 ms.  A part of
-// 256 units is 8 staged chunks; the Hubbard MPO (2 rows) has one part.
-__global__ __launch_bounds__(kThreads) void k_diag(const DiagBlk* __restrict__ blks, const int* __restrict__ zlist,
-                                                     const double* __restrict__ M, int nmix, int Dl,
-                                                     const double* __restrict__ Rd, int nzr, int Dr, int G,
-                                                     double* __restrict__ dh, double* __restrict__ dn,
-                                                     double* __restrict__ part, long long ntot) {
+// A tile of an outer-product sum out(r, c) = sum over units u0 .. u1 of
+// lv(u, r) rv(u, c), staged through LDS 32 units at a time with the next
+// chunk's loads issued before the products of the current one; a thread owns
+// column tid % 32 and rows tid / 32 + 8 i.  value(u, x, l, r) gives the left
+// value of row x and the right one of column x.
+template <class F>
+__device__ inline void diag_tile(const DiagBlk& b, int u0, int u1, double* __restrict__ out, F value) {
     constexpr int T = kDiagTile, U = 32, PER = U * T / kThreads;
     static_assert(PER == 4 && T == 32, "four staged values of either operand per thread");
     __shared__ double Ls[U][T], Rs[U][T];
-    const DiagBlk b = blks[blockIdx.x];
-    const int nsplit = b.is_n ? 1 : gridDim.y, j = blockIdx.y;
-    if (j >= nsplit) return;
-    const int UT = G * b.nrow;
-    const int u0 = int((long long)UT * j / nsplit), u1 = int((long long)UT * (j + 1) / nsplit);
     const int x = threadIdx.x % T, y = threadIdx.x / T;
     double lv[PER], rv[PER], acc[PER] = {0.0, 0.0, 0.0, 0.0};
     auto fetch = [&](int ub) {
@@ -215,11 +202,7 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagBlk* __restrict__ b
         for (int i = 0; i < PER; ++i) {
             const int u = ub + y + 8 * i;
             lv[i] = rv[i] = 0.0;
-            if (u < u1) {
-                const int g = u / b.nrow, q = u - g * b.nrow;
-                if (x < b.rows) lv[i] = M[((long long)g * nmix + b.row0 + q) * Dl + b.p0 + x];
-                if (x < b.cols) rv[i] = Rd[((long long)g * nzr + zlist[b.zl0 + q]) * Dr + b.q0 + x];
-            }
+            if (u < u1) value(u, x, lv[i], rv[i]);
         }
     };
     if (u0 < u1) fetch(u0);
@@ -240,12 +223,56 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagBlk* __restrict__ b
         }
         __syncthreads();
     }
-    double* __restrict__ out = b.is_n ? dn : (nsplit == 1 ? dh : part + (long long)j * ntot);
     if (x < b.cols) {
 #pragma unroll
         for (int i = 0; i < PER; ++i)
             if (y + 8 * i < b.rows) out[b.x_off + (y + 8 * i) * b.ldc + x] = acc[i];
     }
+}
+
+// One tile of the diagonal of H_eff or N_eff from the gathered diagonals, its
+// units u = (g, row).  Every environment value is read once per tile instead of
+// once per element, and a right channel's terms are mixed once per bond state:
+// the centre of the K = 12, D = 128, G = 11 ab-initio state has 8600 terms per
+// sigma but 250 rows, and its three launches take the diagonal from 3.8 ms (one
+// work-group summing every term of every element of a block) to under 0.1 ms.
+// A part of 256 units is 8 staged chunks.
+__global__ __launch_bounds__(kThreads) void k_diag(const DiagBlk* __restrict__ blks, const int* __restrict__ zlist,
+                                                     const double* __restrict__ M, int nmix, int Dl,
+                                                     const double* __restrict__ Rd, int nzr, int Dr, int G,
+                                                     double* __restrict__ dh, double* __restrict__ dn,
+                                                     double* __restrict__ part, long long ntot) {
+    const DiagBlk b = blks[blockIdx.x];
+    const int nsplit = b.is_n ? 1 : gridDim.y, j = blockIdx.y;
+    if (j >= nsplit) return;
+    const int UT = G * b.nrow;
+    const int u0 = int((long long)UT * j / nsplit), u1 = int((long long)UT * (j + 1) / nsplit);
+    double* __restrict__ out = b.is_n ? dn : (nsplit == 1 ? dh : part + (long long)j * ntot);
+    diag_tile(b, u0, u1, out, [&](int u, int x, double& l, double& r) {
+        const int g = u / b.nrow, q = u - g * b.nrow;
+        if (x < b.rows) l = M[((long long)g * nmix + b.row0 + q) * Dl + b.p0 + x];
+        if (x < b.cols) r = Rd[((long long)g * nzr + zlist[b.zl0 + q]) * Dr + b.q0 + x];
+    });
+}
+
+// The same tile from the environments themselves, its units (g, term): one
+// launch for both diagonals.  A chain of dependent reads bounds it (tile, term,
+// coefficient and diagonals, 4 us in all for a few units); every tile reads the
+// strided diagonals again, which many units or tiles make dearer than the
+// gathered rows of three launches.
+__global__ __launch_bounds__(kThreads) void k_diag_direct(const DiagBlk* __restrict__ blks, const DiagTerm* __restrict__ terms,
+                                                            const double* __restrict__ lenv, long long lsize,
+                                                            const double* __restrict__ renv, long long rsize,
+                                                            const double* __restrict__ coef, int ncoef, int G,
+                                                            double* __restrict__ dh, double* __restrict__ dn) {
+    const DiagBlk b = blks[blockIdx.x];
+    const int nt = b.t1 - b.t0;
+    diag_tile(b, 0, G * nt, b.is_n ? dn : dh, [&](int u, int x, double& l, double& r) {
+        const int g = u / nt;
+        const DiagTerm t = terms[b.t0 + u - g * nt];
+        if (x < b.rows) l = coef[(long long)g * ncoef + t.cidx] * lenv[g * lsize + t.l_off + (b.r0 + x) * (t.l_ld + 1LL)];
+        if (x < b.cols) r = renv[g * rsize + t.r_off + (b.c0 + x) * (t.r_ld + 1LL)];
+    });
 }
 
 __global__ __launch_bounds__(kThreads) void k_diag_sum(const double* __restrict__ part, int nsplit, long long ntot,
@@ -1132,6 +1159,12 @@ void diag_blocks(hipStream_t s, const DiagBlk* blks, int nb, const int* zlist, c
     if (nsplit > 1)
         hipLaunchKernelGGL(k_diag_sum, dim3((unsigned)((ntot + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, part,
                            nsplit, ntot, dh);
+}
+void diag_direct(hipStream_t s, const DiagBlk* blks, int nb, const DiagTerm* terms, const double* lenv, long long lsize,
+                 const double* renv, long long rsize, const double* coef, int ncoef, int G, double* dh, double* dn) {
+    if (nb > 0)
+        hipLaunchKernelGGL(k_diag_direct, dim3(nb), dim3(kThreads), 0, s, blks, terms, lenv, lsize, renv, rsize, coef, ncoef,
+                           G, dh, dn);
 }
 void qr_sectors(hipStream_t s, const QrTask* tasks, int ntasks, const QrPiece* pieces, double* site,
                 double* scratch, double* rout, const QrShape& shape) {

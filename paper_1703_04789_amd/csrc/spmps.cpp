@@ -492,11 +492,14 @@ struct SitePlan {
     std::vector<spk::DiagMix> dg_mix;
     std::vector<spk::DiagMixTerm> dg_term;
     std::vector<spk::DiagBlk> dg_blk;
+    bool dg_direct = false;                     // one launch over dg_dterm, without the lists above
+    std::vector<spk::DiagTerm> dg_dterm;
     DRef<spk::DiagSrc> ddg_src;
     DRef<int> ddg_idx;
     DRef<spk::DiagMix> ddg_mix;
     DRef<spk::DiagMixTerm> ddg_term;
     DRef<spk::DiagBlk> ddg_blk;
+    DRef<spk::DiagTerm> ddg_dterm;
     // gauge moves
     std::vector<spk::QrTask> qr_tasks, lq_tasks;
     std::vector<spk::QrPiece> qr_pieces, lq_pieces;
@@ -1173,10 +1176,26 @@ void build_plan(sp_handle* h, int k) {
                 }
             }
         }
-    // ---- diagonal of H_eff and N_eff: the particle-conserving channels z of
-    // both bonds, per sigma one mixed row per right channel with terms, and
-    // tiles of the site's blocks
-    {
+    // ---- diagonal of H_eff and N_eff: tiles of the site's blocks
+    // the particle-conserving blocks of an MPO entry at an (N, M) block
+    auto diag_blocks = [&](int c, int cp, const XBlk& X, int& e, int& re) {
+        const int i = bl.sec[X.sa].nb, j = br.sec[X.sb].nb;
+        e = el.find(c, i);
+        re = er.find(cp, j);
+        return e >= 0 && el.blk[e].j == i && re >= 0 && er.blk[re].j == j;
+    };
+    P.dg_direct = true;
+    for (size_t q = 0; q < si.blk.size() && P.dg_direct; ++q) {
+        int units = 0, e, re;
+        for (const auto& ent : byD[si.blk[q].s])
+            if (diag_blocks(ent[0], ent[1], si.blk[q], e, re) && (units += G) > spk::kDiagDirectMax) break;
+        P.dg_direct = units <= spk::kDiagDirectMax;
+    }
+    std::array<int, 4> row0{}, nrow{}, zl0{}, row_n{};
+    int zn = 0;
+    // with many terms: the particle-conserving channels z of both bonds, and
+    // per sigma one mixed row per right channel with terms
+    if (!P.dg_direct) {
         std::vector<int> zl(wl, -1), zr(wr, -1);
         auto side = [&](const Bond& bd, const EnvLayout& e, std::vector<int>& z, int& nz) {
             for (int c = 0; c < e.nc; ++c) {
@@ -1198,7 +1217,6 @@ void build_plan(sp_handle* h, int k) {
         side(bl, el, zl, P.dg_nzl);
         side(br, er, zr, P.dg_nzr);
         SP_REQUIRE(zl[0] >= 0 && zr[lastR] >= 0, "internal: identity channels must conserve N");
-        std::array<int, 4> row0{}, nrow{}, zl0{}, row_n{};
         int most = 1;
         for (int sig = 0; sig < 4; ++sig) {
             std::vector<std::vector<spk::DiagMixTerm>> of(wr);
@@ -1216,37 +1234,54 @@ void build_plan(sp_handle* h, int k) {
             nrow[sig] = int(P.dg_mix.size()) - row0[sig];
             most = std::max(most, G * nrow[sig]);
         }
-        const int zn = int(P.dg_idx.size());  // N_eff: the two identity strings
+        zn = int(P.dg_idx.size());  // N_eff: the two identity strings
         P.dg_idx.push_back(zr[lastR]);
         for (int sig = 0; sig < 4; ++sig) {
             row_n[sig] = int(P.dg_mix.size());
             P.dg_term.push_back({zl[0], P.c_gr(sig, sig)});
             P.dg_mix.push_back(spk::DiagMix{int(P.dg_term.size()) - 1, int(P.dg_term.size())});
         }
-        for (const XBlk& X : si.blk) {
-            const Sector& SA = bl.sec[X.sa];
-            const Sector& SB = br.sec[X.sb];
-            SP_REQUIRE(X.off + (long long)X.rows * X.cols < INT32_MAX, "site too large for 32-bit offsets");
-            for (int r = 0; r < X.rows; r += spk::kDiagTile)
-                for (int c = 0; c < X.cols; c += spk::kDiagTile)
-                    for (int n = 0; n < 2; ++n) {
-                        spk::DiagBlk d{};
-                        d.x_off = int(X.off) + r * X.cols + c;
-                        d.ldc = X.cols;
-                        d.rows = std::min(spk::kDiagTile, X.rows - r);
-                        d.cols = std::min(spk::kDiagTile, X.cols - c);
-                        d.row0 = n ? row_n[X.s] : row0[X.s];
-                        d.nrow = n ? 1 : nrow[X.s];
-                        d.p0 = SA.off + r;
-                        d.q0 = SB.off + c;
-                        d.zl0 = n ? zn : zl0[X.s];
-                        d.is_n = n;
-                        P.dg_blk.push_back(d);
-                    }
-        }
         // parts of a tile: about 256 units (8 staged chunks) each, so that
         // the hundreds of rows of a wide MPO run as parallel work-groups
         P.dg_split = std::min(std::max(most / 256, 1), spk::kDiagSplitMax);
+    }
+    for (const XBlk& X : si.blk) {
+        const Sector& SA = bl.sec[X.sa];
+        const Sector& SB = br.sec[X.sb];
+        const int t0 = int(P.dg_dterm.size());
+        int t1 = t0;  // H_eff: terms t0 .. t1, N_eff: the one after them
+        if (P.dg_direct) {
+            auto term = [&](int c, int cp, int cidx) {
+                int e, re;
+                if (!diag_blocks(c, cp, X, e, re)) return;
+                const EnvBlk &l = el.blk[e], &r = er.blk[re];
+                P.dg_dterm.push_back(spk::DiagTerm{l.off + SA.ro * (l.cols + 1LL), r.off + SB.ro * (r.cols + 1LL), l.cols, r.cols, cidx, 0});
+            };
+            for (const auto& ent : byD[X.s]) term(ent[0], ent[1], P.c_cwt(ent[2]));
+            t1 = int(P.dg_dterm.size());
+            term(0, lastR, P.c_gr(X.s, X.s));
+        }
+        SP_REQUIRE(X.off + (long long)X.rows * X.cols < INT32_MAX, "site too large for 32-bit offsets");
+        for (int r = 0; r < X.rows; r += spk::kDiagTile)
+            for (int c = 0; c < X.cols; c += spk::kDiagTile)
+                for (int n = 0; n < 2; ++n) {
+                    spk::DiagBlk d{};
+                    d.x_off = int(X.off) + r * X.cols + c;
+                    d.ldc = X.cols;
+                    d.rows = std::min(spk::kDiagTile, X.rows - r);
+                    d.cols = std::min(spk::kDiagTile, X.cols - c);
+                    d.row0 = n ? row_n[X.s] : row0[X.s];
+                    d.nrow = n ? 1 : nrow[X.s];
+                    d.p0 = SA.off + r;
+                    d.q0 = SB.off + c;
+                    d.zl0 = n ? zn : zl0[X.s];
+                    d.is_n = n;
+                    d.t0 = n ? t1 : t0;
+                    d.t1 = n ? int(P.dg_dterm.size()) : t1;
+                    d.r0 = r;
+                    d.c0 = c;
+                    P.dg_blk.push_back(d);
+                }
     }
     // ---- QR per right sector (left-orthonormalise) and LQ per left sector
     P.qr_roff.assign(br.sec.size(), -1);
@@ -1766,6 +1801,7 @@ void upload_plan(sp_handle* h, int k, Upload& u) {
     u.add(P.ddg_mix, P.dg_mix);
     u.add(P.ddg_term, P.dg_term);
     u.add(P.ddg_blk, P.dg_blk);
+    u.add(P.ddg_dterm, P.dg_dterm);
     u.add(P.dqr_tasks, P.qr_tasks);
     u.add(P.dlq_tasks, P.lq_tasks);
     u.add(P.dqr_pieces, P.qr_pieces);
@@ -1891,7 +1927,8 @@ void validate_diag(const sp_handle* h, int k) {
     const Bond& br = h->bonds[k];
     const int nidx = int(P.dg_idx.size()), nmix = int(P.dg_mix.size());
     const size_t nl = size_t(P.dg_nzl) * bl.nb.size(), nr = size_t(P.dg_nzr) * br.nb.size();
-    if (P.dg_src.size() != nl + nr || nidx < 2 * (bl.D + br.D)) throw SpError(SP_EINVAL, "internal: diagonal sources");
+    const bool direct = P.dg_direct;
+    if (P.dg_src.size() != nl + nr || (!direct && nidx < 2 * (bl.D + br.D))) throw SpError(SP_EINVAL, "internal: diagonal sources");
     for (size_t q = 0; q < nl + nr; ++q) {
         const spk::DiagSrc& d = P.dg_src[q];
         if (d.ld < 0) continue;
@@ -1908,6 +1945,17 @@ void validate_diag(const sp_handle* h, int k) {
         if (d.rows < 1 || d.cols < 1 || d.rows > spk::kDiagTile || d.cols > spk::kDiagTile || d.nrow < 0)
             throw SpError(SP_EINVAL, "internal: diagonal tile");
         check_span(d.x_off, d.x_off + (long long)(d.rows - 1) * d.ldc + d.cols - 1, h->sites[k - 1].size, "diagonal block");
+        if (direct) {
+            if (d.t0 < 0 || d.t1 < d.t0 || d.t1 > int(P.dg_dterm.size()) || d.r0 < 0 || d.c0 < 0)
+                throw SpError(SP_EINVAL, "internal: diagonal terms");
+            for (int i = d.t0; i < d.t1; ++i) {
+                const spk::DiagTerm& t = P.dg_dterm[i];
+                check_span(t.l_off, t.l_off + (d.r0 + d.rows - 1) * (t.l_ld + 1LL), h->env[k - 1].size, "diagonal rows");
+                check_span(t.r_off, t.r_off + (d.c0 + d.cols - 1) * (t.r_ld + 1LL), h->env[k].size, "diagonal columns");
+                check_span(t.cidx, t.cidx, P.nc, "diagonal coefficient");
+            }
+            continue;
+        }
         check_span(d.p0, d.p0 + d.rows - 1, bl.D, "diagonal rows");
         check_span(d.q0, d.q0 + d.cols - 1, br.D, "diagonal columns");
         if (d.nrow == 0) continue;
@@ -2326,6 +2374,11 @@ void env_right(sp_handle* h, int k) {
 void diag(sp_handle* h, int k, double* dh, double* dn) {
     if (!h->Lvalid[k - 1] || !h->Rvalid[k]) throw SpError(SP_ESTATE, "environments for the diagonal are not built");
     SitePlan& P = h->plan[k - 1];
+    if (P.dg_direct) {
+        spk::diag_direct(h->stream, P.ddg_blk.p, int(P.dg_blk.size()), P.ddg_dterm.p, h->envL[k - 1].p, h->env[k - 1].size,
+                         h->envR[k].p, h->env[k].size, P.coef.p, P.nc, h->G, dh, dn);
+        return;
+    }
     const Bond& bl = h->bonds[k - 1];
     const Bond& br = h->bonds[k];
     const int* idx = P.ddg_idx.p;

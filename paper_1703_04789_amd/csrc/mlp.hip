@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_targets_grouped(const doubl
 // column + ncol for every nsplit-th row, so that a row read from LDS serves
 // two units; the splits' sums are added in order at the end.  FP64 FMAs bound
 // it (7 us for 60001 rows of 256 units); four rows per work-group-wide
-// reduction took 585 us, this form 27.
+// reduction took 585 us, this form 26.
 __global__ __launch_bounds__(kTileThreads) void k_mlp_grad(const float* __restrict__ w, int H,
                                                            const float* __restrict__ F, const float* __restrict__ Y,
                                                            long long row0, long long stride, long long count,
@@ -404,42 +404,128 @@ __global__ __launch_bounds__(kTileThreads) void k_mlp_grad(const float* __restri
     }
 }
 
-// Adam step: gradient = scale * (sum of the partials, 16 interleaved runs of
-// work-groups added in order).  A work-group takes 16 neighbouring parameters,
-// so that the partials are read as whole lines by many CUs (one work-group for
-// all of them took 109 us for 1793 parameters, this 6).
-constexpr int kAdamPar = 16, kAdamRun = kMlpThreads / kAdamPar;
+// The same for up to kFewRows rows: a thread per hidden unit, and the rows'
+// outputs summed by 16 lanes each.  The tiles above take 5 to 10 us however few
+// their rows are (512 threads, six barriers and the splits' sums): with 256
+// units 1 row 9.6 -> 4.0 us, 16 rows 10.4 -> 5.7; 20 rows in tiles 10.5.
+constexpr int kFewRows = 16;
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_few(const float* __restrict__ w, int H,
+                                                              const float* __restrict__ F, const float* __restrict__ Y,
+                                                              long long row0, long long stride, int count,
+                                                              double* __restrict__ gpart) {
+    static_assert(kMlpMaxHidden <= kMlpThreads && kFewRows * 16 <= kMlpThreads, "a thread per hidden unit, 16 per row");
+    constexpr int NG = kMlpIn + 2, AT = 4;  // rows at once
+    __shared__ double sf[kFewRows][kRow], hid[kFewRows][kMlpThreads + 2], err[kFewRows];
+    const int j = threadIdx.x;
+    double W[NG], g[NG], z[kFewRows];
+#pragma unroll
+    for (int c = 0; c < NG; ++c) {
+        W[c] = j < H ? double(w[c < kMlpIn ? j * kMlpIn + c : H * c + j]) : 0.0;
+        g[c] = 0.0;
+    }
+    const double b2 = w[H * NG];
+    if (j < kFewRows * kRow) {
+        const int r = j / kRow, c = j % kRow;
+        const long long row = row0 + r * stride;
+        sf[r][c] = r < count ? double(c < kMlpIn ? F[row * kMlpIn + c] : Y[row]) : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r0 = 0; r0 < kFewRows; r0 += AT) {
+        if (r0 >= count) break;
+#pragma unroll
+        for (int r = r0; r < r0 + AT; ++r) {
+            z[r] = W[kMlpIn];
+#pragma unroll
+            for (int c = 0; c < kMlpIn; ++c) z[r] = fma(W[c], sf[r][c], z[r]);
+            hid[r][j] = W[kMlpIn + 1] * fmax(z[r], 0.0);
+        }
+    }
+    __syncthreads();
+    if (j < 16 * count) {
+        const int r = j / 16, q = j % 16;
+        double p = 0.0;
+        for (int i = 0; i < H; i += 64)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) p += hid[r][i + 16 * t + q];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) p += __shfl_xor(p, o, 16);
+        if (q == 0) err[r] = b2 + p - sf[r][kMlpIn];
+    }
+    __syncthreads();
+    double gb2 = 0.0, loss = 0.0;
+#pragma unroll
+    for (int r0 = 0; r0 < kFewRows; r0 += AT) {
+        if (r0 >= count) break;
+#pragma unroll
+        for (int r = r0; r < r0 + AT; ++r) {
+            const double dy = r < count ? err[r] : 0.0;
+            gb2 += dy;
+            loss = fma(dy, dy, loss);
+            g[kMlpIn + 1] = fma(dy, fmax(z[r], 0.0), g[kMlpIn + 1]);
+            if (z[r] > 0.0) {
+                const double dz = dy * W[kMlpIn + 1];
+                g[kMlpIn] += dz;
+#pragma unroll
+                for (int c = 0; c < kMlpIn; ++c) g[c] = fma(dz, sf[r][c], g[c]);
+            }
+        }
+    }
+    if (j < H)
+#pragma unroll
+        for (int c = 0; c < NG; ++c) gpart[c < kMlpIn ? j * kMlpIn + c : H * c + j] = g[c];
+    if (j == 0) {
+        gpart[H * NG] = gb2;
+        gpart[mlp_size(H)] = loss;
+    }
+}
+
+// Adam step: gradient = scale * (sum of the partials, interleaved runs of
+// work-groups added in order).  A work-group takes PAR neighbouring parameters:
+// 16 of them where there are partials to sum, so that these are read as whole
+// lines by many CUs (one work-group for all parameters took 109 us for 1793 of
+// them, this 6); a single partial has nothing to spread, and fewer work-groups
+// end sooner.
+template <int PAR>
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_adam(float* __restrict__ w, double* __restrict__ m,
                                                           double* __restrict__ v, int H,
                                                           const double* __restrict__ gpart, int nparts,
                                                           double scale, double lr, int step,
                                                           double* __restrict__ loss_out) {
-    __shared__ double run[kAdamRun][kAdamPar];
+    constexpr int RUN = kMlpThreads / PAR;
+    __shared__ double run[RUN][PAR];
     const long long P = mlp_size(H) + 1;
-    const int i = threadIdx.x % kAdamPar, r = threadIdx.x / kAdamPar;
-    const long long p = (long long)blockIdx.x * kAdamPar + i;
-    double g = 0.0;
+    const int i = threadIdx.x % PAR, r = threadIdx.x / PAR;
+    const long long p = (long long)blockIdx.x * PAR + i;
+    const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
+    double g = 0.0, mp = 0.0, vp = 0.0, wp = 0.0;
+    if (r == 0 && p < P - 1) {  // read while the partials are
+        mp = m[p];
+        vp = v[p];
+        wp = double(w[p]);
+    }
+    const double c1 = 1.0 - pow(b1, step), c2 = 1.0 - pow(b2, step);
     if (p < P)
 #pragma unroll 8
-        for (int b = r; b < nparts; b += kAdamRun) g += gpart[b * P + p];
-    run[r][i] = g;
-    __syncthreads();
-    if (r > 0 || p >= P) return;
-    g = 0.0;
+        for (int b = r; b < nparts; b += RUN) g += gpart[b * P + p];
+    if constexpr (RUN > 1) {
+        run[r][i] = g;
+        __syncthreads();
+        g = 0.0;
 #pragma unroll
-    for (int q = 0; q < kAdamRun; ++q) g += run[q][i];
+        for (int q = 0; q < RUN; ++q) g += run[q][i];
+    }
+    if (r > 0 || p >= P) return;
     if (p == P - 1) {
         if (loss_out) *loss_out = 0.5 * g * scale;
         return;
     }
-    const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
-    const double c1 = 1.0 - pow(b1, step), c2 = 1.0 - pow(b2, step);
     g *= scale;
-    const double mm = b1 * m[p] + (1.0 - b1) * g;
-    const double vv = b2 * v[p] + (1.0 - b2) * g * g;
+    const double mm = b1 * mp + (1.0 - b1) * g;
+    const double vv = b2 * vp + (1.0 - b2) * g * g;
     m[p] = mm;
     v[p] = vv;
-    w[p] = float(double(w[p]) - lr * (mm / c1) / (sqrt(vv / c2) + eps));
+    w[p] = float(wp - lr * (mm / c1) / (sqrt(vv / c2) + eps));
 }
 
 inline int blocks_for(long long n) { return int((n + kMlpThreads - 1) / kMlpThreads); }
@@ -496,14 +582,21 @@ void mlp_targets_grouped(hipStream_t s, const double* X, long long ldx, int nrec
 
 void mlp_grad(hipStream_t s, const float* w, int H, const float* F, const float* Y, long long row0, long long stride,
               long long count, double* gpart, int nparts) {
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nparts), dim3(kTileThreads), 0, s, w, H, F, Y, row0, stride, count, gpart);
+    if (count <= kFewRows && nparts == 1)
+        hipLaunchKernelGGL(k_mlp_grad_few, dim3(1), dim3(kMlpThreads), 0, s, w, H, F, Y, row0, stride, int(count), gpart);
+    else
+        hipLaunchKernelGGL(k_mlp_grad, dim3(nparts), dim3(kTileThreads), 0, s, w, H, F, Y, row0, stride, count, gpart);
 }
 
 void mlp_adam(hipStream_t s, float* w, double* m, double* v, int H, const double* gpart, int nparts, double scale,
               double lr, int step, double* loss_out) {
-    const int groups = int((mlp_size(H) + 1 + kAdamPar - 1) / kAdamPar);
-    hipLaunchKernelGGL(k_mlp_adam, dim3(groups), dim3(kMlpThreads), 0, s, w, m, v, H, gpart, nparts, scale, lr, step,
-                       loss_out);
+    const long long P = mlp_size(H) + 1;
+    if (nparts == 1)
+        hipLaunchKernelGGL(k_mlp_adam<kMlpThreads>, dim3(blocks_for(P)), dim3(kMlpThreads), 0, s, w, m, v, H, gpart, nparts,
+                           scale, lr, step, loss_out);
+    else
+        hipLaunchKernelGGL(k_mlp_adam<16>, dim3(int((P + 15) / 16)), dim3(kMlpThreads), 0, s, w, m, v, H, gpart, nparts,
+                           scale, lr, step, loss_out);
 }
 
 }  // namespace spk

@@ -34,8 +34,8 @@ def log(msg):
 
 
 def fused_kernel_sha256():
-    """sha256 of the fused kernel's source and the header of its task
-    layout, which key the committed hardware-counter summaries."""
+    """sha256 of the product kernel's source and the header of its lists,
+    which key the committed hardware-counter summaries."""
     import hashlib
     hs = hashlib.sha256()
     for f in ("chain.hip", "kernels.h"):
@@ -44,7 +44,7 @@ def fused_kernel_sha256():
 
 
 def measured_traffic():
-    """HBM bytes per launch of the fused kernel from the committed rocprofv3
+    """HBM bytes per launch of the chained product from the committed rocprofv3
     summary (FETCH_SIZE and WRITE_SIZE, calibrated on a 64 MiB copy), or None
     when the kernel source has changed since those counters were taken."""
     import hashlib
@@ -236,15 +236,15 @@ def abinitio_runs(sp, W, torch, sweeps=6):
     f32["dE_vs_fp64_per_sweep"] = [a - b for a, b in zip(f32["energies"], t64["energies"])]
     f32["matched"] = abs(f32["dE_vs_fp64_per_sweep"][-1]) <= 1e-6
     f32["speedup_site_steps_vs_fp64_tiled"] = f32["value"] / t64["value"] if f32["matched"] else None
-    f32["note"] = "fused and tiled products: FP32 fused kernel, FP64 block products; FP64 Rayleigh quotient per step"
+    f32["note"] = "products FP32 at sites with a fused plan, FP64 at the others; FP64 Rayleigh quotient per step"
     target = t64["energies"][-1] + 1e-6
     b16, _ = run("tiled", "bf16x3", 1e-5, 2 * sweeps, target=target)
     n_eq = min(len(b16["energies"]), len(t64["energies"]))
     b16["dE_vs_fp64_per_sweep"] = [a - b for a, b in zip(b16["energies"][:n_eq], t64["energies"][:n_eq])]
     b16["reached_fp64_energy"] = b16["energies"][-1] <= target
     b16["time_to_fp64_energy_speedup"] = (t64["seconds"] / b16["seconds"]) if b16["reached_fp64_energy"] else None
-    b16["note"] = ("block products in split BF16 (hi+lo, three matrix-core products, FP32 accumulation), fused "
-                   "products FP32, FP64 Rayleigh quotient per step; its looser local solves and metric threshold "
+    b16["note"] = ("block products in split BF16 (hi+lo, three matrix-core products, FP32 accumulation), products "
+                   "FP32 at sites with a fused plan, FP64 Rayleigh quotient per step; its looser local solves and metric threshold "
                    "follow another trajectory, so it is compared by the time to reach the FP64 run's energy "
                    f"after {sweeps} sweeps (within 1e-6), not at equal sweep counts")
     log(f"[bench] {wl.name}: FP32 dE {f32['dE_vs_fp64_per_sweep'][-1]:.2e} (matched {f32['matched']}); split BF16 "
@@ -475,7 +475,7 @@ def main():
     ap.add_argument("--tol", type=float, default=1e-9)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-autotune", action="store_true",
-                    help="keep the default fused-kernel plans instead of timing them per site (sp_autotune)")
+                    help="keep the default H_eff plans instead of timing them per site (sp_autotune)")
     ap.add_argument("--path", default="tiled", choices=["tiled", "plain"])
     ap.add_argument("--precision", default="fp64", choices=["fp64", "fp32", "bf16x3"],
                     help="precision of the H_eff products inside the local solves (SP_FP64 / SP_FP32 / SP_BF16X3)")
@@ -575,7 +575,7 @@ def main():
                        precision=precision)
         tuned = None
         if path == "tiled" and not args.no_autotune:
-            # the fused kernel's LDS budget (rows per task) of every site, by timing
+            # the H_eff plan of every site (in FP64 all plans run the same products)
             tuned = gpu.autotune(reps=5)
         kw = dict(tol=tol, max_iter=args.max_iter, max_sub=args.max_sub, keep=args.keep)
         if path == "tiled":

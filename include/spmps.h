@@ -248,14 +248,14 @@ int sp_autotune(sp_handle* h, int reps, int* budget_out, int* rows_out, double* 
 
 /* Current H_eff plan of a site: rows per task of the fused plan and its
  * LDS in doubles, or 0 and 0 (plain path, or a tiled-path site that runs the
- * tiled block products).  Host only. */
+ * block products).  Host only. */
 int sp_heff_plan(const sp_handle* h, int site, int* rows, int* lds_doubles);
 
 /* Choose the H_eff plan of one site (tiled path): a fused plan with an LDS
  * budget of `lds_budget` doubles per work-group (1..18432; it sets the rows
  * per task), or 0 for the block products.  A budget that no
- * particle-number block of the site fits also selects the tiled products.
- * *rows (optional) receives the rows per task, 0 for the tiled products.
+ * particle-number block of the site fits also selects the block products.
+ * *rows (optional) receives the rows per task, 0 for the block products.
  * In FP64 the products are the same either way.  Synchronises. */
 int sp_set_heff_plan(sp_handle* h, int site, int lds_budget, int* rows);
 

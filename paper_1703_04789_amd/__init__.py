@@ -561,7 +561,7 @@ class SPMPS:
 
     def heff_plan(self, site):
         """(rows per task, LDS doubles) of the site's fused plan; (0, 0) when
-        the site runs the tiled block products or the plain path."""
+        the site runs the block products or the plain path."""
         rows, lds = ctypes.c_int(0), ctypes.c_int(0)
         _check(lib().sp_heff_plan(self._h, site, ctypes.byref(rows), ctypes.byref(lds)))
         return rows.value, lds.value

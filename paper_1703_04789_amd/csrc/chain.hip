@@ -15,14 +15,15 @@
 // dealt to the wavefronts, whose sums are added through LDS in a fixed order.
 // What bounds it: at narrow MPOs the latency of a wavefront's chain of loads
 // (matrix cores 22 % busy at the L = 32, D = 256, G = 9 Hubbard centre); at
-// wide ones the L2 (39 % busy, 12 TB/s of L2 reads at the K = 12, D = 128,
-// G = 11 ab-initio centre).  The next chunk's loads are issued before the
-// current chunk's products; deeper prefetch and tiles of 48 x 48 were slower
-// (registers, so fewer wavefronts).  Calls of H_eff x and N_eff x, before
-// (FP64 FMAs through LDS; block products with intermediates in memory) and now:
-// Hubbard L = 32, D = 256 45 -> 24 us, L = 48, D = 512 145 -> 63, ab-initio
-// K = 12, D = 128 496 -> 227; an environment update at L = 32, D = 256 (four
-// launches of block products before) 75 -> 26 us.
+// wide ones the reads from the L2 (12.5 TB/s at the K = 12, D = 128, G = 11
+// ab-initio centre, the matrix cores 41 % busy there, three fifths of that on
+// padding).  The next chunk's loads are issued before the current chunk's
+// products; deeper prefetch and tiles of 48 x 48 were slower (registers, so
+// fewer wavefronts).  Calls of H_eff x and N_eff x, before (FP64 FMAs through
+// LDS; block products with intermediates in memory) and now: Hubbard L = 32,
+// D = 256 45 -> 24 us, L = 48, D = 512 145 -> 63, ab-initio K = 12, D = 128
+// 497 -> 224; an environment update at L = 32, D = 256 (four launches of block
+// products before) 75 -> 28 us.
 #include "kernels.h"
 
 #include <type_traits>

@@ -524,8 +524,9 @@ struct SitePlan {
     MixList mix_l, mix_r;                    // empty: the products read the environment itself
     std::vector<int> rmap_h;
     DRef<int> rmap;
-    // fused plan of H_eff x: rows per task and LDS (doubles) of the row-chunk
-    // form; 0: the site's MPO is too wide for one
+    // fused plan of H_eff x, which sets its arithmetic in the reduced
+    // precisions: rows per task and LDS (doubles); 0: the site's MPO is too
+    // wide for one
     int h_rows = 0;
     int h_lds = 0;
 };
@@ -561,7 +562,7 @@ struct sp_handle {
     std::vector<SitePlan> plan;            // index k-1
     int path = SP_PATH_TILED;
     DArr<double> T, V, qr_scratch, qr_r, tmp_site, Xd, Xr, ypart, nypart;
-    // pre-mixed left environment of one site (tiled block products); valid
+    // pre-mixed environment of one site (tiled path): the left one is valid
     // for site lt_site while the generation of L[lt_site - 1] is lt_gen
     DArr<double> LT;
     long long LT_cap = 0;
@@ -615,8 +616,8 @@ struct sp_handle {
     }
 };
 
-// reduced-precision local solves (SP_FP32 or SP_BF16X3): FP32 fused products,
-// FP64 Rayleigh quotient per site step, looser canonical orthogonalisation
+// reduced-precision local solves (SP_FP32 or SP_BF16X3): FP32 products at
+// sites with a fused plan, FP64 Rayleigh quotient per site step, looser canonical orthogonalisation
 inline bool reduced(const sp_handle* h) { return h->precision != SP_FP64; }
 // canonical orthogonalisation of the projected metric: eigenvalues below
 // drop x the largest are discarded; the threshold sits above the relative
@@ -1397,6 +1398,11 @@ void build_plan(sp_handle* h, int k) {
 constexpr long long kNoAllocSlots = 1LL << 21;
 
 // H_eff x of a wide MPO: work-groups aimed at, and the fewest channels of one
+// (centre products in us, ab initio).  4096 work-groups: K = 14, D = 181 662 ->
+// 793, K = 12, D = 128 194 -> 217, but K = 14, D = 64 76 -> 71; 16384: the first
+// two 4 % slower.  4 channels: K = 8, D = 48 31 -> 34, K = 10, D = 24 21 -> 26;
+// 16: K = 6, D = 16 13.5 -> 15.8, outer sites 10-20 % slower, K = 10, D = 24
+// 21 -> 20
 constexpr long long kChainGroups = 8192;
 constexpr int kChainMinChannels = 8;
 
@@ -1479,7 +1485,11 @@ void build_chain(sp_handle* h, int k) {
     // the same coefficients up to a common sign (an operator that acts as the
     // identity or the parity gives one group per local state), and groups of
     // one term read the environment block itself (K = 12 centre: 231 mixed
-    // blocks instead of 1414)
+    // blocks instead of 1414).  The line is at 1.5 entries per group: at 1 the
+    // Hubbard chain would mix (L = 32, D = 256 environment update 28 -> 67 us);
+    // at 3, K = 8, D = 100 updates next to the centre go from 25 to 43 us and the
+    // K = 6, D = 16 product from 13.5 to 22, while outer sites of small states,
+    // where a mixing launch is half the call, would gain (18 -> 10 us)
     std::vector<std::vector<std::array<int, 3>>> byR(size_t(4) * wr), byL(size_t(4) * wl);
     std::set<std::array<int, 3>> gl, gr;
     for (int e = 0; e < int(P.wr_ent.size()); ++e) {
@@ -1549,15 +1559,17 @@ void build_chain(sp_handle* h, int k) {
         return sh;
     };
     // Two blocks in n halve the reads of A and P per product.  The BF16 matrix
-    // cores wait for reads and splits, and gain (K = 14, D = 181: 538 us
-    // against 635); FP64 needs its registers for wavefronts in flight (K = 12,
-    // D = 128, site 7: 300 us against 293 with one)
+    // cores wait for reads and splits, and gain (K = 14, D = 181, site 6: 541 us
+    // against 645 with one; K = 12, D = 128 200 against 203); FP64 needs its
+    // registers for wavefronts in flight (K = 12, D = 128, site 7: 361 us against
+    // 297 with one; at the wider blocks of K = 16, D = 256 1837 against 2056)
     const bool wide_h = mixed_l && h->precision == SP_BF16X3;
     // Environment updates: an output block is a sum over few steps with a
-    // narrow MPO, split over four wavefronts (L = 32, D = 256: 25 us against
-    // 50 with one); a wide MPO has thousands of blocks of many steps each, and
-    // a wavefront per tile saves the LDS sums (K = 12, D = 128: 226 and 405 us
-    // for left and right against 264 and 416)
+    // narrow MPO, split over four wavefronts (L = 32, D = 256: 28 us against
+    // 70 with one); a wide MPO has thousands of blocks of many steps each, and
+    // a wavefront per tile saves the LDS sums (K = 12, D = 128, site 6: 221 us
+    // against 260 with four for the left update, 380 with either for the right;
+    // small wide states have too few tiles for it: K = 6, D = 16 16 us against 13)
     if (mixed_l || mixed_r) P.c_envl.waves = P.c_envr.waves = 1;
     int dl = 1, dr = 1;
     for (const NBlock& nb : bl.nb) dl = std::max(dl, nb.dim);
@@ -1594,13 +1606,10 @@ void build_chain(sp_handle* h, int k) {
         std::stable_sort(tiles.begin(), tiles.end(), [&](const Tile& x, const Tile& y) { return br.nb[x.b].dim > br.nb[y.b].dim; });
         // channels of a tile in chunks, each its own work-group and partial
         // slot, where the tiles alone leave the chip short of work-groups
-        std::vector<int> nch(tiles.size(), 0);
-        long long total = 0;
         int most = 1;
         for (const Tile& t : tiles) {
             int n = 0;
             for (int cp = 0; cp < wr; ++cp) n += vsrc.count({t.q, cp, t.i}) && er.find(cp, t.b) >= 0;
-            total += n;
             most = std::max(most, n);
         }
         long long want = std::max<long long>(1, kChainGroups / std::max<long long>(1, (long long)tiles.size() * h->G));
@@ -1701,7 +1710,7 @@ void build_chain(sp_handle* h, int k) {
     }
 }
 
-// LDS budget of a row-chunk plan of H_eff x (doubles): the default, and the
+// LDS budget of a fused plan of H_eff x (doubles): the default, and the
 // largest the autotuner tries (the 160 KB of a CU less static arrays)
 constexpr int kHeffLdsBudget = 9216;
 constexpr int kHeffLdsMax = 18432;
@@ -1709,11 +1718,10 @@ constexpr int kHeffMaxRows = 8;
 
 // The fused plan of site k for an LDS budget: rows per task RC such that RC
 // rows of every left-environment block, of every product L(c) x[sigma'] and
-// of the right channels of one sigma fit.  It decides which sites run H_eff x
-// as one fused contraction in the precision of the local solves (RC >= 1) and
-// which as block products (RC = 0: the MPO is too wide, or the caller chose
-// so); the kernel itself keeps its intermediates in registers.  Returns false
-// where no row fits.
+// of the right channels of one sigma fit.  Every site runs the same chained
+// lists; the plan decides in which arithmetic they run in the reduced
+// precisions: FP32 (RC >= 1), or as block products (RC = 0: the MPO is too
+// wide, or the caller chose so).  Returns false where no row fits.
 bool build_fused(sp_handle* h, int k, int lds_budget = kHeffLdsBudget) {
     SitePlan& P = h->plan[k - 1];
     const Bond& bl = h->bonds[k - 1];
@@ -3927,7 +3935,7 @@ int sp_sweep_batch(sp_handle** hs, int n, const sp_sweep_opts* o, sp_sweep_repor
 int sp_autotune(sp_handle* h, int reps, int* budget_out, int* rows_out, double* usec_out) {
     return guarded([&]() -> int {
         SP_REQUIRE(h && reps >= 1, "bad arguments");
-        SP_REQUIRE(h->path == SP_PATH_TILED, "the autotuner tunes the fused kernel of the tiled path");
+        SP_REQUIRE(h->path == SP_PATH_TILED, "the autotuner tunes the H_eff plans of the tiled path");
         forget_mix(h);
         const int candidates[] = {4608, 9216, 13824, kHeffLdsMax};
         hipStream_t s = h->stream;
@@ -4505,9 +4513,8 @@ int sp_heff_profile(sp_handle* h, int site, int reps, const double* x, double* y
             out[7] = 8.0 * (G * P.Tsize + G * P.Vsize);
             out[8] = 8.0 * (G * P.Vsize + G * P.Tsize + Rb + 2.0 * xs);
         } else {
-            // the product into per-g partials (the fused launch, or the tiled
-            // lists at a site without a fused plan): environments and x read
-            // once, per-g partials written
+            // the product into per-g partials: environments and x read once,
+            // per-g partials written
             out[1] = premix_ms;
             out[3] = P.heff_flops;
             out[4] = G * P.mix_l.flops;

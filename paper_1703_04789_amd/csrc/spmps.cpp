@@ -576,6 +576,7 @@ struct sp_handle {
     // write the scratch and the environments
     unsigned long long lt_capture = 0;
     bool recorded = false;
+    bool mixes = false;  // some site's MPO is mixed into an environment
     long long Xr_cap = 0;
     long long Xd_cap = 0;
     int y_split_max = 1;  // partial slots of y per quadrature point
@@ -2326,7 +2327,7 @@ bool heff_apply(sp_handle* h, int k, const double* x, double* y, double* ny, boo
 void env_chain(sp_handle* h, int k, const ChainList& C, const MixList& mix, const double* env, long long esize, double* out,
                long long osize) {
     const SitePlan& P = h->plan[k - 1];
-    (void)capture_of(h);  // a recorded update writes an environment when it is replayed
+    if (h->mixes) (void)capture_of(h);  // a recorded update writes an environment when it is replayed
     site_vectors(h, k, site_ptr(h, k));
     if (&mix == &P.mix_l) {
         premix_left(h, k, spk::kChainF64);  // there already if H_eff was applied at this site
@@ -3715,6 +3716,7 @@ int sp_init_mps(const sp_problem* p, const sp_mpo* W, const sp_block_table* bond
             Tmax = std::max({Tmax, P.Tsize, P.Zsize, dgT});
             Vmax = std::max({Vmax, P.Vsize, P.Ztsize, (long long)P.dg_mix.size() * h->bonds[k - 1].D});
             LTmax = std::max({LTmax, P.mix_l.size, P.mix_r.size});
+            h->mixes = h->mixes || !P.mix_l.empty() || !P.mix_r.empty();
             qrs = std::max({qrs, P.qr_scratch, P.lq_scratch});
             qrr = std::max({qrr, P.qr_rsize, P.lq_rsize});
         }

@@ -8,6 +8,8 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from gpu_util import make_pair  # noqa: E402
+
 import paper_1703_04789_amd as sp  # noqa: E402
 import workloads as W  # noqa: E402
 from oracle import precond as pre  # noqa: E402
@@ -39,6 +41,32 @@ def test_steps_of_few_rows(hidden, rows):
         got = m.params()
         for k in ("W1", "b1", "w2", "b2"):
             assert np.abs(np.asarray(got[k], np.float64) - ref[k]).max() < 2e-7, k
+
+
+@pytest.mark.parametrize("batch", [3, 16, 17])
+def test_interleaved_batches_of_few_rows(batch):
+    # batch b takes rows b, b + nb, ..: strided rows in either form.  An FP32
+    # weight may round the other way in each of the nb steps
+    wl = W.hubbard_small()
+    gpu = make_pair(wl.L, wl.N, wl.twoM, wl.D, wl.twoS, wl.G, U=wl.U, seed=wl.seed, oracle=False)[1]
+    p = W.mlp_init(64, 5)
+    rec = sp.MLP(p, capacity=400)
+    gpu.set_precond(record=rec)
+    gpu.sweep(1, max_sub=32, max_iter=64)
+    F, Y = (a.astype(np.float64) for a in rec.dataset())
+    rows = len(Y)
+    nb = -(-rows // batch)
+    assert rows > 2 * batch
+    losses = rec.train(1, batch, 1e-3)
+    ref, state, want = _fp32(p), {}, []
+    for b in range(nb):
+        loss, g = pre.loss_and_grads(ref, F[b::nb], Y[b::nb])
+        want.append(loss)
+        ref = _fp32(pre.adam_step(ref, g, state, 1e-3))
+    assert abs(losses[0] - np.mean(want)) < 1e-6 * np.mean(want)
+    got = rec.params()
+    for k in ("W1", "b1", "w2", "b2"):
+        assert np.abs(np.asarray(got[k], np.float64) - ref[k]).max() < 2e-7 * nb, k
 
 
 def _usec(m, rows):

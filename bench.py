@@ -497,7 +497,7 @@ def main():
                          "stated size (K=30, D=500)")
     ap.add_argument("--abinitio-full", action="store_true",
                     help="only the 30-orbital ab-initio workload at K=30, D=500, G=11: FP64 sweeps, then split "
-                         "BF16 until it reaches the FP64 energy (about 15 minutes); one JSON line")
+                         "BF16 until it reaches the FP64 energy (about 6 minutes); one JSON line")
     ap.add_argument("--abinitio-sweeps", type=int, default=3, help="FP64 sweeps of --abinitio-full")
     ap.add_argument("--heff-only", type=int, default=0,
                     help="only run this many H_eff x applications at the centre site, after a 64 MiB "
